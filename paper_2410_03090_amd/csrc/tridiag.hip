@@ -5,16 +5,10 @@
 // One workgroup of 256 threads per matrix:
 //   1. add the Gram partials of the matrix in fp64, subtract the mean term s s^T / N
 //      (Eq. 1; the common factor 1/(N-1) drops out under the unit-trace scaling) and divide
-//      by the trace.  The matrix lives in registers: thread (c, hf) holds rows 64*hf .. +64
-//      of column c as 64 doubles.
+//      by the trace.  The matrix lives in registers: wave q holds the row blocks q and q + 4
+//      (16 rows each), lane l their columns l and l + 64: 64 doubles per lane.
 //   2. 126 Householder reflections H = I - beta v v^T bring it to tridiagonal form
-//      (A <- A - v w^T - w v^T with p = beta A v, w = p - (beta/2)(v^T p) v).  Per reflection:
-//      the pivot row was left in LDS by the previous update, every wave forms the norm of its
-//      tail on its own (identical bits in all waves, so the whole workgroup takes the same
-//      branch), a matrix-vector product with v read from LDS at wave-uniform addresses, one
-//      exchange of the two row halves, every wave forms v^T A v on its own, and the rank-2
-//      update; three workgroup barriers.  Rows that are already done are skipped by uniform
-//      branches; no register is ever indexed dynamically.
+//      (A <- A - v w^T - w v^T with p = beta A v, w = p - (beta/2)(v^T p) v).
 //   3. The eigenvalues of the tridiagonal matrix (d, e) are found by counting sign changes of
 //      the characteristic-polynomial recurrence p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}
 //      (= number of eigenvalues below x; no division, rescaled against underflow): every
@@ -25,27 +19,37 @@
 //      the definition asks for.  Only the k largest are computed unless the caller wants the
 //      whole spectrum.
 //   4. truncated entropy in fp64.
+//
+// What bounds step 2 is the serial chain of 126 reflections (latency, with one matrix per CU) and
+// the number of vector instructions (with two), so both are kept short:
+//   - Row values reach the lanes through the DPP broadcast inside rows of 16 lanes
+//     (v_fmac_f64_dpp row_newbcast, the one DPP form the fp64 pipe has): a register pair whose lane
+//     l%16 holds row 16b + l%16 serves the 16 rows of a block.  Reading the same values from LDS at
+//     uniform addresses was one 128-bit read per FMA pair, which kept the LDS pipe busier than the
+//     vector pipe and set the time of the launch.
+//   - One barrier per reflection.  Before it every wave leaves its part of A x and the owner of row
+//     i + 2 leaves that row; after it every wave forms the reflection's scalars, w, and rows i + 1
+//     and i + 2 as the update will leave them (x and y of the next reflection) for itself, with the
+//     same operations in the same order, so all waves hold identical bits and none waits for another.
+//   - Rows and columns that are done are skipped at the grain of a 16-row block and a 64-column
+//     half, alike in all four waves.
 #include "common.h"
 #include "device_utils.h"
+
+#include <type_traits>
 
 namespace uncomp {
 
 namespace {
 
-// The kernel comes in two shapes.  kParts = 4: 512 threads per matrix, 32 rows of a column per
-// thread, two waves per SIMD from the one matrix a CU works on (a launch with fewer matrices
-// than the chip can hold two per CU).  kParts = 2: 256 threads, 64 rows per thread, registers
-// capped so that two matrices share a CU and fill each other's waits (large launches).
+constexpr int kTriThreads = 256, kTriWaves = kTriThreads / 64;
 
-template <int kParts>
 struct TriSmem {
     double s[kD];            // column sums of X (for the mean correction)
-    double red[8];
-    double xbuf[kD];         // pivot row i, entries at columns <= i zeroed
-    double ybuf[kD];         // row i + 1
-    double pbuf[kParts][kD]; // the row slices of A x
-    double2 vw[kD];          // (v_r, w_r)
-    double2 de[kD];          // (d_i, e_{i-1}^2), e_{-1} = 0
+    double red[kTriWaves];
+    double pbuf[2][kTriWaves][kD];   // the waves' parts of A x, double buffered over reflections
+    double zrow[2][kD];      // row i + 2
+    double d[kD], e2[kD];    // diagonal; e2[i] = e_{i-1}^2, e_{-1} = 0
     double lam[kD];          // eigenvalues, descending
 };
 
@@ -80,7 +84,6 @@ __device__ __forceinline__ double wave_allsum(double v) {
     return v;
 }
 
-template <int kWaves>
 __device__ __forceinline__ double block_sum(double v, double* red, int tid) {
     v = wave_allsum(v);
     __syncthreads();
@@ -88,58 +91,81 @@ __device__ __forceinline__ double block_sum(double v, double* red, int tid) {
     __syncthreads();
     double t = red[0];
 #pragma unroll
-    for (int x = 1; x < kWaves; ++x) t += red[x];
+    for (int x = 1; x < kTriWaves; ++x) t += red[x];
     return t;
+}
+
+// acc +- rows[lane row's lane U] * m.  The DPP operand must not have been written by the two vector
+// instructions before (the compiler does not look into the statement): dpp_ready() stands between.
+template <int U>
+__device__ __forceinline__ void fmac_bc(double& acc, double rows, double m) {
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(rows), "v"(m), "n"(U));
+}
+template <int U>
+__device__ __forceinline__ void fnmac_bc(double& acc, double rows, double m) {
+    asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(rows), "v"(m), "n"(U));
+}
+__device__ __forceinline__ void dpp_ready(double& a, double& b) { asm volatile("s_nop 1" : "+v"(a), "+v"(b)); }
+
+// value of lane `l` (wave-uniform) in every lane
+__device__ __forceinline__ double lane_value(double v, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+// entry r (wave-uniform, 0 .. 127) of a vector held as entries lane and lane + 64
+__device__ __forceinline__ double entry(double lo, double hi, int r) { return lane_value(r < 64 ? lo : hi, r & 63); }
+
+template <int U, typename F>
+__device__ __forceinline__ void each16(F&& f) {
+    if constexpr (U < 16) {
+        f(std::integral_constant<int, U>{});
+        each16<U + 1>(f);
+    }
 }
 
 // Number of eigenvalues of the tridiagonal matrix below x: sign changes along
 // 1, p_0, p_1, ..., p_{n-1} (a zero takes the sign '+', which gives the same total as the
 // textbook rule because the next term then has the opposite sign of the previous one).
-// The (d_i, e_{i-1}^2) pairs come from LDS eight at a time, the next eight requested before
-// the current eight are used.
-__device__ __forceinline__ int sturm_count(const double2* de, double x) {
+// dr / er: d and e^2 of entries 16 j + lane%16.  Signs are shifted into a word, 32 terms at a time.
+__device__ __forceinline__ int sturm_count(const double (&dr)[8], const double (&er)[8], double x) {
     double pp = 0.0, p = 1.0;                      // p_{-2}, p_{-1}
     int cnt = 0;
-    double2 cur[8], nxt[8];
+    uint32_t last = 0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) cur[u] = de[u];
-#pragma clang loop unroll(disable)
-    for (int base = 0; base < kD; base += 8) {
-        const int nb = base + 8 < kD ? base + 8 : base;          // the last prefetch re-reads its own chunk
+    for (int j2 = 0; j2 < 4; ++j2) {
+        uint32_t signs = 0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) nxt[u] = de[nb + u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const double pn = fma(cur[u].x - x, p, -(cur[u].y * pp));
-            cnt += (int)((unsigned)(__double2hiint(pn) ^ __double2hiint(p)) >> 31);
-            pp = p;
-            p = pn;
+        for (int h = 0; h < 2; ++h) {
+            const int j = 2 * j2 + h;
+            each16<0>([&](auto U) {
+                double t = 0.0;
+                fnmac_bc<U.value>(t, er[j], pp);
+                fmac_bc<U.value>(t, dr[j], p);
+                t = fma(-x, p, t);
+                signs = __builtin_amdgcn_alignbit(signs, (uint32_t)__double2hiint(t), 31);   // signs << 1 | sign of t
+                pp = p;
+                p = t;
+            });
+            // |p| shrinks by at most ~2^-35 per step and grows by at most 1.25: keep the pair normal
+            const double sc = fmax(fabs(p), fabs(pp)) < 0x1p-300 ? 0x1p300 : 1.0;
+            p *= sc;
+            pp *= sc;
         }
-        // |p| shrinks by at most ~2^-35 per step and grows by at most 1.25: keep it normal
-        const double sc = fabs(p) < 0x1p-300 ? 0x1p300 : 1.0;
-        p *= sc;
-        pp *= sc;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) cur[u] = nxt[u];
+        cnt += __popc(signs ^ (signs >> 1 | last << 31));
+        last = signs & 1u;
     }
     return cnt;
 }
 
 }  // namespace
 
-template <int kParts>
-__global__ __launch_bounds__(kD * kParts, kParts == 2 ? 2 : 1) void tridiag_entropy_kernel(
+__global__ __launch_bounds__(kTriThreads, 2) void tridiag_entropy_kernel(
     const float* __restrict__ gram_part, const float* __restrict__ sum_part, int n_chunks, int N,
     int k_trunc, unsigned flags, float* __restrict__ entropy_out, float* __restrict__ eig_out, int eig_ld,
     const double* __restrict__ trace_total) {
-    constexpr int kThreads = kD * kParts, kWaves = kThreads / 64;
-    constexpr int kHalf = kD / kParts;                           // rows of a column per thread
-    __shared__ TriSmem<kParts> sm;
+    __shared__ TriSmem sm;
     const int m = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int c = tid & (kD - 1);
-    const int hf = __builtin_amdgcn_readfirstlane(tid >> 7);     // wave-uniform: which slice of rows
-    const int col_hi = __builtin_amdgcn_readfirstlane(c | 63);   // last column of this wave
+    const int q = __builtin_amdgcn_readfirstlane(tid >> 6);      // this wave's row blocks: q and q + 4
     const float* Gm = gram_part + (int64_t)m * n_chunks * (kD * kD);
     const float* Sm = sum_part + (int64_t)m * n_chunks * kD;
 
@@ -159,8 +185,8 @@ __global__ __launch_bounds__(kD * kParts, kParts == 2 ? 2 : 1) void tridiag_entr
         tr_u = acc;
         tr_c = center ? acc - sm.s[tid] * sm.s[tid] * inv_n : acc;
     }
-    const double trace = block_sum<kWaves>(tr_c, sm.red, tid);
-    const double trace_u = block_sum<kWaves>(tr_u, sm.red, tid);
+    const double trace = block_sum(tr_c, sm.red, tid);
+    const double trace_u = block_sum(tr_u, sm.red, tid);
     // Zero spread: a single token, or a centred trace so far below the second moment that
     // the fp32 partial sums cannot tell it from zero.
     bool degenerate = !(trace > 0.0) || (center && (N < 2 || trace < trace_u * 0x1p-20));
@@ -176,124 +202,169 @@ __global__ __launch_bounds__(kD * kParts, kParts == 2 ? 2 : 1) void tridiag_entr
         if (eig_out != nullptr && tid < eig_ld) eig_out[(int64_t)m * eig_ld + tid] = 0.f;
         return;
     }
-    double a[kHalf];                                             // a[k] = A[64 hf + k][c]
+    double a[2][2][16];                                          // a[j][s][u] = A[16 (q + 4 j) + u][lane + 64 s]
 #pragma unroll
-    for (int k = 0; k < kHalf; ++k) a[k] = 0.0;
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int u = 0; u < 16; ++u) a[j][s][u] = 0.0;
     for (int ch = 0; ch < n_chunks; ++ch) {
-        const float* g = Gm + (int64_t)ch * (kD * kD) + (hf * kHalf) * kD + c;
+        const float* g = Gm + (int64_t)ch * (kD * kD) + 16 * q * kD + lane;
 #pragma unroll
-        for (int kb = 0; kb < kHalf; kb += 16) {                 // 16 independent loads in flight
-            float t[16];
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int u = 0; u < 16; ++u) t[u] = g[(kb + u) * kD];
+            for (int s = 0; s < 2; ++s) {                        // 16 independent loads in flight
+                float t[16];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) a[kb + u] += (double)t[u];
-        }
+                for (int u = 0; u < 16; ++u) t[u] = g[(64 * j + u) * kD + 64 * s];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) a[j][s][u] += (double)t[u];
+            }
     }
     {
         const double inv_tr = 1.0 / trace;
-        const double sc = center ? sm.s[c] * inv_n : 0.0;
+        const double sc0 = center ? sm.s[lane] * inv_n : 0.0, sc1 = center ? sm.s[lane + 64] * inv_n : 0.0;
 #pragma unroll
-        for (int k = 0; k < kHalf; ++k) a[k] = (a[k] - sm.s[hf * kHalf + k] * sc) * inv_tr;
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const double sr = sm.s[16 * q + 64 * j + u];
+                a[j][0][u] = (a[j][0][u] - sr * sc0) * inv_tr;
+                a[j][1][u] = (a[j][1][u] - sr * sc1) * inv_tr;
+            }
     }
 
     // ---- 2. Householder tridiagonalisation ---------------------------------------------------
-    // Leaves rows `row` and `row + 1` of the matrix in LDS for the next reflection: row `row` in
-    // xbuf with the entries at columns <= row zeroed (its diagonal entry goes to de[row].x), row
-    // `row + 1` in ybuf.  A row is held by the 128 threads of one half in a register whose number
-    // depends on the row; a switch on that (wave-uniform) number reaches it without indexing.
-#define UNCOMP_TRI_CASE(K)                                                      \
-    case K:                                                                     \
-        if constexpr (K < kHalf) {                                              \
-            sm.xbuf[c] = c > row ? a[K] : 0.0;                                  \
-            if (c == row) sm.de[row].x = a[K];                                  \
-            if (K + 1 < kHalf) sm.ybuf[c] = a[K + 1 < kHalf ? K + 1 : K];       \
-        }                                                                       \
+    // Row `row` of the matrix (in the registers of one wave) to LDS: a switch on the wave-uniform register
+    // number reaches it without indexing.
+#define UNCOMP_TRI_CASE(K)                             \
+    case K:                                            \
+        to[lane] = a[(K) >> 4][0][(K) & 15];           \
+        to[lane + 64] = a[(K) >> 4][1][(K) & 15];      \
         break;
 #define UNCOMP_TRI_CASE8(K)                                                                          \
     UNCOMP_TRI_CASE(K) UNCOMP_TRI_CASE(K + 1) UNCOMP_TRI_CASE(K + 2) UNCOMP_TRI_CASE(K + 3)          \
     UNCOMP_TRI_CASE(K + 4) UNCOMP_TRI_CASE(K + 5) UNCOMP_TRI_CASE(K + 6) UNCOMP_TRI_CASE(K + 7)
-    auto publish2 = [&](int row) {
-        switch (row - hf * kHalf) {
-            case -1:                                             // row + 1 is the first row of this half
-                sm.ybuf[c] = a[0];
-                break;
+    auto publish = [&](int row, double* to) {
+        if (((row >> 4) & 3) != q) return;
+        switch ((row >> 6) * 16 + (row & 15)) {
             UNCOMP_TRI_CASE8(0) UNCOMP_TRI_CASE8(8) UNCOMP_TRI_CASE8(16) UNCOMP_TRI_CASE8(24)
-            UNCOMP_TRI_CASE8(32) UNCOMP_TRI_CASE8(40) UNCOMP_TRI_CASE8(48) UNCOMP_TRI_CASE8(56)
             default:
                 break;
         }
     };
 #undef UNCOMP_TRI_CASE8
 #undef UNCOMP_TRI_CASE
-    publish2(0);
-    for (int i = 0; i < kD - 2; ++i) {
-        __syncthreads();                                         // xbuf = row i (masked), ybuf = row i + 1
-        const double x1 = sm.xbuf[i + 1];
-        const double xa = lane > i + 1 ? sm.xbuf[lane] : 0.0;
-        const double xb = lane + 64 > i + 1 ? sm.xbuf[lane + 64] : 0.0;
-        // This thread's part of (A x)_c over the rows of its half (x is zero on the rows that are
-        // done).  It does not depend on the reflection's scalars, so it runs beside their reduction.
-        double p0 = 0.0, p1 = 0.0, p2 = 0.0, p3 = 0.0;
-        // rows of this slice still in play, and columns of this wave still in play (both wave-uniform)
-        const bool half_live = hf * kHalf + kHalf - 1 > i && col_hi > i;
-        if (half_live) {
+    // Every wave carries x = row i (entries at columns <= i zeroed) and y = row i + 1, twice: as entries
+    // lane, lane + 64 (index s) and as entries 16 (q + 4 j) + lane%16, the DPP operands of its rows (index j).
+    const int row0 = 16 * q + (lane & 15);
+    double x[2], y[2], xr[2], yr[2];
+    publish(0, sm.pbuf[1][0]);
+    publish(1, sm.pbuf[1][1]);
+    __syncthreads();
 #pragma unroll
-            for (int k = 0; k < kHalf; k += 4) {
-                const double2 xv0 = *reinterpret_cast<const double2*>(&sm.xbuf[hf * kHalf + k]);
-                const double2 xv1 = *reinterpret_cast<const double2*>(&sm.xbuf[hf * kHalf + k + 2]);
-                p0 = fma(a[k], xv0.x, p0);
-                p1 = fma(a[k + 1], xv0.y, p1);
-                p2 = fma(a[k + 2], xv1.x, p2);
-                p3 = fma(a[k + 3], xv1.y, p3);
-            }
-        }
-        const double tail = wave_allsum(xa * xa + xb * xb);      // sum_{r > i+1} x_r^2, same bits in every wave
-        if (tail == 0.0) {
-            // the column is already in tridiagonal form: nothing to reflect
-            if (tid == 0) sm.de[i + 1].y = x1 * x1;
-            __syncthreads();                                     // both rows read by all before they are replaced
-        } else {
-            // v = x - alpha e_{i+1};  A v = A x - alpha (row i + 1)
-            const double sigma = tail + x1 * x1;
-            const double nrm = sqrt(sigma);
-            const double alpha = x1 >= 0.0 ? -nrm : nrm;
-            const double den = sigma - alpha * x1;               // = sigma + |x1| sqrt(sigma) > 0
-            double beta = __builtin_amdgcn_rcp(den);
-            beta = fma(fma(-den, beta, 1.0), beta, beta);        // two Newton steps on the hardware estimate
-            beta = fma(fma(-den, beta, 1.0), beta, beta);
-            if (tid == 0) sm.de[i + 1].y = sigma;                // e_i^2 = alpha^2
-            sm.pbuf[hf][c] = (p0 + p1) + (p2 + p3);
-            __syncthreads();
-            auto v_of = [&](int r) { return sm.xbuf[r] - (r == i + 1 ? alpha : 0.0); };
-            auto Av_of = [&](int r) {
-                double t = sm.pbuf[0][r];
-#pragma unroll
-                for (int x = 1; x < kParts; ++x) t += sm.pbuf[x][r];
-                return t - alpha * sm.ybuf[r];
-            };
-            const double vAv = wave_allsum(v_of(lane) * Av_of(lane) + v_of(lane + 64) * Av_of(lane + 64));
-            const double K = 0.5 * beta * beta * vAv;
-            const double vc = v_of(c);
-            const double wc = c > i ? beta * Av_of(c) - K * vc : 0.0;
-            if (hf == 0) sm.vw[c] = make_double2(vc, wc);
-            __syncthreads();
-            if (half_live) {
-#pragma unroll
-                for (int k = 0; k < kHalf; ++k) {
-                    const double2 t = sm.vw[hf * kHalf + k];
-                    a[k] = fma(-t.x, wc, fma(-t.y, vc, a[k]));
-                }
-            }
-        }
-        publish2(i + 1);
+    for (int s = 0; s < 2; ++s) {
+        x[s] = sm.pbuf[1][0][lane + 64 * s];
+        y[s] = sm.pbuf[1][1][lane + 64 * s];
+        xr[s] = sm.pbuf[1][0][row0 + 64 * s];
+        yr[s] = sm.pbuf[1][1][row0 + 64 * s];
     }
-    __syncthreads();                                             // xbuf = row 126 (masked)
     if (tid == 0) {
-        sm.de[kD - 1].y = sm.xbuf[kD - 1] * sm.xbuf[kD - 1];
-        sm.de[0].y = 0.0;
+        sm.d[0] = x[0];
+        sm.e2[0] = 0.0;
     }
-    if (tid == kThreads - 1) sm.de[kD - 1].x = a[kHalf - 1];
+    if (lane == 0) x[0] = 0.0;
+    if (row0 == 0) xr[0] = 0.0;
+
+    for (int i = 0; i < kD - 2; ++i) {
+        double* pb = sm.pbuf[i & 1][0];
+        double* zb = sm.zrow[i & 1];
+        publish(i + 2, zb);
+        const bool top = 16 * q + 15 > i, bottom = 16 * q + 79 > i;     // row blocks still in play
+        const bool left = i < 63;                                       // columns 0 .. 63 still in play
+        // the wave's part of A x
+        double p[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+        dpp_ready(xr[0], xr[1]);
+        if (bottom) {
+            if (left) each16<0>([&](auto U) { fmac_bc<U.value>(p[1][0], xr[1], a[1][0][U.value]); fmac_bc<U.value>(p[1][1], xr[1], a[1][1][U.value]); });
+            else each16<0>([&](auto U) { fmac_bc<U.value>(p[1][U.value & 1], xr[1], a[1][1][U.value]); });
+        }
+        if (!left) { p[0][1] = p[1][0]; p[1][0] = 0.0; }
+        if (top) each16<0>([&](auto U) { fmac_bc<U.value>(p[0][0], xr[0], a[0][0][U.value]); fmac_bc<U.value>(p[0][1], xr[0], a[0][1][U.value]); });
+        pb[q * kD + lane] = p[0][0] + p[1][0];
+        pb[q * kD + lane + 64] = p[0][1] + p[1][1];
+        // v = x - alpha e_{i+1}, |alpha| = |x|, sign against cancellation; e_i^2 = alpha^2.  Independent of A x.
+        const double sigma = wave_allsum(fma(x[0], x[0], x[1] * x[1]));
+        const double x1 = entry(x[0], x[1], i + 1);
+        double rs = __builtin_amdgcn_rsq(sigma);                        // 1 / |x|: hardware estimate, two Newton steps
+        rs = fma(0.5 * rs, fma(-sigma * rs, rs, 1.0), rs);
+        rs = fma(0.5 * rs, fma(-sigma * rs, rs, 1.0), rs);
+        double nrm = sigma * rs;
+        nrm = fma(0.5 * rs, fma(-nrm, nrm, sigma), nrm);
+        const bool some = sigma > 0x1p-900;                             // nothing to reflect: beta = 0 leaves the matrix as it is
+        const double alpha = some ? (x1 >= 0.0 ? -nrm : nrm) : 0.0;
+        const double den = fma(fabs(x1), nrm, sigma);
+        double beta = __builtin_amdgcn_rcp(den);
+        beta = fma(fma(-den, beta, 1.0), beta, beta);
+        beta = fma(fma(-den, beta, 1.0), beta, beta);
+        beta = some ? beta : 0.0;
+        if (tid == 0) sm.e2[i + 1] = sigma;
+        __syncthreads();
+        double Av[2], Avr[2], z[2], zr[2], v[2], vr[2], w[2], wr[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const double* pc = pb + lane + 64 * s;
+            const double* pr = pb + row0 + 64 * s;
+            Av[s] = fma(-alpha, y[s], (pc[0] + pc[kD]) + (pc[2 * kD] + pc[3 * kD]));
+            Avr[s] = fma(-alpha, yr[s], (pr[0] + pr[kD]) + (pr[2 * kD] + pr[3 * kD]));
+            z[s] = zb[lane + 64 * s];
+            zr[s] = zb[row0 + 64 * s];
+            v[s] = lane + 64 * s == i + 1 ? x[s] - alpha : x[s];
+            vr[s] = row0 + 64 * s == i + 1 ? xr[s] - alpha : xr[s];
+            Av[s] = lane + 64 * s > i ? Av[s] : 0.0;                    // columns that are done hold no part of A x
+            Avr[s] = row0 + 64 * s > i ? Avr[s] : 0.0;
+        }
+        const double vAv = wave_allsum(fma(v[0], Av[0], v[1] * Av[1]));
+        const double K = -0.5 * beta * beta * vAv;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            w[s] = fma(beta, Av[s], K * v[s]);
+            wr[s] = fma(beta, Avr[s], K * vr[s]);
+        }
+        // rows i + 1 and i + 2 as the update leaves them
+        const double v1 = x1 - alpha, w1 = entry(w[0], w[1], i + 1);
+        const double v2 = entry(v[0], v[1], i + 2), w2 = entry(w[0], w[1], i + 2);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            x[s] = fma(-v1, w[s], fma(-w1, v[s], y[s]));
+            xr[s] = fma(-v1, wr[s], fma(-w1, vr[s], yr[s]));
+            y[s] = fma(-v2, w[s], fma(-w2, v[s], z[s]));
+            yr[s] = fma(-v2, wr[s], fma(-w2, vr[s], zr[s]));
+            if (q == 0 && lane + 64 * s == i + 1) sm.d[i + 1] = x[s];
+            x[s] = lane + 64 * s > i + 1 ? x[s] : 0.0;
+            xr[s] = row0 + 64 * s > i + 1 ? xr[s] : 0.0;
+        }
+        dpp_ready(vr[0], vr[1]);
+        dpp_ready(wr[0], wr[1]);
+        auto update = [&](double (&block)[16], double rv, double rw, double cv, double cw) {
+            each16<0>([&](auto U) { fnmac_bc<U.value>(block[U.value], rv, cw); });
+            each16<0>([&](auto U) { fnmac_bc<U.value>(block[U.value], rw, cv); });
+        };
+        if (bottom) {
+            update(a[1][1], vr[1], wr[1], v[1], w[1]);
+            if (left) update(a[1][0], vr[1], wr[1], v[0], w[0]);
+        }
+        if (top) {
+            update(a[0][0], vr[0], wr[0], v[0], w[0]);
+            update(a[0][1], vr[0], wr[0], v[1], w[1]);
+        }
+    }
+    // x = row 126 (masked), y = row 127
+    if (tid == 63) {
+        sm.e2[kD - 1] = x[1] * x[1];
+        sm.d[kD - 1] = y[1];
+    }
     if (tid < kD) sm.lam[tid] = 0.0;
     __syncthreads();
 
@@ -301,16 +372,24 @@ __global__ __launch_bounds__(kD * kParts, kParts == 2 ? 2 : 1) void tridiag_entr
     const int k = k_trunc < kD ? k_trunc : kD;
     const int n_need = eig_out != nullptr ? kD : k;
     // lanes per eigenvalue: as many as the workgroup can give every wanted eigenvalue
-    const int L = kThreads / 16 >= n_need ? 16 : (kThreads / 8 >= n_need ? 8 : (kThreads / 4 >= n_need ? 4 : 2));
-    const int rounds = L == 16 ? 8 : (L == 8 ? 10 : (L == 4 ? 14 : 20));           // (L+1)^rounds >= 2^31
+    const int L = kTriThreads / 8 >= n_need ? 8 : (kTriThreads / 4 >= n_need ? 4 : 2);
+    const int rounds = L == 8 ? 10 : (L == 4 ? 14 : 20);         // (L+1)^rounds >= 2^31
     {
-        const int q = tid / L, s = tid % L;                      // eigenvalue q (0 = largest), piece s
-        const int j = kD - 1 - q;                                // its index in ascending order
+        double dr[8], er[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            dr[j] = sm.d[16 * j + (lane & 15)];
+            er[j] = sm.e2[16 * j + (lane & 15)];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) dpp_ready(dr[j], er[j]);
+        const int n = tid / L, s = tid % L;                      // eigenvalue n (0 = largest), piece s
+        const int j = kD - 1 - n;                                // its index in ascending order
         const double inv = 1.0 / (double)(L + 1);
         double lo = 0.0, hi = 1.0 + 0x1p-10;
         for (int it = 0; it < rounds; ++it) {
             const double step = (hi - lo) * inv;
-            const int cnt = sturm_count(sm.de, lo + step * (double)(s + 1));
+            const int cnt = sturm_count(dr, er, lo + step * (double)(s + 1));
             const unsigned long long mask = __ballot(cnt > j);
             const unsigned bits = (unsigned)(mask >> (lane - s)) & ((1u << L) - 1u);
             const int piece = bits ? __builtin_ctz(bits) : L;    // first cut with more than j eigenvalues below it
@@ -318,17 +397,17 @@ __global__ __launch_bounds__(kD * kParts, kParts == 2 ? 2 : 1) void tridiag_entr
             hi = piece == L ? hi : lo + step * (double)(piece + 1);
             lo = nlo;
         }
-        if (s == 0 && q < n_need) {
+        if (s == 0 && n < n_need) {
             const double v = 0.5 * (lo + hi);
-            sm.lam[q] = v > 0.0 ? v : 0.0;
+            sm.lam[n] = v > 0.0 ? v : 0.0;
         }
     }
     __syncthreads();
 
     // ---- 4. entropy --------------------------------------------------------------------------
     const double mine = tid < kD ? sm.lam[tid] : 0.0;
-    const double total = block_sum<kWaves>(tid < kD ? sm.de[tid].x : 0.0, sm.red, tid);   // the trace: sum of all eigenvalues
-    const double topk = block_sum<kWaves>(tid < k ? mine : 0.0, sm.red, tid);
+    const double total = block_sum(tid < kD ? sm.d[tid] : 0.0, sm.red, tid);   // the trace: sum of all eigenvalues
+    const double topk = block_sum(tid < k ? mine : 0.0, sm.red, tid);
     // total = 1 up to rounding (the matrix was scaled to unit trace).  When the matrix is a projection
     // of a larger one, the eigenvalues' share of the larger trace is what Eq. 5 and eig_out mean.
     const double whole = trace_total != nullptr ? total * (whole_raw / trace) : total;
@@ -338,7 +417,7 @@ __global__ __launch_bounds__(kD * kParts, kParts == 2 ? 2 : 1) void tridiag_entr
         const double sgm = mine / denom;
         term = -sgm * log(sgm);
     }
-    const double H = block_sum<kWaves>(term, sm.red, tid);
+    const double H = block_sum(term, sm.red, tid);
     if (tid == 0) entropy_out[m] = (float)H;
     if (eig_out != nullptr && tid < eig_ld)        // eig_ld values per matrix: all 128, or the leading 64 of a 64-wide input
         eig_out[(int64_t)m * eig_ld + tid] = whole > 0.0 ? (float)(mine / whole) : 0.f;
@@ -350,12 +429,8 @@ hipError_t launch_tridiag_entropy(int n_mat, int N, int k_trunc, unsigned flags,
     const float* gram = reinterpret_cast<const float*>(ws + p.gram_off);
     const float* sums = reinterpret_cast<const float*>(ws + p.sum_off);
     env.begin("tridiag_entropy");
-    if (n_mat < 512)
-        tridiag_entropy_kernel<4><<<dim3(n_mat), dim3(4 * kD), 0, env.s>>>(gram, sums, p.n_chunks, N, k_trunc, flags,
-                                                                         entropy_out, eig_out, eig_ld, trace_total);
-    else
-        tridiag_entropy_kernel<2><<<dim3(n_mat), dim3(2 * kD), 0, env.s>>>(gram, sums, p.n_chunks, N, k_trunc, flags,
-                                                                         entropy_out, eig_out, eig_ld, trace_total);
+    tridiag_entropy_kernel<<<dim3(n_mat), dim3(kTriThreads), 0, env.s>>>(gram, sums, p.n_chunks, N, k_trunc, flags, entropy_out,
+                                                                         eig_out, eig_ld, trace_total);
     env.end();
     return hipGetLastError();
 }
