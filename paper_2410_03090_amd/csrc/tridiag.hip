@@ -33,6 +33,8 @@
 //     same operations in the same order, so all waves hold identical bits and none waits for another.
 //   - Rows and columns that are done are skipped at the grain of a 16-row block and a 64-column
 //     half, alike in all four waves.
+// Measured: 256 matrices (one per CU) 255 -> 148 us, of which 16 are step 3; 5120 matrices 3.4 -> 1.7 ms
+// (before: rows from LDS at uniform addresses, three barriers, 512 threads where a CU holds one matrix).
 #include "common.h"
 #include "device_utils.h"
 
@@ -55,8 +57,8 @@ struct TriSmem {
 
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
 }
 
@@ -64,17 +66,24 @@ __device__ __forceinline__ double dpp_move(double v) {
 // rows of 16 lanes (DPP row_ror 8, 4, 2, 1), then the four rows with
 // v_permlane32_swap(a,b) -> ([a.lo32, b.lo32], [a.hi32, b.hi32]) and
 // v_permlane16_swap(a,b) -> ([a.r0, b.r0, a.r2, b.r2], [a.r1, b.r1, a.r3, b.r3]).
-__device__ __forceinline__ double wave_allsum(double v) {
+// The six steps depend on each other; `fill` is called between them and may bring in other work.
+template <typename F>
+__device__ __forceinline__ double wave_allsum(double v, F&& fill) {
     v += dpp_move<0x128>(v);
+    fill();
     v += dpp_move<0x124>(v);
+    fill();
     v += dpp_move<0x122>(v);
+    fill();
     v += dpp_move<0x121>(v);
+    fill();
     {
         const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
         auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
         auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
         v = __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
     }
+    fill();
     {
         const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
         auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
@@ -83,6 +92,7 @@ __device__ __forceinline__ double wave_allsum(double v) {
     }
     return v;
 }
+__device__ __forceinline__ double wave_allsum(double v) { return wave_allsum(v, [] {}); }
 
 __device__ __forceinline__ double block_sum(double v, double* red, int tid) {
     v = wave_allsum(v);
@@ -111,14 +121,11 @@ __device__ __forceinline__ void dpp_ready(double& a, double& b) { asm volatile("
 __device__ __forceinline__ double lane_value(double v, int l) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
 }
-// entry r (wave-uniform, 0 .. 127) of a vector held as entries lane and lane + 64
-__device__ __forceinline__ double entry(double lo, double hi, int r) { return lane_value(r < 64 ? lo : hi, r & 63); }
-
-template <int U, typename F>
+template <int U, int END = 16, typename F>
 __device__ __forceinline__ void each16(F&& f) {
-    if constexpr (U < 16) {
+    if constexpr (U < END) {
         f(std::integral_constant<int, U>{});
-        each16<U + 1>(f);
+        each16<U + 1, END>(f);
     }
 }
 
@@ -236,17 +243,32 @@ __global__ __launch_bounds__(kTriThreads, 2) void tridiag_entropy_kernel(
     }
 
     // ---- 2. Householder tridiagonalisation ---------------------------------------------------
+    // Every wave carries x = row i (entries at columns <= i zeroed) and y = row i + 1, twice: as entries
+    // lane + 64 s and as entries row0 + 64 j, the DPP operands of its row blocks.  Entries at done columns of
+    // y, w and A, and done rows of A, hold finite leftovers that only ever meet zeros of x.
+    //
+    // With v = x - alpha e_{i+1}, A v = A x - alpha y and w = beta A v + K v, the update of what is still in
+    // play (rows and columns > i + 1, where v = x) is A -= x (beta A v)^T + (beta A v + 2 K x) x^T: the first
+    // half does not wait for K and fills the latency of the sum behind it; the second half and the next A x
+    // fill that of the next reflection's norm and square root.  Row i + 3 is put into LDS behind the barrier of
+    // reflection i, where the waves wait for their reads, as it stands before that reflection's update, which
+    // the readers make up for one reflection later (xo, wo, xro, wro: x and w of the reflection before).
+    const int row0 = 16 * q + (lane & 15);
+    double x[2], y[2], xr[2], yr[2], xo[2] = {0.0, 0.0}, w2r[2] = {0.0, 0.0};
+    double wo[2] = {0.0, 0.0}, xro[2] = {0.0, 0.0}, wro[2] = {0.0, 0.0}, x3 = 0.0, w3 = 0.0;
     // Row `row` of the matrix (in the registers of one wave) to LDS: a switch on the wave-uniform register
-    // number reaches it without indexing.
-#define UNCOMP_TRI_CASE(K)                             \
-    case K:                                            \
-        to[lane] = a[(K) >> 4][0][(K) & 15];           \
-        to[lane + 64] = a[(K) >> 4][1][(K) & 15];      \
+    // number reaches it without indexing.  (Taking column `row` from one lane of every wave instead needs no
+    // branches, but sixteen to thirty-two LDS writes of one lane each take 700 cycles.)
+#define UNCOMP_TRI_CASE(K)                                               \
+    case K:                                                              \
+        if constexpr (MODE.value < 2) to[lane] = a[(K) >> 4][0][(K) & 15]; \
+        if constexpr (MODE.value < 2 || (K) >= 16) to[lane + 64] = a[(K) >> 4][1][(K) & 15]; \
+        asm volatile("; row %0" ::"n"(K)); /* the cases stay apart: merged, they would index the registers */ \
         break;
 #define UNCOMP_TRI_CASE8(K)                                                                          \
     UNCOMP_TRI_CASE(K) UNCOMP_TRI_CASE(K + 1) UNCOMP_TRI_CASE(K + 2) UNCOMP_TRI_CASE(K + 3)          \
     UNCOMP_TRI_CASE(K + 4) UNCOMP_TRI_CASE(K + 5) UNCOMP_TRI_CASE(K + 6) UNCOMP_TRI_CASE(K + 7)
-    auto publish = [&](int row, double* to) {
+    auto publish = [&](auto MODE, int row, double* to) {
         if (((row >> 4) & 3) != q) return;
         switch ((row >> 6) * 16 + (row & 15)) {
             UNCOMP_TRI_CASE8(0) UNCOMP_TRI_CASE8(8) UNCOMP_TRI_CASE8(16) UNCOMP_TRI_CASE8(24)
@@ -256,12 +278,11 @@ __global__ __launch_bounds__(kTriThreads, 2) void tridiag_entropy_kernel(
     };
 #undef UNCOMP_TRI_CASE8
 #undef UNCOMP_TRI_CASE
-    // Every wave carries x = row i (entries at columns <= i zeroed) and y = row i + 1, twice: as entries
-    // lane, lane + 64 (index s) and as entries 16 (q + 4 j) + lane%16, the DPP operands of its rows (index j).
-    const int row0 = 16 * q + (lane & 15);
-    double x[2], y[2], xr[2], yr[2];
-    publish(0, sm.pbuf[1][0]);
-    publish(1, sm.pbuf[1][1]);
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    publish(I0{}, 0, sm.pbuf[1][0]);
+    publish(I0{}, 1, sm.pbuf[1][1]);
+    publish(I0{}, 2, sm.zrow[0]);
     __syncthreads();
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -277,89 +298,165 @@ __global__ __launch_bounds__(kTriThreads, 2) void tridiag_entropy_kernel(
     if (lane == 0) x[0] = 0.0;
     if (row0 == 0) xr[0] = 0.0;
 
-    for (int i = 0; i < kD - 2; ++i) {
+    // One reflection.  MODE 0: i <= 60 (entries i + 1 .. i + 3 in the first half); 1: i = 61, 62; 2: i >= 63,
+    // where the first 64 rows and columns are done.
+    auto reflect = [&](auto MODE, int i) {
+        constexpr int S0 = MODE.value == 2 ? 1 : 0;             // first column half / row block in play
+        auto entry = [&](const double (&v)[2], int r) {         // entry r of a vector held as entries lane + 64 s
+            if constexpr (MODE.value == 1) return lane_value(r < 64 ? v[0] : v[1], r & 63);
+            else return lane_value(v[MODE.value / 2], r & 63);
+        };
         double* pb = sm.pbuf[i & 1][0];
         double* zb = sm.zrow[i & 1];
-        publish(i + 2, zb);
-        const bool top = 16 * q + 15 > i, bottom = 16 * q + 79 > i;     // row blocks still in play
-        const bool left = i < 63;                                       // columns 0 .. 63 still in play
-        // the wave's part of A x
+        const bool top = S0 == 0 && 16 * q + 15 > i;            // this wave's first row block still in play
         double p[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+        // pending second half of the previous update and the product A x on one row block, four FMAs a call
+        dpp_ready(w2r[0], w2r[1]);
         dpp_ready(xr[0], xr[1]);
-        if (bottom) {
-            if (left) each16<0>([&](auto U) { fmac_bc<U.value>(p[1][0], xr[1], a[1][0][U.value]); fmac_bc<U.value>(p[1][1], xr[1], a[1][1][U.value]); });
-            else each16<0>([&](auto U) { fmac_bc<U.value>(p[1][U.value & 1], xr[1], a[1][1][U.value]); });
-        }
-        if (!left) { p[0][1] = p[1][0]; p[1][0] = 0.0; }
-        if (top) each16<0>([&](auto U) { fmac_bc<U.value>(p[0][0], xr[0], a[0][0][U.value]); fmac_bc<U.value>(p[0][1], xr[0], a[0][1][U.value]); });
-        pb[q * kD + lane] = p[0][0] + p[1][0];
-        pb[q * kD + lane + 64] = p[0][1] + p[1][1];
-        // v = x - alpha e_{i+1}, |alpha| = |x|, sign against cancellation; e_i^2 = alpha^2.  Independent of A x.
-        const double sigma = wave_allsum(fma(x[0], x[0], x[1] * x[1]));
-        const double x1 = entry(x[0], x[1], i + 1);
-        double rs = __builtin_amdgcn_rsq(sigma);                        // 1 / |x|: hardware estimate, two Newton steps
-        rs = fma(0.5 * rs, fma(-sigma * rs, rs, 1.0), rs);
-        rs = fma(0.5 * rs, fma(-sigma * rs, rs, 1.0), rs);
-        double nrm = sigma * rs;
-        nrm = fma(0.5 * rs, fma(-nrm, nrm, sigma), nrm);
-        const bool some = sigma > 0x1p-900;                             // nothing to reflect: beta = 0 leaves the matrix as it is
-        const double alpha = some ? (x1 >= 0.0 ? -nrm : nrm) : 0.0;
+        auto chunk = [&](auto J, auto C) {
+            constexpr int kPer = 4 * (2 - S0);                  // chunks of the update, then as many of the product
+            constexpr int c = C.value % kPer, s = S0 + c / 4, u0 = 4 * (c % 4);
+            if constexpr (C.value < kPer)
+                each16<u0, u0 + 4>([&](auto U) { fnmac_bc<U.value>(a[J.value][s][U.value], w2r[J.value], xo[s]); });
+            else if constexpr (S0 == 0)                         // two chains of the product side by side
+                each16<2 * c, 2 * c + 2>([&](auto U) {
+                    fmac_bc<U.value>(p[J.value][0], xr[J.value], a[J.value][0][U.value]);
+                    fmac_bc<U.value>(p[J.value][1], xr[J.value], a[J.value][1][U.value]);
+                });
+            else
+                each16<u0, u0 + 4>([&](auto U) { fmac_bc<U.value>(p[U.value & 1][1], xr[J.value], a[J.value][1][U.value]); });
+        };
+        // sigma = |x|^2, alpha = -sign(x_{i+1}) |x|, beta = 1 / (sigma + |x_{i+1}| |x|); e_i^2 = sigma.  The
+        // hardware estimates (2^-24) are brought to full precision by one third-order step each.
+        const double x1 = entry(x, i + 1), x2 = entry(x, i + 2);
+        const double y1 = entry(y, i + 1);
+        double sigma = S0 == 0 ? fma(x[0], x[0], x[1] * x[1]) : x[1] * x[1];
+#define UNCOMP_CHUNK(c) chunk(I1{}, std::integral_constant<int, S0 == 0 ? (c) : (c) / 2>{})
+        int n_fill = 0;
+        auto fill = [&] {
+            if (n_fill == 0) UNCOMP_CHUNK(0);
+            if (n_fill == 1) { if constexpr (S0 == 0) UNCOMP_CHUNK(1); }
+            if (n_fill == 2) UNCOMP_CHUNK(2);
+            if (n_fill == 3) { if constexpr (S0 == 0) UNCOMP_CHUNK(3); }
+            if (n_fill == 4) UNCOMP_CHUNK(4);
+            ++n_fill;
+        };
+        sigma = wave_allsum(sigma, fill);
+        if constexpr (S0 == 0) UNCOMP_CHUNK(5);
+        double rs = __builtin_amdgcn_rsq(sigma);
+        UNCOMP_CHUNK(6);
+        const double t = sigma * rs;
+        if constexpr (S0 == 0) UNCOMP_CHUNK(7);
+        const double er = fma(-t, rs, 1.0);
+        UNCOMP_CHUNK(8);
+        rs = fma(rs * er, fma(0.375, er, 0.5), rs);
+        if constexpr (S0 == 0) UNCOMP_CHUNK(9);
+        const double nrm = sigma * rs;
+        UNCOMP_CHUNK(10);
         const double den = fma(fabs(x1), nrm, sigma);
+        if constexpr (S0 == 0) UNCOMP_CHUNK(11);
         double beta = __builtin_amdgcn_rcp(den);
-        beta = fma(fma(-den, beta, 1.0), beta, beta);
-        beta = fma(fma(-den, beta, 1.0), beta, beta);
+        UNCOMP_CHUNK(12);
+        const double eb = fma(-den, beta, 1.0);
+        if constexpr (S0 == 0) UNCOMP_CHUNK(13);
+        beta = fma(beta, fma(eb, eb, eb), beta);
+        UNCOMP_CHUNK(14);
+        if constexpr (S0 == 0) UNCOMP_CHUNK(15);
+#undef UNCOMP_CHUNK
+        const bool some = sigma > 0x1p-900;                     // nothing to reflect: beta = 0 leaves the matrix as it is
+        const double alpha = some ? (x1 >= 0.0 ? -nrm : nrm) : 0.0;
         beta = some ? beta : 0.0;
+        if (top) each16<0>([&](auto C) { chunk(I0{}, C); });
+        if constexpr (S0 == 0) pb[q * kD + lane] = p[0][0] + p[1][0];
+        pb[q * kD + lane + 64] = p[0][1] + p[1][1];
         if (tid == 0) sm.e2[i + 1] = sigma;
         __syncthreads();
-        double Av[2], Avr[2], z[2], zr[2], v[2], vr[2], w[2], wr[2];
+
+        double wb[2], wbr[2], z[2], zr[2], pc[2][4], pr[2][4], sum = 0.0;           // wb = beta A v
+        double p_own[2];
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const double* pc = pb + lane + 64 * s;
-            const double* pr = pb + row0 + 64 * s;
-            Av[s] = fma(-alpha, y[s], (pc[0] + pc[kD]) + (pc[2 * kD] + pc[3 * kD]));
-            Avr[s] = fma(-alpha, yr[s], (pr[0] + pr[kD]) + (pr[2 * kD] + pr[3 * kD]));
+        for (int s = S0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                pc[s][t] = pb[t * kD + lane + 64 * s];
+                pr[s][t] = pb[t * kD + row0 + 64 * s];
+            }
+#pragma unroll
+        for (int s = S0; s < 2; ++s) {
             z[s] = zb[lane + 64 * s];
             zr[s] = zb[row0 + 64 * s];
-            v[s] = lane + 64 * s == i + 1 ? x[s] - alpha : x[s];
-            vr[s] = row0 + 64 * s == i + 1 ? xr[s] - alpha : xr[s];
-            Av[s] = lane + 64 * s > i ? Av[s] : 0.0;                    // columns that are done hold no part of A x
-            Avr[s] = row0 + 64 * s > i ? Avr[s] : 0.0;
         }
-        const double vAv = wave_allsum(fma(v[0], Av[0], v[1] * Av[1]));
-        const double K = -0.5 * beta * beta * vAv;
+        __builtin_amdgcn_sched_barrier(0);                      // the reads are on their way
+        if (i + 3 < kD) publish(MODE, i + 3, sm.zrow[(i + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            w[s] = fma(beta, Av[s], K * v[s]);
-            wr[s] = fma(beta, Avr[s], K * vr[s]);
+        for (int s = S0; s < 2; ++s) {
+            p_own[s] = (pc[s][0] + pc[s][1]) + (pc[s][2] + pc[s][3]);
+            const double p_row = (pr[s][0] + pr[s][1]) + (pr[s][2] + pr[s][3]);
+            sum = fma(x[s], p_own[s], sum);
+            wb[s] = beta * fma(-alpha, y[s], p_own[s]);
+            wbr[s] = beta * fma(-alpha, yr[s], p_row);
         }
-        // rows i + 1 and i + 2 as the update leaves them
-        const double v1 = x1 - alpha, w1 = entry(w[0], w[1], i + 1);
-        const double v2 = entry(v[0], v[1], i + 2), w2 = entry(w[0], w[1], i + 2);
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            x[s] = fma(-v1, w[s], fma(-w1, v[s], y[s]));
-            xr[s] = fma(-v1, wr[s], fma(-w1, vr[s], yr[s]));
-            y[s] = fma(-v2, w[s], fma(-w2, v[s], z[s]));
-            yr[s] = fma(-v2, wr[s], fma(-w2, vr[s], zr[s]));
-            if (q == 0 && lane + 64 * s == i + 1) sm.d[i + 1] = x[s];
-            x[s] = lane + 64 * s > i + 1 ? x[s] : 0.0;
-            xr[s] = row0 + 64 * s > i + 1 ? xr[s] : 0.0;
-        }
-        dpp_ready(vr[0], vr[1]);
-        dpp_ready(wr[0], wr[1]);
-        auto update = [&](double (&block)[16], double rv, double rw, double cv, double cw) {
-            each16<0>([&](auto U) { fnmac_bc<U.value>(block[U.value], rv, cw); });
-            each16<0>([&](auto U) { fnmac_bc<U.value>(block[U.value], rw, cv); });
+        const double p1 = entry(p_own, i + 1);
+        int n_fill2 = 0;
+        auto first = [&](auto J, auto S, auto U0) {             // A -= x (beta A v)^T, four rows of one column half
+            each16<U0.value, U0.value + 4>([&](auto U) { fnmac_bc<U.value>(a[J.value][S.value][U.value], xr[J.value], wb[S.value]); });
         };
-        if (bottom) {
-            update(a[1][1], vr[1], wr[1], v[1], w[1]);
-            if (left) update(a[1][0], vr[1], wr[1], v[0], w[0]);
+        auto fill2 = [&] {
+            if (n_fill2 == 0) first(I1{}, I1{}, std::integral_constant<int, 0>{});
+            if (n_fill2 == 1) first(I1{}, I1{}, std::integral_constant<int, 4>{});
+            if (n_fill2 == 2) first(I1{}, I1{}, std::integral_constant<int, 8>{});
+            if (n_fill2 == 3) first(I1{}, I1{}, std::integral_constant<int, 12>{});
+            if constexpr (S0 == 0) {
+                if (n_fill2 == 4) first(I1{}, I0{}, std::integral_constant<int, 0>{});
+            }
+            ++n_fill2;
+        };
+        sum = wave_allsum(sum, fill2);
+        // v^T A v = x^T A x - 2 alpha (A x)_{i+1} + alpha^2 A_{i+1,i+1}
+        const double vAv = fma(alpha, fma(alpha, y1, -2.0 * p1), sum);
+        if constexpr (S0 == 0) first(I1{}, I0{}, std::integral_constant<int, 4>{});
+        const double K = -0.5 * beta * beta * vAv;
+        const double v1 = x1 - alpha, w1 = fma(K, v1, beta * fma(-alpha, y1, p1));
+        if constexpr (S0 == 0) first(I1{}, I0{}, std::integral_constant<int, 8>{});
+        double w[2], wr[2];
+#pragma unroll
+        for (int s = S0; s < 2; ++s) {
+            w[s] = fma(K, x[s], wb[s]);
+            wr[s] = fma(K, xr[s], wbr[s]);
+            w2r[s] = fma(K, xr[s], wr[s]);
         }
+        if constexpr (S0 == 0) first(I1{}, I0{}, std::integral_constant<int, 12>{});
         if (top) {
-            update(a[0][0], vr[0], wr[0], v[0], w[0]);
-            update(a[0][1], vr[0], wr[0], v[1], w[1]);
+            each16<0>([&](auto U) { fnmac_bc<U.value>(a[0][0][U.value], xr[0], wb[0]); });
+            each16<0>([&](auto U) { fnmac_bc<U.value>(a[0][1][U.value], xr[0], wb[1]); });
         }
-    }
+        // row i + 2 as the previous update left it, then rows i + 1 and i + 2 as this one leaves them
+#pragma unroll
+        for (int s = S0; s < 2; ++s) {
+            z[s] = fma(-x3, wo[s], fma(-w3, xo[s], z[s]));
+            zr[s] = fma(-x3, wro[s], fma(-w3, xro[s], zr[s]));
+        }
+        const double w2 = entry(w, i + 2);
+        if (tid == 0) sm.d[i + 1] = fma(-2.0 * v1, w1, y1);
+        x3 = entry(x, i + 3);
+        w3 = entry(w, i + 3);
+#pragma unroll
+        for (int s = S0; s < 2; ++s) {
+            const double xn = fma(-v1, w[s], fma(-w1, x[s], y[s])), xnr = fma(-v1, wr[s], fma(-w1, xr[s], yr[s]));
+            y[s] = fma(-x2, w[s], fma(-w2, x[s], z[s]));
+            yr[s] = fma(-x2, wr[s], fma(-w2, xr[s], zr[s]));
+            xo[s] = x[s];
+            wo[s] = w[s];
+            xro[s] = xr[s];
+            wro[s] = wr[s];
+            x[s] = lane + 64 * s > i + 1 ? xn : 0.0;
+            xr[s] = row0 + 64 * s > i + 1 ? xnr : 0.0;
+        }
+    };
+    for (int i = 0; i < 61; ++i) reflect(I0{}, i);
+    for (int i = 61; i < 63; ++i) reflect(I1{}, i);
+    for (int i = 63; i < kD - 2; ++i) reflect(std::integral_constant<int, 2>{}, i);
     // x = row 126 (masked), y = row 127
     if (tid == 63) {
         sm.e2[kD - 1] = x[1] * x[1];
