@@ -181,6 +181,8 @@ __global__ __launch_bounds__(256) void score_stats_lastrow_kernel(
 // are clamped to the last valid token instead of predicated: straight-line loads let the
 // compiler keep exact counts of the loads in flight (a predicated load makes it wait for all
 // of them), and whatever a token past the end contributes is masked or never stored.
+// Heads of 64 features (DD = 64) halve the matrix work and the key bytes per token; the exponentials stay, so these
+// variants are bound by vector-instruction issue.
 // ---------------------------------------------------------------------------------------
 
 // pass 1 without barriers: same streaming scheme as the vote kernel below (queries in LDS, every
@@ -188,78 +190,85 @@ __global__ __launch_bounds__(256) void score_stats_lastrow_kernel(
 // holds ONE query row (lane%16 of the block) and 16 tokens of the tile: a row's running
 // (reference, sum of exp2) is then a single pair of registers per block, updated once per tile.
 // Every wave writes its own partial statistics (4 per chunk); the merge kernel combines them.
-template <int NRB>     // 16-row blocks the LDS and the per-lane state are sized for
+template <int NRB, int DD>     // 16-row blocks the LDS and the per-lane state are sized for, features per head
 __global__ __launch_bounds__(256, 2) void score_stats_wave_kernel(
-    const bf16_bits* __restrict__ Q, const bf16_bits* __restrict__ K, int H, int R, int N, int w,
+    const bf16_bits* __restrict__ Q, const bf16_bits* __restrict__ K, int H, int R, int n_rg, int N, int w,
     int64_t ks_b, int64_t ks_h, int64_t ks_t, int n_chunks, int chunk, float2* __restrict__ stats) {
+    constexpr int kRowBytes = row_bytes(DD), kPieces = DD / 8;
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* qs = smem;                                             // [16*NRB][kRowBytes]
-    const int bh = blockIdx.x / n_chunks, c = blockIdx.x % n_chunks;
+    // the row groups of a chunk are neighbours in the launch: the second one finds the keys in the last-level cache
+    const int rg = blockIdx.x % n_rg, bc = blockIdx.x / n_rg;
+    const int bh = bc / n_chunks, c = bc % n_chunks;
     const int b = bh / H, h = bh % H;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const bf16_bits* Qh = Q + (int64_t)bh * R * kD;
-    for (int idx = tid; idx < 16 * NRB * 16; idx += 256) {
-        const int row = idx >> 4, piece = idx & 15;
+    const int R_head = R * n_rg, row0 = R * rg;        // rows of the KV head, first row of this group
+    const bf16_bits* Qh = Q + ((int64_t)bh * R_head + row0) * DD;
+    for (int idx = tid; idx < 16 * NRB * kPieces; idx += 256) {
+        const int row = idx / kPieces, piece = idx % kPieces;
         uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (row < R) v = *reinterpret_cast<const uint4*>(Qh + (int64_t)row * kD + piece * 8);
+        if (row < R) v = *reinterpret_cast<const uint4*>(Qh + (int64_t)row * DD + piece * 8);
         *reinterpret_cast<uint4*>(qs + row * kRowBytes + piece * 16) = v;
     }
     __syncthreads();
     const int t_begin = c * chunk, t_end = min(N, t_begin + chunk);
-    score_stats_wave_body<NRB>(qs, K + b * ks_b + h * ks_h, ks_t, t_begin, t_end, N - w, w, R, wv, lane,
-                               stats + ((int64_t)bh * (n_chunks * 4) + c * 4 + wv) * R);
+    score_stats_wave_body<NRB, DD>(qs, K + b * ks_b + h * ks_h, ks_t, t_begin, t_end, N - w, w, R, wv, lane,
+                               stats + ((int64_t)bh * (n_chunks * 4) + c * 4 + wv) * R_head + row0);
 }
-template <int NRB, bool W8 = false>     // LDS is sized for 16*NRB query rows; W8: the window is 8 positions
+template <int NRB, bool W8, int DD>     // LDS is sized for 16*NRB query rows; W8: the window is 8 positions
 __global__ __launch_bounds__(256) void score_vote_wave_kernel(
     const bf16_bits* __restrict__ Q, const bf16_bits* __restrict__ K, const float* __restrict__ lse, int H,
-    int G, int N, int w, int64_t ks_b, int64_t ks_h, int64_t ks_t, int n_chunks, int chunk,
+    int G, int n_rg, int N, int w, int64_t ks_b, int64_t ks_h, int64_t ks_t, int n_chunks, int chunk,
     float* __restrict__ vote) {
+    constexpr int kRowBytes = row_bytes(DD), kPieces = DD / 8, kKs = DD / 32;
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* qs = smem;                                             // [16*NRB][kRowBytes]
     float* nls = reinterpret_cast<float*>(smem + 16 * NRB * kRowBytes);   // [16*NRB] minus lse (base 2)
-    const int bh = blockIdx.x / n_chunks, c = blockIdx.x % n_chunks;
+    const int rg = blockIdx.x % n_rg, bc = blockIdx.x / n_rg;
+    const int bh = bc / n_chunks, c = bc % n_chunks;
     const int b = bh / H, h = bh % H;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int m = lane & 15, g = lane >> 4;
-    const int R = G * w, P = N - w;
+    const int R = G / n_rg * w, P = N - w;         // rows of this group of query heads
     const int n_rb = R >> 4, bph = w >> 4;          // 16-row blocks per KV head / per query head
     const bf16_bits* Kh = K + b * ks_b + h * ks_h;
-    const float scale2 = kLog2e * rsqrtf((float)kD);
+    const float scale2 = kLog2e * rsqrtf((float)DD);
     const int t_begin = c * chunk, t_end = min(P, t_begin + chunk);
     if (t_begin >= t_end) return;
     const int n_tiles = (t_end - t_begin + kTile - 1) / kTile;
 
-    const bf16_bits* Qh = Q + (int64_t)bh * R * kD;
-    for (int idx = tid; idx < 16 * NRB * 16; idx += 256) {
-        const int row = idx >> 4, piece = idx & 15;
+    const int64_t row0 = (int64_t)bh * G * w + R * rg;
+    const bf16_bits* Qh = Q + row0 * DD;
+    for (int idx = tid; idx < 16 * NRB * kPieces; idx += 256) {
+        const int row = idx / kPieces, piece = idx % kPieces;
         uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (row < R) v = *reinterpret_cast<const uint4*>(Qh + (int64_t)row * kD + piece * 8);
+        if (row < R) v = *reinterpret_cast<const uint4*>(Qh + (int64_t)row * DD + piece * 8);
         *reinterpret_cast<uint4*>(qs + row * kRowBytes + piece * 16) = v;
     }
-    for (int r = tid; r < 16 * NRB; r += 256) nls[r] = r < R ? -lse[(int64_t)bh * R + r] : 0.f;
+    for (int r = tid; r < 16 * NRB; r += 256) nls[r] = r < R ? -lse[row0 + r] : 0.f;
     __syncthreads();
 
-    float* vote_h = vote + (int64_t)bh * G * P;
-    uint4 ka[4][4], kb[4][4];                        // [sub-tile][k-step] B operands of two tiles
-    auto load_tile = [&](uint4 dst[4][4], int tile) {            // clamped, never predicated
+    float* vote_h = vote + ((int64_t)bh * G + G / n_rg * rg) * P;
+    uint4 ka[4][kKs], kb[4][kKs];                        // [sub-tile][k-step] B operands of two tiles
+    auto load_tile = [&](uint4 dst[4][kKs], int tile) {            // clamped, never predicated
         const int t0 = t_begin + tile * kTile;
 #pragma unroll
         for (int st = 0; st < 4; ++st) {
             const int tok = min(t0 + 16 * st + m, t_end - 1);
             const bf16_bits* src = Kh + (int64_t)tok * ks_t + 8 * g;
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) dst[st][ks] = *reinterpret_cast<const uint4*>(src + 32 * ks);
+            for (int ks = 0; ks < kKs; ++ks) dst[st][ks] = *reinterpret_cast<const uint4*>(src + 32 * ks);
         }
     };
-    struct RowBlock { bf16x8_t a[4]; float4 nl; };     // A operands and normalisers of one 16-row block
+    struct RowBlock { bf16x8_t a[kKs]; float4 nl; };     // A operands and normalisers of one 16-row block
     auto read_block = [&](RowBlock& rbk, int rb) {
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
+        for (int ks = 0; ks < kKs; ++ks)
             rbk.a[ks] = __builtin_bit_cast(
                 bf16x8_t, *reinterpret_cast<const uint4*>(qs + (16 * rb + m) * kRowBytes + 64 * ks + 16 * g));
         rbk.nl = *reinterpret_cast<const float4*>(nls + 16 * rb + 4 * g);
     };
-    auto process = [&](const uint4 cur[4][4], uint4 nxt[4][4], int tile) {
+    auto process = [&](const uint4 cur[4][kKs], uint4 nxt[4][kKs], int tile) {
         load_tile(nxt, tile + 4);
         const int t0 = t_begin + tile * kTile;
         float pq[4] = {0.f, 0.f, 0.f, 0.f};          // per sub-tile: this lane's rows of the current query head
@@ -270,7 +279,7 @@ __global__ __launch_bounds__(256) void score_vote_wave_kernel(
             for (int st = 0; st < 4; ++st) acc[st] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             __builtin_amdgcn_s_setprio(1);                        // matrix work first: the partner wave fills the gaps
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
+            for (int ks = 0; ks < kKs; ++ks)
 #pragma unroll
                 for (int st = 0; st < 4; ++st)
                     acc[st] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
@@ -510,17 +519,47 @@ __global__ __launch_bounds__(256) void score_pool_kernel(const float* __restrict
     }
 }
 
-// staged query rows of the MFMA kernels: up to 128 / 256 rows per KV head
-constexpr int kScoreLds8 = 16 * 8 * kRowBytes, kScoreLds16 = 16 * 16 * kRowBytes;
+// The MFMA kernels in the variant for `rows` query rows (up to 128, or up to 256), a window of 8 or not, D features.
+typedef void (*StatsKernel)(const bf16_bits*, const bf16_bits*, int, int, int, int, int, int64_t, int64_t, int64_t, int, int,
+                            float2*);
+typedef void (*VoteKernel)(const bf16_bits*, const bf16_bits*, const float*, int, int, int, int, int, int64_t, int64_t,
+                           int64_t, int, int, float*);
+constexpr int kScoreRows = 256;     // rows one workgroup of the MFMA kernels holds at most
+static StatsKernel stats_kernel(int rows, int D) {
+    if (D == 64) return rows <= 128 ? score_stats_wave_kernel<8, 64> : score_stats_wave_kernel<16, 64>;
+    return rows <= 128 ? score_stats_wave_kernel<8, kD> : score_stats_wave_kernel<16, kD>;
+}
+static VoteKernel vote_kernel(int rows, bool w8, int D) {
+    if (D == 64) {
+        if (w8) return rows <= 128 ? score_vote_wave_kernel<8, true, 64> : score_vote_wave_kernel<16, true, 64>;
+        return rows <= 128 ? score_vote_wave_kernel<8, false, 64> : score_vote_wave_kernel<16, false, 64>;
+    }
+    if (w8) return rows <= 128 ? score_vote_wave_kernel<8, true, kD> : score_vote_wave_kernel<16, true, kD>;
+    return rows <= 128 ? score_vote_wave_kernel<8, false, kD> : score_vote_wave_kernel<16, false, kD>;
+}
+static int stats_lds_bytes(int rows, int D) { return (rows <= 128 ? 128 : 256) * row_bytes(D); }
+static int vote_lds_bytes(int rows, int D) { return (rows <= 128 ? 128 : 256) * (row_bytes(D) + (int)sizeof(float)); }
 
 hipError_t init_score_kernels() {
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(score_stats_wave_kernel<8>), kScoreLds8);
-    if (e == hipSuccess) e = allow_dynamic_lds(reinterpret_cast<const void*>(score_stats_wave_kernel<16>), kScoreLds16);
-    if (e == hipSuccess) e = allow_dynamic_lds(reinterpret_cast<const void*>(score_vote_wave_kernel<8, true>), kScoreLds8 + 16 * 8 * 4);
-    if (e == hipSuccess) e = allow_dynamic_lds(reinterpret_cast<const void*>(score_vote_wave_kernel<8, false>), kScoreLds8 + 16 * 8 * 4);
-    if (e == hipSuccess) e = allow_dynamic_lds(reinterpret_cast<const void*>(score_vote_wave_kernel<16, true>), kScoreLds16 + 16 * 16 * 4);
-    if (e == hipSuccess) e = allow_dynamic_lds(reinterpret_cast<const void*>(score_vote_wave_kernel<16, false>), kScoreLds16 + 16 * 16 * 4);
+    hipError_t e = hipSuccess;
+    for (int D : {64, kD})
+        for (int rows : {128, 256}) {
+            if (e == hipSuccess) e = allow_dynamic_lds(reinterpret_cast<const void*>(stats_kernel(rows, D)), stats_lds_bytes(rows, D));
+            for (bool w8 : {false, true})
+                if (e == hipSuccess) e = allow_dynamic_lds(reinterpret_cast<const void*>(vote_kernel(rows, w8, D)), vote_lds_bytes(rows, D));
+        }
     return e;
+}
+
+// Row groups (whole query heads each) that the MFMA kernels cut the G*w query rows of a KV head into, so that a group
+// is at most kScoreRows rows in whole 16-row blocks; 0 where there is no such cut.  Each group streams the keys once
+// more, which the matrix cores still do an order of magnitude faster than the plain-ALU kernels: 256 heads of 64
+// features, 5003 tokens, 128 rows take 78 us for both passes where the plain-ALU kernels took 2.46 ms.
+static int row_groups(int G, int w) {
+    if (w % 16 != 0 && w != 8) return 0;
+    for (int n = 1; n <= G; ++n)
+        if (G % n == 0 && G / n * w <= kScoreRows && G / n * w % 16 == 0) return n;
+    return 0;
 }
 
 ScorePlan plan_score(int B, int H, int G, int N, int w) {
@@ -549,14 +588,16 @@ ScorePlan plan_score(int B, int H, int G, int N, int w) {
 template <typename T>
 static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, int w, int pool,
                             const int64_t ks[3], const ScorePlan& p, char* ws, float* score_out,
-                            const Env& env, bool mfma, const float* lse_nat, int D) {
+                            const Env& env, int n_rg, const float* lse_nat, int D) {
     hipStream_t s = env.s;
     const int BH = B * H, P = N - w;
     float2* stats = reinterpret_cast<float2*>(ws + p.stats_off);
     float* lse = reinterpret_cast<float*>(ws + p.lse_off);
     float* vote = reinterpret_cast<float*>(ws + p.vote_off);
     uint32_t* tile_range = reinterpret_cast<uint32_t*>(ws + p.range_off);
-    const dim3 grid1((unsigned)(BH * p.n_chunks));
+    const bool mfma = n_rg > 0;          // row groups of the MFMA kernels, 0 for the plain-ALU ones
+    const int R_group = mfma ? p.R / n_rg : 0;
+    const dim3 grid1((unsigned)(BH * p.n_chunks * (mfma ? n_rg : 1)));
     int n_parts = p.n_chunks;            // partial statistics per query row
     const int rows = BH * p.R;
     const bool own_stats = lse_nat == nullptr;
@@ -568,15 +609,8 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
     if constexpr (sizeof(T) == 2) {
         if (mfma && own_stats) {
             env.begin("score_stats_wave");
-            if (p.R <= 128) {
-                constexpr int lds_bytes = kScoreLds8;
-                score_stats_wave_kernel<8><<<grid1, dim3(256), lds_bytes, s>>>(Q, K, H, p.R, N, w, ks[0], ks[1], ks[2],
-                                                                               p.n_chunks, p.chunk, stats);
-            } else {
-                constexpr int lds_bytes = kScoreLds16;
-                score_stats_wave_kernel<16><<<grid1, dim3(256), lds_bytes, s>>>(Q, K, H, p.R, N, w, ks[0], ks[1], ks[2],
-                                                                                p.n_chunks, p.chunk, stats);
-            }
+            stats_kernel(R_group, D)<<<grid1, dim3(256), stats_lds_bytes(R_group, D), s>>>(
+                Q, K, H, R_group, n_rg, N, w, ks[0], ks[1], ks[2], p.n_chunks, p.chunk, stats);
             env.end();
             n_parts = p.n_chunks * 4;
         }
@@ -619,15 +653,8 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
     if constexpr (sizeof(T) == 2) {
         if (mfma) {
             env.begin("score_vote_wave");
-            auto launch_vote = [&](auto kern, int lds_bytes) -> hipError_t {
-                kern<<<grid1, dim3(256), lds_bytes, s>>>(Q, K, lse, H, G, N, w, ks[0], ks[1], ks[2], p.n_chunks, p.chunk, vote);
-                return hipSuccess;
-            };
-            constexpr int lds8 = kScoreLds8 + 16 * 8 * 4, lds16 = kScoreLds16 + 16 * 16 * 4;
-            hipError_t ve;
-            if (w == 8) ve = p.R <= 128 ? launch_vote(score_vote_wave_kernel<8, true>, lds8) : launch_vote(score_vote_wave_kernel<16, true>, lds16);
-            else ve = p.R <= 128 ? launch_vote(score_vote_wave_kernel<8, false>, lds8) : launch_vote(score_vote_wave_kernel<16, false>, lds16);
-            if (ve != hipSuccess) return ve;
+            vote_kernel(R_group, w == 8, D)<<<grid1, dim3(256), vote_lds_bytes(R_group, D), s>>>(
+                Q, K, lse, H, G, n_rg, N, w, ks[0], ks[1], ks[2], p.n_chunks, p.chunk, vote);
             env.end();
         }
     }
@@ -659,14 +686,13 @@ hipError_t launch_window_score(const void* Q, const void* K, uncomp_dtype dt, in
                                int N, int w, int pool, const int64_t ks[3], const ScorePlan& p,
                                char* ws, float* score_out, const Env& env, const float* lse_nat, int D) {
     if (dt == UNCOMP_BF16) {
-        // the MFMA kernels need whole 16-row blocks per KV head, a window of 8 (the paper's l) or a multiple of 16,
-        // and at most 256 rows per KV head
-        const bool mfma = !env.force_alu && D == kD && (w % 16 == 0 || w == 8) && p.R <= 256 && p.R % 16 == 0;
+        // The MFMA kernels need whole 16-row blocks of query heads: a window of 8 (the paper's l) or a multiple of 16.
+        const int n_rg = env.force_alu ? 0 : row_groups(G, w);
         return run_score<bf16_bits>(static_cast<const bf16_bits*>(Q), static_cast<const bf16_bits*>(K), B, H,
-                                    G, N, w, pool, ks, p, ws, score_out, env, mfma, lse_nat, D);
+                                    G, N, w, pool, ks, p, ws, score_out, env, n_rg, lse_nat, D);
     }
     return run_score<float>(static_cast<const float*>(Q), static_cast<const float*>(K), B, H, G, N, w,
-                            pool, ks, p, ws, score_out, env, false, lse_nat, D);
+                            pool, ks, p, ws, score_out, env, 0, lse_nat, D);
 }
 
 }  // namespace uncomp

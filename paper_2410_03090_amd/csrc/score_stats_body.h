@@ -9,19 +9,20 @@
 namespace uncomp {
 
 constexpr int kTile = 64;                 // tokens per key tile
-constexpr int kRowBytes = 2 * kD + 16;    // padded LDS row of one query
+constexpr int row_bytes(int d) { return 2 * d + 16; }   // padded LDS row of one query of d features
 constexpr float kLog2e = 1.4426950408889634f;
 
-// qs: the head's query rows staged in LDS (rows of kRowBytes).  The wave (wv = 0..3 of the four that share a
+// qs: the head's query rows staged in LDS (rows of row_bytes(DD)).  The wave (wv = 0..3 of the four that share a
 // chunk) streams key tiles wv, wv + 4, ... of tokens [t_begin, t_end) and writes its partial (reference,
 // sum) of every query row to stats_rows[row].  No workgroup barrier inside.
-template <int NRB>
+template <int NRB, int DD>      // 16-row blocks held, features per head (128 or 64)
 __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, const bf16_bits* __restrict__ Kh,
                                                       int64_t ks_t, int t_begin, int t_end, int P, int w, int R,
                                                       int wv, int lane, float2* __restrict__ stats_rows) {
+    constexpr int kKs = DD / 32, kRowBytes = row_bytes(DD);
     const int m = lane & 15, g = lane >> 4;
     const int n_rb = R >> 4;
-    const float scale2 = kLog2e * rsqrtf((float)kD);
+    const float scale2 = kLog2e * rsqrtf((float)DD);
     const int n_tiles = t_end > t_begin ? (t_end - t_begin + kTile - 1) / kTile : 0;
     float nref[NRB], sum[NRB];         // of row 16*rb + m: minus the running reference, sum of exp2(logit - reference)
 #pragma unroll
@@ -29,30 +30,30 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
         nref[rb] = INFINITY;
         sum[rb] = 0.f;
     }
-    uint4 ka[4][4], kb[4][4];          // [sub-tile][k-step] key operands of two tiles
-    auto load_tile = [&](uint4 dst[4][4], int tile) {            // clamped, never predicated
+    uint4 ka[4][kKs], kb[4][kKs];          // [sub-tile][k-step] key operands of two tiles
+    auto load_tile = [&](uint4 dst[4][kKs], int tile) {            // clamped, never predicated
         const int t0 = t_begin + tile * kTile;
 #pragma unroll
         for (int st = 0; st < 4; ++st) {
             const int tok = min(t0 + 16 * st + m, t_end - 1);
             const bf16_bits* src = Kh + (int64_t)tok * ks_t + 8 * g;
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) dst[st][ks] = *reinterpret_cast<const uint4*>(src + 32 * ks);
+            for (int ks = 0; ks < kKs; ++ks) dst[st][ks] = *reinterpret_cast<const uint4*>(src + 32 * ks);
         }
     };
-    auto read_block = [&](bf16x8_t a[4], int rb) {
+    auto read_block = [&](bf16x8_t a[kKs], int rb) {
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
+        for (int ks = 0; ks < kKs; ++ks)
             a[ks] = __builtin_bit_cast(
                 bf16x8_t, *reinterpret_cast<const uint4*>(qs + (16 * rb + m) * kRowBytes + 64 * ks + 16 * g));
     };
-    auto process = [&](const uint4 cur[4][4], uint4 nxt[4][4], int tile) {
+    auto process = [&](const uint4 cur[4][kKs], uint4 nxt[4][kKs], int tile) {
         load_tile(nxt, tile + 4);
         const int t0 = t_begin + tile * kTile;
         const bool edge = t0 + kTile > P || t0 + kTile > t_end;   // causal window or ragged end inside
         // query operands are read one block ahead where registers allow (NRB = 8)
         constexpr bool kAhead = NRB <= 8;
-        bf16x8_t qa[kAhead ? 2 : 1][4];
+        bf16x8_t qa[kAhead ? 2 : 1][kKs];
         if (kAhead) read_block(qa[0], 0);
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb) {
@@ -68,7 +69,7 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
                 for (int st = 0; st < 4; ++st) acc[st] = f32x4_t{0.f, 0.f, 0.f, 0.f};
                 __builtin_amdgcn_s_setprio(1);                    // matrix work first: the partner wave fills the gaps
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks)
+                for (int ks = 0; ks < kKs; ++ks)
 #pragma unroll
                     for (int st = 0; st < 4; ++st)
                         acc[st] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(

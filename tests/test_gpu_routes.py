@@ -1,0 +1,47 @@
+"""Every form that a kernel route accepts against the float64 oracle, at the sizes where the route can go wrong:
+edges of tiles and chunks, remainders, the smallest and largest of its range, padded strides."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import uncomp_oracle as O
+from paper_2410_03090_amd import synth
+from tests._util import to_f64
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2410_03090_amd import binding
+    c = binding.Context(0, 256 << 20)
+    yield c
+    c.close()
+
+
+def _padded(t, extra):
+    """The same values with rows `extra` elements further apart."""
+    big = torch.full((*t.shape[:-1], t.shape[-1] + extra), 7.0, dtype=t.dtype, device=t.device)
+    view = big[..., : t.shape[-1]]
+    view.copy_(t)
+    return view
+
+
+# 64-wide heads and row groups (more than 256 query rows per KV head) through the matrix-core scoring kernels; G * w that
+# has no such cut stays on the plain-arithmetic ones.  Scores are held to 2e-5 relative as everywhere: fp32 logits of
+# magnitude <= ~16 carry ~1e-6 relative error into exp().
+@pytest.mark.parametrize("D,G,N,w", [
+    (64, 1, 17, 16), (64, 2, 65, 8), (64, 4, 2049, 32), (64, 4, 4161, 64), (64, 8, 2500, 16), (64, 8, 700, 64),
+    (64, 3, 300, 5), (128, 8, 4160, 64), (128, 16, 2111, 32), (128, 5, 1000, 64), (128, 64, 530, 8), (128, 17, 333, 16),
+    (128, 1, 1500, 512), (128, 2, 65, 48)])
+def test_score_head_widths_and_row_groups(ctx, D, G, N, w):
+    cfg = synth.tiny_config(dtype="bf16", B=2, H=2, G=G, N=N, D=D, w=w, rank_lo=2, rank_hi=48)
+    K, V, Q = synth.gen_all(cfg, seed0=N + G)
+    ref = O.window_score(to_f64(Q[0]), to_f64(K[0]), G=G, pool=7)
+    Qd, Kd = Q[0].to(DEV), K[0].to(DEV)
+    np.testing.assert_allclose(ctx.window_score(Qd, Kd, G=G, pool=7).cpu().numpy(), ref, rtol=2e-5)
+    np.testing.assert_allclose(ctx.window_score(Qd, _padded(Kd, 24), G=G, pool=7).cpu().numpy(), ref, rtol=2e-5)
+    lse = torch.from_numpy(O.window_lse(to_f64(Q[0]), to_f64(K[0]), G).astype(np.float32)).to(DEV)
+    np.testing.assert_allclose(ctx.window_score(Qd, Kd, G=G, pool=7, lse=lse).cpu().numpy(), ref, rtol=2e-5)
