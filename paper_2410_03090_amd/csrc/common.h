@@ -98,8 +98,8 @@ struct Env {
 };
 
 // ---- launchers (each returns the hipError_t of its launches) ---------------------------
-// D: features per token, 128, or 64 (then the plain-ALU kernel runs and features 64..127 of the 128-wide
-// partial sums are zero, which leaves the non-zero eigenvalues and the entropy as they are).
+// D: features per token, 128, or 64 (then features 64..127 of the 128-wide partial sums are zero, which leaves
+// the non-zero eigenvalues and the entropy as they are; fp32 takes the plain-ALU kernel).
 hipError_t launch_gram(const void* X, uncomp_dtype dt, int n_mat, int N, int64_t mat_stride,
                        int64_t ldx, const EntropyPlan& p, char* ws, const Env& env, int D = kD);
 hipError_t launch_jacobi_entropy(int n_mat, int N, int k_trunc, unsigned flags,

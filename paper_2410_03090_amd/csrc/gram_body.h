@@ -20,6 +20,9 @@ namespace uncomp {
 // mirrored on output.  Column sums come from v_dot2 against (1,1) on the same operands.
 // The eight waves of a workgroup (two per SIMD) take 32-token steps round-robin with kGramStages
 // steps of loads in flight each, and combine their accumulators through LDS at the end of the chunk.
+// Heads of 64 features (DD = 64): a step is 64 tokens, lanes m = 0..7 hold the first 32 of them and lanes 8..15 the
+// second 32, so every load is still 16 bytes and the instructions are the same; of a block (cA, cB) the quadrants
+// i, j < 8 and i, j >= 8 are the two halves' sums of G[8i'+cA][8j'+cB], the other two mix tokens and are dropped.
 // ---------------------------------------------------------------------------------------
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
@@ -46,20 +49,24 @@ __device__ __forceinline__ void gram_transpose(const uint4 raw[8], GramOperands&
 
 constexpr size_t kGramLdsBytes = (4 * kGramBlocks * 256 + 4 * 64 * 8) * sizeof(float);
 
-// One wave's share of a chunk: steps wv, wv + kWaves, ... of 32 tokens each (wv = 0..kWaves-1).  `base` points at
-// this lane's 8 features (8 * (lane % 16) ..) of token 0 of the matrix; g = lane / 16.
-template <int kGramStages, int kWaves>   // 32-token steps of loads in flight per wave; waves sharing the chunk
+// One wave's share of a chunk: steps wv, wv + kWaves, ... of 32 tokens each (64 for DD = 64; wv = 0..kWaves-1).  `base`
+// points at this lane's 8 features of token 0 of the matrix (gram_lane_feature); m = lane % 16, g = lane / 16.
+template <int DD>
+__device__ __forceinline__ int gram_lane_feature(int m) { return 8 * (DD == 64 ? m & 7 : m); }
+template <int kGramStages, int kWaves, int DD>   // steps of loads in flight per wave; waves sharing the chunk; features
 __device__ __forceinline__ void gram_wave_accumulate(const bf16_bits* __restrict__ base, int64_t ldx, int t_begin,
-                                                     int t_end, int wv, int g, f32x4_t acc[kGramBlocks],
+                                                     int t_end, int wv, int m, int g, f32x4_t acc[kGramBlocks],
                                                      float csum[8]) {
-    const int n_steps = (t_end - t_begin + 31) / 32;
+    constexpr int kStep = 32 * (kD / DD);
+    const int n_steps = (t_end - t_begin + kStep - 1) / kStep;
+    const int t_lane = t_begin + 8 * g + (DD == 64 ? 32 * (m >> 3) : 0);
 #pragma unroll
     for (int b = 0; b < kGramBlocks; ++b) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < 8; ++i) csum[i] = 0.f;
     uint4 buf[kGramStages][8];
     auto load_step = [&](uint4 dst[8], int step) {
-        const int t0 = t_begin + step * 32 + 8 * g;
+        const int t0 = t_lane + step * kStep;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int t = t0 + e;
@@ -133,10 +140,12 @@ __device__ __forceinline__ void gram_wave_add_from_lds(const float* red, int src
 }
 
 // After the barrier: the four waves' partials are added; `nt` threads write the 128x128 sum of the chunk
-// and its 128 column sums.
+// and its 128 column sums (zeros beyond DD features).
+template <int DD>
 __device__ __forceinline__ void gram_reduce_write(const float* red, int tid, int nt, float* __restrict__ G,
                                                   float* __restrict__ sum_out) {
     const float* sums = red + 4 * kGramBlocks * 256;
+    constexpr int kWave = kGramBlocks * 256;
     // element (R, C) = (8i+ca, 8j+cb) lives in block (ca, cb) at lane j + 16*(i/4), register i%4
     for (int e = tid; e < kD * kD; e += nt) {
         int R = e >> 7, C = e & 127;
@@ -146,16 +155,27 @@ __device__ __forceinline__ void gram_reduce_write(const float* red, int tid, int
             t = i; i = j; j = t;
         }
         const int off = tri_index(ca, cb) * 256 + (j + 16 * (i >> 2)) * 4 + (i & 3);
-        G[e] = (red[off] + red[off + kGramBlocks * 256]) + (red[off + 2 * kGramBlocks * 256] + red[off + 3 * kGramBlocks * 256]);
+        float v = 0.f;
+        if (DD == kD || (R < DD && C < DD)) v = (red[off] + red[off + kWave]) + (red[off + 2 * kWave] + red[off + 3 * kWave]);
+        if (DD == 64 && R < DD && C < DD) {           // the other token half: i + 8, j + 8
+            const int o2 = off + (8 + 32) * 4;
+            v += (red[o2] + red[o2 + kWave]) + (red[o2 + 2 * kWave] + red[o2 + 3 * kWave]);
+        }
+        G[e] = v;
     }
     if (tid < kD) {
-        // feature f = 8m + cc: add the 4 token groups g and the 4 waves
+        // feature f = 8m + cc: add the 4 token groups g and the 4 waves (and both token halves)
         const int mm = tid >> 3, cc = tid & 7;
         float t = 0.f;
+        if (tid < DD) {
 #pragma unroll
-        for (int w4 = 0; w4 < 4; ++w4)
+            for (int w4 = 0; w4 < 4; ++w4)
 #pragma unroll
-            for (int gg = 0; gg < 4; ++gg) t += sums[(w4 * 64 + gg * 16 + mm) * 8 + cc];
+                for (int gg = 0; gg < 4; ++gg) {
+                    t += sums[(w4 * 64 + gg * 16 + mm) * 8 + cc];
+                    if (DD == 64) t += sums[(w4 * 64 + gg * 16 + mm + 8) * 8 + cc];
+                }
+        }
         sum_out[tid] = t;
     }
 }

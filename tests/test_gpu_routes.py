@@ -45,3 +45,18 @@ def test_score_head_widths_and_row_groups(ctx, D, G, N, w):
     np.testing.assert_allclose(ctx.window_score(Qd, _padded(Kd, 24), G=G, pool=7).cpu().numpy(), ref, rtol=2e-5)
     lse = torch.from_numpy(O.window_lse(to_f64(Q[0]), to_f64(K[0]), G).astype(np.float32)).to(DEV)
     np.testing.assert_allclose(ctx.window_score(Qd, Kd, G=G, pool=7, lse=lse).cpu().numpy(), ref, rtol=2e-5)
+
+
+# Gram sums of 64-wide heads on the matrix cores: 64-token steps in two halves, N around the steps and the 128-token
+# chunk granularity.  The tolerances are those of the 128-wide kernel's tests (fp32 sums of exact products).
+@pytest.mark.parametrize("N", [2, 31, 33, 64, 65, 127, 129, 1000, 4099, 9001])
+def test_entropy_64_wide_heads(ctx, N):
+    g = torch.Generator().manual_seed(N)
+    X = (torch.randn(5, N, 12, generator=g) @ torch.randn(5, 12, 64, generator=g) / 12 +
+         0.1 * torch.randn(5, N, 64, generator=g) + 0.05).to(torch.bfloat16)
+    for flags in (O.DEFAULT_FLAGS, 0):
+        Href, eref = O.head_entropy(to_f64(X), k_trunc=32, flags=flags)
+        for Xd in (X.to(DEV), _padded(X.to(DEV), 8)):
+            H, eig = ctx.head_entropy(Xd, k_trunc=32, flags=flags, want_eig=True)
+            np.testing.assert_allclose(H.cpu().numpy(), Href, rtol=1e-4, atol=5e-5)
+            np.testing.assert_allclose(eig.cpu().numpy(), eref, rtol=0, atol=2e-5)
