@@ -68,7 +68,7 @@ struct ScorePlan {
     int R;               // query rows per KV head = G*w
     int n_chunks;        // token chunks per head for the softmax-statistics pass
     int chunk;           // tokens per chunk
-    size_t stats_off;    // float2 [BH][n_chunks][R]   (running max, running sum)
+    size_t stats_off;    // float2 [BH][4*n_chunks][R]   (running max, running sum)
     size_t lse_off;      // float  [BH][R]
     size_t vote_off;     // float  [BH][G][P]
     size_t range_off;    // uint32 [BH][n_range_tiles][2]: smallest / largest selection key of every 1024 scores

@@ -185,19 +185,29 @@ __global__ __launch_bounds__(256) void score_stats_lastrow_kernel(
 // variants are bound by vector-instruction issue.
 // ---------------------------------------------------------------------------------------
 
+// adds one partial (reference, sum of exp2 against it) to another
+__device__ __forceinline__ void lse_fold(float& m, float& sum, float2 v) {
+    if (v.y > 0.f) {
+        const float M = fmaxf(m, v.x);
+        sum = sum * exp2f(m - M) + v.y * exp2f(v.x - M);         // m = -inf, sum = 0 at the start: 0 * 0 + ...
+        m = M;
+    }
+}
+
 // pass 1 without barriers: same streaming scheme as the vote kernel below (queries in LDS, every
 // wave streams its own key tiles), with the MFMA operands swapped so that an accumulator lane
 // holds ONE query row (lane%16 of the block) and 16 tokens of the tile: a row's running
 // (reference, sum of exp2) is then a single pair of registers per block, updated once per tile.
-// Every wave writes its own partial statistics (4 per chunk); the merge kernel combines them.
+// Every wave writes its own partial statistics (4 per chunk), or, with `fold`, the workgroup adds its four up in LDS
+// first; the merge kernel combines them.
 template <int NRB, int DD>     // 16-row blocks the LDS and the per-lane state are sized for, features per head
 __global__ __launch_bounds__(256, 2) void score_stats_wave_kernel(
     const bf16_bits* __restrict__ Q, const bf16_bits* __restrict__ K, int H, int R, int n_rg, int N, int w,
-    int64_t ks_b, int64_t ks_h, int64_t ks_t, int n_chunks, int chunk, float2* __restrict__ stats) {
+    int64_t ks_b, int64_t ks_h, int64_t ks_t, int n_chunks, int chunk, int fold, float2* __restrict__ stats) {
     constexpr int kRowBytes = row_bytes(DD), kPieces = DD / 8;
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* qs = smem;                                             // [16*NRB][kRowBytes]
-    // the row groups of a chunk are neighbours in the launch: the second one finds the keys in the last-level cache
+    // the row groups of a chunk are neighbours in the launch: the later ones find the keys in the last-level cache
     const int rg = blockIdx.x % n_rg, bc = blockIdx.x / n_rg;
     const int bh = bc / n_chunks, c = bc % n_chunks;
     const int b = bh / H, h = bh % H;
@@ -211,9 +221,18 @@ __global__ __launch_bounds__(256, 2) void score_stats_wave_kernel(
         *reinterpret_cast<uint4*>(qs + row * kRowBytes + piece * 16) = v;
     }
     __syncthreads();
-    const int t_begin = c * chunk, t_end = min(N, t_begin + chunk);
-    score_stats_wave_body<NRB, DD>(qs, K + b * ks_b + h * ks_h, ks_t, t_begin, t_end, N - w, w, R, wv, lane,
-                               stats + ((int64_t)bh * (n_chunks * 4) + c * 4 + wv) * R_head + row0);
+    float2* part = reinterpret_cast<float2*>(smem + 16 * NRB * kRowBytes);   // [4][16*NRB]
+    float2* mine = fold ? part + wv * (16 * NRB) : stats + ((int64_t)bh * (n_chunks * 4) + c * 4 + wv) * R_head + row0;
+    score_stats_wave_body<NRB, DD>(qs, K + b * ks_b + h * ks_h, ks_t, c * chunk, min(N, (c + 1) * chunk), N - w, w, R, wv, lane, mine);
+    if (fold) {
+        __syncthreads();
+        if (tid < R) {
+            float m = -INFINITY, sum = 0.f;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) lse_fold(m, sum, part[x * (16 * NRB) + tid]);
+            stats[((int64_t)bh * n_chunks + c) * R_head + row0 + tid] = make_float2(m, sum);
+        }
+    }
 }
 template <int NRB, bool W8, int DD>     // LDS is sized for 16*NRB query rows; W8: the window is 8 positions
 __global__ __launch_bounds__(256) void score_vote_wave_kernel(
@@ -343,13 +362,6 @@ __global__ __launch_bounds__(256) void score_lse_import_kernel(const float* __re
 // merge of the partial (maximum, sum) pairs of every query row: a workgroup takes 64 rows, four threads per row
 // each fold every fourth partial (four loads in flight; with a layer's few heads there are hundreds of partials
 // per row and one thread walking them all was 114 us of latency), then the four are folded in order.
-__device__ __forceinline__ void lse_fold(float& m, float& sum, float2 v) {
-    if (v.y > 0.f) {
-        const float M = fmaxf(m, v.x);
-        sum = sum * exp2f(m - M) + v.y * exp2f(v.x - M);         // m = -inf, sum = 0 at the start: 0 * 0 + ...
-        m = M;
-    }
-}
 __global__ __launch_bounds__(256) void score_lse_kernel(const float2* __restrict__ stats, int n_rows_total,
                                                         int R, int n_chunks, float* __restrict__ lse) {
     __shared__ float2 part[3][64];
@@ -521,7 +533,7 @@ __global__ __launch_bounds__(256) void score_pool_kernel(const float* __restrict
 
 // The MFMA kernels in the variant for `rows` query rows (up to 128, or up to 256), a window of 8 or not, D features.
 typedef void (*StatsKernel)(const bf16_bits*, const bf16_bits*, int, int, int, int, int, int64_t, int64_t, int64_t, int, int,
-                            float2*);
+                            int, float2*);
 typedef void (*VoteKernel)(const bf16_bits*, const bf16_bits*, const float*, int, int, int, int, int, int64_t, int64_t,
                            int64_t, int, int, float*);
 constexpr int kScoreRows = 256;     // rows one workgroup of the MFMA kernels holds at most
@@ -537,7 +549,7 @@ static VoteKernel vote_kernel(int rows, bool w8, int D) {
     if (w8) return rows <= 128 ? score_vote_wave_kernel<8, true, kD> : score_vote_wave_kernel<16, true, kD>;
     return rows <= 128 ? score_vote_wave_kernel<8, false, kD> : score_vote_wave_kernel<16, false, kD>;
 }
-static int stats_lds_bytes(int rows, int D) { return (rows <= 128 ? 128 : 256) * row_bytes(D); }
+static int stats_lds_bytes(int rows, int D) { return (rows <= 128 ? 128 : 256) * (row_bytes(D) + 4 * (int)sizeof(float2)); }
 static int vote_lds_bytes(int rows, int D) { return (rows <= 128 ? 128 : 256) * (row_bytes(D) + (int)sizeof(float)); }
 
 hipError_t init_score_kernels() {
@@ -575,8 +587,8 @@ ScorePlan plan_score(int B, int H, int G, int N, int w) {
     nc = (N + chunk - 1) / chunk;
     p.n_chunks = nc;
     p.chunk = chunk;
-    const size_t P = (size_t)(N - w);
     p.stats_off = 0;
+    const size_t P = (size_t)(N - w);
     p.lse_off = align_up((size_t)BH * nc * 4 * p.R * sizeof(float2), 256);   // up to 4 partials per chunk
     p.vote_off = p.lse_off + align_up((size_t)BH * p.R * sizeof(float), 256);
     p.range_off = p.vote_off + align_up((size_t)BH * G * P * sizeof(float), 256);
@@ -584,6 +596,33 @@ ScorePlan plan_score(int B, int H, int G, int N, int w) {
     p.bytes = p.range_off + align_up((size_t)BH * p.n_range_tiles * 2 * sizeof(uint32_t), 256);
     return p;
 }
+
+// Tokens per chunk of the MFMA kernels, one workgroup each (heads: KV heads times row groups).  A CU holds two of
+// these workgroups; a round of four 64-token tiles takes two of them side by side 1 unit, one alone 0.56, and starting
+// up and folding takes 2.1 units whatever the length (statistics of 256 heads of 8192 tokens, 128 rows: 122 / 110 /
+// 123 / 134 us with 1 / 2 / 4 / 8 chunks, a unit being 6 us).  The chunk with the smallest sum wins.  For 8 heads of
+// 16384 tokens the two passes take 21 + 15 us, with the 2048-token chunks that were the least before 43 + 32.
+static int wave_chunk(int64_t heads, int N, int n_parts) {
+    constexpr int kCus = 256, kRound = 4 * kTile;
+    const int rounds = (N + kRound - 1) / kRound;
+    int best = rounds;
+    double best_cost = 0.0;
+    for (int r = (rounds + n_parts - 1) / n_parts; r <= rounds; ++r) {
+        const int64_t nb = heads * ((rounds + r - 1) / r), full = (nb + kCus - 1) / kCus;
+        const double cost = (double)(full / 2) * (r + 2.1) + (double)(full & 1) * (0.56 * r + 2.1);
+        if (best_cost == 0.0 || cost < best_cost) {
+            best_cost = cost;
+            best = r;
+        }
+        if (full <= 1) break;                      // longer chunks only idle CUs from here on
+    }
+    return best * kRound;
+}
+// The statistics take these chunks where those of plan_score would leave the chip short of two workgroups per CU.
+// Longer prompts keep the latter: a normaliser whose terms are added in another order differs in its last bit, and the
+// longer the prompt, the more positions lie within that of a head's threshold.  The vote pass adds nothing up across
+// tokens, so its chunks are free.
+constexpr int kFineChunks = 16384;
 
 template <typename T>
 static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, int w, int pool,
@@ -597,8 +636,10 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
     uint32_t* tile_range = reinterpret_cast<uint32_t*>(ws + p.range_off);
     const bool mfma = n_rg > 0;          // row groups of the MFMA kernels, 0 for the plain-ALU ones
     const int R_group = mfma ? p.R / n_rg : 0;
-    const dim3 grid1((unsigned)(BH * p.n_chunks * (mfma ? n_rg : 1)));
-    int n_parts = p.n_chunks;            // partial statistics per query row
+    const int chunk_w = wave_chunk((int64_t)BH * (mfma ? n_rg : 1), N, 4 * p.n_chunks);
+    const int nc_wave = (N + chunk_w - 1) / chunk_w;
+    const dim3 grid_w((unsigned)(BH * nc_wave * (mfma ? n_rg : 1)));
+    int n_parts = 0;                     // partial statistics per query row
     const int rows = BH * p.R;
     const bool own_stats = lse_nat == nullptr;
     if (!own_stats) {
@@ -609,29 +650,25 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
     if constexpr (sizeof(T) == 2) {
         if (mfma && own_stats) {
             env.begin("score_stats_wave");
-            stats_kernel(R_group, D)<<<grid1, dim3(256), stats_lds_bytes(R_group, D), s>>>(
-                Q, K, H, R_group, n_rg, N, w, ks[0], ks[1], ks[2], p.n_chunks, p.chunk, stats);
+            const int fold = N <= kFineChunks && (int64_t)BH * p.n_chunks * n_rg < 512 ? 1 : 0;
+            const int nc = fold ? nc_wave : p.n_chunks;
+            stats_kernel(R_group, D)<<<dim3((unsigned)(BH * nc * n_rg)), dim3(256), stats_lds_bytes(R_group, D), s>>>(
+                Q, K, H, R_group, n_rg, N, w, ks[0], ks[1], ks[2], nc, fold ? chunk_w : p.chunk, fold, stats);
             env.end();
-            n_parts = p.n_chunks * 4;
+            n_parts = fold ? nc : 4 * nc;
         }
     }
     if (!own_stats) {
         // normalisers already in place
     } else if (!mfma && w == 1 && G <= 16) {
+        const int chunk_l = wave_chunk(BH, N, 4 * p.n_chunks);
+        n_parts = (N + chunk_l - 1) / chunk_l;
+        auto kern = G <= 4 ? score_stats_lastrow_kernel<T, 4> : G <= 8 ? score_stats_lastrow_kernel<T, 8> : score_stats_lastrow_kernel<T, 16>;
         env.begin("score_stats_lastrow");
-        if (G <= 4)
-            score_stats_lastrow_kernel<T, 4><<<grid1, dim3(256), 0, s>>>(Q, K, H, G, N, D, ks[0], ks[1], ks[2], p.n_chunks,
-                                                                         p.chunk, stats);
-        else if (G <= 8)
-            score_stats_lastrow_kernel<T, 8><<<grid1, dim3(256), 0, s>>>(Q, K, H, G, N, D, ks[0], ks[1], ks[2], p.n_chunks,
-                                                                         p.chunk, stats);
-        else
-            score_stats_lastrow_kernel<T, 16><<<grid1, dim3(256), 0, s>>>(Q, K, H, G, N, D, ks[0], ks[1], ks[2], p.n_chunks,
-                                                                          p.chunk, stats);
+        kern<<<dim3((unsigned)(BH * n_parts)), dim3(256), 0, s>>>(Q, K, H, G, N, D, ks[0], ks[1], ks[2], n_parts, chunk_l, stats);
         env.end();
     } else if (!mfma) {
-        // This kernel writes one partial per chunk where the wave kernels write four: the statistics region has room
-        // for chunks a quarter as long, which is what a short prompt needs to occupy more than a few CUs.
+        // one partial per chunk; chunks short enough for a short prompt to occupy more than a few CUs
         int nca = 4 * p.n_chunks;
         if (nca > (N + 63) / 64) nca = (N + 63) / 64;
         const int chunk_a = ((N + nca - 1) / nca + kStatTile - 1) / kStatTile * kStatTile;
@@ -653,8 +690,8 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
     if constexpr (sizeof(T) == 2) {
         if (mfma) {
             env.begin("score_vote_wave");
-            vote_kernel(R_group, w == 8, D)<<<grid1, dim3(256), vote_lds_bytes(R_group, D), s>>>(
-                Q, K, lse, H, G, n_rg, N, w, ks[0], ks[1], ks[2], p.n_chunks, p.chunk, vote);
+            vote_kernel(R_group, w == 8, D)<<<grid_w, dim3(256), vote_lds_bytes(R_group, D), s>>>(
+                Q, K, lse, H, G, n_rg, N, w, ks[0], ks[1], ks[2], nc_wave, chunk_w, vote);
             env.end();
         }
     }

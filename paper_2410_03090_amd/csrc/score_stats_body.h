@@ -14,7 +14,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 // qs: the head's query rows staged in LDS (rows of row_bytes(DD)).  The wave (wv = 0..3 of the four that share a
 // chunk) streams key tiles wv, wv + 4, ... of tokens [t_begin, t_end) and writes its partial (reference,
-// sum) of every query row to stats_rows[row].  No workgroup barrier inside.
+// sum) of every query row to stats_rows[row] (global memory or LDS).  No workgroup barrier inside.
 template <int NRB, int DD>      // 16-row blocks held, features per head (128 or 64)
 __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, const bf16_bits* __restrict__ Kh,
                                                       int64_t ks_t, int t_begin, int t_end, int P, int w, int R,
@@ -48,6 +48,7 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
                 bf16x8_t, *reinterpret_cast<const uint4*>(qs + (16 * rb + m) * kRowBytes + 64 * ks + 16 * g));
     };
     auto process = [&](const uint4 cur[4][kKs], uint4 nxt[4][kKs], int tile) {
+        const bool first = tile == wv;
         load_tile(nxt, tile + 4);
         const int t0 = t_begin + tile * kTile;
         const bool edge = t0 + kTile > P || t0 + kTile > t_end;   // causal window or ragged end inside
@@ -79,7 +80,7 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
                 // (a logit far above the reference, or no reference yet) takes the slow path
                 float t = 0.f;
                 bool redo = edge;
-                if (!edge) {
+                if (!edge && !first) {
                     float t4[4];
 #pragma unroll
                     for (int st = 0; st < 4; ++st)
@@ -89,6 +90,16 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
                                   __builtin_amdgcn_exp2f(fmaf(acc[st][3], scale2, nref[rb])));
                     t = (t4[0] + t4[1]) + (t4[2] + t4[3]);
                     redo = !(t <= 4096.f);
+                } else if (!edge) {                               // no reference yet: the largest of these 16 logits
+                    float mx = -INFINITY;
+#pragma unroll
+                    for (int st = 0; st < 4; ++st)
+                        mx = fmaxf(mx, fmaxf(fmaxf(acc[st][0], acc[st][1]), fmaxf(acc[st][2], acc[st][3])));
+                    nref[rb] = -(mx * scale2);
+#pragma unroll
+                    for (int st = 0; st < 4; ++st)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) t += __builtin_amdgcn_exp2f(fmaf(acc[st][v], scale2, nref[rb]));
                 }
                 if (__builtin_amdgcn_ballot_w64(redo) == 0ull) {
                     sum[rb] += t;
@@ -104,7 +115,7 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
                         }
                     const float r = -nref[rb];                     // -inf before the first token
                     if (mx > r) {
-                        sum[rb] *= exp2f(r - mx);                  // exp2(-inf) = 0 on first use
+                        sum[rb] *= __builtin_amdgcn_exp2f(r - mx);  // exp2(-inf) = 0 on first use
                         nref[rb] = -mx;
                     }
 #pragma unroll
@@ -112,7 +123,7 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             const int j = t0 + 16 * st + 4 * g + v;
-                            if (j < t_end && j <= last) sum[rb] += exp2f(fmaf(acc[st][v], scale2, nref[rb]));
+                            if (j < t_end && j <= last) sum[rb] += __builtin_amdgcn_exp2f(fmaf(acc[st][v], scale2, nref[rb]));
                         }
                 }
             }
@@ -135,8 +146,8 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
             for (int o = 16; o < 64; o <<= 1) {
                 const float r2 = __shfl_xor(r, o, 64), s2 = __shfl_xor(sm, o, 64);
                 const float nr = fmaxf(r, r2);
-                const float a = sm > 0.f ? sm * exp2f(r - nr) : 0.f;
-                const float bb = s2 > 0.f ? s2 * exp2f(r2 - nr) : 0.f;
+                const float a = sm > 0.f ? sm * __builtin_amdgcn_exp2f(r - nr) : 0.f;
+                const float bb = s2 > 0.f ? s2 * __builtin_amdgcn_exp2f(r2 - nr) : 0.f;
                 r = nr;
                 sm = a + bb;
             }

@@ -60,3 +60,18 @@ def test_entropy_64_wide_heads(ctx, N):
             H, eig = ctx.head_entropy(Xd, k_trunc=32, flags=flags, want_eig=True)
             np.testing.assert_allclose(H.cpu().numpy(), Href, rtol=1e-4, atol=5e-5)
             np.testing.assert_allclose(eig.cpu().numpy(), eref, rtol=0, atol=2e-5)
+
+
+# Chunks of the scoring passes: from one 256-token round to many, a last chunk that holds fewer tokens than the window
+# or than a tile, logits that grow along the prompt (the running reference of a row must follow them).
+@pytest.mark.parametrize("H,G,N,w", [(1, 4, 256, 32), (1, 4, 257, 32), (2, 2, 1025, 64), (8, 4, 8200, 32), (3, 8, 40009, 32),
+                                     (1, 1, 2049, 16)])
+def test_score_chunks(ctx, H, G, N, w):
+    cfg = synth.tiny_config(dtype="bf16", B=1, H=H, G=G, N=N, w=w, rank_lo=2, rank_hi=24)
+    K, V, Q = synth.gen_all(cfg, seed0=N)
+    ramp = torch.linspace(0.02, 3.0, N).view(1, 1, N, 1)
+    for k in (K[0], (K[0].float() * ramp).to(torch.bfloat16)):
+        ref = O.window_score(to_f64(Q[0]), to_f64(k), G=G, pool=7)
+        got = ctx.window_score(Q[0].to(DEV), k.to(DEV), G=G, pool=7).cpu().numpy()
+        # logits up to three times those of the other tests: exp() carries three times their relative error
+        np.testing.assert_allclose(got, ref, rtol=6e-5, atol=1e-12)
