@@ -122,6 +122,14 @@ hipError_t launch_window_score(const void* Q, const void* K, uncomp_dtype dt, in
                                int N, int w, int pool, const int64_t ks[3], const ScorePlan& p,
                                char* ws, float* score_out, const Env& env, const float* lse_nat = nullptr,
                                int D = kD);
+// The two scoring passes with fp32 logits on the matrix cores (score_f32.hip; T: float or uint16_t holding bf16).
+// stats: at most max_parts partials per row, their number in *n_parts; vote: [BH][G][N - w].
+template <typename T>
+hipError_t launch_stats_f32(const T* Q, const T* K, int BH, int H, int R, int N, int w, const int64_t ks[3], int max_parts,
+                            float2* stats, int* n_parts, hipStream_t s, int D);
+template <typename T>
+hipError_t launch_vote_f32(const T* Q, const T* K, const float* lse, int BH, int H, int G, int N, int w, const int64_t ks[3],
+                           float* vote, hipStream_t s, int D);
 hipError_t launch_select_gather(const float* score, const int32_t* budget, const void* K,
                                 const void* V, uncomp_dtype dt, int B, int H, int N, int w,
                                 const int64_t ks[3], int cap, void* K_out, void* V_out,

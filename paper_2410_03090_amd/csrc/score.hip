@@ -642,6 +642,10 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
     int n_parts = 0;                     // partial statistics per query row
     const int rows = BH * p.R;
     const bool own_stats = lse_nat == nullptr;
+    // fp32 logits on the matrix cores (score_f32.hip).  Windows of less than eight rows stay on the plain ALUs: those
+    // blocks would be mostly padding.
+    const bool f32_mfma = !mfma && !env.force_alu && w >= 8;
+    hipError_t launched = hipSuccess;
     if (!own_stats) {
         env.begin("score_lse_import");
         score_lse_import_kernel<<<dim3((rows + 255) / 256), dim3(256), 0, s>>>(lse_nat, rows, lse);
@@ -660,6 +664,10 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
     }
     if (!own_stats) {
         // normalisers already in place
+    } else if (f32_mfma) {
+        env.begin("score_stats_f32");
+        launched = launch_stats_f32<T>(Q, K, BH, H, p.R, N, w, ks, 4 * p.n_chunks, stats, &n_parts, s, D);
+        env.end();
     } else if (!mfma && w == 1 && G <= 16) {
         const int chunk_l = wave_chunk(BH, N, 4 * p.n_chunks);
         n_parts = (N + chunk_l - 1) / chunk_l;
@@ -695,7 +703,13 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
             env.end();
         }
     }
-    if (!mfma) {
+    if (launched != hipSuccess) return launched;
+    if (f32_mfma) {
+        env.begin("score_vote_f32");
+        launched = launch_vote_f32<T>(Q, K, lse, BH, H, G, N, w, ks, vote, s, D);
+        env.end();
+        if (launched != hipSuccess) return launched;
+    } else if (!mfma) {
         env.begin("score_vote_alu");
         score_vote_alu_kernel<T><<<dim3((unsigned)(BH * n_tiles)), dim3(256), 0, s>>>(
             Q, K, lse, H, G, N, D, w, ks[0], ks[1], ks[2], n_tiles, vote);

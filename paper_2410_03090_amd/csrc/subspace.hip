@@ -337,7 +337,11 @@ typedef double f64x4_t __attribute__((ext_vector_type(4)));
 // MODE 2 (fp32 token matrices of uncomp_head_entropy, 128 features): blockIdx.y is the matrix (mat_stride elements
 // apart, rows lda apart), blockIdx.x its token chunk; the chunk's mirrored Gram and column sums go out as fp32 in
 // the layout the eigenvalue kernels add up: fpart[(matrix, chunk)][128][128], fsum[(matrix, chunk)][128].
-template <int MODE>
+// SLOTS: how many of a wave's nine tiles the workgroup computes, slots SLOTS * blockIdx.z and on.  A short fp32 prompt has
+// one chunk per matrix, whose products keep a CU's fp64 matrix cores busy for 100 us: splitting the tiles over nine
+// workgroups fills the chip without more partials, at the price of reading the tokens from the caches nine times.
+// 8 matrices of 1024 tokens: 110 us with all nine slots, 31 with one.  Every entry is the same sum in the same order.
+template <int MODE, int SLOTS = 9>
 __global__ __launch_bounds__(256) void sub_gram64_kernel(const float* __restrict__ A_all, int64_t mat_stride, int64_t lda,
                                                          int n_rows, int rows_per_wg, double* __restrict__ gpart,
                                                          float* __restrict__ fpart, double* __restrict__ spart,
@@ -351,9 +355,10 @@ __global__ __launch_bounds__(256) void sub_gram64_kernel(const float* __restrict
     const int r_begin = blockIdx.x * rows_per_wg;
     const int r_end = min(n_rows, r_begin + rows_per_wg);
     const int I1 = wv, I2 = 7 - wv, n1 = 8 - wv;             // slot s < n1: tile (I1, I1 + s); else (I2, I2 + s - n1)
-    f64x4_t acc[9];
+    const int slot0 = SLOTS == 9 ? 0 : SLOTS * blockIdx.z;
+    f64x4_t acc[SLOTS];
 #pragma unroll
-    for (int sl = 0; sl < 9; ++sl) acc[sl] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+    for (int sl = 0; sl < SLOTS; ++sl) acc[sl] = f64x4_t{0.0, 0.0, 0.0, 0.0};
     double csum = 0.0;
     float4 pre[8];
     auto fetch = [&](int r0) {
@@ -374,7 +379,7 @@ __global__ __launch_bounds__(256) void sub_gram64_kernel(const float* __restrict
         }
         __syncthreads();
         if (r0 + kGramRows < r_end) fetch(r0 + kGramRows);
-        if ((MODE == 2 || spart != nullptr) && tid < kP) {
+        if ((MODE == 2 ? slot0 == 0 : spart != nullptr) && tid < kP) {
 #pragma unroll 8
             for (int rr = 0; rr < kGramRows; ++rr) csum += (double)rows[rr][tid];
         }
@@ -382,18 +387,18 @@ __global__ __launch_bounds__(256) void sub_gram64_kernel(const float* __restrict
             const float* row = rows[k0 + kk];
             const double a1 = (double)row[16 * I1 + c], a2 = (double)row[16 * I2 + c];
 #pragma unroll
-            for (int sl = 0; sl < 9; ++sl) {
-                const bool first = sl < n1;
-                const int J = first ? I1 + sl : I2 + sl - n1;
+            for (int sl = 0; sl < SLOTS; ++sl) {
+                const bool first = slot0 + sl < n1;
+                const int J = first ? I1 + slot0 + sl : I2 + slot0 + sl - n1;
                 const double bv = (double)row[16 * J + c];
                 acc[sl] = __builtin_amdgcn_mfma_f64_16x16x4f64(first ? a1 : a2, bv, acc[sl], 0, 0, 0);
             }
         }
     }
 #pragma unroll
-    for (int sl = 0; sl < 9; ++sl) {
-        const bool first = sl < n1;
-        const int I = first ? I1 : I2, J = first ? I1 + sl : I2 + sl - n1;
+    for (int sl = 0; sl < SLOTS; ++sl) {
+        const bool first = slot0 + sl < n1;
+        const int I = first ? I1 : I2, J = first ? I1 + slot0 + sl : I2 + slot0 + sl - n1;
         if constexpr (PACKED) {
             float* o = fpart + (out_idx * kGramTiles + (I * 8 - I * (I - 1) / 2 + J - I)) * 256;
 #pragma unroll
@@ -417,7 +422,7 @@ __global__ __launch_bounds__(256) void sub_gram64_kernel(const float* __restrict
         }
     }
     if (MODE == 2) {
-        if (tid < kP) fsum[out_idx * kP + tid] = (float)csum;
+        if (slot0 == 0 && tid < kP) fsum[out_idx * kP + tid] = (float)csum;
     } else if (spart != nullptr && tid < kP) {
         spart[out_idx * kP + tid] = csum;
     }
@@ -427,8 +432,12 @@ __global__ __launch_bounds__(256) void sub_gram64_kernel(const float* __restrict
 // exact products, fp64 sums inside a chunk, on the fp64 matrix cores instead of the fp32 ALUs.
 hipError_t launch_gram_f32_mfma(const float* X, int n_mat, int N, int64_t mat_stride, int64_t ldx, int n_chunks, int chunk,
                                 float* gram_part, float* sum_part, hipStream_t s) {
-    sub_gram64_kernel<2><<<dim3((unsigned)n_chunks, (unsigned)n_mat), dim3(256), 0, s>>>(X, mat_stride, ldx, N, chunk, nullptr,
-                                                                                    gram_part, nullptr, sum_part);
+    // the most workgroups per chunk that still leave the launch under two per CU
+    const int64_t n = (int64_t)n_chunks * n_mat;
+    const int split = n * 9 <= 512 ? 9 : (n * 3 <= 512 ? 3 : 1);
+    auto kern = split == 9 ? sub_gram64_kernel<2, 1> : (split == 3 ? sub_gram64_kernel<2, 3> : sub_gram64_kernel<2>);
+    kern<<<dim3((unsigned)n_chunks, (unsigned)n_mat, (unsigned)split), dim3(256), 0, s>>>(X, mat_stride, ldx, N, chunk, nullptr,
+                                                                                  gram_part, nullptr, sum_part);
     return hipGetLastError();
 }
 

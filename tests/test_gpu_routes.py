@@ -75,3 +75,33 @@ def test_score_chunks(ctx, H, G, N, w):
         got = ctx.window_score(Q[0].to(DEV), k.to(DEV), G=G, pool=7).cpu().numpy()
         # logits up to three times those of the other tests: exp() carries three times their relative error
         np.testing.assert_allclose(got, ref, rtol=6e-5, atol=1e-12)
+
+
+# fp32 logits on the matrix cores: fp32 inputs, and bf16 windows without a cut into 16-row blocks.  128-token tiles and
+# 16-row blocks with remainders, windows of eight in pairs and alone, rows split over workgroups and not, the widest R.
+@pytest.mark.parametrize("dtype,D,H,G,N,w", [
+    ("f32", 128, 2, 1, 9, 8), ("f32", 128, 1, 4, 160, 32), ("f32", 128, 2, 2, 161, 8), ("f32", 64, 2, 3, 1025, 8),
+    ("f32", 128, 2, 3, 700, 20), ("f32", 64, 1, 8, 2333, 64), ("f32", 128, 8, 4, 1024, 32), ("f32", 128, 1, 7, 290, 33),
+    ("f32", 128, 1, 1, 1500, 512), ("f32", 128, 64, 8, 1100, 16), ("bf16", 128, 2, 3, 700, 20), ("bf16", 64, 2, 5, 333, 9)])
+def test_score_fp32_logits(ctx, dtype, D, H, G, N, w):
+    cfg = synth.tiny_config(dtype=dtype, B=1, H=H, G=G, N=N, D=D, w=w, rank_lo=2, rank_hi=48)
+    K, V, Q = synth.gen_all(cfg, seed0=N + G)
+    ref = O.window_score(to_f64(Q[0]), to_f64(K[0]), G=G, pool=5)
+    Qd, Kd = Q[0].to(DEV), K[0].to(DEV)
+    # as above: fp32 logits of magnitude <= ~16
+    np.testing.assert_allclose(ctx.window_score(Qd, Kd, G=G, pool=5).cpu().numpy(), ref, rtol=2e-5)
+    np.testing.assert_allclose(ctx.window_score(Qd, _padded(Kd, 24), G=G, pool=5).cpu().numpy(), ref, rtol=2e-5)
+    lse = torch.from_numpy(O.window_lse(to_f64(Q[0]), to_f64(K[0]), G).astype(np.float32)).to(DEV)
+    np.testing.assert_allclose(ctx.window_score(Qd, Kd, G=G, pool=5, lse=lse).cpu().numpy(), ref, rtol=2e-5)
+
+
+# Gram of fp32 matrices with its tiles over nine, three and one workgroup per chunk (few, more and many matrices).
+@pytest.mark.parametrize("n_mat,N", [(1, 2), (3, 65), (8, 1024), (57, 130), (171, 70)])
+def test_entropy_fp32_tile_split(ctx, n_mat, N):
+    g = torch.Generator().manual_seed(N)
+    X = torch.randn(n_mat, N, 12, generator=g) @ torch.randn(n_mat, 12, 128, generator=g) / 12 + \
+        0.1 * torch.randn(n_mat, N, 128, generator=g) + 0.05
+    Href, eref = O.head_entropy(to_f64(X), k_trunc=32, flags=O.DEFAULT_FLAGS)
+    H, eig = ctx.head_entropy(X.to(DEV), k_trunc=32, flags=O.DEFAULT_FLAGS, want_eig=True)
+    np.testing.assert_allclose(H.cpu().numpy(), Href, rtol=1e-4, atol=5e-5)
+    np.testing.assert_allclose(eig.cpu().numpy(), eref, rtol=0, atol=2e-5)
