@@ -197,16 +197,24 @@ hipError_t launch_matrix_entropy(const void* X, uncomp_dtype dt, int n_mat, int 
 // Workspace of the bf16 decode path (two kernels per step).
 struct DecodePlan {
     int GT;              // query heads per KV head rounded up to 4, 8 or 16
-    int wave_rows;       // rows of one head that one wave owns (128 or 256)
+    int wave_rows;       // rows of one head that one wave owns (64, 128 or 256)
     int s_rows;          // rows per head in the probability table (cap + 1 rounded up to whole waves)
-    int np_max;          // waves (128-row parts) per head
+    int np_max;          // waves (parts of wave_rows rows) per head
     size_t out_off;      // float [n_heads][G][D]: attention output when the caller wants none
     size_t p_off;        // float [n_heads][s_rows][GT]
     size_t ml_off;       // float [n_heads][np_max][GT][2]
     size_t acc_off;      // float [n_heads][np_max][GT][D]
     size_t bytes;
 };
-DecodePlan plan_decode(int n_heads, int G, int cap);
+DecodePlan plan_decode(int n_heads, int G, int cap, int wave_rows = 0);       // wave_rows 0: 128 or 256
+// The one-kernel step (decode_head_kernel) for at least kHeadStepHeads heads whose tables fit kDecodeHeadLdsMax bytes of
+// LDS (two workgroups per CU); from kHeadStepWide heads on with four waves per head.
+constexpr int kHeadStepHeads = 256, kHeadStepWide = 1024;
+constexpr size_t kDecodeHeadLdsMax = 80 * 1024 - 1024;
+size_t decode_head_lds_bytes(int n_heads, int G, int cap);
+hipError_t launch_decode_head(const void* q, const void* k_new, const void* v_new, int n_heads, int G, const int32_t* pos,
+                              const int32_t* budget, int w, int cap, void* Kc, void* Vc, int32_t* idx, float* cum,
+                              int32_t* len, float* out, int32_t* evicted, const Env& env);
 hipError_t launch_decode_wave(const void* q, const void* k_new, const void* v_new, int n_heads, int G,
                               const int32_t* pos, const int32_t* budget, int w, int cap, void* Kc, void* Vc,
                               int32_t* idx, float* cum, int32_t* len, float* out, int32_t* evicted,

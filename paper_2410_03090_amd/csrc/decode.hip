@@ -7,11 +7,12 @@
 // The evicted entry's slot receives the new token, so nothing is moved: slot order is free,
 // idx names each slot.
 //
-// bf16 caches take two kernels.  decode_attend_wave_kernel: every wave owns 128 consecutive
-// rows of one head and runs on its own (no workgroup barrier): keys stream straight into
-// MFMA operand layout, the 128 x G logits stay in registers, the wave's softmax (its own
-// maximum and sum) goes through LDS to the lanes that stream the value rows, and the wave
-// leaves (maximum, sum, unnormalised output, unnormalised probabilities) in the workspace.
+// bf16 caches of many heads take decode_head_kernel, one workgroup per head.  Fewer heads (and more than 8 query heads per
+// KV head, or caches whose probabilities do not fit in LDS) take two kernels.  decode_attend_wave_kernel: every wave
+// owns 64, 128 or 256 consecutive rows of one head and runs on its own (no workgroup barrier): keys stream straight into
+// MFMA operand layout, the logits stay in registers, the wave's softmax (its own maximum and sum) goes through LDS to
+// the lanes that stream the value rows, and the wave leaves (maximum, sum, unnormalised output, unnormalised
+// probabilities) in the workspace.
 // decode_update_kernel: one workgroup per head merges the waves' partials into the output,
 // turns the stored probabilities into each row's share, updates the cumulative scores,
 // finds the row to give up and places the new token.
@@ -319,9 +320,8 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_step_kernel(
 
 
 // ---- bf16: wave-per-128-rows attention pass ----------------------------------------------
-// A wave owns WR = 128 or 256 consecutive rows of one head: 128 when the launch would
-// otherwise have too few waves to fill the chip, 256 when there are plenty (half the
-// partial results to write and merge).
+// A wave owns WR = 64, 128 or 256 consecutive rows of one head: the fewer, the fewer waves the launch would otherwise
+// have for the chip; 256 when there are plenty (half the partial results to write and merge).
 
 // Workspace per head: prob [s_rows][GT] (unnormalised, relative to the owning wave's maximum),
 // ml [np_max][GT][2] (maximum in the exp2 domain, sum), acc [np_max][GT][128].
@@ -360,13 +360,13 @@ __global__ __launch_bounds__(256) void decode_attend_wave_kernel(
     }
     // rows past the end re-read the new token (clamped, never predicated: straight-line loads
     // keep exact counts of the loads in flight); what they produce is masked below
-    auto load_k = [&](uint4 dst[4], int t) {
+    auto load_k = [&](uint4 (&dst)[4], int t) {
         const int r = row0 + 16 * t + c16;
         const bf16_bits* src = (r < n ? Kh + (int64_t)r * kD : kn) + 8 * j;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) dst[ks] = *reinterpret_cast<const uint4*>(src + 32 * ks);
     };
-    auto load_v = [&](uint4 dst[4], int t) {
+    auto load_v = [&](uint4 (&dst)[4], int t) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int r = row0 + 16 * t + 4 * u + j;
@@ -376,29 +376,41 @@ __global__ __launch_bounds__(256) void decode_attend_wave_kernel(
     };
 
     // ---- pass 1: logits of the wave's rows; lane holds query head c16, rows 16t + 4j + v ----
+    // Short waves (kAll) have all their keys and values in flight at once: with few waves on the chip their time is
+    // that of the round trips to memory (8 heads of 2048 rows: 8.4 us, two tiles ahead 9.6).
+    constexpr bool kAll = WR == 64 && GT <= 8;
+    constexpr int kSlots = kAll ? kTiles : 2;
     f32x4_t s[kTiles];
-    uint4 ka[4], kb[4];
-    auto dots = [&](const uint4 kt[4], int t) {
+    uint4 kt[kSlots][4], vt[kSlots][4];
+    auto dots = [&](const uint4 (&x)[4], int t) {
         f32x4_t c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kt[ks]), qb[ks], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x[ks]), qb[ks], c, 0, 0, 0);
         s[t] = c;
     };
-    load_k(ka, 0);
+    if constexpr (kAll) {
 #pragma unroll
-    for (int t = 0; t < kTiles; t += 2) {
-        if (t < n_t) {
-            load_k(kb, t + 1);
-            dots(ka, t);
+        for (int t = 0; t < kTiles; ++t) load_k(kt[t], t);
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) load_v(vt[t], t);
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) dots(kt[t], t);
+    } else {
+        load_k(kt[0], 0);
+#pragma unroll
+        for (int t = 0; t < kTiles; t += 2) {
+            if (t < n_t) {
+                load_k(kt[1], t + 1);
+                dots(kt[0], t);
+            }
+            if (t + 1 < n_t) {
+                load_k(kt[0], t + 2);
+                dots(kt[1], t + 1);
+            }
         }
-        if (t + 1 < n_t) {
-            load_k(ka, t + 2);
-            dots(kb, t + 1);
-        }
+        load_v(vt[0], 0);                                           // under way during the softmax arithmetic
     }
-    uint4 va[4], vb[4];
-    load_v(va, 0);                                                  // under way during the softmax arithmetic
 
     const float qs = 0.08838834764831845f * 1.4426950408889634f;    // 1/sqrt(128) * log2(e)
     float mx = -INFINITY;
@@ -452,7 +464,7 @@ __global__ __launch_bounds__(256) void decode_attend_wave_kernel(
     for (int g = 0; g < GT; ++g)
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
-    auto weigh = [&](const uint4 vt[4], int t) {
+    auto weigh = [&](const uint4 (&vt)[4], int t) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             float vf[8];
@@ -474,15 +486,21 @@ __global__ __launch_bounds__(256) void decode_attend_wave_kernel(
             }
         }
     };
+    if constexpr (kAll) {
 #pragma unroll
-    for (int t = 0; t < kTiles; t += 2) {
-        if (t < n_t) {
-            load_v(vb, t + 1);
-            weigh(va, t);
-        }
-        if (t + 1 < n_t) {
-            load_v(va, t + 2);
-            weigh(vb, t + 1);
+        for (int t = 0; t < kTiles; ++t)
+            if (t < n_t) weigh(vt[t], t);
+    } else {
+#pragma unroll
+        for (int t = 0; t < kTiles; t += 2) {
+            if (t < n_t) {
+                load_v(vt[1], t + 1);
+                weigh(vt[0], t);
+            }
+            if (t + 1 < n_t) {
+                load_v(vt[0], t + 2);
+                weigh(vt[1], t + 1);
+            }
         }
     }
     // sum over the four lane rows; lane row j keeps query head g4 + {0,2,1,3}[j]
@@ -499,19 +517,49 @@ __global__ __launch_bounds__(256) void decode_attend_wave_kernel(
     }
 }
 
-template <int GT, int NT>
-__global__ __launch_bounds__(NT) void decode_update_kernel(
+// The new token takes the slot of the entry that leaves, or the next free one.  Called by the whole workgroup.
+// victim: slot of the entry outside the window with the lowest score, -1 if none; victim_id: its position.
+__device__ __forceinline__ void place_token(const bf16_bits* kn, const bf16_bits* vn, bf16_bits* Kh, bf16_bits* Vh,
+                                            int32_t* idxh, float* cumh, int32_t* len, int32_t* evicted, int tid, int n,
+                                            int cap, bool over, int victim, int victim_id, int posh, float new_cum) {
+    int slot = n, ev = -1;
+    if (over) {
+        slot = victim;
+        if (slot >= 0) {
+            ev = victim_id;
+        } else if (n < cap) {
+            slot = n;                               // nothing may leave: grow if there is room
+        } else {
+            ev = -2;                                // no room and nothing may leave: token dropped
+        }
+    }
+    if (slot >= 0) {
+        if (tid < 16) copy8(kn + 8 * tid, Kh + (int64_t)slot * kD + 8 * tid);
+        else if (tid < 32) copy8(vn + 8 * (tid - 16), Vh + (int64_t)slot * kD + 8 * (tid - 16));
+        else if (tid == 32) {
+            idxh[slot] = posh;
+            cumh[slot] = new_cum;
+        }
+    }
+    if (tid == 0) {
+        *len = (slot == n) ? n + 1 : n;
+        if (evicted != nullptr) *evicted = ev;
+    }
+}
+
+// Bound by its chain of memory round trips (a few heads' tables are a few hundred KB): the rows' probabilities, scores and
+// positions are requested before the parts' maxima are known, the parts' outputs eight at a time.  One layer of 8 heads,
+// 2048 rows: 10.0 -> 8.4 us.
+template <int GT>
+__global__ __launch_bounds__(512) void decode_update_kernel(
     const bf16_bits* __restrict__ k_new, const bf16_bits* __restrict__ v_new, int G,
     const int32_t* __restrict__ pos, const int32_t* __restrict__ budget, int w, int cap, bf16_bits* Kc,
     bf16_bits* Vc, int32_t* idx, float* cum, int32_t* len, float* __restrict__ out,
     int32_t* __restrict__ evicted, int wave_rows, int np_max, int s_rows, const float* __restrict__ ws_p,
     const float* __restrict__ ws_ml, const float* __restrict__ ws_acc) {
-    constexpr int NW = NT / 64;
-    extern __shared__ __align__(16) float dynf[];                   // three tables of [np_max][GT]
-    float* coef = dynf;                                             // exp2(m_part - m) / sum
-    float* pm = dynf + np_max * GT;                                 // the parts' maxima
-    float* pl = dynf + 2 * np_max * GT;                             // the parts' sums
-    __shared__ float head_m[GT], head_inv[GT];
+    constexpr int NT = 512, NW = NT / 64, U = GT <= 8 ? 4 : 2;
+    extern __shared__ __align__(16) float coef[];                   // [np_max][GT]: exp2(m_part - m) / sum
+    __shared__ __align__(16) float4 part_out[NT];
     __shared__ unsigned long long wave_best[NW];
     __shared__ int victim_slot;
     __shared__ float new_cum_s;
@@ -525,127 +573,373 @@ __global__ __launch_bounds__(NT) void decode_update_kernel(
     int32_t* idxh = idx + (int64_t)h * cap;
     float* cumh = cum + (int64_t)h * cap;
     const float2* ml = reinterpret_cast<const float2*>(ws_ml) + (int64_t)h * np_max * GT;
+    const float* ph = ws_p + (int64_t)h * s_rows * GT;
     const int posh = pos[h];
     int b = budget[h];
     b = b < w ? w : b;
     b = b > cap ? cap : b;
     const bool over = n1 > b;
     if (tid == 0) victim_slot = -1;
-    for (int i = tid; i < np * GT; i += NT) {
-        float2 v = make_float2(0.f, 0.f);
-        if ((i % GT) < G) v = ml[i];                                // columns beyond G were never written
-        pm[i] = v.x;
-        pl[i] = v.y;
-    }
-    __syncthreads();
-    if (tid < GT) {
-        float m = -INFINITY, l = 0.f;
-        for (int p = 0; p < np; ++p) m = fmaxf(m, pm[p * GT + tid]);
-        for (int p = 0; p < np; ++p) l += pl[p * GT + tid] * exp2f(pm[p * GT + tid] - m);
-        head_m[tid] = m;
-        head_inv[tid] = tid < G ? 1.0f / l : 0.f;
-    }
-    __syncthreads();
-    for (int i = tid; i < np * GT; i += NT) coef[i] = exp2f(pm[i] - head_m[i % GT]) * head_inv[i % GT];
-    __syncthreads();
-    // attention output: the parts' unnormalised sums, rescaled to the head's maximum
-    const float* acch = ws_acc + (int64_t)h * np_max * GT * kD;
-    for (int o = tid; o < G * kD; o += NT) {
-        const int g = o >> 7, f = o & (kD - 1);
-        float v = 0.f;
-        for (int p = 0; p < np; ++p) v = fmaf(acch[(p * GT + g) * kD + f], coef[p * GT + g], v);
-        out[(int64_t)h * G * kD + o] = v;
-    }
-    // cumulative scores and the candidate for eviction; two rows per thread in flight
-    const float* ph = ws_p + (int64_t)h * s_rows * GT;
-    unsigned long long best = ~0ull;
-    auto share = [&](int r) {                                       // sum over the query heads of p_gr
-        const float* cf = coef + (r / wave_rows) * GT;
-        float inc = 0.f;
+    float4 pr[U][GT / 4];
+    float c_in[U];
+    int id_in[U];
+    auto load_rows = [&](int r0) {                                  // clamped, never predicated
 #pragma unroll
-        for (int g4 = 0; g4 < GT; g4 += 4) {
-            const float4 pr = *reinterpret_cast<const float4*>(ph + (int64_t)r * GT + g4);
-            const float4 cc = *reinterpret_cast<const float4*>(cf + g4);
-            inc += pr.x * cc.x;
-            inc += pr.y * cc.y;
-            inc += pr.z * cc.z;
-            inc += pr.w * cc.w;
+        for (int u = 0; u < U; ++u) {
+            const int r = min(r0 + u * NT, n), rc = min(r, cap - 1);
+#pragma unroll
+            for (int g4 = 0; g4 < GT / 4; ++g4) pr[u][g4] = *reinterpret_cast<const float4*>(ph + (int64_t)r * GT + 4 * g4);
+            c_in[u] = cumh[rc];
+            id_in[u] = idxh[rc];
         }
-        return inc;
     };
-    for (int r0 = tid; r0 < n1; r0 += 2 * NT) {
-        const int r1 = r0 + NT;
-        const int ra = r0 < n ? r0 : (n > 0 ? n - 1 : 0), rb = r1 < n ? r1 : ra;   // clamped: loads first
-        const float inc0 = share(r0), inc1 = share(r1 < n1 ? r1 : r0);
-        const float c0 = n > 0 ? cumh[ra] : 0.f, c1 = n > 0 ? cumh[rb] : 0.f;
-        const int id0 = n > 0 ? idxh[ra] : 0, id1 = n > 0 ? idxh[rb] : 0;
-        if (r0 < n) {
-            const float c = c0 + inc0;
-            cumh[r0] = c;
-            if (id0 <= posh - w) {
-                const unsigned long long key = ((unsigned long long)ascending_key(c) << 32) | (uint32_t)id0;
-                best = key < best ? key : best;
+    load_rows(tid);
+    // a wave per query head: maximum and sum over the parts
+    for (int g = wave; g < GT; g += NW) {
+        if (g < G) {                                                 // columns beyond G were never written
+            float m = -INFINITY, l = 0.f;
+            for (int x = lane; x < np; x += 64) m = fmaxf(m, ml[x * GT + g].x);
+            m = wave_max(m);
+            for (int x = lane; x < np; x += 64) {
+                const float2 v = ml[x * GT + g];
+                l += v.y * exp2f(v.x - m);
             }
+            const float inv = 1.0f / wave_sum(l);
+            for (int x = lane; x < np; x += 64) coef[x * GT + g] = exp2f(ml[x * GT + g].x - m) * inv;
         } else {
-            new_cum_s = inc0;
-        }
-        if (r1 < n) {
-            const float c = c1 + inc1;
-            cumh[r1] = c;
-            if (id1 <= posh - w) {
-                const unsigned long long key = ((unsigned long long)ascending_key(c) << 32) | (uint32_t)id1;
-                best = key < best ? key : best;
-            }
-        } else if (r1 == n) {
-            new_cum_s = inc1;
+            for (int x = lane; x < np; x += 64) coef[x * GT + g] = 0.f;
         }
     }
+    __syncthreads();
+    // attention output: the parts' unnormalised sums, rescaled to the head's maximum.  128 threads per four heads'
+    // outputs (four features each), four groups of them share the parts.
+    const float* acch = ws_acc + (int64_t)h * np_max * GT * kD;
+    for (int g4 = 0; g4 < GT; g4 += 4) {
+        const int o = tid & 127, grp = tid >> 7, g = g4 + (o >> 5), f = 4 * (o & 31);
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int x0 = grp; x0 < np; x0 += 32) {
+            float4 a[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                a[e] = *reinterpret_cast<const float4*>(acch + ((int64_t)min(x0 + 4 * e, np - 1) * GT + g) * kD + f);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (x0 + 4 * e < np) {
+                    const float cf = coef[(x0 + 4 * e) * GT + g];
+                    v.x = fmaf(a[e].x, cf, v.x);
+                    v.y = fmaf(a[e].y, cf, v.y);
+                    v.z = fmaf(a[e].z, cf, v.z);
+                    v.w = fmaf(a[e].w, cf, v.w);
+                }
+            }
+        }
+        if (g4 > 0) __syncthreads();                                 // the previous heads' sums have been read
+        part_out[tid] = v;
+        __syncthreads();
+        if (grp == 0 && g < G) {
+#pragma unroll
+            for (int x = 1; x < 4; ++x) {
+                const float4 t = part_out[o + 128 * x];
+                v.x += t.x;
+                v.y += t.y;
+                v.z += t.z;
+                v.w += t.w;
+            }
+            *reinterpret_cast<float4*>(out + ((int64_t)h * G + g) * kD + f) = v;
+        }
+    }
+    // cumulative scores and the candidate for eviction
+    unsigned long long best = ~0ull;
+    int best_r = -1;
+    for (int r0 = tid; r0 < n1; r0 += U * NT) {
+        if (r0 != tid) load_rows(r0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + u * NT;
+            if (r < n1) {
+                const float* cf = coef + (r / wave_rows) * GT;
+                float inc = 0.f;                                     // sum over the query heads of p_gr
+#pragma unroll
+                for (int g4 = 0; g4 < GT / 4; ++g4) {
+                    const float4 cc = *reinterpret_cast<const float4*>(cf + 4 * g4);
+                    inc += pr[u][g4].x * cc.x;
+                    inc += pr[u][g4].y * cc.y;
+                    inc += pr[u][g4].z * cc.z;
+                    inc += pr[u][g4].w * cc.w;
+                }
+                if (r < n) {
+                    const float c = c_in[u] + inc;
+                    cumh[r] = c;
+                    if (id_in[u] <= posh - w) {
+                        const unsigned long long key = ((unsigned long long)ascending_key(c) << 32) | (uint32_t)id_in[u];
+                        if (key < best) {
+                            best = key;
+                            best_r = r;
+                        }
+                    }
+                } else {
+                    new_cum_s = inc;
+                }
+            }
+        }
+    }
+    const unsigned long long mine = best;
     best = wave_min_u64(best);
     if (lane == 0) wave_best[wave] = best;
     __syncthreads();
     best = wave_best[0];
 #pragma unroll
     for (int x = 1; x < NW; ++x) best = wave_best[x] < best ? wave_best[x] : best;
-    if (over && best != ~0ull) {
-        const int want = (int)(uint32_t)(best & 0xffffffffull);
-        for (int r = tid; r < n; r += NT)
-            if (idxh[r] == want) victim_slot = r;
-    }
+    if (over && best_r >= 0 && mine == best) victim_slot = best_r;
     __syncthreads();
-    int slot = n, ev = -1;
-    if (over) {
-        slot = victim_slot;
-        if (slot >= 0) {
-            ev = idxh[slot];
-        } else if (n < cap) {
-            slot = n;
-        } else {
-            ev = -2;
-        }
-    }
-    __syncthreads();                                                // idxh[slot] read by all before it is replaced
-    if (slot >= 0) {
-        const bf16_bits* kn = k_new + (int64_t)h * kD;
-        const bf16_bits* vn = v_new + (int64_t)h * kD;
-        if (tid < 16) copy8(kn + 8 * tid, Kh + (int64_t)slot * kD + 8 * tid);
-        else if (tid < 32) copy8(vn + 8 * (tid - 16), Vh + (int64_t)slot * kD + 8 * (tid - 16));
-        else if (tid == 32) {
-            idxh[slot] = posh;
-            cumh[slot] = new_cum_s;
-        }
-    }
-    if (tid == 0) {
-        len[h] = (slot == n) ? n + 1 : n;
-        if (evicted != nullptr) evicted[h] = ev;
-    }
+    place_token(k_new + (int64_t)h * kD, v_new + (int64_t)h * kD, Kh, Vh, idxh, cumh, len + h,
+                evicted != nullptr ? evicted + h : nullptr, tid, n, cap, over, victim_slot, (int)(uint32_t)best, posh, new_cum_s);
 }
 
-DecodePlan plan_decode(int n_heads, int G, int cap) {
+// ---- bf16, enough heads to fill the chip: one workgroup per head does the whole step ------------------------------
+// The two kernels above write every probability and every part's output to memory and read them back, a fifth of the
+// traffic of the step at 8 query heads; here they stay in LDS.  Bound by the key and value stream.  Waves take 16-row
+// tiles in turn, key and value rows of the next tile in flight under the arithmetic of this one; probabilities are kept
+// against a reference per wave, the maximum of its first tile, which is raised (and everything rescaled) only when a
+// logit exceeds it by 2^40: fp32 holds the products of that range without loss.
+// 5120 heads of 768 rows, 8 query heads: 453 + 69 us in two kernels, 410 here; 256 heads of 2048 rows: 58 + 12, 54.
+constexpr float kRefSlack = 40.f;
+template <int GT, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void decode_head_kernel(
+    const bf16_bits* __restrict__ q, const bf16_bits* __restrict__ k_new, const bf16_bits* __restrict__ v_new, int G,
+    const int32_t* __restrict__ pos, const int32_t* __restrict__ budget, int w, int cap, bf16_bits* Kc, bf16_bits* Vc,
+    int32_t* idx, float* cum, int32_t* len, float* __restrict__ out, int32_t* __restrict__ evicted, int s_rows) {
+    constexpr int NT = 64 * NW;
+    extern __shared__ __align__(16) float dynh[];
+    float* prob = dynh;                                              // [s_rows][GT]
+    float* accs = dynh + s_rows * GT;                                // [NW][GT][128]
+    __shared__ float wave_m[NW][GT], wave_l[NW][GT];
+    __shared__ __align__(16) float coef[NW * GT];                    // exp2(m_wave - m) / sum
+    __shared__ unsigned long long wave_best[NW];
+    __shared__ int victim_slot;
+    __shared__ float new_cum_s;
+    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c16 = lane & 15, j = lane >> 4;
+    int n = len[h];
+    n = n < 0 ? 0 : (n > cap ? cap : n);
+    const int n1 = n + 1, n_t = (n1 + 15) >> 4;                      // 16 n_t <= s_rows
+    bf16_bits* Kh = Kc + (int64_t)h * cap * kD;
+    bf16_bits* Vh = Vc + (int64_t)h * cap * kD;
+    int32_t* idxh = idx + (int64_t)h * cap;
+    float* cumh = cum + (int64_t)h * cap;
+    const bf16_bits* kn = k_new + (int64_t)h * kD;
+    const bf16_bits* vn = v_new + (int64_t)h * kD;
+    const int posh = pos[h];
+    int b = budget[h];
+    b = b < w ? w : b;
+    b = b > cap ? cap : b;
+    const bool over = n1 > b;
+    if (tid == 0) victim_slot = -1;
+
+    bf16x8_t qb[4];                                                  // column c16 = query head, zero beyond G
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (c16 < G) v = *reinterpret_cast<const uint4*>(q + ((int64_t)h * G + c16) * kD + 32 * ks + 8 * j);
+        qb[ks] = __builtin_bit_cast(bf16x8_t, v);
+    }
+    auto load_k = [&](uint4 (&dst)[4], int t) {                      // rows past the end re-read the new token
+        const int r = 16 * t + c16;
+        const bf16_bits* src = (r < n ? Kh + (int64_t)r * kD : kn) + 8 * j;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) dst[ks] = *reinterpret_cast<const uint4*>(src + 32 * ks);
+    };
+    auto load_v = [&](uint4 (&dst)[4], int t) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = 16 * t + 4 * u + j;
+            const bf16_bits* src = (r < n ? Vh + (int64_t)r * kD : vn) + 8 * c16;
+            dst[u] = *reinterpret_cast<const uint4*>(src);
+        }
+    };
+    const float qs = 0.08838834764831845f * 1.4426950408889634f;     // 1/sqrt(128) * log2(e)
+    constexpr float kNoRow = -1e30f;                                 // reference of a wave without rows (finite: no NaN)
+    float ref = kNoRow, sum = 0.f;                                   // of column c16; sum over this lane's rows
+    float acc[GT][8];
+#pragma unroll
+    for (int g = 0; g < GT; ++g)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
+    auto column_max = [&](const f32x4_t& s) {
+        float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        return fmaxf(mx, __shfl_xor(mx, 32, 64));
+    };
+    auto tile = [&](const uint4 (&kt)[4], const uint4 (&vt)[4], int t) {
+        f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kt[ks]), qb[ks], s, 0, 0, 0);
+        bool above = false;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            s[v] = 16 * t + 4 * j + v < n1 ? s[v] * qs : -INFINITY;
+            above |= s[v] > ref + kRefSlack;
+        }
+        if (__any(above)) {                                          // the first tile (t = wave), hardly ever later
+            const float m = fmaxf(ref, column_max(s)), f = exp2f(ref - m);
+            sum *= f;
+#pragma unroll
+            for (int g = 0; g < GT; ++g) {
+                const float fg = __shfl(f, g, 64);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[g][e] *= fg;
+            }
+            if (c16 < GT)
+                for (int u = wave; u < t; u += NW)                   // the entries this lane has written
+                    for (int v = 0; v < 4; ++v) prob[(16 * u + 4 * j + v) * GT + c16] *= f;
+            ref = m;
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float e = exp2f(s[v] - ref);
+            sum += e;
+            if (c16 < GT) prob[(16 * t + 4 * j + v) * GT + c16] = e;
+        }
+        // LDS traffic of one wave is processed in issue order; the fences keep the compiler from moving the reads
+        // below over the writes above
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            float vf[8];
+            const uint32_t wds[4] = {vt[u].x, vt[u].y, vt[u].z, vt[u].w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                vf[2 * i] = __uint_as_float(wds[i] << 16);
+                vf[2 * i + 1] = __uint_as_float(wds[i] & 0xffff0000u);
+            }
+            const float* prow = prob + (16 * t + 4 * u + j) * GT;
+#pragma unroll
+            for (int g4 = 0; g4 < GT; g4 += 4) {
+                const float4 pr = *reinterpret_cast<const float4*>(prow + g4);
+                const float prs[4] = {pr.x, pr.y, pr.z, pr.w};
+#pragma unroll
+                for (int gg = 0; gg < 4; ++gg)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[g4 + gg][e] = fmaf(prs[gg], vf[e], acc[g4 + gg][e]);
+            }
+        }
+    };
+    uint4 ka[4], va[4], kb[4], vb[4];
+    load_k(ka, wave);
+    load_v(va, wave);
+    for (int t = wave; t < n_t; t += 2 * NW) {
+        load_k(kb, t + NW);
+        load_v(vb, t + NW);
+        tile(ka, va, t);
+        if (t + NW < n_t) {
+            load_k(ka, t + 2 * NW);
+            load_v(va, t + 2 * NW);
+            tile(kb, vb, t + NW);
+        }
+    }
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    if (j == 0 && c16 < GT) {
+        wave_m[wave][c16] = ref;
+        wave_l[wave][c16] = sum;
+    }
+    // sum over the four lane rows; lane row j keeps query head g4 + {0,2,1,3}[j]
+    const int gsel = ((j & 1) << 1) | (j >> 1);
+#pragma unroll
+    for (int g4 = 0; g4 < GT; g4 += 4) {
+        float tot[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            tot[e] = reduce4_over_rows(acc[g4][e], acc[g4 + 1][e], acc[g4 + 2][e], acc[g4 + 3][e]);
+        float* dst = accs + (wave * GT + g4 + gsel) * kD + 8 * c16;
+        reinterpret_cast<float4*>(dst)[0] = make_float4(tot[0], tot[1], tot[2], tot[3]);
+        reinterpret_cast<float4*>(dst)[1] = make_float4(tot[4], tot[5], tot[6], tot[7]);
+    }
+    __syncthreads();
+    if (tid < GT) {
+        float m = wave_m[0][tid], l = 0.f;
+#pragma unroll
+        for (int x = 1; x < NW; ++x) m = fmaxf(m, wave_m[x][tid]);
+#pragma unroll
+        for (int x = 0; x < NW; ++x) l += wave_l[x][tid] * exp2f(wave_m[x][tid] - m);
+        const float inv = tid < G ? 1.0f / l : 0.f;
+#pragma unroll
+        for (int x = 0; x < NW; ++x) coef[x * GT + tid] = exp2f(wave_m[x][tid] - m) * inv;
+    }
+    __syncthreads();
+    for (int o = tid; o < G * kD; o += NT) {
+        const int g = o >> 7;
+        float v = 0.f;
+#pragma unroll
+        for (int x = 0; x < NW; ++x) v = fmaf(accs[x * GT * kD + o], coef[x * GT + g], v);
+        out[(int64_t)h * G * kD + o] = v;
+    }
+    // cumulative scores and the candidate for eviction
+    unsigned long long best = ~0ull;
+    int best_r = -1;
+    constexpr int U = 4;
+    for (int r0 = tid; r0 < n1; r0 += U * NT) {
+        float c_in[U];
+        int id_in[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int rc = min(r0 + u * NT, cap - 1);
+            c_in[u] = cumh[rc];
+            id_in[u] = idxh[rc];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + u * NT;
+            if (r < n1) {
+                const float* cf = coef + ((r >> 4) % NW) * GT;
+                float inc = 0.f;                                     // sum over the query heads of p_gr
+#pragma unroll
+                for (int g4 = 0; g4 < GT; g4 += 4) {
+                    const float4 pr = *reinterpret_cast<const float4*>(prob + r * GT + g4);
+                    const float4 cc = *reinterpret_cast<const float4*>(cf + g4);
+                    inc += pr.x * cc.x;
+                    inc += pr.y * cc.y;
+                    inc += pr.z * cc.z;
+                    inc += pr.w * cc.w;
+                }
+                if (r < n) {
+                    const float c = c_in[u] + inc;
+                    cumh[r] = c;
+                    if (id_in[u] <= posh - w) {
+                        const unsigned long long key = ((unsigned long long)ascending_key(c) << 32) | (uint32_t)id_in[u];
+                        if (key < best) {
+                            best = key;
+                            best_r = r;
+                        }
+                    }
+                } else {
+                    new_cum_s = inc;
+                }
+            }
+        }
+    }
+    const unsigned long long mine = best;
+    best = wave_min_u64(best);
+    if (lane == 0) wave_best[wave] = best;
+    __syncthreads();
+    best = wave_best[0];
+#pragma unroll
+    for (int x = 1; x < NW; ++x) best = wave_best[x] < best ? wave_best[x] : best;
+    if (over && best_r >= 0 && mine == best) victim_slot = best_r;
+    __syncthreads();
+    place_token(kn, vn, Kh, Vh, idxh, cumh, len + h, evicted != nullptr ? evicted + h : nullptr, tid, n, cap, over,
+                victim_slot, (int)(uint32_t)best, posh, new_cum_s);
+}
+
+DecodePlan plan_decode(int n_heads, int G, int cap, int wave_rows) {
     DecodePlan p;
     p.GT = G <= 4 ? 4 : (G <= 8 ? 8 : 16);
     // 256-row waves when that still leaves a few thousand waves to spread over the chip
     const int64_t waves256 = (int64_t)n_heads * ((cap + 1 + 255) / 256);
-    p.wave_rows = (p.GT <= 8 && waves256 >= 2048) ? 256 : 128;
+    p.wave_rows = wave_rows > 0 ? wave_rows : (p.GT <= 8 && waves256 >= 2048) ? 256 : 128;
     p.s_rows = (cap + 1 + p.wave_rows - 1) / p.wave_rows * p.wave_rows;
     p.np_max = p.s_rows / p.wave_rows;
     size_t off = 0;
@@ -678,21 +972,11 @@ static hipError_t launch_decode_wave_t(const void* q, const void* k_new, const v
         n_heads, G, cap, static_cast<const bf16_bits*>(Kc), static_cast<const bf16_bits*>(Vc), len, p.np_max,
         p.s_rows, ws_p, ws_ml, ws_acc);
     env.end();
-    const size_t lds_b = (size_t)3 * p.np_max * GT * sizeof(float);
-    const bf16_bits* kn = static_cast<const bf16_bits*>(k_new);
-    const bf16_bits* vn = static_cast<const bf16_bits*>(v_new);
-    bf16_bits* Kp = static_cast<bf16_bits*>(Kc);
-    bf16_bits* Vp = static_cast<bf16_bits*>(Vc);
     env.begin("decode_update");
-    // few heads: larger workgroups to have more loads in flight; many heads: more workgroups per CU
-    if (n_heads < 2048)
-        decode_update_kernel<GT, 512><<<n_heads, 512, lds_b, env.s>>>(kn, vn, G, pos, budget, w, cap, Kp, Vp, idx, cum,
-                                                                      len, out, evicted, WR, p.np_max, p.s_rows, ws_p,
-                                                                      ws_ml, ws_acc);
-    else
-        decode_update_kernel<GT, 256><<<n_heads, 256, lds_b, env.s>>>(kn, vn, G, pos, budget, w, cap, Kp, Vp, idx, cum,
-                                                                      len, out, evicted, WR, p.np_max, p.s_rows, ws_p,
-                                                                      ws_ml, ws_acc);
+    decode_update_kernel<GT><<<n_heads, 512, (size_t)p.np_max * GT * sizeof(float), env.s>>>(
+        static_cast<const bf16_bits*>(k_new), static_cast<const bf16_bits*>(v_new), G, pos, budget, w, cap,
+        static_cast<bf16_bits*>(Kc), static_cast<bf16_bits*>(Vc), idx, cum, len, out, evicted, WR, p.np_max, p.s_rows, ws_p,
+        ws_ml, ws_acc);
     env.end();
     return hipGetLastError();
 }
@@ -708,10 +992,40 @@ hipError_t launch_decode_wave(const void* q, const void* k_new, const void* v_ne
         if (p.GT == 4) UNCOMP_WAVE_CASE(4, 256);
         UNCOMP_WAVE_CASE(8, 256);
     }
+    if (p.wave_rows == 64) {
+        if (p.GT == 4) UNCOMP_WAVE_CASE(4, 64);
+        if (p.GT == 8) UNCOMP_WAVE_CASE(8, 64);
+        UNCOMP_WAVE_CASE(16, 64);
+    }
     if (p.GT == 4) UNCOMP_WAVE_CASE(4, 128);
     if (p.GT == 8) UNCOMP_WAVE_CASE(8, 128);
     UNCOMP_WAVE_CASE(16, 128);
 #undef UNCOMP_WAVE_CASE
+}
+
+// Waves of one workgroup of the one-kernel step: eight while a CU gets one or two heads, four beyond.
+static int head_waves(int n_heads) { return n_heads < kHeadStepWide ? 8 : 4; }
+
+size_t decode_head_lds_bytes(int n_heads, int G, int cap) {
+    const int GT = G <= 4 ? 4 : 8;
+    return ((size_t)(cap + 16) / 16 * 16 + (size_t)head_waves(n_heads) * kD) * GT * sizeof(float);
+}
+
+hipError_t launch_decode_head(const void* q, const void* k_new, const void* v_new, int n_heads, int G, const int32_t* pos,
+                              const int32_t* budget, int w, int cap, void* Kc, void* Vc, int32_t* idx, float* cum,
+                              int32_t* len, float* out, int32_t* evicted, const Env& env) {
+    const int nw = head_waves(n_heads);
+    const size_t lds = decode_head_lds_bytes(n_heads, G, cap);
+    if (lds > kDecodeHeadLdsMax || G > 8) return hipErrorInvalidValue;   // the interface checks before
+    auto kern = G <= 4 ? (nw == 8 ? decode_head_kernel<4, 8> : decode_head_kernel<4, 4>)
+                       : (nw == 8 ? decode_head_kernel<8, 8> : decode_head_kernel<8, 4>);
+    env.begin("decode_head");
+    kern<<<n_heads, 64 * nw, lds, env.s>>>(static_cast<const bf16_bits*>(q), static_cast<const bf16_bits*>(k_new),
+                                           static_cast<const bf16_bits*>(v_new), G, pos, budget, w, cap,
+                                           static_cast<bf16_bits*>(Kc), static_cast<bf16_bits*>(Vc), idx, cum, len, out,
+                                           evicted, (cap + 16) / 16 * 16);
+    env.end();
+    return hipGetLastError();
 }
 
 hipError_t launch_decode_init(const float* score, const int32_t* idx, const int32_t* len, int n_heads,
@@ -727,6 +1041,7 @@ hipError_t launch_decode_init(const float* score, const int32_t* idx, const int3
 // dynamic LDS the one-kernel decode path may ask for: G*(cap+1) <= 36864 floats plus rounding of cap
 constexpr size_t kDecodeStepLdsMax = (36864 + 64) * sizeof(float);
 
+// what the update kernel may ask for at most (it takes one such table, and 8 KB)
 size_t decode_update_lds_bytes(const DecodePlan& p) { return (size_t)3 * p.np_max * p.GT * sizeof(float); }
 
 size_t decode_step_lds_bytes(int G, int cap) {
@@ -777,6 +1092,12 @@ static hipError_t allow_decode_step() {
     return allow_dynamic_lds(reinterpret_cast<const void*>(decode_step_kernel<T, GT>), kDecodeStepLdsMax);
 }
 
+template <int GT>
+static hipError_t allow_decode_head() {
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(decode_head_kernel<GT, 4>), kDecodeHeadLdsMax);
+    return e == hipSuccess ? allow_dynamic_lds(reinterpret_cast<const void*>(decode_head_kernel<GT, 8>), kDecodeHeadLdsMax) : e;
+}
+
 hipError_t init_decode_kernels() {
     hipError_t e = allow_decode_step<bf16_bits, 4>();
     if (e == hipSuccess) e = allow_decode_step<bf16_bits, 8>();
@@ -784,6 +1105,8 @@ hipError_t init_decode_kernels() {
     if (e == hipSuccess) e = allow_decode_step<float, 4>();
     if (e == hipSuccess) e = allow_decode_step<float, 8>();
     if (e == hipSuccess) e = allow_decode_step<float, 16>();
+    if (e == hipSuccess) e = allow_decode_head<4>();
+    if (e == hipSuccess) e = allow_decode_head<8>();
     return e;
 }
 

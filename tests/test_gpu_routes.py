@@ -105,3 +105,64 @@ def test_entropy_fp32_tile_split(ctx, n_mat, N):
     H, eig = ctx.head_entropy(X.to(DEV), k_trunc=32, flags=O.DEFAULT_FLAGS, want_eig=True)
     np.testing.assert_allclose(H.cpu().numpy(), Href, rtol=1e-4, atol=5e-5)
     np.testing.assert_allclose(eig.cpu().numpy(), eref, rtol=0, atol=2e-5)
+
+
+# The decode step of many heads in one kernel: eight and four waves per head, lengths around the 16-row tiles and the
+# waves' turns, evictions, growth and full caches, and a key far down the cache whose logit is 34 above all others (the
+# waves' reference has to follow it).  Tolerances of the step as everywhere (_check_step).
+@pytest.mark.parametrize("n_heads,G,cap,w", [(256, 4, 300, 8), (257, 7, 270, 3), (1024, 8, 290, 16), (1030, 1, 150, 5),
+                                             (256, 2, 16, 4)])
+def test_decode_many_heads(ctx, n_heads, G, cap, w):
+    from tests.test_gpu_decode import D, _check_step, _random_state
+    edges = [0, 1, 15, 16, 17, 63, 64, 65, 127, 128, 129, cap - 1, cap, min(cap, 260), min(cap, 200)]
+    lens = [min(cap, edges[h % len(edges)]) for h in range(n_heads)]
+    pos0 = [cap + 50 + h % 90 for h in range(n_heads)]
+    st = _random_state(n_heads, cap, lens, pos0, torch.bfloat16, seed=cap, w=w)
+    budget = torch.tensor([(h * 37) % (cap + 20) if h % 3 else lens[h] for h in range(n_heads)], dtype=torch.int32)
+    g = torch.Generator().manual_seed(G)
+    heads = sorted(set(range(0, n_heads, n_heads // 48)) | set(range(n_heads - len(edges), n_heads)))
+    swaps = 0
+    for t in range(2):
+        q = torch.randn(n_heads, G, D, generator=g).to(torch.bfloat16)
+        kn, vn = (torch.randn(n_heads, D, generator=g).to(torch.bfloat16) for _ in range(2))
+        for h in range(0, n_heads, 2):
+            if lens[h] > 150:
+                q0 = q[h, 0].float()
+                st.Kc[h, lens[h] - 2 - t] = (q0 * (34.0 * D ** 0.5 / float(q0 @ q0))).to(torch.bfloat16).to(DEV)
+        pos = torch.tensor([p + t for p in pos0], dtype=torch.int32)
+        before = st.host()
+        out, ev = ctx.decode_step(q.to(DEV), kn.to(DEV), vn.to(DEV), pos.to(DEV), budget.to(DEV), w, st.Kc, st.Vc, st.idx,
+                                  st.cum, st.ln)
+        torch.cuda.synchronize()
+        swaps += _check_step(before, st.host(), out.cpu().numpy(), ev.cpu().numpy(), q, kn, vn, pos.numpy(),
+                             budget.numpy(), w, cap, heads=heads)
+    assert swaps <= 2                               # near ties at fp32 resolution, each checked to be one
+
+
+# Few heads: 64-row waves, and the 128-row ones of a workspace that only holds their partials.
+@pytest.mark.parametrize("n_heads,G,cap", [(1, 4, 63), (3, 8, 64), (5, 16, 130), (8, 4, 1290)])
+def test_decode_few_heads_both_plans(ctx, n_heads, G, cap):
+    from paper_2410_03090_amd import binding
+    from tests.test_gpu_decode import D, _check_step, _random_state
+    coarse = 256 * 4                                # offsets are rounded up to 256 bytes
+    np128, GT = (cap + 128) // 128, 4 if G <= 4 else (8 if G <= 8 else 16)
+    coarse += n_heads * (G * D + np128 * 128 * GT + np128 * GT * (2 + D)) * 4
+    small = binding.Context(0, coarse)
+    try:
+        for c in (ctx, small):
+            lens = [min(cap, cap - 3 * h) for h in range(n_heads)]
+            pos0 = [cap + 50 + h for h in range(n_heads)]
+            st = _random_state(n_heads, cap, lens, pos0, torch.bfloat16, seed=cap, w=4)
+            budget = torch.tensor([cap - h for h in range(n_heads)], dtype=torch.int32)
+            g = torch.Generator().manual_seed(G)
+            q = torch.randn(n_heads, G, D, generator=g).to(torch.bfloat16)
+            kn, vn = (torch.randn(n_heads, D, generator=g).to(torch.bfloat16) for _ in range(2))
+            pos = torch.tensor(pos0, dtype=torch.int32)
+            before = st.host()
+            out, ev = c.decode_step(q.to(DEV), kn.to(DEV), vn.to(DEV), pos.to(DEV), budget.to(DEV), 4, st.Kc, st.Vc, st.idx,
+                                    st.cum, st.ln)
+            torch.cuda.synchronize()
+            assert _check_step(before, st.host(), out.cpu().numpy(), ev.cpu().numpy(), q, kn, vn, pos.numpy(),
+                               budget.numpy(), 4, cap) == 0
+    finally:
+        small.close()
