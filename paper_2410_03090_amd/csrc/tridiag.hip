@@ -363,7 +363,9 @@ __global__ __launch_bounds__(kTriThreads, 2) void tridiag_entropy_kernel(
         UNCOMP_CHUNK(14);
         if constexpr (S0 == 0) UNCOMP_CHUNK(15);
 #undef UNCOMP_CHUNK
-        const bool some = sigma > 0x1p-900;                     // nothing to reflect: beta = 0 leaves the matrix as it is
+        // Nothing to reflect: beta = 0 leaves the matrix as it is.  The trace is one, so entries below 2^-200 are nothing,
+        // and beta^2 ~ sigma^-2 stays finite: a matrix with zero rows left residues of 1e-160, infinities and then NaN.
+        const bool some = sigma > 0x1p-400;
         const double alpha = some ? (x1 >= 0.0 ? -nrm : nrm) : 0.0;
         beta = some ? beta : 0.0;
         if (top) each16<0>([&](auto C) { chunk(I0{}, C); });

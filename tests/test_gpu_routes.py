@@ -166,3 +166,18 @@ def test_decode_few_heads_both_plans(ctx, n_heads, G, cap):
                                budget.numpy(), 4, cap) == 0
     finally:
         small.close()
+
+
+# Wide-matrix entropy where the Cholesky step retires columns (rank below 128 from few tokens), at one and several splits
+# of the sum over the features, ragged token counts, no mean correction.
+@pytest.mark.parametrize("N,D,r", [(40, 256, 100), (129, 384, 60), (1000, 2048, 30), (3001, 640, 90)])
+def test_matrix_entropy_ranks_and_splits(ctx, N, D, r):
+    g = torch.Generator().manual_seed(N)
+    X = (torch.randn(N, r, generator=g) @ (torch.randn(r, D, generator=g) * torch.linspace(1.0, 0.05, r)[:, None]) / r + 0.1
+         ).to(torch.bfloat16)
+    for flags in (O.DEFAULT_FLAGS, O.DEFAULT_FLAGS & ~O.FLAG_CENTER):
+        Href, eref = O.head_entropy(to_f64(X[None]), k_trunc=32, flags=flags)
+        H, eig = ctx.matrix_entropy(X[None].to(DEV), k_trunc=32, n_iter=12, flags=flags, want_eig=True)
+        # as the other tests of this call: the Ritz values of the leading 32 against the fp64 eigenvalues
+        np.testing.assert_allclose(H.cpu().numpy(), Href, rtol=1e-4)
+        np.testing.assert_allclose(eig.cpu().numpy()[:, :32], eref[:, :32], rtol=0, atol=2e-5)
