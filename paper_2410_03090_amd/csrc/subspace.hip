@@ -4,7 +4,7 @@
 // 128-dimensional subspace that block power iteration drives onto the dominant eigenvectors.
 //
 //   x_bar = mean token, C = sum_t (x_t - x_bar)(x_t - x_bar)^T            (never stored)
-//   Q_0   = fixed pseudo-random D x 128 block, orthonormalised
+//   Q_0   = fixed pseudo-random D x 128 block
 //   repeat:  Z = X Q  (N x 128),  W = C Q = X^T Z - s (s^T Q)/N  (D x 128),  Q = orth(W)
 //   end:     Z = X Q;  the centred covariance of the N projected tokens z_t is Q^T C Q, whose
 //            eigenvalues (the ordinary 128-wide entropy path) are the Ritz values; Eq. 5 without
@@ -38,9 +38,13 @@ __device__ __forceinline__ float start_value(uint32_t d, uint32_t j) {
 
 }  // namespace
 
-__global__ __launch_bounds__(256) void sub_start_kernel(float* __restrict__ W, int D) {
+// The start block, and as Rinv the multiple of the identity that gives its columns a norm of about one.  A random block is
+// well conditioned as it is (singular values within a factor of six even at 256 features), and what the first round
+// needs is its span: orthonormalising it too was one Cholesky step in ten, 75 us.
+__global__ __launch_bounds__(256) void sub_start_kernel(float* __restrict__ W, int D, float* __restrict__ Rinv) {
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e < D * kP) W[e] = start_value((uint32_t)(e / kP), (uint32_t)(e % kP));
+    if (e < kP * kP) Rinv[e] = e / kP == e % kP ? sqrtf(3.f / (float)D) : 0.f;      // D >= 128: one thread per entry
 }
 
 // Column sums and sums of squares of X over a chunk of tokens, in fp64: part[chunk][2][D].
@@ -208,51 +212,54 @@ __global__ __launch_bounds__(256) void sub_gemm_kernel(const T* __restrict__ A, 
     }
 }
 
-// Q = W Rinv for 32 rows of W per workgroup (fp32 ALUs, a thread owns 2 rows x 8 columns, Rinv staged 16 rows
-// at a time), together with what the next round needs of Q besides: its transposed bf16 halves Qt_hi / Qt_lo
+// Q = W Rinv for 32 rows of W per workgroup (fp32 ALUs, a thread owns 2 rows x 8 columns), together with what the next
+// round needs of Q besides: its transposed bf16 halves Qt_hi / Qt_lo
 // [128][D] (the operand that the MFMA version of Z = X Q streams; skipped when Qt_hi is null) and, when centring
 // (s not null), this row block's share of s^T Q in fp64: zpart[block][128].  D is a multiple of 128.
+// Bound by latency: Rinv goes to LDS whole, all of it in flight at once (11 us at D = 4096; 14 with sixteen rows
+// at a time).
 constexpr int kQRows = 32;
+constexpr size_t kQLdsBytes = (size_t)(kP * kP + kQRows * (kP + 4)) * sizeof(float);
 __global__ __launch_bounds__(256) void sub_q_kernel(const float* __restrict__ W, const float* __restrict__ Rinv, int D,
                                                     const double* __restrict__ s, float* __restrict__ Q,
                                                     uint16_t* __restrict__ Qt_hi, uint16_t* __restrict__ Qt_lo,
                                                     double* __restrict__ zpart) {
-    __shared__ __align__(16) float Ws[kQRows][kP + 4];
-    __shared__ __align__(16) float Rs[16][kP];
-    __shared__ float Qs[kQRows][kP + 1];
+    extern __shared__ __align__(16) float qlds[];
+    float(*Rs)[kP] = reinterpret_cast<float(*)[kP]>(qlds);
+    float(*Ws)[kP + 4] = reinterpret_cast<float(*)[kP + 4]>(qlds + kP * kP);
+    float(*Qs)[kP + 1] = reinterpret_cast<float(*)[kP + 1]>(qlds);   // over Rs, once that has been read
     const int d0 = blockIdx.x * kQRows;
     const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+    {
+        float4 wr[4], rr[16];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int idx = tid + 256 * e, r = idx >> 5, q = idx & 31;
-        *reinterpret_cast<float4*>(&Ws[r][4 * q]) = *reinterpret_cast<const float4*>(W + (int64_t)(d0 + r) * kP + 4 * q);
+        for (int e = 0; e < 4; ++e) wr[e] = *reinterpret_cast<const float4*>(W + (int64_t)d0 * kP + 4 * (tid + 256 * e));
+#pragma unroll
+        for (int e = 0; e < 16; ++e) rr[e] = *reinterpret_cast<const float4*>(Rinv + 4 * (tid + 256 * e));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) *reinterpret_cast<float4*>(&Ws[(tid + 256 * e) >> 5][4 * (tid & 31)]) = wr[e];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) *reinterpret_cast<float4*>(qlds + 4 * (tid + 256 * e)) = rr[e];
     }
+    __syncthreads();
     float acc[2][8];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[i][j] = 0.f;
-    for (int k0 = 0; k0 < kP; k0 += 16) {
-        __syncthreads();                                             // Ws written / the previous 16 rows of Rinv read
+#pragma unroll 8
+    for (int k = 0; k < kP; ++k) {
+        const float a0 = Ws[2 * ty][k], a1 = Ws[2 * ty + 1][k];
+        const float4 b0 = *reinterpret_cast<const float4*>(&Rs[k][8 * tx]);
+        const float4 b1 = *reinterpret_cast<const float4*>(&Rs[k][8 * tx + 4]);
+        const float bv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int idx = tid + 256 * e, k = idx >> 5, q = idx & 31;
-            *reinterpret_cast<float4*>(&Rs[k][4 * q]) = *reinterpret_cast<const float4*>(Rinv + (int64_t)(k0 + k) * kP + 4 * q);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const float a0 = Ws[2 * ty][k0 + k], a1 = Ws[2 * ty + 1][k0 + k];
-            const float4 b0 = *reinterpret_cast<const float4*>(&Rs[k][8 * tx]);
-            const float4 b1 = *reinterpret_cast<const float4*>(&Rs[k][8 * tx + 4]);
-            const float bv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                acc[0][j] = fmaf(a0, bv[j], acc[0][j]);
-                acc[1][j] = fmaf(a1, bv[j], acc[1][j]);
-            }
+        for (int j = 0; j < 8; ++j) {
+            acc[0][j] = fmaf(a0, bv[j], acc[0][j]);
+            acc[1][j] = fmaf(a1, bv[j], acc[1][j]);
         }
     }
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         float* o = Q + (int64_t)(d0 + 2 * ty + i) * kP + 8 * tx;
@@ -509,34 +516,40 @@ __device__ __forceinline__ double lane_value(double x, int src) {
     return __hiloint2double(hi, lo);
 }
 
+// 1 / sqrt(x) of a positive fp64 number: the hardware's estimate (2^-24) and one third-order step (the library function
+// spends more on denormals and infinities, which a pivot above the tolerance of a finite Gram is not).
+__device__ __forceinline__ double inv_sqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
 // One workgroup: Cholesky G = L L^T in LDS (fp64), then Rinv = L^-T as fp32 so that Q = W Rinv has
 // orthonormal columns.  A pivot below 1e-12 of the largest diagonal entry retires its column (its
-// row and column of Rinv are zero).  Both halves work on 16-wide blocks, two workgroup barriers
-// per block instead of two per column:
-//   factor   the 16 x 16 diagonal block in the registers of one wave (lane = row, values of other
-//            rows by v_readlane), the rows below it by forward substitution (one thread per row),
-//            the trailing triangle by a rank-16 update in 16 x 16 tiles (v_mfma_f64_16x16x4_f64);
-//   invert   X = L^-1: the eight 16 x 16 inverses of the diagonal blocks at once (one thread per
-//            column), then block row by block row as products of tiles.  X[k][c], k > c, lives at
-//            G[c][k] in the unused upper triangle.
-// Phase times of one call (100 MHz wall clock, warm input): first diagonal block 3 us, rows below 9,
-// trailing tiles with the next diagonal block beside them 22, diagonal inverses 2, block rows of the
-// inverse 12: 49 us.  With the tiled parts on the vector ALUs, a substitution per block row and the
-// diagonal blocks on their own it was 101.
-__global__ __launch_bounds__(256) void sub_chol_kernel(const double* __restrict__ gsum, float* __restrict__ Rinv) {
+// row and column of Rinv are zero).  Bound by the chain of the 128 pivots.  By 16-wide block columns, three barriers each:
+//   factor   lanes 0-15 of three waves hold the 16 rows of the diagonal block (values of other rows by v_readlane) and
+//            factor it, each for itself; their other lanes carry the rows below it and the rows of a 16 x 16 identity
+//            through the same instructions, which leaves them as the panel of L and as the inverse of the diagonal
+//            block.  The other five waves meanwhile update what the previous panel left to be updated;
+//   update   the next block column, one 16 x 16 tile per wave (v_mfma_f64_16x16x4_f64).
+// Then X = L^-1 block row by block row as products of tiles.  X[k][c], k > c, lives at G[c][k] in the unused upper triangle.
+// With the diagonal block on one wave, the panel a substitution with a thread per row and four waves: 55 us; now 47.
+constexpr int kCholThreads = 512;
+__global__ __launch_bounds__(kCholThreads) void sub_chol_kernel(const double* __restrict__ gsum, float* __restrict__ Rinv) {
     extern __shared__ __align__(16) double G[];                // [128][129]
     __shared__ double dinv[kP];
     __shared__ double maxdiag;
-    constexpr int LD = kP + 1, B = 16, NB = kP / B;
+    constexpr int LD = kP + 1, B = 16, NB = kP / B, NT = kCholThreads, NW = NT / 64, kFactorWaves = 3;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const double2* g2 = reinterpret_cast<const double2*>(gsum);
-    for (int e0 = tid; e0 < kP * kP / 2; e0 += 256 * 16) {         // 32 loads per thread, sixteen in flight
-        double2 v[16];
+    {
+        const double2* g2 = reinterpret_cast<const double2*>(gsum);
+        constexpr int kLoads = kP * kP / 2 / NT;
+        double2 v[kLoads];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = g2[e0 + 256 * u];
+        for (int u = 0; u < kLoads; ++u) v[u] = g2[tid + NT * u];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int e = e0 + 256 * u, row = e >> 6, col = 2 * (e & 63);
+        for (int u = 0; u < kLoads; ++u) {
+            const int e = tid + NT * u, row = e >> 6, col = 2 * (e & 63);
             G[row * LD + col] = v[u].x;
             G[row * LD + col + 1] = v[u].y;
         }
@@ -550,46 +563,12 @@ __global__ __launch_bounds__(256) void sub_chol_kernel(const double* __restrict_
     }
     __syncthreads();
     const double tol = maxdiag * 1e-12;
-    // diagonal block p, by one wave: lane i (and its copies in the upper lanes) holds row 16 p + i
-    auto factor_diagonal = [&](int p) {
-        const int j0 = B * p;
-        const int i = lane & (B - 1);
-        double a[B];
-#pragma unroll
-        for (int k = 0; k < B; ++k) a[k] = G[(j0 + i) * LD + j0 + k];
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            const double piv = lane_value(a[j], j);
-            const bool live = piv > tol;
-            const double di = live ? rsqrt(piv) : 0.0;              // one reciprocal square root instead of a root and a division
-            const double d = piv * di;
-            a[j] = i == j ? d : a[j] * di;                           // rows i < j: values nobody reads
-#pragma unroll
-            for (int k = j + 1; k < B; ++k) {
-                const double lkj = lane_value(a[j], k);              // L[k][j]
-                a[k] = fma(-a[j], lkj, a[k]);                        // G[i][k] -= L[i][j] L[k][j]; only j < k <= i is read later
-            }
-            if (lane == 0) dinv[j0 + j] = di;
-        }
-        if (lane < B) {
-#pragma unroll
-            for (int k = 0; k < B; ++k)
-                if (k <= i) G[(j0 + i) * LD + j0 + k] = a[k];
-        }
-    };
-    // Trailing tile t of block p (t = ti (ti + 1) / 2 + tk, tk <= ti: tile (p + 1 + ti, p + 1 + tk)) on the fp64
-    // matrix cores: -= L[I][p] L[K][p]^T.  Operand lane (c, kk) holds row c of its factor at column 4 s + kk of the
-    // panel; result register v is row 4 v + kk, column c.  Diagonal tiles are computed whole: what lands above
-    // the diagonal is not read by the factorisation.
-    auto update_tile = [&](int p, int t) {
-        const int j0 = B * p;
+    // Tile (I, K) -= L[I][p] L[K][p]^T on the fp64 matrix cores.  Operand lane (c, kk) holds row c of its factor at column
+    // 4 s + kk of the panel; result register v is row 4 v + kk, column c.  Diagonal tiles are computed whole: what lands
+    // above the diagonal is not read by the factorisation.
+    auto update_tile = [&](int p, int I, int K) {
+        const int j0 = B * p, r0 = B * I, c0 = B * K;
         const int c = lane & 15, kk = lane >> 4;
-        int ti = 0, rem = t;
-        while (rem > ti) {
-            rem -= ti + 1;
-            ++ti;
-        }
-        const int r0 = B * (p + 1 + ti), c0 = B * (p + 1 + rem);
         f64x4_t acc;
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[v] = G[(r0 + 4 * v + kk) * LD + c0 + c];
@@ -602,66 +581,64 @@ __global__ __launch_bounds__(256) void sub_chol_kernel(const double* __restrict_
 #pragma unroll
         for (int v = 0; v < 4; ++v) G[(r0 + 4 * v + kk) * LD + c0 + c] = acc[v];
     };
-    if (wv == 0) factor_diagonal(0);
-    __syncthreads();
     for (int p = 0; p < NB; ++p) {
         const int j0 = B * p;
-        {
-            // rows below the block: L[r][j0 + j] = (G[r][j0 + j] - sum_{k<j} L[r][j0 + k] L[j0 + j][j0 + k]) / L[j0 + j][j0 + j]
-            const int r = j0 + B + tid;
-            if (r < kP) {
-                // column by column: once l[j] is known, the entries to its right take their updates, which do not
-                // depend on one another (the chain through the row is 16 multiplications long, not 120 FMAs)
-                double l[B];
+        if (p > 0 && p + wv < NB) update_tile(p - 1, p + wv, p);
+        __syncthreads();
+        // ext: -1 a row of the diagonal block, 0..15 a row of the identity, from 16 on the rows below
+        const int i = lane & (B - 1);
+        const int ext = lane < B ? -1 : (64 - B) * wv + lane - B;
+        const int row = ext < 0 ? j0 + i : j0 + ext;                 // of G; the identity rows (j0 .. j0 + 15) are not read from it
+        const bool factoring = wv < kFactorWaves && (64 - B) * wv < kP - j0;
+        const bool live_row = row < kP;
+        double a[B];
+        if (factoring) {
 #pragma unroll
-                for (int j = 0; j < B; ++j) l[j] = G[r * LD + j0 + j];
-#pragma unroll
-                for (int j = 0; j < B; ++j) {
-                    l[j] *= dinv[j0 + j];
-#pragma unroll
-                    for (int k = j + 1; k < B; ++k) l[k] = fma(-l[j], G[(j0 + k) * LD + j0 + j], l[k]);
-                }
-#pragma unroll
-                for (int j = 0; j < B; ++j) G[r * LD + j0 + j] = l[j];
+            for (int k = 0; k < B; ++k) {
+                const double g = G[(live_row ? row : j0) * LD + j0 + k];
+                a[k] = ext >= 0 && ext < B ? (k == ext ? 1.0 : 0.0) : g;
             }
         }
-        __syncthreads();
-        {
-            // Trailing lower triangle.  Wave 0 updates the next diagonal tile (tile 0) and factors it straight away,
-            // while the other three waves share the remaining tiles: the one-wave factorisation, the longest step of
-            // a block, runs beside the update instead of after it.
-            const int m = NB - 1 - p;
-            const int n_tiles = m * (m + 1) / 2;
-            if (wv == 0) {
-                if (n_tiles > 0) {
-                    update_tile(p, 0);
-                    factor_diagonal(p + 1);
+        __syncthreads();                                             // every wave has its copy of the diagonal block
+        if (factoring) {
+#pragma unroll
+            for (int j = 0; j < B; ++j) {
+                const double piv = lane_value(a[j], j);
+                const double di = piv > tol ? inv_sqrt(piv) : 0.0;
+                a[j] = lane == j ? piv * di : a[j] * di;             // diagonal rows above j: values nobody reads
+#pragma unroll
+                for (int k = j + 1; k < B; ++k) a[k] = fma(-a[j], lane_value(a[j], k), a[k]);   // L[k][j] is in lane k
+                if (wv == 0 && lane == 0) dinv[j0 + j] = di;
+            }
+            if (ext < 0) {
+                if (wv == 0) {
+#pragma unroll
+                    for (int k = 0; k < B; ++k)
+                        if (k <= i) G[row * LD + j0 + k] = a[k];
                 }
-            } else {
-                for (int t = wv; t < n_tiles; t += 3) update_tile(p, t);
+            } else if (ext < B) {                                    // row c of L_pp^-T: X[j0 + k][j0 + c] for k > c
+#pragma unroll
+                for (int k = 0; k < B; ++k)
+                    if (k > ext) G[row * LD + j0 + k] = a[k];
+            } else if (live_row) {
+#pragma unroll
+                for (int k = 0; k < B; ++k) G[row * LD + j0 + k] = a[k];
+            }
+        } else if (p > 0 && wv >= kFactorWaves) {
+            // the columns behind the next one, which the previous panel has not reached yet: tile t of the triangle
+            const int m = NB - 1 - p, n_tiles = m * (m + 1) / 2;
+            for (int t = wv - kFactorWaves; t < n_tiles; t += NW - kFactorWaves) {
+                int ti = 0, rem = t;
+                while (rem > ti) {
+                    rem -= ti + 1;
+                    ++ti;
+                }
+                update_tile(p - 1, p + 1 + ti, p + 1 + rem);
             }
         }
         __syncthreads();
     }
-    // X = L^-1.  X[k][c] (k > c) is kept at G[c][k], in the unused upper triangle; X[c][c] = dinv[c].
-    // First the eight diagonal tiles T_I = L_II^-1, all at once: thread c solves column c of its tile (the chain
-    // through the 16 rows is paid once, not once per block row).
-    if (tid < kP) {
-        const int c = tid, i0 = c & ~(B - 1);
-        double x[B];
-#pragma unroll
-        for (int ii = 0; ii < B; ++ii) x[ii] = i0 + ii == c ? 1.0 : 0.0;
-#pragma unroll
-        for (int ii = 0; ii < B; ++ii) {
-            x[ii] = i0 + ii < c ? 0.0 : x[ii] * dinv[i0 + ii];
-#pragma unroll
-            for (int jj = ii + 1; jj < B; ++jj) x[jj] = fma(-G[(i0 + jj) * LD + i0 + ii], x[ii], x[jj]);
-        }
-#pragma unroll
-        for (int ii = 0; ii < B; ++ii)
-            if (i0 + ii > c) G[c * LD + i0 + ii] = x[ii];
-    }
-    __syncthreads();
+    // X = L^-1.  X[k][c] (k > c) is kept at G[c][k]; X[c][c] = dinv[c].  The diagonal tiles T_I = L_II^-1 are there.
     // Then block row I by tiles on the fp64 matrix cores:
     //   S(I, C) = -sum_{K=C}^{I-1} L(I, K) X(K, C)   (X(K, C) sits transposed in the upper triangle, so both operands
     //                                                 are read along rows of G; X(C, C) = T_C is lower triangular)
@@ -670,7 +647,7 @@ __global__ __launch_bounds__(256) void sub_chol_kernel(const double* __restrict_
     for (int I = 1; I < NB; ++I) {
         const int i0 = B * I;
         const int c = lane & 15, kk = lane >> 4;
-        for (int C = wv; C < I; C += 4) {                            // wave w takes the column tiles w and w + 4
+        for (int C = wv; C < I; C += NW) {                           // a wave per column tile
             f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
             for (int K = C; K < I; ++K) {
 #pragma unroll
@@ -696,7 +673,7 @@ __global__ __launch_bounds__(256) void sub_chol_kernel(const double* __restrict_
     }
     // Rinv = (L^-1)^T: Rinv[c][i] = X[i][c], zero for i < c.  Written once, in rows, after the loop: a store to
     // global memory inside it would be waited for at every workgroup barrier.
-    for (int e = tid; e < kP * kP; e += 256) {
+    for (int e = tid; e < kP * kP; e += NT) {
         const int c = e >> 7, i = e & (kP - 1);
         Rinv[e] = i > c ? (float)G[c * LD + i] : (i == c ? (float)dinv[c] : 0.f);
     }
@@ -794,14 +771,17 @@ static hipError_t run_matrix_entropy(const T* X, int n_mat, int N, int D, int64_
                ldx <= ((int64_t)1 << 22);
     bf16_bits* Qt_hi = reinterpret_cast<bf16_bits*>(ws + p.qt_off);
     bf16_bits* Qt_lo = Qt_hi + (size_t)kP * D;
+    auto apply_rinv = [&]() {
+        sub_q_kernel<<<dim3((unsigned)(D / kQRows)), dim3(256), kQLdsBytes, s>>>(W, Rinv, D, center ? sv : nullptr, Q,
+                                                                       mfma ? Qt_hi : nullptr, Qt_lo, zsum + kP);
+    };
     // Q = orth(W): Cholesky QR with the Gram in fp64; the last kernel also leaves the bf16 halves of Q^T and the
     // shares of s^T Q for the round that follows
     auto orth = [&]() {
         sub_gram64_kernel<0><<<dim3((unsigned)p.gram_slices), dim3(256), 0, s>>>(W, 0, kP, D, p.gram_rows, gpart, nullptr, nullptr, nullptr);
         sub_gram64_sum_kernel<<<dim3(kP * kP / 256), dim3(256), 0, s>>>(gpart, p.gram_slices, gsum);
-        sub_chol_kernel<<<dim3(1), dim3(256), chol_lds, s>>>(gsum, Rinv);
-        sub_q_kernel<<<dim3((unsigned)(D / kQRows)), dim3(256), 0, s>>>(W, Rinv, D, center ? sv : nullptr, Q,
-                                                                       mfma ? Qt_hi : nullptr, Qt_lo, zsum + kP);
+        sub_chol_kernel<<<dim3(1), dim3(kCholThreads), chol_lds, s>>>(gsum, Rinv);
+        apply_rinv();
     };
     float* Zpart = reinterpret_cast<float*>(ws + p.zpart_off);
     bf16_bits* Zt = reinterpret_cast<bf16_bits*>(ws + p.zsplit_off);
@@ -814,13 +794,13 @@ static hipError_t run_matrix_entropy(const T* X, int n_mat, int N, int D, int64_
     // the fp64 reference: entropy off by 1.6e-6 relative at most; 5e-5 if the last round rounds Q as well; keeping
     // both halves of Z in the last round too changes nothing).
     const int first_precise = n_iter - 1;
-    bool zt_ready = false;                                // the last projection left the transposed halves of Z, not Z
+    bool zsum_ready = false;                              // the last projection added up the shares of s^T Q as well
     auto project = [&](const T* Xm, bool precise, bool for_round) {       // Z = X Q
-        zt_ready = false;
+        zsum_ready = false;
         if constexpr (sizeof(T) == 2) {
             if (mfma) {
                 hipError_t e = launch_xq_mfma(Xm, ldx, N, D, Qt_hi, Qt_lo, p.z_splits, Zpart, Z, s, precise, for_round, Zt,
-                                              &zt_ready);
+                                              center ? zsum + kP : nullptr, D / kQRows, zsum, &zsum_ready);
                 if (e != hipSuccess) perr = e;
                 return;
             }
@@ -837,19 +817,19 @@ static hipError_t run_matrix_entropy(const T* X, int n_mat, int N, int D, int64_
         sub_trace_kernel<<<dim3(1), dim3(64), 0, s>>>(trace + 2, (D + 255) / 256, trace);
         env.end();
         env.begin("matrix_subspace");
-        sub_start_kernel<<<dim3(dp_blocks), dim3(256), 0, s>>>(W, D);
-        orth();
+        sub_start_kernel<<<dim3(dp_blocks), dim3(256), 0, s>>>(W, D, Rinv);
+        apply_rinv();
         for (int it = 0; it < n_iter; ++it) {
             const bool precise = it >= first_precise;
             project(Xm, precise, true);
-            if (center) {
+            if (center && !zsum_ready) {
                 sub_zsum_kernel<<<dim3(1), dim3(1024), 0, s>>>(zsum + kP, D / kQRows, zsum);
             }
             int w_parts = p.w_chunks;
             bool done = false;
             if constexpr (sizeof(T) == 2) {
                 if (mfma) {
-                    hipError_t e = launch_xtz_mfma(Xm, ldx, Z, N, D, Zt, p.t_chunk, p.t_chunks, Wpart, s, zt_ready);
+                    hipError_t e = launch_xtz_mfma(Xm, ldx, N, D, Zt, p.t_chunk, p.t_chunks, Wpart, s);
                     if (e != hipSuccess) return e;
                     w_parts = p.t_chunks;
                     done = true;
@@ -900,6 +880,8 @@ hipError_t init_subspace_mfma_kernels();
 
 hipError_t init_subspace_kernels() {
     hipError_t e = init_subspace_mfma_kernels();
+    if (e != hipSuccess) return e;
+    e = allow_dynamic_lds(reinterpret_cast<const void*>(sub_q_kernel), kQLdsBytes);
     if (e != hipSuccess) return e;
     return allow_dynamic_lds(reinterpret_cast<const void*>(sub_chol_kernel), (size_t)kP * (kP + 1) * sizeof(double));
 }

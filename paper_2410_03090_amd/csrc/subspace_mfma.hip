@@ -209,19 +209,56 @@ __global__ __launch_bounds__(256) void sub_xq_mfma_kernel(const bf16_bits* __res
 }
 
 
-// Zt [128][n_pad] bf16 from Z [N][128] fp32: Z^T rounded to bf16, as the X^T Z kernel streams it (n_pad = N rounded
-// up to 128; the tokens past N are written as zeros).  Tile: 64 tokens x 32 columns.  Only for matrices so short
-// that the sum over d of Z = X Q is split over workgroups; otherwise the X Q kernel writes Zt itself.
-__global__ __launch_bounds__(256) void sub_z_split_kernel(const float* __restrict__ Z, int N, int64_t n_pad,
-                                                          bf16_bits* __restrict__ Zt) {
+// Zt [128][n_pad] bf16: Z^T rounded to bf16, as the X^T Z kernel streams it (n_pad = N rounded up to 128; the tokens past
+// N are written as zeros), from the n_parts partial sums of Z (part[c][N][128], added in order).  Tile: 64 tokens x 32
+// columns.  Only for matrices so short that the sum over d of Z = X Q is split over workgroups; otherwise the X Q kernel
+// writes Zt itself.  zshare not null: the first workgroup of a fifth row of the grid adds up the n_share shares of s^T Q
+// (zsum[j], in the order of sub_zsum_kernel).  On their own the sum of the parts and that one took 12 us per round.
+__global__ __launch_bounds__(256) void sub_z_split_kernel(const float* __restrict__ part, int n_parts, int N, int64_t n_pad,
+                                                          bf16_bits* __restrict__ Zt, const double* __restrict__ zshare,
+                                                          int n_share, double* __restrict__ zsum) {
     __shared__ float tile[64][33];
+    __shared__ double zpart[8][kP];
     const int t0 = blockIdx.x * 64, j0 = blockIdx.y * 32;
     const int tid = threadIdx.x;
+    if (blockIdx.y == kP / 32) {
+        if (blockIdx.x != 0) return;
+        const int j = tid & (kP - 1), q = tid >> 7;
+        double t[4] = {0.0, 0.0, 0.0, 0.0};                           // interleaved sums q, q + 2, q + 4, q + 6
+        for (int b = q; b < n_share; b += 32) {                       // sixteen loads in flight, clamped
+            double v[16];
+#pragma unroll
+            for (int x = 0; x < 16; ++x) v[x] = zshare[(int64_t)min(b + 2 * x, n_share - 1) * kP + j];
+#pragma unroll
+            for (int x = 0; x < 16; ++x) t[x & 3] += b + 2 * x < n_share ? v[x] : 0.0;
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) zpart[q + 2 * x][j] = t[x];
+        __syncthreads();
+        if (q == 0) {
+            double z = zpart[0][j];
+#pragma unroll
+            for (int x = 1; x < 8; ++x) z += zpart[x][j];
+            zsum[j] = z;
+        }
+        return;
+    }
 #pragma unroll
     for (int rep = 0; rep < 2; ++rep) {
         const int r = (tid >> 3) + 32 * rep, q = tid & 7;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (t0 + r < N) v = *reinterpret_cast<const float4*>(Z + (int64_t)(t0 + r) * kP + j0 + 4 * q);
+        if (t0 + r < N) {
+            const float* src = part + (int64_t)(t0 + r) * kP + j0 + 4 * q;
+            v = *reinterpret_cast<const float4*>(src);
+#pragma unroll 4
+            for (int c = 1; c < n_parts; ++c) {
+                const float4 b = *reinterpret_cast<const float4*>(src + (int64_t)c * N * kP);
+                v.x += b.x;
+                v.y += b.y;
+                v.z += b.z;
+                v.w += b.w;
+            }
+        }
         tile[r][4 * q] = v.x;
         tile[r][4 * q + 1] = v.y;
         tile[r][4 * q + 2] = v.z;
@@ -372,18 +409,18 @@ __global__ __launch_bounds__(256) void sub_sum_parts_kernel(const float* __restr
 }
 
 // Z = X Q, given Q^T as two bf16 halves [128][D] (left by the orthonormalisation); precise: multiply by both.
-// want_zt: the caller only needs Z as the operand of launch_xtz_mfma; when the sum over d is not split the kernel
-// then writes Zt itself and *zt_written tells launch_xtz_mfma to skip its own rounding pass.
+// want_zt: the caller only needs Z as the operand of launch_xtz_mfma: Zt is written instead of Z, and where the sum over d
+// is split, zsum from the n_share shares in zshare as well if there are any (*zsum_written tells).
 hipError_t launch_xq_mfma(const bf16_bits* X, int64_t ldx, int N, int D, const bf16_bits* Qt_hi, const bf16_bits* Qt_lo,
                           int n_split, float* Zpart, float* Z, hipStream_t s, bool precise, bool want_zt, bf16_bits* Zt,
-                          bool* zt_written) {
+                          const double* zshare, int n_share, double* zsum, bool* zsum_written) {
     const int k_chunk = ((D + n_split - 1) / n_split + kQStep - 1) / kQStep * kQStep;
     const int splits = (D + k_chunk - 1) / k_chunk;
     float* dst = splits == 1 ? Z : Zpart;
     const dim3 grid((unsigned)((N + 255) / 256), (unsigned)splits);
     const int64_t n_pad = ((int64_t)N + 127) / 128 * 128;
     const bool zt = want_zt && splits == 1;
-    if (zt_written != nullptr) *zt_written = zt;
+    *zsum_written = want_zt && splits > 1 && zshare != nullptr;
     if (zt && precise)
         sub_xq_mfma_kernel<true, true><<<grid, dim3(256), xq_lds_bytes<true>(), s>>>(X, ldx, Qt_hi, Qt_lo, N, D, k_chunk, dst, Zt, n_pad);
     else if (zt)
@@ -392,7 +429,10 @@ hipError_t launch_xq_mfma(const bf16_bits* X, int64_t ldx, int N, int D, const b
         sub_xq_mfma_kernel<true, false><<<grid, dim3(256), xq_lds_bytes<true>(), s>>>(X, ldx, Qt_hi, Qt_lo, N, D, k_chunk, dst, Zt, n_pad);
     else
         sub_xq_mfma_kernel<false, false><<<grid, dim3(256), xq_lds_bytes<false>(), s>>>(X, ldx, Qt_hi, Qt_lo, N, D, k_chunk, dst, Zt, n_pad);
-    if (splits > 1) {
+    if (splits > 1 && want_zt) {
+        sub_z_split_kernel<<<dim3((unsigned)(n_pad / 64), kP / 32 + (zshare != nullptr ? 1 : 0)), dim3(256), 0, s>>>(
+            Zpart, splits, N, n_pad, Zt, zshare, n_share, zsum);
+    } else if (splits > 1) {
         const int64_t total = (int64_t)N * kP;
         sub_sum_parts_kernel<<<dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, s>>>(Zpart, splits, total, Z);
     }
@@ -400,12 +440,11 @@ hipError_t launch_xq_mfma(const bf16_bits* X, int64_t ldx, int N, int D, const b
 }
 
 // Wpart[tc][D][128] = partial X^T bf16(Z) over token chunks (t_chunk a multiple of 128); Zt: Z^T rounded to bf16,
-// [128][n_pad] with n_pad = N rounded up to 128, made here from Z unless zt_ready.
-hipError_t launch_xtz_mfma(const bf16_bits* X, int64_t ldx, const float* Z, int N, int D, bf16_bits* Zt, int t_chunk,
-                           int n_tchunks, float* Wpart, hipStream_t s, bool zt_ready) {
+// [128][n_pad] with n_pad = N rounded up to 128.
+hipError_t launch_xtz_mfma(const bf16_bits* X, int64_t ldx, int N, int D, const bf16_bits* Zt, int t_chunk, int n_tchunks,
+                           float* Wpart, hipStream_t s) {
     const int64_t n_pad = ((int64_t)N + 127) / 128 * 128;
     const int n_slabs = D / 128;
-    if (!zt_ready) sub_z_split_kernel<<<dim3((unsigned)(n_pad / 64), kP / 32), dim3(256), 0, s>>>(Z, N, n_pad, Zt);
     sub_xtz_mfma_kernel<<<dim3((unsigned)(n_slabs * n_tchunks)), dim3(256), 0, s>>>(X, ldx, Zt, n_pad, N, D, n_slabs, t_chunk, Wpart);
     return hipGetLastError();
 }
