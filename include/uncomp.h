@@ -303,7 +303,7 @@ uncomp_status uncomp_decode_init(uncomp_ctx* ctx, const float* score, const int3
  * old enough to leave appends while n < cap, else drops the token and reports -2.
  * Requires 1 <= w <= cap, 1 <= G <= 16, D == 128, 16-byte aligned q / k_new / v_new / K_c /
  * V_c.  bf16 caches need uncomp_decode_workspace_bytes(n_heads, G, cap) of workspace (partial
- * results of the two kernels the step is split into) and are limited to caches whose
+ * results of the two kernels that the step of fewer than 256 heads is split into) and are limited to caches whose
  * per-head merge tables fit 64 KiB of LDS (cap up to about 43 000 rows at G > 8, 87 000 at
  * G > 4, 349 000 at G <= 4 when the launch uses 256-row parts, half of that with 128-row
  * parts; beyond it UNCOMP_ERR_UNSUPPORTED, before anything is launched); fp32 caches need no
