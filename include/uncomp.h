@@ -130,10 +130,10 @@ uncomp_status uncomp_measure_peaks(uncomp_ctx* ctx, const void* buf, size_t byte
 uncomp_status uncomp_set_overlap(uncomp_ctx* ctx, int on);
 uncomp_status uncomp_join(uncomp_ctx* ctx, void* stream);
 
-/* Kernel selection for testing: plain_alu != 0 makes the bf16 calls use the plain-ALU
- * kernels (the ones fp32 inputs always use) instead of the MFMA kernels, the eigen stage the
+/* Kernel selection for testing: plain_alu != 0 makes the calls use the plain-ALU
+ * kernels instead of the matrix-core ones, the eigen stage the
  * fp32 Jacobi iteration instead of the fp64 tridiagonalisation, uncomp_decode_step its
- * one-kernel path, and uncomp_select_gather the one-workgroup-per-head selection also for a
+ * plain-ALU path, and uncomp_select_gather the one-workgroup-per-head selection also for a
  * few long rows (which it otherwise splits over many workgroups).  Default 0. */
 uncomp_status uncomp_set_kernel_path(uncomp_ctx* ctx, int plain_alu);
 

@@ -634,7 +634,7 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
     float* lse = reinterpret_cast<float*>(ws + p.lse_off);
     float* vote = reinterpret_cast<float*>(ws + p.vote_off);
     uint32_t* tile_range = reinterpret_cast<uint32_t*>(ws + p.range_off);
-    const bool mfma = n_rg > 0;          // row groups of the MFMA kernels, 0 for the plain-ALU ones
+    const bool mfma = n_rg > 0;          // row groups of the bf16 MFMA kernels, 0 for the others
     const int R_group = mfma ? p.R / n_rg : 0;
     const int chunk_w = wave_chunk((int64_t)BH * (mfma ? n_rg : 1), N, 4 * p.n_chunks);
     const int nc_wave = (N + chunk_w - 1) / chunk_w;
