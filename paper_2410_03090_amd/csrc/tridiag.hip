@@ -11,7 +11,7 @@
 //      (A <- A - v w^T - w v^T with p = beta A v, w = p - (beta/2)(v^T p) v).
 //   3. The eigenvalues of the tridiagonal matrix (d, e) are found by counting sign changes of
 //      the characteristic-polynomial recurrence p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}
-//      (= number of eigenvalues below x; no division, rescaled against underflow): every
+//      (= number of eigenvalues below x; no division, rescaled every 16 terms): every
 //      wanted eigenvalue owns a group of L lanes that cut its bracket into L+1 pieces per
 //      round (ballot + count-trailing-zeros picks the piece).  Brackets start at
 //      [0, 1 + 2^-10]: the matrix has unit trace and is positive semi-definite up to rounding,
@@ -152,10 +152,11 @@ __device__ __forceinline__ int sturm_count(const double (&dr)[8], const double (
                 pp = p;
                 p = t;
             });
-            // |p| shrinks by at most ~2^-35 per step and grows by at most 1.25: keep the pair normal
-            const double sc = fmax(fabs(p), fabs(pp)) < 0x1p-300 ? 0x1p300 : 1.0;
-            p *= sc;
-            pp *= sc;
+            // Cuts are 2^-32 apart, so |p| shrinks by about 2^-32 a step along a run of equal eigenvalues without coupling
+            // (the zeros of a matrix of low rank) and grows by at most 1.25: from [1/2, 1) sixteen steps stay normal.
+            const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pp)));
+            p = ldexp(p, -ex);
+            pp = ldexp(pp, -ex);
         }
         cnt += __popc(signs ^ (signs >> 1 | last << 31));
         last = signs & 1u;

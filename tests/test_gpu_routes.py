@@ -62,6 +62,26 @@ def test_entropy_64_wide_heads(ctx, N):
             np.testing.assert_allclose(eig.cpu().numpy(), eref, rtol=0, atol=2e-5)
 
 
+# Matrices of low rank: long runs of zero eigenvalues, along which the terms of the Sturm recurrence shrink by 2^-32 a step.
+# The inputs are small whole numbers, so the Gram is exact.  The last bracket of an eigenvalue is 2.9e-10 wide: its middle is
+# off by half of that, which is 3.3e-9 in a term -s log s and 1.1e-7 in the sum of 32; rounding to fp32 adds 2.4e-7.
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("rank", [1, 4, 8, 40])
+def test_entropy_low_rank(ctx, D, rank):
+    g = torch.Generator().manual_seed(rank)
+    U = torch.randint(-1, 2, (2, 64, rank), generator=g).double()
+    X = U @ torch.randint(-1, 2, (2, rank, D), generator=g).double()
+    X[1] = 3.0 * torch.eye(D, dtype=torch.float64)[torch.arange(64) % rank]      # `rank` equal eigenvalues, not centred
+    for dtype in (torch.bfloat16, torch.float32):
+        for flags in (O.DEFAULT_FLAGS, O.DEFAULT_FLAGS & ~O.FLAG_CENTER):
+            Href, eref = O.head_entropy(X.numpy(), k_trunc=32, flags=flags)
+            Xd = X.to(dtype).to(DEV)
+            H, eig = ctx.head_entropy(Xd, k_trunc=32, flags=flags, want_eig=True)
+            np.testing.assert_allclose(eig.cpu().numpy(), eref, rtol=1.2e-7, atol=1e-9)
+            for h in (H, ctx.head_entropy(Xd, k_trunc=32, flags=flags)):         # all eigenvalues and the 32 largest alone
+                np.testing.assert_allclose(h.cpu().numpy(), Href, rtol=0, atol=5e-7)
+
+
 # Chunks of the scoring passes: from one 256-token round to many, a last chunk that holds fewer tokens than the window
 # or than a tile, logits that grow along the prompt (the running reference of a row must follow them).
 @pytest.mark.parametrize("H,G,N,w", [(1, 4, 256, 32), (1, 4, 257, 32), (2, 2, 1025, 64), (8, 4, 8200, 32), (3, 8, 40009, 32),
