@@ -758,7 +758,8 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_head_kernel(
         }
     };
     const float qs = 0.08838834764831845f * 1.4426950408889634f;     // 1/sqrt(128) * log2(e)
-    constexpr float kNoRow = -1e30f;                                 // reference of a wave without rows (finite: no NaN)
+    // Reference before the first row: finite, so that logits of -inf give zeros and not NaN, and below every finite logit.
+    constexpr float kNoRow = -3.402823466e38f;
     float ref = kNoRow, sum = 0.f;                                   // of column c16; sum over this lane's rows
     float acc[GT][8];
 #pragma unroll

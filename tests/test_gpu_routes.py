@@ -159,6 +159,43 @@ def test_decode_many_heads(ctx, n_heads, G, cap, w):
     assert swaps <= 2                               # near ties at fp32 resolution, each checked to be one
 
 
+# Logits at the end of the range and beyond it: the one-kernel step of many heads gives what the two kernels of few heads
+# give for the same heads, and what the oracle gives where that is finite.
+def test_decode_many_heads_extreme_logits(ctx):
+    from tests.test_gpu_decode import D, State, _check_step, _random_state
+    n_heads, G, cap, w = 256, 4, 60, 4
+    lens, pos0 = [cap - 1 - h % 7 for h in range(n_heads)], [200] * n_heads
+    st = _random_state(n_heads, cap, lens, pos0, torch.bfloat16, seed=3, w=w)
+    g = torch.Generator().manual_seed(4)
+    q = torch.rand(n_heads, G, D, generator=g) + 0.5
+    kn, vn = torch.randn(n_heads, D, generator=g), torch.randn(n_heads, D, generator=g).to(torch.bfloat16)
+    kinds = ["all below -1e30", "one +inf", "some -inf", "one NaN"]
+    row = torch.arange(1, cap + 1).view(1, cap, 1)
+    q[0::4], kn[0::4] = 1e16 * q[0::4], -4e16                       # logits of -1e33 and less, one or more per cent apart
+    st.Kc[0::4] = (-1e16 * (1 + 0.02 * row)).to(torch.bfloat16).expand(n_heads // 4, cap, D).to(DEV)
+    st.Kc[1::4, 37, 5] = float("inf")
+    st.Kc[2::4, ::3, 9] = float("-inf")
+    st.Kc[3::4, 11, 0] = float("nan")
+    q, kn = q.to(torch.bfloat16), kn.to(torch.bfloat16)
+    pos, budget = torch.tensor(pos0, dtype=torch.int32), torch.full((n_heads,), cap, dtype=torch.int32)
+    before = st.host()
+    few = State(*(t[:8].clone() for t in (st.Kc, st.Vc, st.idx, st.cum, st.ln)))
+    args = [t.to(DEV) for t in (q, kn, vn, pos, budget)]
+    out, ev = ctx.decode_step(*args, w, st.Kc, st.Vc, st.idx, st.cum, st.ln)
+    out8, ev8 = ctx.decode_step(*(t[:8].contiguous() for t in args), w, few.Kc, few.Vc, few.idx, few.cum, few.ln)
+    torch.cuda.synchronize()
+    # both kernels sum in fp32 over the same rows, in another order: the tolerances of _check_step
+    np.testing.assert_allclose(out[:8].cpu().numpy(), out8.cpu().numpy(), rtol=0, atol=1e-4)
+    np.testing.assert_allclose(st.cum[:8].cpu().numpy(), few.cum.cpu().numpy(), rtol=2e-5, atol=2e-6)
+    assert torch.equal(ev[:8], ev8) and torch.equal(st.ln[:8], few.ln)
+    for h in range(n_heads):
+        assert bool(torch.isfinite(out[h]).all()) == (h % 4 in (0, 2)), kinds[h % 4]
+        assert bool(torch.isnan(out[h]).all()) == (h % 4 in (1, 3)), kinds[h % 4]
+    finite = [h for h in range(n_heads) if h % 4 in (0, 2)]
+    assert _check_step(before, st.host(), out.cpu().numpy(), ev.cpu().numpy(), q, kn, vn, pos.numpy(), budget.numpy(), w, cap,
+                       heads=finite) == 0
+
+
 # Few heads: 64-row waves, and the 128-row ones of a workspace that only holds their partials.
 @pytest.mark.parametrize("n_heads,G,cap", [(1, 4, 63), (3, 8, 64), (5, 16, 130), (8, 4, 1290)])
 def test_decode_few_heads_both_plans(ctx, n_heads, G, cap):
