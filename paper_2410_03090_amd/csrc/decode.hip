@@ -44,6 +44,9 @@ __device__ __forceinline__ uint32_t ascending_key(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// Four floats at any float's address: the caller's attention output need not be aligned to more than a float.
+typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
+
 __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -645,7 +648,8 @@ __global__ __launch_bounds__(512) void decode_update_kernel(
                 v.z += t.z;
                 v.w += t.w;
             }
-            *reinterpret_cast<float4*>(out + ((int64_t)h * G + g) * kD + f) = v;
+            const f32x4_any_t o4 = {v.x, v.y, v.z, v.w};
+            *reinterpret_cast<f32x4_any_t*>(out + ((int64_t)h * G + g) * kD + f) = o4;
         }
     }
     // cumulative scores and the candidate for eviction

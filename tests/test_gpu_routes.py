@@ -196,6 +196,28 @@ def test_decode_many_heads_extreme_logits(ctx):
                        heads=finite) == 0
 
 
+# The attention output needs a float's alignment and no more, on each route of the step.
+@pytest.mark.parametrize("n_heads,G", [(3, 4), (3, 16), (256, 8)])
+def test_decode_output_at_any_float(ctx, n_heads, G):
+    from tests.test_gpu_decode import D, State, _random_state
+    cap, w = 150, 4
+    st = _random_state(n_heads, cap, [cap - h % 50 for h in range(n_heads)], [300] * n_heads, torch.bfloat16, seed=G, w=w)
+    g = torch.Generator().manual_seed(G)
+    q = torch.randn(n_heads, G, D, generator=g).to(torch.bfloat16).to(DEV)
+    kn, vn = (torch.randn(n_heads, D, generator=g).to(torch.bfloat16).to(DEV) for _ in range(2))
+    pos, budget = (torch.full((n_heads,), v, dtype=torch.int32, device=DEV) for v in (300, cap))
+    outs = []
+    for off in range(4):
+        s = State(*(t.clone() for t in (st.Kc, st.Vc, st.idx, st.cum, st.ln)))
+        buf = torch.full((n_heads * G * D + 8,), 7.0, device=DEV)
+        out = buf[off:off + n_heads * G * D].view(n_heads, G, D)
+        ctx.decode_step(q, kn, vn, pos, budget, w, s.Kc, s.Vc, s.idx, s.cum, s.ln, out=out)
+        torch.cuda.synchronize()
+        assert bool((buf[:off] == 7.0).all()) and bool((buf[off + n_heads * G * D:] == 7.0).all())
+        outs.append(out.clone())
+    assert all(torch.equal(outs[0], o) for o in outs[1:])
+
+
 # Few heads: 64-row waves, and the 128-row ones of a workspace that only holds their partials.
 @pytest.mark.parametrize("n_heads,G,cap", [(1, 4, 63), (3, 8, 64), (5, 16, 130), (8, 4, 1290)])
 def test_decode_few_heads_both_plans(ctx, n_heads, G, cap):
