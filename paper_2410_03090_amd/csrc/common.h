@@ -208,8 +208,8 @@ struct DecodePlan {
 };
 DecodePlan plan_decode(int n_heads, int G, int cap, int wave_rows = 0);       // wave_rows 0: 128 or 256
 // The one-kernel step (decode_head_kernel) for at least kHeadStepHeads heads whose tables fit kDecodeHeadLdsMax bytes of
-// LDS (two workgroups per CU); from kHeadStepWide heads on with four waves per head.
-constexpr int kHeadStepHeads = 256, kHeadStepWide = 1024;
+// LDS (two workgroups per CU).
+constexpr int kHeadStepHeads = 256;
 constexpr size_t kDecodeHeadLdsMax = 80 * 1024 - 1024;
 size_t decode_head_lds_bytes(int n_heads, int G, int cap);
 hipError_t launch_decode_head(const void* q, const void* k_new, const void* v_new, int n_heads, int G, const int32_t* pos,

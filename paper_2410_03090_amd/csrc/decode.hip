@@ -708,6 +708,15 @@ __global__ __launch_bounds__(512) void decode_update_kernel(
 // logit exceeds it by 2^40: fp32 holds the products of that range without loss.
 // 5120 heads of 768 rows, 8 query heads: 453 + 69 us in two kernels, 410 here; 256 heads of 2048 rows: 58 + 12, 54.
 constexpr float kRefSlack = 40.f;
+
+// Head of workgroup b.  Workgroups go to the eight XCDs in turn, and lengths often repeat with the head's number (the
+// budgets of a layer's eight heads): in order, one XCD would get all the long ones.  Every eight heads are turned by
+// another amount instead (1000 heads of 1450 rows, every sixteenth full and the others an eighth: 65 -> 42 us).
+__device__ __forceinline__ int spread_head(unsigned b, unsigned n) {
+    const unsigned o = b >> 3;
+    return b < (n & ~7u) ? 8 * o + ((b + o + (o >> 1) + (o >> 2) + (o >> 3)) & 7) : b;
+}
+
 template <int GT, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void decode_head_kernel(
     const bf16_bits* __restrict__ q, const bf16_bits* __restrict__ k_new, const bf16_bits* __restrict__ v_new, int G,
@@ -722,7 +731,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_head_kernel(
     __shared__ unsigned long long wave_best[NW];
     __shared__ int victim_slot;
     __shared__ float new_cum_s;
-    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int h = spread_head(blockIdx.x, gridDim.x), tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c16 = lane & 15, j = lane >> 4;
     int n = len[h];
     n = n < 0 ? 0 : (n > cap ? cap : n);
@@ -1008,22 +1017,31 @@ hipError_t launch_decode_wave(const void* q, const void* k_new, const void* v_ne
 #undef UNCOMP_WAVE_CASE
 }
 
-// Waves of one workgroup of the one-kernel step: eight while a CU gets one or two heads, four beyond.
-static int head_waves(int n_heads) { return n_heads < kHeadStepWide ? 8 : 4; }
+// Waves of one workgroup of the one-kernel step (us, 4 query heads unless noted; even, ragged and mostly empty caches).
+// Four, of which a CU holds two or three workgroups: a head's start and end run under the others' streams.
+//   1000 heads of 300 rows: 29 with four, 38 with eight; 2048 heads of 2000 rows: 384, two kernels 457.
+// Eight where a CU gets one head anyway (256 heads of up to 4000 rows, ragged: 47, with four 55), or two that are long
+// (300 heads of up to 4000 rows: 107 and 125 with eight budgets among them, 55 and 82 ragged).
+// Two for thousands of short heads, whose time is that of their starts and ends: 5120 heads of 130 rows: 74, with four 78;
+// 8 query heads, caches of 300 rows an eighth full: 42 and 60.
+static int head_waves(int n_heads, int cap) {
+    if (n_heads <= 256 || (n_heads <= 512 && cap > 1536)) return 8;
+    return n_heads >= 2048 && cap <= 768 ? 2 : 4;
+}
 
 size_t decode_head_lds_bytes(int n_heads, int G, int cap) {
     const int GT = G <= 4 ? 4 : 8;
-    return ((size_t)(cap + 16) / 16 * 16 + (size_t)head_waves(n_heads) * kD) * GT * sizeof(float);
+    return ((size_t)(cap + 16) / 16 * 16 + (size_t)head_waves(n_heads, cap) * kD) * GT * sizeof(float);
 }
 
 hipError_t launch_decode_head(const void* q, const void* k_new, const void* v_new, int n_heads, int G, const int32_t* pos,
                               const int32_t* budget, int w, int cap, void* Kc, void* Vc, int32_t* idx, float* cum,
                               int32_t* len, float* out, int32_t* evicted, const Env& env) {
-    const int nw = head_waves(n_heads);
+    const int nw = head_waves(n_heads, cap);
     const size_t lds = decode_head_lds_bytes(n_heads, G, cap);
     if (lds > kDecodeHeadLdsMax || G > 8) return hipErrorInvalidValue;   // the interface checks before
-    auto kern = G <= 4 ? (nw == 8 ? decode_head_kernel<4, 8> : decode_head_kernel<4, 4>)
-                       : (nw == 8 ? decode_head_kernel<8, 8> : decode_head_kernel<8, 4>);
+    auto kern = G <= 4 ? (nw == 8 ? decode_head_kernel<4, 8> : nw == 4 ? decode_head_kernel<4, 4> : decode_head_kernel<4, 2>)
+                       : (nw == 8 ? decode_head_kernel<8, 8> : nw == 4 ? decode_head_kernel<8, 4> : decode_head_kernel<8, 2>);
     env.begin("decode_head");
     kern<<<n_heads, 64 * nw, lds, env.s>>>(static_cast<const bf16_bits*>(q), static_cast<const bf16_bits*>(k_new),
                                            static_cast<const bf16_bits*>(v_new), G, pos, budget, w, cap,
@@ -1099,7 +1117,8 @@ static hipError_t allow_decode_step() {
 
 template <int GT>
 static hipError_t allow_decode_head() {
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(decode_head_kernel<GT, 4>), kDecodeHeadLdsMax);
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(decode_head_kernel<GT, 2>), kDecodeHeadLdsMax);
+    if (e == hipSuccess) e = allow_dynamic_lds(reinterpret_cast<const void*>(decode_head_kernel<GT, 4>), kDecodeHeadLdsMax);
     return e == hipSuccess ? allow_dynamic_lds(reinterpret_cast<const void*>(decode_head_kernel<GT, 8>), kDecodeHeadLdsMax) : e;
 }
 

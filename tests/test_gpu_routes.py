@@ -127,11 +127,11 @@ def test_entropy_fp32_tile_split(ctx, n_mat, N):
     np.testing.assert_allclose(eig.cpu().numpy(), eref, rtol=0, atol=2e-5)
 
 
-# The decode step of many heads in one kernel: eight and four waves per head, lengths around the 16-row tiles and the
+# The decode step of many heads in one kernel: eight, four and two waves per head, lengths around the 16-row tiles and the
 # waves' turns, evictions, growth and full caches, and a key far down the cache whose logit is 34 above all others (the
 # waves' reference has to follow it).  Tolerances of the step as everywhere (_check_step).
 @pytest.mark.parametrize("n_heads,G,cap,w", [(256, 4, 300, 8), (257, 7, 270, 3), (1024, 8, 290, 16), (1030, 1, 150, 5),
-                                             (256, 2, 16, 4)])
+                                             (256, 2, 16, 4), (2050, 8, 270, 8), (2048, 3, 100, 4), (300, 4, 1700, 8)])
 def test_decode_many_heads(ctx, n_heads, G, cap, w):
     from tests.test_gpu_decode import D, _check_step, _random_state
     edges = [0, 1, 15, 16, 17, 63, 64, 65, 127, 128, 129, cap - 1, cap, min(cap, 260), min(cap, 200)]
