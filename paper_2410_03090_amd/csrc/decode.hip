@@ -1020,24 +1020,25 @@ hipError_t launch_decode_wave(const void* q, const void* k_new, const void* v_ne
 // Waves of one workgroup of the one-kernel step (us, 4 query heads unless noted; even, ragged and mostly empty caches).
 // Four, of which a CU holds two or three workgroups: a head's start and end run under the others' streams.
 //   1000 heads of 300 rows: 29 with four, 38 with eight; 2048 heads of 2000 rows: 384, two kernels 457.
-// Eight where a CU gets one head anyway (256 heads of up to 4000 rows, ragged: 47, with four 55), or two that are long
-// (300 heads of up to 4000 rows: 107 and 125 with eight budgets among them, 55 and 82 ragged).
+// Eight, where their tables fit, if a CU gets one head anyway (256 heads of up to 4000 rows, ragged: 47, with four 55) or a
+// few long ones (up to 4000 rows: 300 heads, with eight budgets among them 107, with four 125; 700 heads 206 and 218).
 // Two for thousands of short heads, whose time is that of their starts and ends: 5120 heads of 130 rows: 74, with four 78;
-// 8 query heads, caches of 300 rows an eighth full: 42 and 60.
-static int head_waves(int n_heads, int cap) {
-    if (n_heads <= 256 || (n_heads <= 512 && cap > 1536)) return 8;
-    return n_heads >= 2048 && cap <= 768 ? 2 : 4;
+// 8 query heads, caches of 300 rows an eighth full: 42 and 60; but 2048 heads of 768 rows: 163 and 152.
+static size_t head_lds_bytes(int waves, int G, int cap) {
+    return ((size_t)(cap + 16) / 16 * 16 + (size_t)waves * kD) * (G <= 4 ? 4 : 8) * sizeof(float);
+}
+static int head_waves(int n_heads, int G, int cap) {
+    const bool long_heads = n_heads <= 256 || (n_heads < 1024 && cap > 1536);
+    if (long_heads && head_lds_bytes(8, G, cap) <= kDecodeHeadLdsMax) return 8;
+    return n_heads >= 2048 && cap <= 512 ? 2 : 4;
 }
 
-size_t decode_head_lds_bytes(int n_heads, int G, int cap) {
-    const int GT = G <= 4 ? 4 : 8;
-    return ((size_t)(cap + 16) / 16 * 16 + (size_t)head_waves(n_heads, cap) * kD) * GT * sizeof(float);
-}
+size_t decode_head_lds_bytes(int n_heads, int G, int cap) { return head_lds_bytes(head_waves(n_heads, G, cap), G, cap); }
 
 hipError_t launch_decode_head(const void* q, const void* k_new, const void* v_new, int n_heads, int G, const int32_t* pos,
                               const int32_t* budget, int w, int cap, void* Kc, void* Vc, int32_t* idx, float* cum,
                               int32_t* len, float* out, int32_t* evicted, const Env& env) {
-    const int nw = head_waves(n_heads, cap);
+    const int nw = head_waves(n_heads, G, cap);
     const size_t lds = decode_head_lds_bytes(n_heads, G, cap);
     if (lds > kDecodeHeadLdsMax || G > 8) return hipErrorInvalidValue;   // the interface checks before
     auto kern = G <= 4 ? (nw == 8 ? decode_head_kernel<4, 8> : nw == 4 ? decode_head_kernel<4, 4> : decode_head_kernel<4, 2>)
