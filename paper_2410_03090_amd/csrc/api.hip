@@ -533,15 +533,19 @@ uncomp_status uncomp_budgets_from_labels(uncomp_ctx* ctx, const int32_t* labels,
 }
 
 namespace {
-// 64 rows per wave while 128 would leave fewer than two waves per SIMD: one layer of 8 heads, 2048 rows takes 14.3 us of
-// attention with 128 rows and 8.4 with 64
-bool fine_decode_waves(int n_heads, int cap) { return (int64_t)n_heads * ((cap + 128) / 128) < 2048; }
+// 64 rows per wave while 128 would leave fewer than one and a half waves per SIMD: one layer of 8 heads, 2048 rows takes
+// 14.3 us of attention with 128 rows and 8.4 with 64.  At most one where more than four query heads have many parts to merge:
+// 32 heads of 4000 rows, 8 query heads, the whole step 29.7 us with 128 rows and 32.7 with 64; 200 heads of 768 rows 31.2 and 29.4.
+bool fine_decode_waves(int n_heads, int G, int cap) {
+    const int64_t waves = (int64_t)n_heads * (((int64_t)cap + 128) / 128);
+    return waves < (G <= 4 || cap <= 1024 ? 1536 : 1024);
+}
 }  // namespace
 
 size_t uncomp_decode_workspace_bytes(int n_heads, int G, int cap) {
     if (n_heads <= 0 || G <= 0 || cap <= 0) return 0;
     const size_t bytes = plan_decode(n_heads, G, cap).bytes;
-    const size_t fine = fine_decode_waves(n_heads, cap) ? plan_decode(n_heads, G, cap, 64).bytes : 0;
+    const size_t fine = fine_decode_waves(n_heads, G, cap) ? plan_decode(n_heads, G, cap, 64).bytes : 0;
     return fine > bytes ? fine : bytes;
 }
 
@@ -597,7 +601,7 @@ uncomp_status uncomp_decode_step(uncomp_ctx* ctx, const void* q, const void* k_n
     const bool one_kernel = wave_path && n_heads >= kHeadStepHeads && G <= 8 &&
                             decode_head_lds_bytes(n_heads, G, cap) <= kDecodeHeadLdsMax;
     const DecodePlan pf = plan_decode(n_heads, G, cap, 64);
-    const bool fine = wave_path && fine_decode_waves(n_heads, cap) && pf.bytes <= ctx->ws_bytes &&
+    const bool fine = wave_path && fine_decode_waves(n_heads, G, cap) && pf.bytes <= ctx->ws_bytes &&
                       decode_update_lds_bytes(pf) <= kLdsDefaultLimit;
     hipError_t e = one_kernel  ? launch_decode_head(q, k_new, v_new, n_heads, G, pos, budget, w, cap, K_c, V_c, idx, cum, len,
                                                     out_p, evicted, env)

@@ -550,19 +550,22 @@ __device__ __forceinline__ void place_token(const bf16_bits* kn, const bf16_bits
     }
 }
 
-// Bound by its chain of memory round trips (a few heads' tables are a few hundred KB): the rows' probabilities, scores and
-// positions are requested before the parts' maxima are known, the parts' outputs eight at a time.  One layer of 8 heads,
-// 2048 rows: 10.0 -> 8.4 us.
-template <int GT>
-__global__ __launch_bounds__(512) void decode_update_kernel(
+// kEarly (a few heads): bound by the chain of memory round trips, their tables being a few hundred KB: the rows'
+// probabilities, scores and positions are requested before the parts' maxima are known, a wave per query head walks the
+// parts, their outputs are requested eight at a time.  8 heads of 2048 rows: 10.0 -> 8.4 us.
+// Otherwise the work per head counts, which other heads' round trips hide or many query heads make plenty: a thread per
+// query head walks the parts, a thread per output adds them.
+template <int GT, int NT, bool kEarly>
+__global__ __launch_bounds__(NT) void decode_update_kernel(
     const bf16_bits* __restrict__ k_new, const bf16_bits* __restrict__ v_new, int G,
     const int32_t* __restrict__ pos, const int32_t* __restrict__ budget, int w, int cap, bf16_bits* Kc,
     bf16_bits* Vc, int32_t* idx, float* cum, int32_t* len, float* __restrict__ out,
     int32_t* __restrict__ evicted, int wave_rows, int np_max, int s_rows, const float* __restrict__ ws_p,
     const float* __restrict__ ws_ml, const float* __restrict__ ws_acc) {
-    constexpr int NT = 512, NW = NT / 64, U = GT <= 8 ? 4 : 2;
+    constexpr int NW = NT / 64, U = kEarly ? 4 : 2;
     extern __shared__ __align__(16) float coef[];                   // [np_max][GT]: exp2(m_part - m) / sum
-    __shared__ __align__(16) float4 part_out[NT];
+    __shared__ __align__(16) float4 part_out[kEarly ? NT : 1];
+    __shared__ float head_m[GT], head_inv[GT];
     __shared__ unsigned long long wave_best[NW];
     __shared__ int victim_slot;
     __shared__ float new_cum_s;
@@ -586,9 +589,10 @@ __global__ __launch_bounds__(512) void decode_update_kernel(
     float4 pr[U][GT / 4];
     float c_in[U];
     int id_in[U];
-    auto load_rows = [&](int r0) {                                  // clamped, never predicated
+    auto load_rows = [&](int r0) {                                  // clamped; skipped where no thread has a row
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            if (kEarly && u > 0 && r0 - tid + u * NT > n) continue;
             const int r = min(r0 + u * NT, n), rc = min(r, cap - 1);
 #pragma unroll
             for (int g4 = 0; g4 < GT / 4; ++g4) pr[u][g4] = *reinterpret_cast<const float4*>(ph + (int64_t)r * GT + 4 * g4);
@@ -596,9 +600,29 @@ __global__ __launch_bounds__(512) void decode_update_kernel(
             id_in[u] = idxh[rc];
         }
     };
-    load_rows(tid);
+    if constexpr (kEarly) load_rows(tid);
+    if constexpr (!kEarly) {
+        float* pm = coef + np_max * GT;                             // the parts' maxima and sums
+        float* pl = coef + 2 * np_max * GT;
+        for (int i = tid; i < np * GT; i += NT) {
+            float2 v = make_float2(0.f, 0.f);
+            if ((i % GT) < G) v = ml[i];                            // columns beyond G were never written
+            pm[i] = v.x;
+            pl[i] = v.y;
+        }
+        __syncthreads();
+        if (tid < GT) {
+            float m = -INFINITY, l = 0.f;
+            for (int x = 0; x < np; ++x) m = fmaxf(m, pm[x * GT + tid]);
+            for (int x = 0; x < np; ++x) l += pl[x * GT + tid] * exp2f(pm[x * GT + tid] - m);
+            head_m[tid] = m;
+            head_inv[tid] = tid < G ? 1.0f / l : 0.f;
+        }
+        __syncthreads();
+        for (int i = tid; i < np * GT; i += NT) coef[i] = exp2f(pm[i] - head_m[i % GT]) * head_inv[i % GT];
+    }
     // a wave per query head: maximum and sum over the parts
-    for (int g = wave; g < GT; g += NW) {
+    for (int g = kEarly ? wave : GT; g < GT; g += NW) {
         if (g < G) {                                                 // columns beyond G were never written
             float m = -INFINITY, l = 0.f;
             for (int x = lane; x < np; x += 64) m = fmaxf(m, ml[x * GT + g].x);
@@ -614,10 +638,18 @@ __global__ __launch_bounds__(512) void decode_update_kernel(
         }
     }
     __syncthreads();
-    // attention output: the parts' unnormalised sums, rescaled to the head's maximum.  128 threads per four heads'
-    // outputs (four features each), four groups of them share the parts.
+    // attention output: the parts' unnormalised sums, rescaled to the head's maximum.  kEarly: 128 threads per four
+    // heads' outputs (four features each), four groups of them share the parts.
     const float* acch = ws_acc + (int64_t)h * np_max * GT * kD;
-    for (int g4 = 0; g4 < GT; g4 += 4) {
+    if constexpr (!kEarly) {
+        for (int o = tid; o < G * kD; o += NT) {
+            const int g = o >> 7, f = o & (kD - 1);
+            float v = 0.f;
+            for (int x = 0; x < np; ++x) v = fmaf(acch[((int64_t)x * GT + g) * kD + f], coef[x * GT + g], v);
+            out[(int64_t)h * G * kD + o] = v;
+        }
+    }
+    for (int g4 = kEarly ? 0 : GT; g4 < GT; g4 += 4) {
         const int o = tid & 127, grp = tid >> 7, g = g4 + (o >> 5), f = 4 * (o & 31);
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int x0 = grp; x0 < np; x0 += 32) {
@@ -656,7 +688,7 @@ __global__ __launch_bounds__(512) void decode_update_kernel(
     unsigned long long best = ~0ull;
     int best_r = -1;
     for (int r0 = tid; r0 < n1; r0 += U * NT) {
-        if (r0 != tid) load_rows(r0);
+        if (!kEarly || r0 != tid) load_rows(r0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int r = r0 + u * NT;
@@ -969,6 +1001,22 @@ DecodePlan plan_decode(int n_heads, int G, int cap, int wave_rows) {
     return p;
 }
 
+typedef void (*UpdateKernel)(const bf16_bits*, const bf16_bits*, int, const int32_t*, const int32_t*, int, int, bf16_bits*,
+                             bf16_bits*, int32_t*, float*, int32_t*, float*, int32_t*, int, int, int, const float*,
+                             const float*, const float*);
+template <int GT>
+static UpdateKernel update_few(bool early) {
+    if constexpr (GT == 4) return decode_update_kernel<GT, 512, true>;
+    else if constexpr (GT == 8) return early ? decode_update_kernel<GT, 512, true> : decode_update_kernel<GT, 1024, false>;
+    else return decode_update_kernel<GT, 1024, false>;
+}
+// Threads of the update kernel (both kernels of the step, us).  Thousands of heads: 256 (5120 heads of 768 rows, 16 query
+// heads: 683, with 512 threads 716); some hundreds: 512 (600 heads of 300 rows, 8 query heads: 30.5, with 1024 threads 34.2);
+// fewer: kEarly for up to four query heads (2 heads of 700 rows: 13.4, with 1024 threads and not early 14.3) and for up to
+// eight with many parts to walk (8 heads of up to 4000 rows: 21.3 and 23.0; 1000: 16.6 and 17.5; 700: 16.4 and 15.9),
+// else 1024 threads (8 heads of 1000 rows, 16 query heads: 20.1, kEarly 23.2).
+constexpr int kUpdateManyHeads = 1280, kUpdateSomeHeads = 512, kUpdateEarlyParts = 16;
+
 template <int GT, int WR>
 static hipError_t launch_decode_wave_t(const void* q, const void* k_new, const void* v_new, int n_heads, int G,
                                        const int32_t* pos, const int32_t* budget, int w, int cap, void* Kc,
@@ -987,7 +1035,12 @@ static hipError_t launch_decode_wave_t(const void* q, const void* k_new, const v
         p.s_rows, ws_p, ws_ml, ws_acc);
     env.end();
     env.begin("decode_update");
-    decode_update_kernel<GT><<<n_heads, 512, (size_t)p.np_max * GT * sizeof(float), env.s>>>(
+    const bool some = n_heads >= kUpdateSomeHeads, many = n_heads >= kUpdateManyHeads;
+    const bool early = !some && (GT == 4 || (GT == 8 && p.np_max >= kUpdateEarlyParts));
+    const int threads = many ? 256 : some || early ? 512 : 1024;
+    UpdateKernel update = many ? decode_update_kernel<GT, 256, false> : some ? decode_update_kernel<GT, 512, false> : update_few<GT>(early);
+    const size_t lds_u = decode_update_lds_bytes(p) / (early ? 3 : 1);          // early: the weights alone
+    update<<<n_heads, threads, lds_u, env.s>>>(
         static_cast<const bf16_bits*>(k_new), static_cast<const bf16_bits*>(v_new), G, pos, budget, w, cap,
         static_cast<bf16_bits*>(Kc), static_cast<bf16_bits*>(Vc), idx, cum, len, out, evicted, WR, p.np_max, p.s_rows, ws_p,
         ws_ml, ws_acc);
@@ -1065,7 +1118,7 @@ hipError_t launch_decode_init(const float* score, const int32_t* idx, const int3
 // dynamic LDS the one-kernel decode path may ask for: G*(cap+1) <= 36864 floats plus rounding of cap
 constexpr size_t kDecodeStepLdsMax = (36864 + 64) * sizeof(float);
 
-// what the update kernel may ask for at most (it takes one such table, and 8 KB)
+// the update kernel's tables: the parts' maxima, sums and weights
 size_t decode_update_lds_bytes(const DecodePlan& p) { return (size_t)3 * p.np_max * p.GT * sizeof(float); }
 
 size_t decode_step_lds_bytes(int G, int cap) {
@@ -1116,6 +1169,14 @@ static hipError_t allow_decode_step() {
     return allow_dynamic_lds(reinterpret_cast<const void*>(decode_step_kernel<T, GT>), kDecodeStepLdsMax);
 }
 
+// the tables may fill the default limit by themselves, and the kernels have a few hundred bytes besides
+template <int GT>
+static hipError_t allow_decode_update() {
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(decode_update_kernel<GT, 256, false>), kLdsDefaultLimit);
+    if (e == hipSuccess) e = allow_dynamic_lds(reinterpret_cast<const void*>(decode_update_kernel<GT, 512, false>), kLdsDefaultLimit);
+    return e == hipSuccess ? allow_dynamic_lds(reinterpret_cast<const void*>(update_few<GT>(false)), kLdsDefaultLimit) : e;
+}
+
 template <int GT>
 static hipError_t allow_decode_head() {
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(decode_head_kernel<GT, 2>), kDecodeHeadLdsMax);
@@ -1130,6 +1191,9 @@ hipError_t init_decode_kernels() {
     if (e == hipSuccess) e = allow_decode_step<float, 4>();
     if (e == hipSuccess) e = allow_decode_step<float, 8>();
     if (e == hipSuccess) e = allow_decode_step<float, 16>();
+    if (e == hipSuccess) e = allow_decode_update<4>();
+    if (e == hipSuccess) e = allow_decode_update<8>();
+    if (e == hipSuccess) e = allow_decode_update<16>();
     if (e == hipSuccess) e = allow_decode_head<4>();
     if (e == hipSuccess) e = allow_decode_head<8>();
     return e;

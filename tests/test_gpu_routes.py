@@ -218,15 +218,22 @@ def test_decode_output_at_any_float(ctx, n_heads, G):
     assert all(torch.equal(outs[0], o) for o in outs[1:])
 
 
+def _decode_bytes(n_heads, G, cap, wave_rows):
+    """Workspace of the two-kernel step with waves of so many rows (regions are rounded up to 256 bytes)."""
+    GT = 4 if G <= 4 else (8 if G <= 8 else 16)
+    parts = (cap + wave_rows) // wave_rows
+    regions = (G * 128, parts * wave_rows * GT, parts * GT * 2, parts * GT * 128)
+    return sum((n_heads * r * 4 + 255) // 256 * 256 for r in regions)
+
+
 # Few heads: 64-row waves, and the 128-row ones of a workspace that only holds their partials.
-@pytest.mark.parametrize("n_heads,G,cap", [(1, 4, 63), (3, 8, 64), (5, 16, 130), (8, 4, 1290)])
+@pytest.mark.parametrize("n_heads,G,cap", [(1, 4, 64), (3, 8, 64), (5, 16, 130), (8, 4, 1290)])
 def test_decode_few_heads_both_plans(ctx, n_heads, G, cap):
     from paper_2410_03090_amd import binding
     from tests.test_gpu_decode import D, _check_step, _random_state
-    coarse = 256 * 4                                # offsets are rounded up to 256 bytes
-    np128, GT = (cap + 128) // 128, 4 if G <= 4 else (8 if G <= 8 else 16)
-    coarse += n_heads * (G * D + np128 * 128 * GT + np128 * GT * (2 + D)) * 4
-    small = binding.Context(0, coarse)
+    fine, coarse = _decode_bytes(n_heads, G, cap, 64), _decode_bytes(n_heads, G, cap, 128)
+    assert fine > coarse and binding.Context.decode_workspace_bytes(n_heads, G, cap) == fine
+    small = binding.Context(0, coarse)              # too small for 64-row waves
     try:
         for c in (ctx, small):
             lens = [min(cap, cap - 3 * h) for h in range(n_heads)]
@@ -245,6 +252,43 @@ def test_decode_few_heads_both_plans(ctx, n_heads, G, cap):
                                budget.numpy(), 4, cap) == 0
     finally:
         small.close()
+
+
+# The two-kernel step in every form: waves of 64, 128 and 256 rows, the update kernel of few (early and not), some and many
+# heads, lengths around the waves' parts, evictions and growth.  Sampled heads against the oracle.
+@pytest.mark.parametrize("n_heads,G,cap,rows", [
+    (255, 4, 2300, 256), (255, 8, 2300, 256), (512, 8, 2050, 256), (1280, 8, 2050, 256), (512, 4, 5100, 256), (1290, 3, 5100, 256),
+    (8, 8, 3100, 64), (9, 8, 700, 64), (2, 16, 3100, 64), (600, 16, 70, 64), (255, 7, 900, 128), (1300, 16, 200, 128)])
+def test_decode_two_kernels(n_heads, G, cap, rows):
+    from paper_2410_03090_amd import binding
+    from tests.test_gpu_decode import D, State, _check_step
+    need = binding.Context.decode_workspace_bytes(n_heads, G, cap)
+    assert need == _decode_bytes(n_heads, G, cap, rows)
+    w, g = 8, torch.Generator(device=DEV).manual_seed(cap + G)
+    rand = lambda *sh: torch.randn(*sh, generator=g, device=DEV).to(torch.bfloat16)  # noqa: E731
+    edges = [0, 1, rows - 1, rows, rows + 1, 2 * rows - 1, 2 * rows, cap // 2, cap - 1, cap]
+    ln = torch.tensor([min(cap, edges[h % len(edges)]) for h in range(n_heads)], dtype=torch.int32, device=DEV)
+    budget = torch.where(torch.arange(n_heads, device=DEV) % 3 == 0, ln + 5, ln).to(torch.int32)
+    idx = torch.argsort(torch.rand(n_heads, cap + 60, generator=g, device=DEV), dim=1)[:, :cap].to(torch.int32).contiguous()
+    cum = torch.rand(n_heads, cap, generator=g, device=DEV) * 2
+    st = State(rand(n_heads, cap, D), rand(n_heads, cap, D), idx, cum, ln)
+    q, kn, vn = 2 * rand(n_heads, G, D), rand(n_heads, D), rand(n_heads, D)
+    pos = torch.full((n_heads,), cap + 100, dtype=torch.int32, device=DEV)
+    pick = torch.tensor(sorted(set(range(min(n_heads, 11))) | set(range(n_heads - min(n_heads, 10), n_heads))), device=DEV)
+    sample = lambda: State(*(t[pick] for t in (st.Kc, st.Vc, st.idx, st.cum, st.ln))).host()  # noqa: E731
+    c = binding.Context(0, need)
+    try:
+        before, ln0 = sample(), ln.clone()
+        out, ev = c.decode_step(q, kn, vn, pos, budget, w, st.Kc, st.Vc, st.idx, st.cum, st.ln)
+        torch.cuda.synchronize()
+        after = sample()
+        assert torch.isfinite(out).all() and torch.isfinite(st.cum).all()
+        host = [t[pick].cpu() for t in (out, ev, q, kn, vn, pos, budget)]
+        assert _check_step(before, after, host[0].numpy(), host[1].numpy(), *host[2:5], host[5].numpy(), host[6].numpy(), w,
+                           cap) <= 1
+        assert torch.equal(st.ln, torch.where(ev == -1, ln0 + 1, ln0)) and bool((ev >= -1).all())
+    finally:
+        c.close()
 
 
 # Wide-matrix entropy where the Cholesky step retires columns (rank below 128 from few tokens), at one and several splits
