@@ -232,7 +232,8 @@ uncomp_status uncomp_assign_budgets(uncomp_ctx* ctx, const float* entropy,
  * vote_q[j] = sum_i p_ij for j < P; pooled_q[j] = max of vote_q over |j' - j| <= pool/2,
  * 0 <= j' < P; score_out[b][h][j] = sum over the G query heads of pooled_q[j], j in [0, P).
  * score_out is dense [B][H][P] floats.  Strides are multiples of 8 elements, K and Qwin
- * 16-byte aligned; G*w <= 512.
+ * 16-byte aligned; G*w <= 512.  A logit of -inf is a token without weight; one of +inf or NaN
+ * leaves its row without a normaliser, and no score of the KV head is a finite number then.
  *
  * lse_opt (DEVICE, [B][H*G][w] floats, or NULL): the natural-log normaliser of every window
  * row, lse[b][q][i] = ln sum over j <= P+i of exp(q_i . k_j / sqrt(D)), as the attention

@@ -50,7 +50,7 @@ __global__ __launch_bounds__(512) void score_stats_alu_kernel(
             if (d < D) load8(qp + d, q + d);
     }
 
-    float mx = -INFINITY, sum = 0.f;
+    float mx = kNoLogit, sum = 0.f;
     const int t_begin = c * chunk, t_end = min(N, t_begin + chunk);
     const int last = P + i;                       // last token this row may see
     for (int t0 = t_begin; t0 < t_end; t0 += kStatTile) {
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256) void score_stats_lastrow_kernel(
     float mx[GT], sum[GT];
 #pragma unroll
     for (int g = 0; g < GT; ++g) {
-        mx[g] = -INFINITY;
+        mx[g] = kNoLogit;
         sum[g] = 0.f;
     }
     const int t_begin = c * chunk, t_end = min(N, t_begin + chunk);
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256) void score_stats_lastrow_kernel(
         float l = 0.f;
         for (int r = 0; r < 16; ++r) {
             const float2 pr = part[r][tid];
-            if (pr.y > 0.f) l += pr.y * exp2f(pr.x - m);               // groups that saw no token hold (-inf, 0)
+            if (pr.y != 0.f) l += pr.y * exp2f(pr.x - m);              // groups that saw no token hold a sum of zero
         }
         stats[((int64_t)bh * n_chunks + c) * G + tid] = make_float2(m, l);
     }
@@ -185,9 +185,9 @@ __global__ __launch_bounds__(256) void score_stats_lastrow_kernel(
 // variants are bound by vector-instruction issue.
 // ---------------------------------------------------------------------------------------
 
-// adds one partial (reference, sum of exp2 against it) to another
+// adds one partial (reference, sum of exp2 against it) to another; sums that are NaN are kept
 __device__ __forceinline__ void lse_fold(float& m, float& sum, float2 v) {
-    if (v.y > 0.f) {
+    if (v.y != 0.f) {
         const float M = fmaxf(m, v.x);
         sum = sum * exp2f(m - M) + v.y * exp2f(v.x - M);         // m = -inf, sum = 0 at the start: 0 * 0 + ...
         m = M;

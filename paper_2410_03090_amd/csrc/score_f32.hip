@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void score_stats_f32_kernel(const T* __restric
     const float scale2 = kLog2e * rsqrtf((float)DD);
     const int P = N - w;
     float2* mine = run + wv * 16 * blocks_per;
-    for (int i = lane; i < 16 * blocks_per; i += 64) run[wv * 16 * blocks_per + i] = make_float2(-INFINITY, 0.f);
+    for (int i = lane; i < 16 * blocks_per; i += 64) run[wv * 16 * blocks_per + i] = make_float2(kNoLogit, 0.f);
     __syncthreads();
     const int t_end = min(N, (c + 1) * chunk);
     for (int t0 = c * chunk + kWaveTokens * wv; t0 < t_end; t0 += kWgTokens) {
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256) void score_stats_f32_kernel(const T* __restric
         for (int x = 0; x < 4; ++x) m = fmaxf(m, run[x * 16 * blocks_per + i].x);
         for (int x = 0; x < 4; ++x) {
             const float2 v = run[x * 16 * blocks_per + i];
-            if (v.y != 0.f) l += v.y * exp2f(v.x - m);               // a wave without a token for this row holds (-inf, 0)
+            if (v.y != 0.f) l += v.y * exp2f(v.x - m);               // a wave without a token for this row holds a sum of zero
         }
         stats[((int64_t)bh * n_chunks + c) * R + row0 + i] = make_float2(m, l);
     }

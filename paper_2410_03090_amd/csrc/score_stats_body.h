@@ -11,6 +11,10 @@ namespace uncomp {
 constexpr int kTile = 64;                 // tokens per key tile
 constexpr int row_bytes(int d) { return 2 * d + 16; }   // padded LDS row of one query of d features
 constexpr float kLog2e = 1.4426950408889634f;
+// A row's maximum before its first token: finite, so that logits of -inf count as zeros instead of making it NaN, and below
+// every finite logit.  Logits of +inf and NaN do make a row's sum NaN, and partial sums that are NaN are kept: such a row
+// has no normaliser.
+constexpr float kNoLogit = -3.402823466e38f;
 
 // qs: the head's query rows staged in LDS (rows of row_bytes(DD)).  The wave (wv = 0..3 of the four that share a
 // chunk) streams key tiles wv, wv + 4, ... of tokens [t_begin, t_end) and writes its partial (reference,
@@ -27,7 +31,7 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
     float nref[NRB], sum[NRB];         // of row 16*rb + m: minus the running reference, sum of exp2(logit - reference)
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
-        nref[rb] = INFINITY;
+        nref[rb] = -kNoLogit;
         sum[rb] = 0.f;
     }
     uint4 ka[4][kKs], kb[4][kKs];          // [sub-tile][k-step] key operands of two tiles
@@ -95,7 +99,7 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
 #pragma unroll
                     for (int st = 0; st < 4; ++st)
                         mx = fmaxf(mx, fmaxf(fmaxf(acc[st][0], acc[st][1]), fmaxf(acc[st][2], acc[st][3])));
-                    nref[rb] = -(mx * scale2);
+                    nref[rb] = -fmaxf(mx * scale2, kNoLogit);
 #pragma unroll
                     for (int st = 0; st < 4; ++st)
 #pragma unroll
@@ -113,9 +117,9 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
                             const int j = t0 + 16 * st + 4 * g + v;
                             if (j < t_end && j <= last) mx = fmaxf(mx, acc[st][v] * scale2);
                         }
-                    const float r = -nref[rb];                     // -inf before the first token
+                    const float r = -nref[rb];                     // kNoLogit before the first token
                     if (mx > r) {
-                        sum[rb] *= __builtin_amdgcn_exp2f(r - mx);  // exp2(-inf) = 0 on first use
+                        sum[rb] *= __builtin_amdgcn_exp2f(r - mx);  // zero on first use
                         nref[rb] = -mx;
                     }
 #pragma unroll
@@ -146,8 +150,8 @@ __device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, c
             for (int o = 16; o < 64; o <<= 1) {
                 const float r2 = __shfl_xor(r, o, 64), s2 = __shfl_xor(sm, o, 64);
                 const float nr = fmaxf(r, r2);
-                const float a = sm > 0.f ? sm * __builtin_amdgcn_exp2f(r - nr) : 0.f;
-                const float bb = s2 > 0.f ? s2 * __builtin_amdgcn_exp2f(r2 - nr) : 0.f;
+                const float a = sm != 0.f ? sm * __builtin_amdgcn_exp2f(r - nr) : 0.f;
+                const float bb = s2 != 0.f ? s2 * __builtin_amdgcn_exp2f(r2 - nr) : 0.f;
                 r = nr;
                 sm = a + bb;
             }

@@ -115,6 +115,34 @@ def test_score_fp32_logits(ctx, dtype, D, H, G, N, w):
     np.testing.assert_allclose(ctx.window_score(Qd, Kd, G=G, pool=5, lse=lse).cpu().numpy(), ref, rtol=2e-5)
 
 
+# Logits beyond the numbers, on every scoring route: -inf is a token without weight (whole tiles of them, the first ones
+# among them), +inf and NaN leave a row without a normaliser, and its KV head without scores, whichever chunk they fall in.
+@pytest.mark.parametrize("dtype,D,G,w,plain", [
+    ("bf16", 128, 4, 16, False), ("bf16", 64, 4, 16, False), ("bf16", 128, 16, 32, False), ("bf16", 128, 3, 20, False),
+    ("bf16", 128, 4, 1, False), ("f32", 128, 4, 16, False), ("f32", 64, 2, 8, False), ("f32", 128, 4, 4, False),
+    ("f32", 128, 2, 1, False), ("bf16", 128, 4, 16, True), ("f32", 64, 4, 16, True)])
+@pytest.mark.parametrize("N", [331, 5000])
+def test_score_infinities_and_nan(ctx, dtype, D, G, w, plain, N):
+    cfg = synth.tiny_config(dtype=dtype, B=1, H=5, G=G, N=N, D=D, w=w, rank_lo=2, rank_hi=48)
+    K, V, Q = synth.gen_all(cfg, seed0=N)
+    K, Q = K[0].clone(), Q[0].clone()
+    Q[..., 5] = 0.5                                                 # every row's logit takes the sign of the key's entry
+    K[0, 0, 2 * N // 3, 5] = float("inf")
+    K[0, 1, :70, 5] = K[0, 1, 150:290, 5] = float("-inf")
+    K[0, 2, 7, 5] = float("nan")
+    K[0, 3, N // 2, 5] = K[0, 3, N // 2 + 1, 5] = float("inf")
+    with np.errstate(invalid="ignore"):
+        ref = O.window_score(to_f64(Q), to_f64(K), G=G, pool=7)
+    assert [bool(np.isnan(ref[0, h]).all()) for h in range(5)] == [True, False, True, True, False]
+    ctx.set_kernel_path(plain)
+    try:
+        got = ctx.window_score(Q.to(DEV), K.to(DEV), G=G, pool=7).cpu().numpy()
+    finally:
+        ctx.set_kernel_path(False)
+    assert not np.isfinite(got[0, [0, 2, 3]]).any()                 # (NaN; -inf where the pool reaches past the prefix)
+    np.testing.assert_allclose(got[0, [1, 4]], ref[0, [1, 4]], rtol=2e-5)        # as everywhere
+
+
 # Gram of fp32 matrices with its tiles over nine, three and one workgroup per chunk (few, more and many matrices).
 @pytest.mark.parametrize("n_mat,N", [(1, 2), (3, 65), (8, 1024), (57, 130), (171, 70)])
 def test_entropy_fp32_tile_split(ctx, n_mat, N):
