@@ -497,10 +497,9 @@ __global__ __launch_bounds__(kTriThreads, 2) void tridiag_entropy_kernel(
             hi = piece == L ? hi : lo + step * (double)(piece + 1);
             lo = nlo;
         }
-        if (s == 0 && n < n_need) {
-            const double v = 0.5 * (lo + hi);
-            sm.lam[n] = v > 0.0 ? v : 0.0;
-        }
+        // a bracket that still starts at zero (3e-10 of the trace) is a zero eigenvalue: a matrix of low rank has up to 128,
+        // and their middles would add 1e-7 to the entropy
+        if (s == 0 && n < n_need) sm.lam[n] = lo > 0.0 ? 0.5 * (lo + hi) : 0.0;
     }
     __syncthreads();
 
