@@ -1073,8 +1073,10 @@ hipError_t launch_decode_wave(const void* q, const void* k_new, const void* v_ne
 // Waves of one workgroup of the one-kernel step (us, 4 query heads unless noted; even, ragged and mostly empty caches).
 // Four, of which a CU holds two or three workgroups: a head's start and end run under the others' streams.
 //   1000 heads of 300 rows: 29 with four, 38 with eight; 2048 heads of 2000 rows: 384, two kernels 457.
-// Eight, where their tables fit, if a CU gets one head anyway (256 heads of up to 4000 rows, ragged: 47, with four 55) or a
-// few long ones (up to 4000 rows: 300 heads, with eight budgets among them 107, with four 125; 700 heads 206 and 218).
+// Eight, if a CU gets one head anyway (256 heads of up to 4000 rows, ragged: 47, with four 55) or a few long ones (up to
+// 4000 rows: 300 heads, with eight budgets among them 107, with four 125; 700 heads 206 and 218).  Where the tables of
+// eight do not fit, up to four query heads take two kernels, more of them four waves (300 heads of up to 2000 rows, 8 query
+// heads: 54, two kernels 64).
 // Two for thousands of short heads, whose time is that of their starts and ends: 5120 heads of 130 rows: 74, with four 78;
 // 8 query heads, caches of 300 rows an eighth full: 42 and 60; but 2048 heads of 768 rows: 163 and 152.
 static size_t head_lds_bytes(int waves, int G, int cap) {
@@ -1082,7 +1084,7 @@ static size_t head_lds_bytes(int waves, int G, int cap) {
 }
 static int head_waves(int n_heads, int G, int cap) {
     const bool long_heads = n_heads <= 256 || (n_heads < 1024 && cap > 1536);
-    if (long_heads && head_lds_bytes(8, G, cap) <= kDecodeHeadLdsMax) return 8;
+    if (long_heads && (G <= 4 || head_lds_bytes(8, G, cap) <= kDecodeHeadLdsMax)) return 8;
     return n_heads >= 2048 && cap <= 512 ? 2 : 4;
 }
 

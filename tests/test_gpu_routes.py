@@ -160,7 +160,8 @@ def test_entropy_fp32_tile_split(ctx, n_mat, N):
 # waves' turns, evictions, growth and full caches, and a key far down the cache whose logit is 34 above all others (the
 # waves' reference has to follow it).  Tolerances of the step as everywhere (_check_step).
 @pytest.mark.parametrize("n_heads,G,cap,w", [(256, 4, 300, 8), (257, 7, 270, 3), (1024, 8, 290, 16), (1030, 1, 150, 5),
-                                             (256, 2, 16, 4), (2050, 8, 270, 8), (2048, 3, 100, 4), (300, 4, 1700, 8)])
+                                             (256, 2, 16, 4), (2050, 8, 270, 8), (2048, 3, 100, 4), (300, 4, 1700, 8),
+                                             (256, 8, 1990, 8)])
 def test_decode_many_heads(ctx, n_heads, G, cap, w):
     from tests.test_gpu_decode import D, _check_step, _random_state
     edges = [0, 1, 15, 16, 17, 63, 64, 65, 127, 128, 129, cap - 1, cap, min(cap, 260), min(cap, 200)]
@@ -286,8 +287,8 @@ def test_decode_few_heads_both_plans(ctx, n_heads, G, cap):
 # The two-kernel step in every form: waves of 64, 128 and 256 rows, the update kernel of few (early and not), some and many
 # heads, lengths around the waves' parts, evictions and growth.  Sampled heads against the oracle.
 @pytest.mark.parametrize("n_heads,G,cap,rows", [
-    (255, 4, 2300, 256), (255, 8, 2300, 256), (512, 8, 2050, 256), (1280, 8, 2050, 256), (512, 4, 5100, 256), (1290, 3, 5100, 256),
-    (8, 8, 3100, 64), (9, 8, 700, 64), (2, 16, 3100, 64), (600, 16, 70, 64), (255, 7, 900, 128), (1300, 16, 200, 128)])
+    (255, 4, 2300, 256), (255, 8, 2300, 256), (512, 8, 2050, 256), (1280, 8, 2050, 256), (300, 4, 4100, 256),
+    (512, 4, 5100, 256), (1290, 3, 5100, 256), (8, 8, 3100, 64), (9, 8, 700, 64), (2, 16, 3100, 64), (600, 16, 70, 64), (255, 7, 900, 128), (1300, 16, 200, 128)])
 def test_decode_two_kernels(n_heads, G, cap, rows):
     from paper_2410_03090_amd import binding
     from tests.test_gpu_decode import D, State, _check_step
@@ -316,6 +317,28 @@ def test_decode_two_kernels(n_heads, G, cap, rows):
         assert _check_step(before, after, host[0].numpy(), host[1].numpy(), *host[2:5], host[5].numpy(), host[6].numpy(), w,
                            cap) <= 1
         assert torch.equal(st.ln, torch.where(ev == -1, ln0 + 1, ln0)) and bool((ev >= -1).all())
+    finally:
+        c.close()
+
+
+# The longest cache that 16 query heads may have: the update kernel's three tables fill 64 KiB but for 64 bytes.
+def test_decode_longest_cache():
+    from paper_2410_03090_amd import binding
+    from tests.test_gpu_decode import D, State, _check_step
+    G, cap, w = 16, 341 * 128 + 127 - 128, 8
+    g = torch.Generator(device=DEV).manual_seed(1)
+    rand = lambda *sh: torch.randn(*sh, generator=g, device=DEV).to(torch.bfloat16)  # noqa: E731
+    idx = torch.randperm(cap + 50, generator=g, device=DEV)[:cap].to(torch.int32).view(1, cap).contiguous()
+    one = lambda v: torch.tensor([v], dtype=torch.int32, device=DEV)  # noqa: E731
+    st = State(rand(1, cap, D), rand(1, cap, D), idx, torch.rand(1, cap, generator=g, device=DEV), one(cap))
+    q, kn, vn, pos = rand(1, G, D), rand(1, D), rand(1, D), one(cap + 60)
+    c = binding.Context(0, binding.Context.decode_workspace_bytes(1, G, cap))
+    try:
+        before = st.host()
+        out, ev = c.decode_step(q, kn, vn, pos, one(cap), w, st.Kc, st.Vc, st.idx, st.cum, st.ln)
+        torch.cuda.synchronize()
+        assert _check_step(before, st.host(), out.cpu().numpy(), ev.cpu().numpy(), q.cpu(), kn.cpu(), vn.cpu(),
+                           pos.cpu().numpy(), np.array([cap]), w, cap) <= 1
     finally:
         c.close()
 
