@@ -303,13 +303,14 @@ uncomp_status uncomp_decode_init(uncomp_ctx* ctx, const float* score, const int3
  * position a row holds.  A malformed state in which the head is over budget but no entry is
  * old enough to leave appends while n < cap, else drops the token and reports -2.
  * Requires 1 <= w <= cap, 1 <= G <= 16, D == 128, 16-byte aligned q / k_new / v_new / K_c /
- * V_c.  bf16 caches need uncomp_decode_workspace_bytes(n_heads, G, cap) of workspace (partial
- * results of the two kernels that the step of fewer than 256 heads is split into) and are limited to caches whose
- * per-head merge tables fit 64 KiB of LDS (cap up to about 43 000 rows at G > 8, 87 000 at
- * G > 4, 349 000 at G <= 4 when the launch uses 256-row parts, half of that with 128-row
- * parts; beyond it UNCOMP_ERR_UNSUPPORTED, before anything is launched); fp32 caches need no
- * workspace but are limited to G*(cap + 1) <= 36864.  The workspace is shared with the prefill
- * calls of the context.
+ * V_c; the others need their type's alignment only.  bf16 caches need
+ * uncomp_decode_workspace_bytes(n_heads, G, cap) of workspace: the step runs as one kernel for
+ * 256 heads and more with G <= 8 and up to some 2 000 (G > 4) or 4 000 rows, and as two that leave
+ * partial results there otherwise.  They are limited to caches whose per-head merge tables fit
+ * 64 KiB of LDS (cap up to about 43 000 rows at G > 8, 87 000 at G > 4, 174 000 at G <= 4, the
+ * latter two doubled when the launch uses 256-row parts; beyond it UNCOMP_ERR_UNSUPPORTED,
+ * before anything is launched); fp32 caches need no workspace but are limited to
+ * G*(cap + 1) <= 36864.  The workspace is shared with the prefill calls of the context.
  */
 size_t uncomp_decode_workspace_bytes(int n_heads, int G, int cap);
 uncomp_status uncomp_decode_step(uncomp_ctx* ctx, const void* q, const void* k_new,

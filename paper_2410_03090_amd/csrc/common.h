@@ -99,7 +99,7 @@ struct Env {
 
 // ---- launchers (each returns the hipError_t of its launches) ---------------------------
 // D: features per token, 128, or 64 (then features 64..127 of the 128-wide partial sums are zero, which leaves
-// the non-zero eigenvalues and the entropy as they are; fp32 takes the plain-ALU kernel).
+// the non-zero eigenvalues and the entropy as they are, and fp32 matrices take the plain-ALU kernel).
 hipError_t launch_gram(const void* X, uncomp_dtype dt, int n_mat, int N, int64_t mat_stride,
                        int64_t ldx, const EntropyPlan& p, char* ws, const Env& env, int D = kD);
 hipError_t launch_jacobi_entropy(int n_mat, int N, int k_trunc, unsigned flags,
@@ -194,7 +194,7 @@ hipError_t launch_gram_f32_mfma(const float* X, int n_mat, int N, int64_t mat_st
 hipError_t launch_matrix_entropy(const void* X, uncomp_dtype dt, int n_mat, int N, int D, int64_t mat_stride,
                                  int64_t ldx, int k_trunc, unsigned flags, int n_iter, const MatrixPlan& p, char* ws,
                                  float* entropy_out, float* eig_out, const Env& env);
-// Workspace of the bf16 decode path (two kernels per step).
+// Workspace of the two-kernel step of bf16 caches.
 struct DecodePlan {
     int GT;              // query heads per KV head rounded up to 4, 8 or 16
     int wave_rows;       // rows of one head that one wave owns (64, 128 or 256)
@@ -208,7 +208,8 @@ struct DecodePlan {
 };
 DecodePlan plan_decode(int n_heads, int G, int cap, int wave_rows = 0);       // wave_rows 0: 128 or 256
 // The one-kernel step (decode_head_kernel) for at least kHeadStepHeads heads whose tables fit kDecodeHeadLdsMax bytes of
-// LDS (two workgroups per CU).
+// LDS: two workgroups of the four-wave variants per CU.  The eight-wave ones use 160 and 211 registers, so that one fits
+// a CU whatever its LDS; they keep the same bound, and what a larger one would give is not measured.
 constexpr int kHeadStepHeads = 256;
 constexpr size_t kDecodeHeadLdsMax = 80 * 1024 - 1024;
 size_t decode_head_lds_bytes(int n_heads, int G, int cap);
@@ -246,7 +247,8 @@ hipError_t init_score_kernels();
 hipError_t init_jacobi_kernels();
 hipError_t init_decode_kernels();
 hipError_t init_subspace_kernels();
-// Largest dynamic LDS request of the bf16 decode update kernel (three tables of [np_max][GT] floats).
+// Largest dynamic LDS request of the bf16 decode update kernel (three tables of [np_max][GT] floats; its early form takes
+// one, and 8 KB of its own).  The interface refuses caches beyond 64 KiB of them whichever form would run.
 size_t decode_update_lds_bytes(const DecodePlan& p);
 
 }  // namespace uncomp

@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_step_kernel(
 }
 
 
-// ---- bf16: wave-per-128-rows attention pass ----------------------------------------------
+// ---- bf16: wave-per-part attention pass ---------------------------------------------------
 // A wave owns WR = 64, 128 or 256 consecutive rows of one head: the fewer, the fewer waves the launch would otherwise
 // have for the chip; 256 when there are plenty (half the partial results to write and merge).
 
@@ -552,7 +552,7 @@ __device__ __forceinline__ void place_token(const bf16_bits* kn, const bf16_bits
 
 // kEarly (a few heads): bound by the chain of memory round trips, their tables being a few hundred KB: the rows'
 // probabilities, scores and positions are requested before the parts' maxima are known, a wave per query head walks the
-// parts, their outputs are requested eight at a time.  8 heads of 2048 rows: 10.0 -> 8.4 us.
+// parts, their outputs are requested eight at a time.  8 heads of 2048 rows: 10.0 -> 8.0 us.
 // Otherwise the work per head counts, which other heads' round trips hide or many query heads make plenty: a thread per
 // query head walks the parts, a thread per output adds them.
 template <int GT, int NT, bool kEarly>
@@ -737,8 +737,8 @@ __global__ __launch_bounds__(NT) void decode_update_kernel(
 // traffic of the step at 8 query heads; here they stay in LDS.  Bound by the key and value stream.  Waves take 16-row
 // tiles in turn, key and value rows of the next tile in flight under the arithmetic of this one; probabilities are kept
 // against a reference per wave, the maximum of its first tile, which is raised (and everything rescaled) only when a
-// logit exceeds it by 2^40: fp32 holds the products of that range without loss.
-// 5120 heads of 768 rows, 8 query heads: 453 + 69 us in two kernels, 410 here; 256 heads of 2048 rows: 58 + 12, 54.
+// probability would exceed 2^40: fp32 holds the products of that range without loss.
+// 5120 heads of 768 rows on average, 8 query heads: 453 + 69 us in two kernels, 405 here; 256 heads of 2048 rows: 58 + 12, 55.
 constexpr float kRefSlack = 40.f;
 
 // Head of workgroup b.  Workgroups go to the eight XCDs in turn, and lengths often repeat with the head's number (the

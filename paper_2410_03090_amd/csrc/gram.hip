@@ -111,9 +111,9 @@ __global__ __launch_bounds__(512, 1) void gram_mfma_kernel(const bf16_bits* __re
 
 EntropyPlan plan_entropy(int n_mat, int N, size_t max_bytes) {
     EntropyPlan p;
-    // Two workgroups of eight waves per CU cover the chip; fewer, longer chunks mean fewer 64 KiB
-    // partials to write and to add up again (128K workload: 8 chunks per matrix 1.54 ms, 2 chunks
-    // 1.46 ms), and chunks stay above 4096 tokens.  A byte limit (max_bytes > 0) lowers the chunk
+    // Two workgroups per CU, one after the other (152 KB of LDS let one in), keep the chip even; fewer, longer
+    // chunks mean fewer 64 KiB partials to write and to add up again (128K workload: 8 chunks per matrix
+    // 1.54 ms, 2 chunks 1.46 ms), and chunks stay above 4096 tokens.  A byte limit (max_bytes > 0) lowers the chunk
     // count until the partials fit; p.bytes still exceeds it if even one chunk per matrix does not.
     int max_chunks = N / 4096 > 0 ? N / 4096 : 1;
     int want = (512 + n_mat - 1) / (n_mat > 0 ? n_mat : 1);
@@ -143,7 +143,7 @@ hipError_t launch_gram(const void* X, uncomp_dtype dt, int n_mat, int N, int64_t
     float* sums = reinterpret_cast<float*>(ws + p.sum_off);
     dim3 grid((unsigned)(p.n_chunks * n_mat)), block(256);
     if (dt == UNCOMP_BF16 && !force_alu) {
-        // both head widths: 256 heads of 64 features, 5003 tokens take 870 us in gram_alu_kernel and under 20 us here
+        // both head widths: 256 heads of 64 features, 5003 tokens take 870 us in gram_alu_kernel and 37 us here
         constexpr size_t lds = kGramLdsBytes;
         env.begin("gram_mfma");
         auto kern = D == 64 ? gram_mfma_kernel<64> : gram_mfma_kernel<kD>;

@@ -1,6 +1,5 @@
-// The bf16 Gram pass as device functions, shared by the Gram kernel and by the kernel that runs it
-// beside the first scoring pass (Sec. 3.1 Eq. 1: the sums S = sum x x^T and s = sum x that the
-// covariance is formed from).
+// The bf16 Gram pass as device functions of the Gram kernel (Sec. 3.1 Eq. 1: the sums S = sum x x^T and
+// s = sum x that the covariance is formed from).
 #pragma once
 
 #include "common.h"

@@ -334,8 +334,8 @@ __global__ __launch_bounds__(256) void score_vote_wave_kernel(
                 ++qh;
             }
         };
-        // fully unrolled over the row blocks, so that the scheduler can run the MFMAs of one
-        // block under the exp2 work of the previous one
+        // unrolled over the row blocks, so that the operands keep fixed registers; the test of the block count
+        // ends a basic block, so the MFMAs of a block do not run under the exp2 work of the one before
         RowBlock blk;
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb) {
@@ -566,7 +566,7 @@ hipError_t init_score_kernels() {
 // Row groups (whole query heads each) that the MFMA kernels cut the G*w query rows of a KV head into, so that a group
 // is at most kScoreRows rows in whole 16-row blocks; 0 where there is no such cut.  Each group streams the keys once
 // more, which the matrix cores still do an order of magnitude faster than the plain-ALU kernels: 256 heads of 64
-// features, 5003 tokens, 128 rows take 78 us for both passes where the plain-ALU kernels took 2.46 ms.
+// features, 5003 tokens, 128 rows take 92 us for both passes where the plain-ALU kernels took 2.46 ms.
 static int row_groups(int G, int w) {
     if (w % 16 != 0 && w != 8) return 0;
     for (int n = 1; n <= G; ++n)
@@ -618,10 +618,10 @@ static int wave_chunk(int64_t heads, int N, int n_parts) {
     }
     return best * kRound;
 }
-// The statistics take these chunks where those of plan_score would leave the chip short of two workgroups per CU.
-// Longer prompts keep the latter: a normaliser whose terms are added in another order differs in its last bit, and the
-// longer the prompt, the more positions lie within that of a head's threshold.  The vote pass adds nothing up across
-// tokens, so its chunks are free.
+// The statistics take these chunks where those of plan_score would leave the chip short of two workgroups per CU, up to
+// this prompt length.  Longer prompts keep the chunks of plan_score, for no reason of accuracy (a normaliser folded from
+// more partials is as good): 8 heads of 40009 tokens are 144 workgroups and take 38.7 us, the vote pass, which takes
+// wave_chunk at every length, 25.1.
 constexpr int kFineChunks = 16384;
 
 template <typename T>

@@ -1,6 +1,5 @@
-// The first scoring pass of one wave as a device function, shared by the scoring kernel and by the
-// kernel that runs the Gram pass beside it (Sec. 3.3.3 "Dynamic KV Cache Eviction": softmax statistics
-// of the observation-window queries over a chunk of keys).
+// The first scoring pass of one wave as a device function of the scoring kernel (Sec. 3.3.3 "Dynamic KV
+// Cache Eviction": softmax statistics of the observation-window queries over a chunk of keys).
 #pragma once
 
 #include "common.h"

@@ -33,7 +33,7 @@
 //     same operations in the same order, so all waves hold identical bits and none waits for another.
 //   - Rows and columns that are done are skipped at the grain of a 16-row block and a 64-column
 //     half, alike in all four waves.
-// Measured: 256 matrices (one per CU) 255 -> 148 us, of which 16 are step 3; 5120 matrices 3.4 -> 1.7 ms
+// Measured: 256 matrices (one per CU) 255 -> 150 us, of which 16 are step 3; 5120 matrices 3.4 -> 2.0 ms
 // (before: rows from LDS at uniform addresses, three barriers, 512 threads where a CU holds one matrix).
 #include "common.h"
 #include "device_utils.h"

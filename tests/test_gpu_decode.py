@@ -347,8 +347,8 @@ def test_decode_steps_replayed_from_a_hip_graph(ctx):
 
 
 def test_decode_many_heads(ctx):
-    """1024 heads with 8 query heads each: enough waves for the 256-rows-per-wave variant (two parts
-    per head, the second ragged).  Sampled heads against the oracle."""
+    """1024 heads with 8 query heads each: the one-kernel step, four waves per head.  Sampled heads against
+    the oracle.  (The two-kernel step with 256-row waves is covered by test_decode_two_kernels.)"""
     n_heads, G, cap, w = 1024, 8, 300, 8
     g = torch.Generator(device=DEV).manual_seed(21)
     Kc = torch.randn(n_heads, cap, D, generator=g, device=DEV).to(torch.bfloat16)
