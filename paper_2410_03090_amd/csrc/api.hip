@@ -535,7 +535,7 @@ uncomp_status uncomp_budgets_from_labels(uncomp_ctx* ctx, const int32_t* labels,
 namespace {
 // 64 rows per wave while 128 would leave fewer than one and a half waves per SIMD: one layer of 8 heads, 2048 rows takes
 // 14.3 us of attention with 128 rows and 8.4 with 64.  At most one where more than four query heads have many parts to merge:
-// 32 heads of 4000 rows, 8 query heads, the whole step 29.7 us with 128 rows and 32.7 with 64; 200 heads of 768 rows 31.2 and 29.4.
+// 32 heads of 4000 rows, 8 query heads, the whole step 27.1 us with 128 rows and 30.5 with 64; 200 heads of 768 rows 31.2 and 29.3.
 bool fine_decode_waves(int n_heads, int G, int cap) {
     const int64_t waves = (int64_t)n_heads * (((int64_t)cap + 128) / 128);
     return waves < (G <= 4 || cap <= 1024 ? 1536 : 1024);

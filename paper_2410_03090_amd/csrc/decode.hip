@@ -552,7 +552,7 @@ __device__ __forceinline__ void place_token(const bf16_bits* kn, const bf16_bits
 
 // kEarly (a few heads): bound by the chain of memory round trips, their tables being a few hundred KB: the rows'
 // probabilities, scores and positions are requested before the parts' maxima are known, a wave per query head walks the
-// parts, their outputs are requested eight at a time.  8 heads of 2048 rows: 10.0 -> 8.0 us.
+// parts, their outputs are requested eight at a time.  8 heads of 2048 rows: 10.0 -> 8.4 us.
 // Otherwise the work per head counts, which other heads' round trips hide or many query heads make plenty: a thread per
 // query head walks the parts, a thread per output adds them.
 template <int GT, int NT, bool kEarly>
@@ -1010,11 +1010,11 @@ static UpdateKernel update_few(bool early) {
     else if constexpr (GT == 8) return early ? decode_update_kernel<GT, 512, true> : decode_update_kernel<GT, 1024, false>;
     else return decode_update_kernel<GT, 1024, false>;
 }
-// Threads of the update kernel (both kernels of the step, us).  Thousands of heads: 256 (5120 heads of 768 rows, 16 query
-// heads: 683, with 512 threads 716); some hundreds: 512 (600 heads of 300 rows, 8 query heads: 30.5, with 1024 threads 34.2);
-// fewer: kEarly for up to four query heads (2 heads of 700 rows: 13.4, with 1024 threads and not early 14.3) and for up to
-// eight with many parts to walk (8 heads of up to 4000 rows: 21.3 and 23.0; 1000: 16.6 and 17.5; 700: 16.4 and 15.9),
-// else 1024 threads (8 heads of 1000 rows, 16 query heads: 20.1, kEarly 23.2).
+// Threads of the update kernel (both kernels of the step, us).  Thousands of heads: 256 (5120 heads of 300 rows, 16 query
+// heads: 284, with 384 threads 302); some hundreds: 512 (600 heads of 300 rows, 16 query heads: 38.4, with 1024 threads 42.0);
+// fewer: kEarly for up to four query heads (8 heads of 2000 rows: 14.3, with 1024 threads and not early 15.4) and for up to
+// eight with many parts to walk (8 heads of up to 4000 rows: 21.3 and 22.9; 1000: 16.5 and 17.4; 700: 16.3 and 16.0),
+// else 1024 threads (8 heads of 1000 rows, 16 query heads: 20.0, kEarly 23.2).
 constexpr int kUpdateManyHeads = 1280, kUpdateSomeHeads = 512, kUpdateEarlyParts = 16;
 
 template <int GT, int WR>
@@ -1072,9 +1072,9 @@ hipError_t launch_decode_wave(const void* q, const void* k_new, const void* v_ne
 
 // Waves of one workgroup of the one-kernel step (us, 4 query heads unless noted; even, ragged and mostly empty caches).
 // Four, of which a CU holds two or three workgroups: a head's start and end run under the others' streams.
-//   1000 heads of 300 rows: 29 with four, 38 with eight; 2048 heads of 2000 rows: 384, two kernels 457.
+//   1000 heads of 300 rows: 29 with four, 38 with eight; 2048 heads of 2000 rows: 382, two kernels 462.
 // Eight, if a CU gets one head anyway (256 heads of up to 4000 rows, ragged: 47, with four 55) or a few long ones (up to
-// 4000 rows: 300 heads, with eight budgets among them 107, with four 125; 700 heads 206 and 218).  Where the tables of
+// 4000 rows: 300 heads, with eight budgets among them 108, with four 124; 700 heads 206 and 218).  Where the tables of
 // eight do not fit, up to four query heads take two kernels, more of them four waves (300 heads of up to 2000 rows, 8 query
 // heads: 54, two kernels 64).
 // Two for thousands of short heads, whose time is that of their starts and ends: 5120 heads of 130 rows: 74, with four 78;

@@ -96,8 +96,8 @@ def _random_state(n_heads, cap, lens, pos0, dtype, seed, w):
 @pytest.mark.parametrize("dtype,plain_alu", [(torch.bfloat16, False), (torch.bfloat16, True), (torch.float32, False)])
 @pytest.mark.parametrize("G", [1, 4, 7, 16])
 def test_decode_step_matches_oracle_every_step(ctx, dtype, plain_alu, G):
-    """bf16 through the two-kernel MFMA path and through the one-kernel path, fp32 through the latter.
-    cap = 300 spans three 128-row wave parts with a ragged last one."""
+    """bf16 through the two MFMA kernels and through the plain-ALU kernel, fp32 through the latter.
+    cap = 300 spans five 64-row wave parts with a ragged last one."""
     cap, w, steps = 300, 8, 28
     lens = [0, 5, 127, 128, 299, 300, 200]
     budgets = [300, 3, 127, 300, 300, 500, 150]   # below w, equal to len, above cap, below len

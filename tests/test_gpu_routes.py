@@ -29,8 +29,8 @@ def _padded(t, extra):
     return view
 
 
-# 64-wide heads and row groups (more than 256 query rows per KV head) through the matrix-core scoring kernels; G * w that
-# has no such cut stays on the plain-arithmetic ones.  Scores are held to 2e-5 relative as everywhere: fp32 logits of
+# 64-wide heads and row groups (more than 256 query rows per KV head) through the matrix-core scoring kernels; windows of
+# under eight rows stay on the plain-arithmetic ones.  Scores are held to 2e-5 relative as everywhere: fp32 logits of
 # magnitude <= ~16 carry ~1e-6 relative error into exp().
 @pytest.mark.parametrize("D,G,N,w", [
     (64, 1, 17, 16), (64, 2, 65, 8), (64, 4, 2049, 32), (64, 4, 4161, 64), (64, 8, 2500, 16), (64, 8, 700, 64),
