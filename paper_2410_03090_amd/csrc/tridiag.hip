@@ -8,7 +8,8 @@
 //      by the trace.  The matrix lives in registers: wave q holds the row blocks q and q + 4
 //      (16 rows each), lane l their columns l and l + 64: 64 doubles per lane.
 //   2. 126 Householder reflections H = I - beta v v^T bring it to tridiagonal form
-//      (A <- A - v w^T - w v^T with p = beta A v, w = p - (beta/2)(v^T p) v).
+//      (A <- A - v w^T - w v^T with p = beta A v, w = p - (beta/2)(v^T p) v).  Once 64 rows are left they move into the
+//      registers of one wave, which goes on alone; a 64-wide matrix starts there.
 //   3. The eigenvalues of the tridiagonal matrix (d, e) are found by counting sign changes of
 //      the characteristic-polynomial recurrence p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}
 //      (= number of eigenvalues below x; no division, rescaled every 16 terms): every
@@ -31,10 +32,10 @@
 //     i + 2 leaves that row; after it every wave forms the reflection's scalars, w, and rows i + 1
 //     and i + 2 as the update will leave them (x and y of the next reflection) for itself, with the
 //     same operations in the same order, so all waves hold identical bits and none waits for another.
-//   - Rows and columns that are done are skipped at the grain of a 16-row block and a 64-column
-//     half, alike in all four waves.
-// Measured: 256 matrices (one per CU) 255 -> 150 us, of which 16 are step 3; 5120 matrices 3.4 -> 2.0 ms
-// (before: rows from LDS at uniform addresses, three barriers, 512 threads where a CU holds one matrix).
+//   - A wave's first row block is skipped once its rows are done.
+// Measured: 8 matrices (one per CU) 129 us: 2630 cycles for each of the first 63 reflections, 1420 for each of the last 63
+// (one wave, neither barriers nor exchange), 13 us for step 3; 5120 matrices 2.0 ms.  256 matrices of 64 columns 143 -> 51 us
+// (before: all 126 reflections of the 128-wide matrix with zeros in half of its rows).
 #include "common.h"
 #include "device_utils.h"
 
@@ -45,6 +46,7 @@ namespace uncomp {
 namespace {
 
 constexpr int kTriThreads = 256, kTriWaves = kTriThreads / 64;
+constexpr int kHalf = kD / 2;
 
 struct TriSmem {
     double s[kD];            // column sums of X (for the mean correction)
@@ -53,6 +55,7 @@ struct TriSmem {
     double zrow[2][kD];      // row i + 2
     double d[kD], e2[kD];    // diagonal; e2[i] = e_{i-1}^2, e_{-1} = 0
     double lam[kD];          // eigenvalues, descending
+    double tail[kHalf][kHalf];   // the second half of the matrix, on its way into one wave
 };
 
 template <int CTRL>
@@ -62,11 +65,22 @@ __device__ __forceinline__ double dpp_move(double v) {
     return __hiloint2double(hi, lo);
 }
 
-// Sum over the 64 lanes, delivered to every lane with identical bits: rotations inside the
-// rows of 16 lanes (DPP row_ror 8, 4, 2, 1), then the four rows with
-// v_permlane32_swap(a,b) -> ([a.lo32, b.lo32], [a.hi32, b.hi32]) and
-// v_permlane16_swap(a,b) -> ([a.r0, b.r0, a.r2, b.r2], [a.r1, b.r1, a.r3, b.r3]).
-// The six steps depend on each other; `fill` is called between them and may bring in other work.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_rows(double v) {          // zero in the rows of 16 lanes that ROWS leaves out
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+
+// value of lane `l` (wave-uniform) in every lane
+__device__ __forceinline__ double lane_value(double v, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// Sum over the 64 lanes, delivered to every lane with identical bits: rotations inside the rows of 16 lanes (DPP row_ror
+// 8, 4, 2, 1), then the last lane of rows 0 and 2 to rows 1 and 3 and of row 1 to rows 2 and 3 (row_bcast 15 and 31), which
+// leaves the total in lane 63.  (v_permlane32/16_swap for the last two steps: 8 cycles of the vector pipe each, four of them.)
+// The steps depend on each other; `fill` is called between them and may bring in other work.
 template <typename F>
 __device__ __forceinline__ double wave_allsum(double v, F&& fill) {
     v += dpp_move<0x128>(v);
@@ -77,20 +91,10 @@ __device__ __forceinline__ double wave_allsum(double v, F&& fill) {
     fill();
     v += dpp_move<0x121>(v);
     fill();
-    {
-        const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
-        auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-        auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-        v = __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
-    }
+    v += dpp_rows<0x142, 0xa>(v);
     fill();
-    {
-        const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
-        auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-        auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-        v = __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
-    }
-    return v;
+    v += dpp_rows<0x143, 0xc>(v);
+    return lane_value(v, 63);
 }
 __device__ __forceinline__ double wave_allsum(double v) { return wave_allsum(v, [] {}); }
 
@@ -117,10 +121,6 @@ __device__ __forceinline__ void fnmac_bc(double& acc, double rows, double m) {
 }
 __device__ __forceinline__ void dpp_ready(double& a, double& b) { asm volatile("s_nop 1" : "+v"(a), "+v"(b)); }
 
-// value of lane `l` (wave-uniform) in every lane
-__device__ __forceinline__ double lane_value(double v, int l) {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
-}
 template <int U, int END = 16, typename F>
 __device__ __forceinline__ void each16(F&& f) {
     if constexpr (U < END) {
@@ -132,22 +132,22 @@ __device__ __forceinline__ void each16(F&& f) {
 // Number of eigenvalues of the tridiagonal matrix below x: sign changes along
 // 1, p_0, p_1, ..., p_{n-1} (a zero takes the sign '+', which gives the same total as the
 // textbook rule because the next term then has the opposite sign of the previous one).
-// dr / er: d and e^2 of entries 16 j + lane%16.  Signs are shifted into a word, 32 terms at a time.
+// dr / er: d and e^2 of entries 16 j + lane%16, from entry FIRST on.  Signs are shifted into a word, 32 terms at a time.
+template <int FIRST>
 __device__ __forceinline__ int sturm_count(const double (&dr)[8], const double (&er)[8], double x) {
     double pp = 0.0, p = 1.0;                      // p_{-2}, p_{-1}
     int cnt = 0;
     uint32_t last = 0;
 #pragma unroll
-    for (int j2 = 0; j2 < 4; ++j2) {
+    for (int j2 = FIRST / 32; j2 < 4; ++j2) {
         uint32_t signs = 0;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int j = 2 * j2 + h;
             each16<0>([&](auto U) {
-                double t = 0.0;
+                double t = -x * p;
                 fnmac_bc<U.value>(t, er[j], pp);
                 fmac_bc<U.value>(t, dr[j], p);
-                t = fma(-x, p, t);
                 signs = __builtin_amdgcn_alignbit(signs, (uint32_t)__double2hiint(t), 31);   // signs << 1 | sign of t
                 pp = p;
                 p = t;
@@ -164,8 +164,88 @@ __device__ __forceinline__ int sturm_count(const double (&dr)[8], const double (
     return cnt;
 }
 
+// The four blocks of 16 entries of a vector held as entry `lane`, each in every row of 16 lanes: the DPP operands of the rows.
+// Through LDS: one write and four reads of a single wave, whose latency the caller fills; the same by v_permlane32/16_swap is
+// twenty vector instructions, six of them of twelve cycles.
+__device__ __forceinline__ void row_forms(double v, double* buf, int lane, double (&rf)[4]) {
+    buf[lane] = v;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int b = 0; b < 4; ++b) rf[b] = buf[16 * b + (lane & 15)];
+    __builtin_amdgcn_wave_barrier();
+}
+
+typedef double f64x16_t __attribute__((ext_vector_type(16)));
+
+// Reflections of a 64 x 64 matrix in the registers of one wave: a[b][u] of lane l is entry (16 b + u, l).  x: the row before
+// the first one in play (entries k and on), y: row k.  d[k] and e2[k] come out.  Rows k + 1 and on are in play: those from 16 J
+// on in the loop that ends at 16 J + 14.  Bound by the chain from one row to the next (norm, square root and reciprocal beside
+// the product, its dot product with the row, w): 1050 cycles a reflection with 16 rows in play, 1650 with 64; one wave alone
+// issues a vector instruction every 5.4 cycles.  The update in two halves that fill the waits of the sums, as in the
+// reflections of the whole matrix, measured the same.
+template <int J>
+__device__ __forceinline__ void tail_reflections(f64x16_t (&a)[4], double& x, double& y, int k, double* d, double* e2, double* buf,
+                                                 int lane) {
+    for (; k < 16 * J + 15; ++k) {
+        // x = x1 at entry k and xt behind it; v = x - alpha e_k = v1 at entry k and xt behind it
+        const double xt = lane > k ? x : 0.0;
+        const double x1 = lane_value(x, k), yk = lane_value(y, k);
+        double xr[4];
+        row_forms(xt, buf, lane, xr);
+        dpp_ready(xr[0], xr[1]);
+        dpp_ready(xr[2], xr[3]);
+        double p4[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int b = J; b < 4; ++b)
+            each16<0>([&](auto U) { fmac_bc<U.value>(p4[U.value & 3], xr[b], a[b][U.value]); });
+        const double p = (p4[0] + p4[1]) + (p4[2] + p4[3]);             // A xt
+        const double s0 = wave_allsum(xt * p);                          // xt^T A xt
+        const double pk = lane_value(p, k);                             // (A xt)_k
+        const double sigma = fma(x1, x1, wave_allsum(xt * xt));
+        double rs = __builtin_amdgcn_rsq(sigma);
+        const double t = sigma * rs, er = fma(-t, rs, 1.0);
+        rs = fma(rs * er, fma(0.375, er, 0.5), rs);
+        const double nrm = sigma * rs, den = fma(fabs(x1), nrm, sigma);
+        double beta = __builtin_amdgcn_rcp(den);
+        const double eb = fma(-den, beta, 1.0);
+        beta = fma(beta, fma(eb, eb, eb), beta);
+        const bool some = sigma > 0x1p-400;                             // as in the reflections of the whole matrix
+        const double alpha = some ? (x1 >= 0.0 ? -nrm : nrm) : 0.0;
+        beta = some ? beta : 0.0;
+        const double v1 = x1 - alpha;
+        const double vAv = fma(v1, fma(v1, yk, 2.0 * pk), s0);
+        const double K = -0.5 * beta * beta * vAv;
+        const double v = lane == k ? v1 : xt;
+        const double w = fma(K, v, beta * fma(v1, y, p));               // beta A v + K v
+        const double wk = lane_value(w, k);
+        const double xn = fma(-v1, w, fma(-wk, v, y));                  // row k after the reflection
+        double wr[4];
+        row_forms(w, buf + kHalf, lane, wr);
+        dpp_ready(wr[0], wr[1]);
+        dpp_ready(wr[2], wr[3]);
+#pragma unroll
+        for (int b = J; b < 4; ++b) {
+            each16<0>([&](auto U) {
+                double e = a[b][U.value];
+                fnmac_bc<U.value>(e, xr[b], w);
+                fnmac_bc<U.value>(e, wr[b], xt);
+                a[b][U.value] = e;
+            });
+        }
+        if (lane == k) {
+            d[k] = xn;
+            e2[k] = sigma;
+        }
+        x = xn;
+        y = a[J][k + 1 - 16 * J];
+    }
+}
+
 }  // namespace
 
+// HALF: the matrix has 64 rows and columns (the partial sums hold zeros beyond them), which take the part of the second half
+// of a 128-wide one.
+template <bool HALF>
 __global__ __launch_bounds__(kTriThreads, 2) void tridiag_entropy_kernel(
     const float* __restrict__ gram_part, const float* __restrict__ sum_part, int n_chunks, int N,
     int k_trunc, unsigned flags, float* __restrict__ entropy_out, float* __restrict__ eig_out, int eig_ld,
@@ -210,36 +290,37 @@ __global__ __launch_bounds__(kTriThreads, 2) void tridiag_entropy_kernel(
         if (eig_out != nullptr && tid < eig_ld) eig_out[(int64_t)m * eig_ld + tid] = 0.f;
         return;
     }
+    constexpr int JS0 = HALF ? 1 : 0;                            // first row block and column half in use
     double a[2][2][16];                                          // a[j][s][u] = A[16 (q + 4 j) + u][lane + 64 s]
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = JS0; j < 2; ++j)
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = JS0; s < 2; ++s)
 #pragma unroll
             for (int u = 0; u < 16; ++u) a[j][s][u] = 0.0;
     for (int ch = 0; ch < n_chunks; ++ch) {
         const float* g = Gm + (int64_t)ch * (kD * kD) + 16 * q * kD + lane;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = JS0; j < 2; ++j)
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {                        // 16 independent loads in flight
+            for (int s = JS0; s < 2; ++s) {                      // 16 independent loads in flight
                 float t[16];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) t[u] = g[(64 * j + u) * kD + 64 * s];
+                for (int u = 0; u < 16; ++u) t[u] = g[(64 * (j - JS0) + u) * kD + 64 * (s - JS0)];
 #pragma unroll
                 for (int u = 0; u < 16; ++u) a[j][s][u] += (double)t[u];
             }
     }
     {
         const double inv_tr = 1.0 / trace;
-        const double sc0 = center ? sm.s[lane] * inv_n : 0.0, sc1 = center ? sm.s[lane + 64] * inv_n : 0.0;
+        const double sc[2] = {center ? sm.s[lane] * inv_n : 0.0, center ? sm.s[lane + 64] * inv_n : 0.0};
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = JS0; j < 2; ++j)
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
-                const double sr = sm.s[16 * q + 64 * j + u];
-                a[j][0][u] = (a[j][0][u] - sr * sc0) * inv_tr;
-                a[j][1][u] = (a[j][1][u] - sr * sc1) * inv_tr;
+                const double sr = sm.s[16 * q + 64 * (j - JS0) + u];
+#pragma unroll
+                for (int s = JS0; s < 2; ++s) a[j][s][u] = (a[j][s][u] - sr * sc[s - JS0]) * inv_tr;
             }
     }
 
@@ -254,223 +335,250 @@ __global__ __launch_bounds__(kTriThreads, 2) void tridiag_entropy_kernel(
     // fill that of the next reflection's norm and square root.  Row i + 3 is put into LDS behind the barrier of
     // reflection i, where the waves wait for their reads, as it stands before that reflection's update, which
     // the readers make up for one reflection later (xo, wo, xro, wro: x and w of the reflection before).
-    const int row0 = 16 * q + (lane & 15);
-    double x[2], y[2], xr[2], yr[2], xo[2] = {0.0, 0.0}, w2r[2] = {0.0, 0.0};
-    double wo[2] = {0.0, 0.0}, xro[2] = {0.0, 0.0}, wro[2] = {0.0, 0.0}, x3 = 0.0, w3 = 0.0;
-    // Row `row` of the matrix (in the registers of one wave) to LDS: a switch on the wave-uniform register
-    // number reaches it without indexing.  (Taking column `row` from one lane of every wave instead needs no
-    // branches, but sixteen to thirty-two LDS writes of one lane each take 700 cycles.)
+    double x_tail = 0.0, y_tail = 0.0;                           // row 63 and row 64, their second halves
+    if constexpr (!HALF) {
+        const int row0 = 16 * q + (lane & 15);
+        double x[2], y[2], xr[2], yr[2], xo[2] = {0.0, 0.0}, w2r[2] = {0.0, 0.0};
+        double wo[2] = {0.0, 0.0}, xro[2] = {0.0, 0.0}, wro[2] = {0.0, 0.0}, x3 = 0.0, w3 = 0.0;
+        // Row `row` of the matrix (in the registers of one wave) to LDS: a switch on the wave-uniform register
+        // number reaches it without indexing.  (Taking column `row` from one lane of every wave instead needs no
+        // branches, but sixteen to thirty-two LDS writes of one lane each take 700 cycles.)
 #define UNCOMP_TRI_CASE(K)                                               \
-    case K:                                                              \
-        if constexpr (MODE.value < 2) to[lane] = a[(K) >> 4][0][(K) & 15]; \
-        if constexpr (MODE.value < 2 || (K) >= 16) to[lane + 64] = a[(K) >> 4][1][(K) & 15]; \
-        asm volatile("; row %0" ::"n"(K)); /* the cases stay apart: merged, they would index the registers */ \
-        break;
+        case K:                                                              \
+            to[lane] = a[(K) >> 4][0][(K) & 15];                                 \
+            to[lane + 64] = a[(K) >> 4][1][(K) & 15];                            \
+            asm volatile("; row %0" ::"n"(K)); /* the cases stay apart: merged, they would index the registers */ \
+            break;
 #define UNCOMP_TRI_CASE8(K)                                                                          \
-    UNCOMP_TRI_CASE(K) UNCOMP_TRI_CASE(K + 1) UNCOMP_TRI_CASE(K + 2) UNCOMP_TRI_CASE(K + 3)          \
-    UNCOMP_TRI_CASE(K + 4) UNCOMP_TRI_CASE(K + 5) UNCOMP_TRI_CASE(K + 6) UNCOMP_TRI_CASE(K + 7)
-    auto publish = [&](auto MODE, int row, double* to) {
-        if (((row >> 4) & 3) != q) return;
-        switch ((row >> 6) * 16 + (row & 15)) {
-            UNCOMP_TRI_CASE8(0) UNCOMP_TRI_CASE8(8) UNCOMP_TRI_CASE8(16) UNCOMP_TRI_CASE8(24)
-            default:
-                break;
-        }
-    };
+        UNCOMP_TRI_CASE(K) UNCOMP_TRI_CASE(K + 1) UNCOMP_TRI_CASE(K + 2) UNCOMP_TRI_CASE(K + 3)          \
+        UNCOMP_TRI_CASE(K + 4) UNCOMP_TRI_CASE(K + 5) UNCOMP_TRI_CASE(K + 6) UNCOMP_TRI_CASE(K + 7)
+        auto publish = [&](int row, double* to) {
+            if (((row >> 4) & 3) != q) return;
+            switch ((row >> 6) * 16 + (row & 15)) {
+                UNCOMP_TRI_CASE8(0) UNCOMP_TRI_CASE8(8) UNCOMP_TRI_CASE8(16) UNCOMP_TRI_CASE8(24)
+                default:
+                    break;
+            }
+        };
 #undef UNCOMP_TRI_CASE8
 #undef UNCOMP_TRI_CASE
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    publish(I0{}, 0, sm.pbuf[1][0]);
-    publish(I0{}, 1, sm.pbuf[1][1]);
-    publish(I0{}, 2, sm.zrow[0]);
-    __syncthreads();
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        x[s] = sm.pbuf[1][0][lane + 64 * s];
-        y[s] = sm.pbuf[1][1][lane + 64 * s];
-        xr[s] = sm.pbuf[1][0][row0 + 64 * s];
-        yr[s] = sm.pbuf[1][1][row0 + 64 * s];
-    }
-    if (tid == 0) {
-        sm.d[0] = x[0];
-        sm.e2[0] = 0.0;
-    }
-    if (lane == 0) x[0] = 0.0;
-    if (row0 == 0) xr[0] = 0.0;
-
-    // One reflection.  MODE 0: i <= 60 (entries i + 1 .. i + 3 in the first half); 1: i = 61, 62; 2: i >= 63,
-    // where the first 64 rows and columns are done.
-    auto reflect = [&](auto MODE, int i) {
-        constexpr int S0 = MODE.value == 2 ? 1 : 0;             // first column half / row block in play
-        auto entry = [&](const double (&v)[2], int r) {         // entry r of a vector held as entries lane + 64 s
-            if constexpr (MODE.value == 1) return lane_value(r < 64 ? v[0] : v[1], r & 63);
-            else return lane_value(v[MODE.value / 2], r & 63);
-        };
-        double* pb = sm.pbuf[i & 1][0];
-        double* zb = sm.zrow[i & 1];
-        const bool top = S0 == 0 && 16 * q + 15 > i;            // this wave's first row block still in play
-        double p[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-        // pending second half of the previous update and the product A x on one row block, four FMAs a call
-        dpp_ready(w2r[0], w2r[1]);
-        dpp_ready(xr[0], xr[1]);
-        auto chunk = [&](auto J, auto C) {
-            constexpr int kPer = 4 * (2 - S0);                  // chunks of the update, then as many of the product
-            constexpr int c = C.value % kPer, s = S0 + c / 4, u0 = 4 * (c % 4);
-            if constexpr (C.value < kPer)
-                each16<u0, u0 + 4>([&](auto U) { fnmac_bc<U.value>(a[J.value][s][U.value], w2r[J.value], xo[s]); });
-            else if constexpr (S0 == 0)                         // two chains of the product side by side
-                each16<2 * c, 2 * c + 2>([&](auto U) {
-                    fmac_bc<U.value>(p[J.value][0], xr[J.value], a[J.value][0][U.value]);
-                    fmac_bc<U.value>(p[J.value][1], xr[J.value], a[J.value][1][U.value]);
-                });
-            else
-                each16<u0, u0 + 4>([&](auto U) { fmac_bc<U.value>(p[U.value & 1][1], xr[J.value], a[J.value][1][U.value]); });
-        };
-        // sigma = |x|^2, alpha = -sign(x_{i+1}) |x|, beta = 1 / (sigma + |x_{i+1}| |x|); e_i^2 = sigma.  The
-        // hardware estimates (2^-24) are brought to full precision by one third-order step each.
-        const double x1 = entry(x, i + 1), x2 = entry(x, i + 2);
-        const double y1 = entry(y, i + 1);
-        double sigma = S0 == 0 ? fma(x[0], x[0], x[1] * x[1]) : x[1] * x[1];
-#define UNCOMP_CHUNK(c) chunk(I1{}, std::integral_constant<int, S0 == 0 ? (c) : (c) / 2>{})
-        int n_fill = 0;
-        auto fill = [&] {
-            if (n_fill == 0) UNCOMP_CHUNK(0);
-            if (n_fill == 1) { if constexpr (S0 == 0) UNCOMP_CHUNK(1); }
-            if (n_fill == 2) UNCOMP_CHUNK(2);
-            if (n_fill == 3) { if constexpr (S0 == 0) UNCOMP_CHUNK(3); }
-            if (n_fill == 4) UNCOMP_CHUNK(4);
-            ++n_fill;
-        };
-        sigma = wave_allsum(sigma, fill);
-        if constexpr (S0 == 0) UNCOMP_CHUNK(5);
-        double rs = __builtin_amdgcn_rsq(sigma);
-        UNCOMP_CHUNK(6);
-        const double t = sigma * rs;
-        if constexpr (S0 == 0) UNCOMP_CHUNK(7);
-        const double er = fma(-t, rs, 1.0);
-        UNCOMP_CHUNK(8);
-        rs = fma(rs * er, fma(0.375, er, 0.5), rs);
-        if constexpr (S0 == 0) UNCOMP_CHUNK(9);
-        const double nrm = sigma * rs;
-        UNCOMP_CHUNK(10);
-        const double den = fma(fabs(x1), nrm, sigma);
-        if constexpr (S0 == 0) UNCOMP_CHUNK(11);
-        double beta = __builtin_amdgcn_rcp(den);
-        UNCOMP_CHUNK(12);
-        const double eb = fma(-den, beta, 1.0);
-        if constexpr (S0 == 0) UNCOMP_CHUNK(13);
-        beta = fma(beta, fma(eb, eb, eb), beta);
-        UNCOMP_CHUNK(14);
-        if constexpr (S0 == 0) UNCOMP_CHUNK(15);
-#undef UNCOMP_CHUNK
-        // Nothing to reflect: beta = 0 leaves the matrix as it is.  The trace is one, so entries below 2^-200 are nothing,
-        // and beta^2 ~ sigma^-2 stays finite: a matrix with zero rows left residues of 1e-160, infinities and then NaN.
-        const bool some = sigma > 0x1p-400;
-        const double alpha = some ? (x1 >= 0.0 ? -nrm : nrm) : 0.0;
-        beta = some ? beta : 0.0;
-        if (top) each16<0>([&](auto C) { chunk(I0{}, C); });
-        if constexpr (S0 == 0) pb[q * kD + lane] = p[0][0] + p[1][0];
-        pb[q * kD + lane + 64] = p[0][1] + p[1][1];
-        if (tid == 0) sm.e2[i + 1] = sigma;
+        using I0 = std::integral_constant<int, 0>;
+        using I1 = std::integral_constant<int, 1>;
+        publish(0, sm.pbuf[1][0]);
+        publish(1, sm.pbuf[1][1]);
+        publish(2, sm.zrow[0]);
         __syncthreads();
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            x[s] = sm.pbuf[1][0][lane + 64 * s];
+            y[s] = sm.pbuf[1][1][lane + 64 * s];
+            xr[s] = sm.pbuf[1][0][row0 + 64 * s];
+            yr[s] = sm.pbuf[1][1][row0 + 64 * s];
+        }
+        if (tid == 0) {
+            sm.d[0] = x[0];
+            sm.e2[0] = 0.0;
+        }
+        if (lane == 0) x[0] = 0.0;
+        if (row0 == 0) xr[0] = 0.0;
 
-        double wb[2], wbr[2], z[2], zr[2], pc[2][4], pr[2][4], sum = 0.0;           // wb = beta A v
-        double p_own[2];
+        // One reflection.  SPLIT: i = 61, 62, where entries i + 1 .. i + 3 lie in both halves; in the first one before.
+        auto reflect = [&](auto SPLIT, int i) {
+            auto entry = [&](const double (&v)[2], int r) {         // entry r of a vector held as entries lane + 64 s
+                return lane_value(!SPLIT.value || r < 64 ? v[0] : v[1], r & 63);
+            };
+            double* pb = sm.pbuf[i & 1][0];
+            double* zb = sm.zrow[i & 1];
+            const bool top = 16 * q + 15 > i;            // this wave's first row block still in play
+            double p[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+            // pending second half of the previous update and the product A x on one row block, four FMAs a call
+            dpp_ready(w2r[0], w2r[1]);
+            dpp_ready(xr[0], xr[1]);
+            auto chunk = [&](auto J, auto C) {
+                constexpr int kPer = 8;                             // chunks of the update, then as many of the product
+                constexpr int c = C.value % kPer, s = c / 4, u0 = 4 * (c % 4);
+                if constexpr (C.value < kPer)
+                    each16<u0, u0 + 4>([&](auto U) { fnmac_bc<U.value>(a[J.value][s][U.value], w2r[J.value], xo[s]); });
+                else                                                // two chains of the product side by side
+                    each16<2 * c, 2 * c + 2>([&](auto U) {
+                        fmac_bc<U.value>(p[J.value][0], xr[J.value], a[J.value][0][U.value]);
+                        fmac_bc<U.value>(p[J.value][1], xr[J.value], a[J.value][1][U.value]);
+                    });
+            };
+            // sigma = |x|^2, alpha = -sign(x_{i+1}) |x|, beta = 1 / (sigma + |x_{i+1}| |x|); e_i^2 = sigma.  The
+            // hardware estimates (2^-24) are brought to full precision by one third-order step each.
+            const double x1 = entry(x, i + 1), x2 = entry(x, i + 2);
+            const double y1 = entry(y, i + 1);
+            double sigma = fma(x[0], x[0], x[1] * x[1]);
+#define UNCOMP_CHUNK(c) chunk(I1{}, std::integral_constant<int, (c)>{})
+            int n_fill = 0;
+            auto fill = [&] {
+                if (n_fill == 0) UNCOMP_CHUNK(0);
+                if (n_fill == 1) UNCOMP_CHUNK(1);
+                if (n_fill == 2) UNCOMP_CHUNK(2);
+                if (n_fill == 3) UNCOMP_CHUNK(3);
+                if (n_fill == 4) UNCOMP_CHUNK(4);
+                ++n_fill;
+            };
+            sigma = wave_allsum(sigma, fill);
+            UNCOMP_CHUNK(5);
+            double rs = __builtin_amdgcn_rsq(sigma);
+            UNCOMP_CHUNK(6);
+            const double t = sigma * rs;
+            UNCOMP_CHUNK(7);
+            const double er = fma(-t, rs, 1.0);
+            UNCOMP_CHUNK(8);
+            rs = fma(rs * er, fma(0.375, er, 0.5), rs);
+            UNCOMP_CHUNK(9);
+            const double nrm = sigma * rs;
+            UNCOMP_CHUNK(10);
+            const double den = fma(fabs(x1), nrm, sigma);
+            UNCOMP_CHUNK(11);
+            double beta = __builtin_amdgcn_rcp(den);
+            UNCOMP_CHUNK(12);
+            const double eb = fma(-den, beta, 1.0);
+            UNCOMP_CHUNK(13);
+            beta = fma(beta, fma(eb, eb, eb), beta);
+            UNCOMP_CHUNK(14);
+            UNCOMP_CHUNK(15);
+#undef UNCOMP_CHUNK
+            // Nothing to reflect: beta = 0 leaves the matrix as it is.  The trace is one, so entries below 2^-200 are nothing,
+            // and beta^2 ~ sigma^-2 stays finite: a matrix with zero rows left residues of 1e-160, infinities and then NaN.
+            const bool some = sigma > 0x1p-400;
+            const double alpha = some ? (x1 >= 0.0 ? -nrm : nrm) : 0.0;
+            beta = some ? beta : 0.0;
+            if (top) each16<0>([&](auto C) { chunk(I0{}, C); });
+            pb[q * kD + lane] = p[0][0] + p[1][0];
+            pb[q * kD + lane + 64] = p[0][1] + p[1][1];
+            if (tid == 0) sm.e2[i + 1] = sigma;
+            __syncthreads();
+
+            double wb[2], wbr[2], z[2], zr[2], pc[2][4], pr[2][4], sum = 0.0;           // wb = beta A v
+            double p_own[2];
 #pragma unroll
-        for (int s = S0; s < 2; ++s)
+            for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                pc[s][t] = pb[t * kD + lane + 64 * s];
-                pr[s][t] = pb[t * kD + row0 + 64 * s];
+                for (int t = 0; t < 4; ++t) {
+                    pc[s][t] = pb[t * kD + lane + 64 * s];
+                    pr[s][t] = pb[t * kD + row0 + 64 * s];
+                }
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                z[s] = zb[lane + 64 * s];
+                zr[s] = zb[row0 + 64 * s];
             }
+            __builtin_amdgcn_sched_barrier(0);                      // the reads are on their way
+            publish(i + 3, sm.zrow[(i + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = S0; s < 2; ++s) {
-            z[s] = zb[lane + 64 * s];
-            zr[s] = zb[row0 + 64 * s];
-        }
-        __builtin_amdgcn_sched_barrier(0);                      // the reads are on their way
-        if (i + 3 < kD) publish(MODE, i + 3, sm.zrow[(i + 1) & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = S0; s < 2; ++s) {
-            p_own[s] = (pc[s][0] + pc[s][1]) + (pc[s][2] + pc[s][3]);
-            const double p_row = (pr[s][0] + pr[s][1]) + (pr[s][2] + pr[s][3]);
-            sum = fma(x[s], p_own[s], sum);
-            wb[s] = beta * fma(-alpha, y[s], p_own[s]);
-            wbr[s] = beta * fma(-alpha, yr[s], p_row);
-        }
-        const double p1 = entry(p_own, i + 1);
-        int n_fill2 = 0;
-        auto first = [&](auto J, auto S, auto U0) {             // A -= x (beta A v)^T, four rows of one column half
-            each16<U0.value, U0.value + 4>([&](auto U) { fnmac_bc<U.value>(a[J.value][S.value][U.value], xr[J.value], wb[S.value]); });
-        };
-        auto fill2 = [&] {
-            if (n_fill2 == 0) first(I1{}, I1{}, std::integral_constant<int, 0>{});
-            if (n_fill2 == 1) first(I1{}, I1{}, std::integral_constant<int, 4>{});
-            if (n_fill2 == 2) first(I1{}, I1{}, std::integral_constant<int, 8>{});
-            if (n_fill2 == 3) first(I1{}, I1{}, std::integral_constant<int, 12>{});
-            if constexpr (S0 == 0) {
+            for (int s = 0; s < 2; ++s) {
+                p_own[s] = (pc[s][0] + pc[s][1]) + (pc[s][2] + pc[s][3]);
+                const double p_row = (pr[s][0] + pr[s][1]) + (pr[s][2] + pr[s][3]);
+                sum = fma(x[s], p_own[s], sum);
+                wb[s] = beta * fma(-alpha, y[s], p_own[s]);
+                wbr[s] = beta * fma(-alpha, yr[s], p_row);
+            }
+            const double p1 = entry(p_own, i + 1);
+            int n_fill2 = 0;
+            auto first = [&](auto J, auto S, auto U0) {             // A -= x (beta A v)^T, four rows of one column half
+                each16<U0.value, U0.value + 4>([&](auto U) { fnmac_bc<U.value>(a[J.value][S.value][U.value], xr[J.value], wb[S.value]); });
+            };
+            auto fill2 = [&] {
+                if (n_fill2 == 0) first(I1{}, I1{}, std::integral_constant<int, 0>{});
+                if (n_fill2 == 1) first(I1{}, I1{}, std::integral_constant<int, 4>{});
+                if (n_fill2 == 2) first(I1{}, I1{}, std::integral_constant<int, 8>{});
+                if (n_fill2 == 3) first(I1{}, I1{}, std::integral_constant<int, 12>{});
                 if (n_fill2 == 4) first(I1{}, I0{}, std::integral_constant<int, 0>{});
+                ++n_fill2;
+            };
+            sum = wave_allsum(sum, fill2);
+            // v^T A v = x^T A x - 2 alpha (A x)_{i+1} + alpha^2 A_{i+1,i+1}
+            const double vAv = fma(alpha, fma(alpha, y1, -2.0 * p1), sum);
+            first(I1{}, I0{}, std::integral_constant<int, 4>{});
+            const double K = -0.5 * beta * beta * vAv;
+            const double v1 = x1 - alpha, w1 = fma(K, v1, beta * fma(-alpha, y1, p1));
+            first(I1{}, I0{}, std::integral_constant<int, 8>{});
+            double w[2], wr[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                w[s] = fma(K, x[s], wb[s]);
+                wr[s] = fma(K, xr[s], wbr[s]);
+                w2r[s] = fma(K, xr[s], wr[s]);
             }
-            ++n_fill2;
+            first(I1{}, I0{}, std::integral_constant<int, 12>{});
+            if (top) {
+                each16<0>([&](auto U) { fnmac_bc<U.value>(a[0][0][U.value], xr[0], wb[0]); });
+                each16<0>([&](auto U) { fnmac_bc<U.value>(a[0][1][U.value], xr[0], wb[1]); });
+            }
+            // row i + 2 as the previous update left it, then rows i + 1 and i + 2 as this one leaves them
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                z[s] = fma(-x3, wo[s], fma(-w3, xo[s], z[s]));
+                zr[s] = fma(-x3, wro[s], fma(-w3, xro[s], zr[s]));
+            }
+            const double w2 = entry(w, i + 2);
+            if (tid == 0) sm.d[i + 1] = fma(-2.0 * v1, w1, y1);
+            x3 = entry(x, i + 3);
+            w3 = entry(w, i + 3);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const double xn = fma(-v1, w[s], fma(-w1, x[s], y[s])), xnr = fma(-v1, wr[s], fma(-w1, xr[s], yr[s]));
+                y[s] = fma(-x2, w[s], fma(-w2, x[s], z[s]));
+                yr[s] = fma(-x2, wr[s], fma(-w2, xr[s], zr[s]));
+                xo[s] = x[s];
+                wo[s] = w[s];
+                xro[s] = xr[s];
+                wro[s] = wr[s];
+                x[s] = lane + 64 * s > i + 1 ? xn : 0.0;
+                xr[s] = row0 + 64 * s > i + 1 ? xnr : 0.0;
+            }
         };
-        sum = wave_allsum(sum, fill2);
-        // v^T A v = x^T A x - 2 alpha (A x)_{i+1} + alpha^2 A_{i+1,i+1}
-        const double vAv = fma(alpha, fma(alpha, y1, -2.0 * p1), sum);
-        if constexpr (S0 == 0) first(I1{}, I0{}, std::integral_constant<int, 4>{});
-        const double K = -0.5 * beta * beta * vAv;
-        const double v1 = x1 - alpha, w1 = fma(K, v1, beta * fma(-alpha, y1, p1));
-        if constexpr (S0 == 0) first(I1{}, I0{}, std::integral_constant<int, 8>{});
-        double w[2], wr[2];
-#pragma unroll
-        for (int s = S0; s < 2; ++s) {
-            w[s] = fma(K, x[s], wb[s]);
-            wr[s] = fma(K, xr[s], wbr[s]);
-            w2r[s] = fma(K, xr[s], wr[s]);
-        }
-        if constexpr (S0 == 0) first(I1{}, I0{}, std::integral_constant<int, 12>{});
-        if (top) {
-            each16<0>([&](auto U) { fnmac_bc<U.value>(a[0][0][U.value], xr[0], wb[0]); });
-            each16<0>([&](auto U) { fnmac_bc<U.value>(a[0][1][U.value], xr[0], wb[1]); });
-        }
-        // row i + 2 as the previous update left it, then rows i + 1 and i + 2 as this one leaves them
-#pragma unroll
-        for (int s = S0; s < 2; ++s) {
-            z[s] = fma(-x3, wo[s], fma(-w3, xo[s], z[s]));
-            zr[s] = fma(-x3, wro[s], fma(-w3, xro[s], zr[s]));
-        }
-        const double w2 = entry(w, i + 2);
-        if (tid == 0) sm.d[i + 1] = fma(-2.0 * v1, w1, y1);
-        x3 = entry(x, i + 3);
-        w3 = entry(w, i + 3);
-#pragma unroll
-        for (int s = S0; s < 2; ++s) {
-            const double xn = fma(-v1, w[s], fma(-w1, x[s], y[s])), xnr = fma(-v1, wr[s], fma(-w1, xr[s], yr[s]));
-            y[s] = fma(-x2, w[s], fma(-w2, x[s], z[s]));
-            yr[s] = fma(-x2, wr[s], fma(-w2, xr[s], zr[s]));
-            xo[s] = x[s];
-            wo[s] = w[s];
-            xro[s] = xr[s];
-            wro[s] = wr[s];
-            x[s] = lane + 64 * s > i + 1 ? xn : 0.0;
-            xr[s] = row0 + 64 * s > i + 1 ? xnr : 0.0;
-        }
-    };
-    for (int i = 0; i < 61; ++i) reflect(I0{}, i);
-    for (int i = 61; i < 63; ++i) reflect(I1{}, i);
-    for (int i = 63; i < kD - 2; ++i) reflect(std::integral_constant<int, 2>{}, i);
-    // x = row 126 (masked), y = row 127
-    if (tid == 63) {
-        sm.e2[kD - 1] = x[1] * x[1];
-        sm.d[kD - 1] = y[1];
+        for (int i = 0; i < 61; ++i) reflect(std::false_type{}, i);
+        for (int i = 61; i < 63; ++i) reflect(std::true_type{}, i);
+        // the second half of what is pending on rows and columns 64 and on, which are all that is in play now
+        dpp_ready(w2r[0], w2r[1]);
+        each16<0>([&](auto U) { fnmac_bc<U.value>(a[1][1][U.value], w2r[1], xo[1]); });
+        x_tail = x[1];
+        y_tail = y[1];
     }
+    // The last 64 rows and columns: one wave keeps them in registers and needs neither LDS nor barriers.
+#pragma unroll
+    for (int u = 0; u < 16; ++u) sm.tail[16 * q + u][lane] = a[1][1][u];
+    if (HALF && tid < kHalf) sm.d[tid] = 0.0;
+    __syncthreads();
+    if (q == 0) {
+        f64x16_t t[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int u = 0; u < 16; ++u) t[b][u] = sm.tail[16 * b + u][lane];
+        double* d = sm.d + kHalf;
+        double* e2 = sm.e2 + kHalf;
+        if constexpr (HALF) {                                    // the first row is there, nothing was reflected yet
+            x_tail = t[0][0];
+            y_tail = t[0][1];
+            if (lane == 0) {
+                d[0] = x_tail;
+                e2[0] = 0.0;
+            }
+        }
+        tail_reflections<0>(t, x_tail, y_tail, HALF ? 1 : 0, d, e2, sm.lam, lane);
+        tail_reflections<1>(t, x_tail, y_tail, 15, d, e2, sm.lam, lane);
+        tail_reflections<2>(t, x_tail, y_tail, 31, d, e2, sm.lam, lane);
+        tail_reflections<3>(t, x_tail, y_tail, 47, d, e2, sm.lam, lane);
+        if (lane == kHalf - 1) {                                 // x: row 62, y: row 63
+            d[kHalf - 1] = y_tail;
+            e2[kHalf - 1] = x_tail * x_tail;
+        }
+    }
+    __syncthreads();
     if (tid < kD) sm.lam[tid] = 0.0;
     __syncthreads();
 
     // ---- 3. eigenvalues by multisection on the Sturm count ------------------------------------
     const int k = k_trunc < kD ? k_trunc : kD;
-    const int n_need = eig_out != nullptr ? kD : k;
+    constexpr int kN = HALF ? kHalf : kD;                        // rows that are there: the eigenvalues beyond them stay zero
+    const int n_need = eig_out != nullptr || k > kN ? kN : k;
     // lanes per eigenvalue: as many as the workgroup can give every wanted eigenvalue
     const int L = kTriThreads / 8 >= n_need ? 8 : (kTriThreads / 4 >= n_need ? 4 : 2);
     const int rounds = L == 8 ? 10 : (L == 4 ? 14 : 20);         // (L+1)^rounds >= 2^31
@@ -484,12 +592,12 @@ __global__ __launch_bounds__(kTriThreads, 2) void tridiag_entropy_kernel(
 #pragma unroll
         for (int j = 0; j < 8; ++j) dpp_ready(dr[j], er[j]);
         const int n = tid / L, s = tid % L;                      // eigenvalue n (0 = largest), piece s
-        const int j = kD - 1 - n;                                // its index in ascending order
+        const int j = kN - 1 - n;                                // its index in ascending order
         const double inv = 1.0 / (double)(L + 1);
         double lo = 0.0, hi = 1.0 + 0x1p-10;
         for (int it = 0; it < rounds; ++it) {
             const double step = (hi - lo) * inv;
-            const int cnt = sturm_count(dr, er, lo + step * (double)(s + 1));
+            const int cnt = sturm_count<kD - kN>(dr, er, lo + step * (double)(s + 1));
             const unsigned long long mask = __ballot(cnt > j);
             const unsigned bits = (unsigned)(mask >> (lane - s)) & ((1u << L) - 1u);
             const int piece = bits ? __builtin_ctz(bits) : L;    // first cut with more than j eigenvalues below it
@@ -528,8 +636,9 @@ hipError_t launch_tridiag_entropy(int n_mat, int N, int k_trunc, unsigned flags,
     const float* gram = reinterpret_cast<const float*>(ws + p.gram_off);
     const float* sums = reinterpret_cast<const float*>(ws + p.sum_off);
     env.begin("tridiag_entropy");
-    tridiag_entropy_kernel<<<dim3(n_mat), dim3(kTriThreads), 0, env.s>>>(gram, sums, p.n_chunks, N, k_trunc, flags, entropy_out,
-                                                                         eig_out, eig_ld, trace_total);
+    auto kern = eig_ld == kHalf ? tridiag_entropy_kernel<true> : tridiag_entropy_kernel<false>;
+    kern<<<dim3(n_mat), dim3(kTriThreads), 0, env.s>>>(gram, sums, p.n_chunks, N, k_trunc, flags, entropy_out, eig_out, eig_ld,
+                                                       trace_total);
     env.end();
     return hipGetLastError();
 }

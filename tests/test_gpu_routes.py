@@ -62,6 +62,21 @@ def test_entropy_64_wide_heads(ctx, N):
             np.testing.assert_allclose(eig.cpu().numpy(), eref, rtol=0, atol=2e-5)
 
 
+# The 64-wide eigen stage knows 64 eigenvalues: more are asked for than there are, and lanes per eigenvalue change at 32.
+# 2e-7: entropies and shares rounded to fp32 (2^-24 of values up to 4.2) on top of brackets of 2.9e-10.
+@pytest.mark.parametrize("k", [1, 32, 33, 64, 65, 128])
+def test_entropy_64_wide_truncation(ctx, k):
+    g = torch.Generator().manual_seed(k)
+    X = torch.randint(-3, 4, (9, 200, 64), generator=g).to(torch.bfloat16)      # exact Grams
+    X[0, :, 32:] = X[0, :, :32]                                                 # rank 32
+    for flags in (O.DEFAULT_FLAGS, 0):
+        Href, eref = O.head_entropy(to_f64(X), k_trunc=k, flags=flags)
+        H, eig = ctx.head_entropy(X.to(DEV), k_trunc=k, flags=flags, want_eig=True)
+        assert torch.equal(H, ctx.head_entropy(X.to(DEV), k_trunc=k, flags=flags))
+        np.testing.assert_allclose(H.cpu().numpy(), Href, rtol=0, atol=5e-7)
+        np.testing.assert_allclose(eig.cpu().numpy(), eref[:, :64], rtol=0, atol=2e-8)
+
+
 # Matrices of low rank: long runs of zero eigenvalues, along which the terms of the Sturm recurrence shrink by 2^-32 a step.
 # The inputs are small whole numbers, so the Gram is exact.  The last bracket of an eigenvalue is 2.9e-10 wide: its middle is
 # off by half of that, and a zero eigenvalue is exactly zero.  The rest of the entropy's error is rounding to fp32 (2.4e-7).
