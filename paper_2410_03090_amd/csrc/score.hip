@@ -214,16 +214,18 @@ __global__ __launch_bounds__(256, 2) void score_stats_wave_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int R_head = R * n_rg, row0 = R * rg;        // rows of the KV head, first row of this group
     const bf16_bits* Qh = Q + ((int64_t)bh * R_head + row0) * DD;
-    for (int idx = tid; idx < 16 * NRB * kPieces; idx += 256) {
-        const int row = idx / kPieces, piece = idx % kPieces;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (row < R) v = *reinterpret_cast<const uint4*>(Qh + (int64_t)row * DD + piece * 8);
-        *reinterpret_cast<uint4*>(qs + row * kRowBytes + piece * 16) = v;
-    }
-    __syncthreads();
+    auto stage = [&] {
+        for (int idx = tid; idx < 16 * NRB * kPieces; idx += 256) {
+            const int row = idx / kPieces, piece = idx % kPieces;
+            uint4 v = make_uint4(0u, 0u, 0u, 0u);
+            if (row < R) v = *reinterpret_cast<const uint4*>(Qh + (int64_t)row * DD + piece * 8);
+            *reinterpret_cast<uint4*>(qs + row * kRowBytes + piece * 16) = v;
+        }
+        __syncthreads();
+    };
     float2* part = reinterpret_cast<float2*>(smem + 16 * NRB * kRowBytes);   // [4][16*NRB]
     float2* mine = fold ? part + wv * (16 * NRB) : stats + ((int64_t)bh * (n_chunks * 4) + c * 4 + wv) * R_head + row0;
-    score_stats_wave_body<NRB, DD>(qs, K + b * ks_b + h * ks_h, ks_t, c * chunk, min(N, (c + 1) * chunk), N - w, w, R, wv, lane, mine);
+    score_stats_wave_body<NRB, DD>(stage, qs, K + b * ks_b + h * ks_h, ks_t, c * chunk, min(N, (c + 1) * chunk), N - w, w, R, wv, lane, mine);
     if (fold) {
         __syncthreads();
         if (tid < R) {
@@ -236,11 +238,13 @@ __global__ __launch_bounds__(256, 2) void score_stats_wave_kernel(
 }
 template <int NRB, bool W8, int DD>     // LDS is sized for 16*NRB query rows; W8: the window is 8 positions
 __global__ __launch_bounds__(256) void score_vote_wave_kernel(
-    const bf16_bits* __restrict__ Q, const bf16_bits* __restrict__ K, const float* __restrict__ lse, int H,
-    int G, int n_rg, int N, int w, int64_t ks_b, int64_t ks_h, int64_t ks_t, int n_chunks, int chunk,
-    float* __restrict__ vote) {
+    const bf16_bits* __restrict__ Q, const bf16_bits* __restrict__ K, const float* __restrict__ lse,
+    const float2* __restrict__ stats, int n_parts, int H, int G, int n_rg, int N, int w, int64_t ks_b, int64_t ks_h,
+    int64_t ks_t, int n_chunks, int chunk, float* __restrict__ vote) {
     constexpr int kRowBytes = row_bytes(DD), kPieces = DD / 8, kKs = DD / 32;
+    constexpr int kRowThreads = 256 / (16 * NRB);                         // threads per row that fold its partial statistics
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ float2 folded[kRowThreads > 1 ? 16 * NRB : 1];
     unsigned char* qs = smem;                                             // [16*NRB][kRowBytes]
     float* nls = reinterpret_cast<float*>(smem + 16 * NRB * kRowBytes);   // [16*NRB] minus lse (base 2)
     const int rg = blockIdx.x % n_rg, bc = blockIdx.x / n_rg;
@@ -256,18 +260,6 @@ __global__ __launch_bounds__(256) void score_vote_wave_kernel(
     if (t_begin >= t_end) return;
     const int n_tiles = (t_end - t_begin + kTile - 1) / kTile;
 
-    const int64_t row0 = (int64_t)bh * G * w + R * rg;
-    const bf16_bits* Qh = Q + row0 * DD;
-    for (int idx = tid; idx < 16 * NRB * kPieces; idx += 256) {
-        const int row = idx / kPieces, piece = idx % kPieces;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (row < R) v = *reinterpret_cast<const uint4*>(Qh + (int64_t)row * DD + piece * 8);
-        *reinterpret_cast<uint4*>(qs + row * kRowBytes + piece * 16) = v;
-    }
-    for (int r = tid; r < 16 * NRB; r += 256) nls[r] = r < R ? -lse[row0 + r] : 0.f;
-    __syncthreads();
-
-    float* vote_h = vote + ((int64_t)bh * G + G / n_rg * rg) * P;
     uint4 ka[4][kKs], kb[4][kKs];                        // [sub-tile][k-step] B operands of two tiles
     auto load_tile = [&](uint4 dst[4][kKs], int tile) {            // clamped, never predicated
         const int t0 = t_begin + tile * kTile;
@@ -279,6 +271,44 @@ __global__ __launch_bounds__(256) void score_vote_wave_kernel(
             for (int ks = 0; ks < kKs; ++ks) dst[st][ks] = *reinterpret_cast<const uint4*>(src + 32 * ks);
         }
     };
+    load_tile(ka, wv);                                   // on its way while queries and normalisers are fetched
+    const int64_t row0 = (int64_t)bh * G * w + R * rg;
+    const bf16_bits* Qh = Q + row0 * DD;
+    for (int idx = tid; idx < 16 * NRB * kPieces; idx += 256) {
+        const int row = idx / kPieces, piece = idx % kPieces;
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (row < R) v = *reinterpret_cast<const uint4*>(Qh + (int64_t)row * DD + piece * 8);
+        *reinterpret_cast<uint4*>(qs + row * kRowBytes + piece * 16) = v;
+    }
+    if (stats == nullptr) {
+        for (int r = tid; r < 16 * NRB; r += 256) nls[r] = r < R ? -lse[row0 + r] : 0.f;
+    } else {
+        // few partials: every workgroup folds them for itself, which saves the launch of the merge kernel
+        constexpr int kLoads = 8;
+        const int r = tid % (16 * NRB), q = tid / (16 * NRB);
+        float sum = 0.f, mx = -INFINITY;
+        if (r < R) {
+            const float2* st = stats + ((int64_t)bh * n_parts * n_rg + rg) * R + r;
+            const int64_t stride = (int64_t)R * n_rg;
+            for (int c = q; c < n_parts; c += kLoads * kRowThreads) {
+                float2 v[kLoads];
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) v[u] = st[min(c + u * kRowThreads, n_parts - 1) * stride];
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u)
+                    if (c + u * kRowThreads < n_parts) lse_fold(mx, sum, v[u]);
+            }
+        }
+        if constexpr (kRowThreads > 1) {
+            if (q == 1) folded[r] = make_float2(mx, sum);
+            __syncthreads();
+            if (q == 0) lse_fold(mx, sum, folded[r]);
+        }
+        if (q == 0) nls[r] = r < R ? -(mx + log2f(sum)) : 0.f;
+    }
+    __syncthreads();
+
+    float* vote_h = vote + ((int64_t)bh * G + G / n_rg * rg) * P;
     struct RowBlock { bf16x8_t a[kKs]; float4 nl; };     // A operands and normalisers of one 16-row block
     auto read_block = [&](RowBlock& rbk, int rb) {
 #pragma unroll
@@ -345,7 +375,6 @@ __global__ __launch_bounds__(256) void score_vote_wave_kernel(
             }
         }
     };
-    load_tile(ka, wv);
     for (int tile = wv; tile < n_tiles; tile += 8) {
         process(ka, kb, tile);
         if (tile + 4 < n_tiles) process(kb, ka, tile + 4);
@@ -534,8 +563,8 @@ __global__ __launch_bounds__(256) void score_pool_kernel(const float* __restrict
 // The MFMA kernels in the variant for `rows` query rows (up to 128, or up to 256), a window of 8 or not, D features.
 typedef void (*StatsKernel)(const bf16_bits*, const bf16_bits*, int, int, int, int, int, int64_t, int64_t, int64_t, int, int,
                             int, float2*);
-typedef void (*VoteKernel)(const bf16_bits*, const bf16_bits*, const float*, int, int, int, int, int, int64_t, int64_t,
-                           int64_t, int, int, float*);
+typedef void (*VoteKernel)(const bf16_bits*, const bf16_bits*, const float*, const float2*, int, int, int, int, int, int,
+                           int64_t, int64_t, int64_t, int, int, float*);
 constexpr int kScoreRows = 256;     // rows one workgroup of the MFMA kernels holds at most
 static StatsKernel stats_kernel(int rows, int D) {
     if (D == 64) return rows <= 128 ? score_stats_wave_kernel<8, 64> : score_stats_wave_kernel<16, 64>;
@@ -618,11 +647,9 @@ static int wave_chunk(int64_t heads, int N, int n_parts) {
     }
     return best * kRound;
 }
-// The statistics take these chunks where those of plan_score would leave the chip short of two workgroups per CU, up to
-// this prompt length.  Longer prompts keep the chunks of plan_score, for no reason of accuracy (a normaliser folded from
-// more partials is as good): 8 heads of 40009 tokens are 144 workgroups and take 38.7 us, the vote pass, which takes
-// wave_chunk at every length, 25.1.
-constexpr int kFineChunks = 16384;
+// Partial statistics per query row that the vote workgroups fold for themselves, at most, for each thread that a row gets:
+// two round trips to memory of eight loads, where the merge kernel is a launch of 5 us.  More go through that kernel.
+constexpr int kFoldPartsPerThread = 32;
 
 template <typename T>
 static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, int w, int pool,
@@ -654,7 +681,8 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
     if constexpr (sizeof(T) == 2) {
         if (mfma && own_stats) {
             env.begin("score_stats_wave");
-            const int fold = N <= kFineChunks && (int64_t)BH * p.n_chunks * n_rg < 512 ? 1 : 0;
+            // the chunks of the votes where those of plan_score leave the chip short of two workgroups per CU
+            const int fold = (int64_t)BH * p.n_chunks * n_rg < 512 ? 1 : 0;
             const int nc = fold ? nc_wave : p.n_chunks;
             stats_kernel(R_group, D)<<<dim3((unsigned)(BH * nc * n_rg)), dim3(256), stats_lds_bytes(R_group, D), s>>>(
                 Q, K, H, R_group, n_rg, N, w, ks[0], ks[1], ks[2], nc, fold ? chunk_w : p.chunk, fold, stats);
@@ -688,7 +716,8 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
         env.end();
         n_parts = nca;
     }
-    if (own_stats) {
+    const bool vote_folds = mfma && own_stats && n_parts <= kFoldPartsPerThread * (R_group <= 128 ? 2 : 1);
+    if (own_stats && !vote_folds) {
         env.begin("score_lse");
         score_lse_kernel<<<dim3((rows + 63) / 64), dim3(256), 0, s>>>(stats, rows, p.R, n_parts, lse);
         env.end();
@@ -699,7 +728,7 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
         if (mfma) {
             env.begin("score_vote_wave");
             vote_kernel(R_group, w == 8, D)<<<grid_w, dim3(256), vote_lds_bytes(R_group, D), s>>>(
-                Q, K, lse, H, G, n_rg, N, w, ks[0], ks[1], ks[2], nc_wave, chunk_w, vote);
+                Q, K, lse, vote_folds ? stats : nullptr, n_parts, H, G, n_rg, N, w, ks[0], ks[1], ks[2], nc_wave, chunk_w, vote);
             env.end();
         }
     }

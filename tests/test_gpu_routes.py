@@ -371,3 +371,13 @@ def test_matrix_entropy_ranks_and_splits(ctx, N, D, r):
         # as the other tests of this call: the Ritz values of the leading 32 against the fp64 eigenvalues
         np.testing.assert_allclose(H.cpu().numpy(), Href, rtol=1e-4)
         np.testing.assert_allclose(eig.cpu().numpy()[:, :32], eref[:, :32], rtol=0, atol=2e-5)
+
+
+# Normalisers folded by the vote workgroups (few partials) and by the merge kernel (many), one and two row groups, rows that
+# do not fill the kernel's, one head of many tokens: 1 head has 8 to 128 partials per row here.
+@pytest.mark.parametrize("H,G,N,w", [(1, 4, 2100, 32), (1, 4, 16500, 16), (1, 8, 33000, 32), (1, 16, 9000, 32), (1, 2, 140000, 64), (4, 3, 20011, 16)])
+def test_score_normalisers_folded(ctx, H, G, N, w):
+    cfg = synth.tiny_config(dtype="bf16", B=1, H=H, G=G, N=N, w=w, rank_lo=2, rank_hi=48)
+    K, V, Q = synth.gen_all(cfg, seed0=N + G)
+    ref = O.window_score(to_f64(Q[0]), to_f64(K[0]), G=G, pool=7)
+    np.testing.assert_allclose(ctx.window_score(Q[0].to(DEV), K[0].to(DEV), G=G, pool=7).cpu().numpy(), ref, rtol=2e-5)
