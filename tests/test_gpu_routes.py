@@ -373,6 +373,52 @@ def test_matrix_entropy_ranks_and_splits(ctx, N, D, r):
         np.testing.assert_allclose(eig.cpu().numpy()[:, :32], eref[:, :32], rtol=0, atol=2e-5)
 
 
+# Rows split over workgroups: chunk counts that are odd, that need longer chunks, rows that are no multiple of 4, 2048 or the
+# chunk; budgets from none to all; scores with one outlier (nearly all in one bin: lists overflow), with a few hundred ties at
+# the threshold, and scores that no longer fit the range that the scoring call left.  Indices are exact.
+@pytest.mark.parametrize("rows,P,w", [(1, 24576, 4), (3, 32769, 8), (2, 67591, 32), (1, 131064, 8), (32, 33333, 1), (1, 1_000_003, 64)])
+def test_select_rows_over_workgroups(ctx, rows, P, w):
+    rng = np.random.default_rng(P)
+    N = P + w
+    for kind in ("spread", "outlier", "ties", "equal"):
+        score = np.exp(rng.standard_normal((1, rows, P)) * 3).astype(np.float32)
+        if kind == "outlier":
+            score = (1.0 + rng.random((1, rows, P)) * 1e-4).astype(np.float32)
+            score[:, :, P // 3] = 1e30
+            score[:, :, P // 2] = -1e30
+        elif kind == "ties":
+            score = (rng.integers(0, P // 300, (1, rows, P)) / 7).astype(np.float32)
+        elif kind == "equal":
+            score[:] = 0.25
+        budget = rng.integers(w, min(P, 60000) + w, (1, rows)).astype(np.int32)
+        budget[0, 0] = {"spread": w + 1, "outlier": w + 2, "ties": N, "equal": N - 1}[kind]
+        cap = int(budget.max())
+        _, _, idx, ln = ctx.select_gather(torch.from_numpy(score).to(DEV), torch.from_numpy(budget).to(DEV), None, None, w, cap, N=N)
+        for r in {0, rows // 2, rows - 1}:
+            ref = O.select_indices(score[0, r].astype(np.float64), budget[0, r], N, w)
+            assert int(ln[0, r]) == len(ref)
+            assert np.array_equal(idx[0, r, : len(ref)].cpu().numpy(), ref), (kind, r)
+
+
+def test_select_over_workgroups_stale_range_and_small_workspace(ctx):
+    from paper_2410_03090_amd import binding
+    cfg = synth.tiny_config(dtype="bf16", B=1, H=2, G=2, N=40009, w=32, rank_lo=2, rank_hi=24)
+    K, V, Q = synth.gen_all(cfg, seed0=3)
+    budget = torch.tensor([[500, 1777]], dtype=torch.int32, device=DEV)
+    small = binding.Context(0, 1 << 16)                             # no room to split the rows: one workgroup each
+    for change in (None, lambda s: s.copy_(torch.randn(s.shape, device=DEV) * 7), lambda s: s.mul_(1e-6)):
+        score = ctx.window_score(Q[0].to(DEV), K[0].to(DEV), G=2, pool=7)
+        if change is not None:
+            change(score)
+        for c in (ctx, ctx, small):                                 # twice: the range is still there, or found again
+            _, _, idx, ln = c.select_gather(score, budget, None, None, 32, 1777, N=40009)
+            sc = score.cpu().numpy().astype(np.float64)
+            for h in range(2):
+                ref = O.select_indices(sc[0, h], int(budget[0, h]), 40009, 32)
+                assert np.array_equal(idx[0, h, : len(ref)].cpu().numpy(), ref)
+    small.close()
+
+
 # Normalisers folded by the vote workgroups (few partials) and by the merge kernel (many), one and two row groups, rows that
 # do not fill the kernel's, one head of many tokens: 1 head has 8 to 128 partials per row here.
 @pytest.mark.parametrize("H,G,N,w", [(1, 4, 2100, 32), (1, 4, 16500, 16), (1, 8, 33000, 32), (1, 16, 9000, 32), (1, 2, 140000, 64), (4, 3, 20011, 16)])
