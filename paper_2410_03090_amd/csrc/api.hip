@@ -55,7 +55,13 @@ uncomp_status uncomp_create(uncomp_ctx** ctx_out, int device, size_t workspace_b
     if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
     if (e == hipSuccess) {
         ctx->num_cu = prop.multiProcessorCount;
-        e = hipMalloc(reinterpret_cast<void**>(&ctx->ws), ctx->ws_bytes);
+        const size_t counter_bytes = kSplitHeads * sizeof(uint32_t);
+        e = hipMalloc(reinterpret_cast<void**>(&ctx->ws), ctx->ws_bytes + counter_bytes);
+        if (e == hipSuccess) {
+            ctx->counters = reinterpret_cast<uint32_t*>(ctx->ws + ctx->ws_bytes);
+            e = hipMemset(ctx->counters, 0, counter_bytes);
+            if (e == hipSuccess) e = hipDeviceSynchronize();     // the first call may come on any stream
+        }
     }
     // kernels with more than 64 KiB of dynamic LDS get their limit raised here, not in the hot calls
     if (e == hipSuccess) e = init_gram_kernels();
@@ -605,18 +611,33 @@ uncomp_status uncomp_decode_step(uncomp_ctx* ctx, const void* q, const void* k_n
     // the kernels always form the output; without a destination it lands in the workspace
     float* out_p = out != nullptr ? out : reinterpret_cast<float*>(ctx->ws + p.out_off);
     const Env env{static_cast<hipStream_t>(stream), &ctx->prof, ctx->force_alu};
-    // few heads: 64-row waves where the workspace holds their partials (a context sized for the 128-row ones keeps those)
-    const bool one_kernel = wave_path && n_heads >= kHeadStepHeads && G <= 8 &&
-                            decode_head_lds_bytes(n_heads, G, cap) <= kDecodeHeadLdsMax;
+    // A workgroup per head for many heads and for short caches, whose time is that of one head's start and end; a few heads of
+    // longer ones spread over workgroups that the last of them merges; two kernels otherwise.  us, up to four query heads
+    // (head / spread / two kernels): 8 heads of 300 rows 8.1 / 9.0 / 11.9, of 500 rows 10.4 / 9.1 / 12.6, of 3238 rows
+    // 34.8 / 13.3 / 15.7; 32 heads of 5000 rows - / 24.0 / 30.6, of 8000 rows - / 37.6 / 36.6; 128 heads of 1000 rows
+    // 20.8 / 17.7 / 21.5, of 1400 rows 25.6 / 27.1 / 26.1; 200 heads of 2000 rows 38.1 / 46.8 / 48.8.
+    const bool head_step = wave_path && G <= 8 && (n_heads >= kHeadStepHeads || cap <= kHeadStepRows) &&
+                           decode_head_lds_bytes(n_heads, G, cap) <= kDecodeHeadLdsMax;
+    const int64_t rows = (int64_t)n_heads * cap;
+    const DecodePlan ps = plan_decode_split(n_heads, G, cap);
+    const bool split = wave_path && !head_step && G <= 8 && n_heads <= kSplitHeads && rows <= kSplitRows &&
+                       ps.np_max <= kSplitParts && ps.bytes <= ctx->ws_bytes;
+    // two kernels: 64-row waves where the workspace holds their partials (a context sized for the 128-row ones keeps those)
     const DecodePlan pf = plan_decode(n_heads, G, cap, 64);
-    const bool fine = wave_path && fine_decode_waves(n_heads, G, cap) && pf.bytes <= ctx->ws_bytes &&
+    const bool fine = (G <= 4 || G > 8) && fine_decode_waves(n_heads, G, cap) && pf.bytes <= ctx->ws_bytes &&
                       decode_update_lds_bytes(pf) <= kLdsDefaultLimit;
-    hipError_t e = one_kernel  ? launch_decode_head(q, k_new, v_new, n_heads, G, pos, budget, w, cap, K_c, V_c, idx, cum, len,
-                                                    out_p, evicted, env)
-                   : wave_path ? launch_decode_wave(q, k_new, v_new, n_heads, G, pos, budget, w, cap, K_c, V_c, idx, cum,
-                                                    len, out_p, evicted, fine ? pf : p, ctx->ws, env)
-                               : launch_decode_step(q, k_new, v_new, dtype, n_heads, G, pos, budget, w, cap, K_c, V_c,
-                                                  idx, cum, len, out_p, evicted, env);
+    hipError_t e;
+    if (head_step)
+        e = launch_decode_head(q, k_new, v_new, n_heads, G, pos, budget, w, cap, K_c, V_c, idx, cum, len, out_p, evicted, env);
+    else if (split)
+        e = launch_decode_split(q, k_new, v_new, n_heads, G, pos, budget, w, cap, K_c, V_c, idx, cum, len, out_p, evicted, ps,
+                                ctx->ws, ctx->counters, env);
+    else if (wave_path)
+        e = launch_decode_wave(q, k_new, v_new, n_heads, G, pos, budget, w, cap, K_c, V_c, idx, cum, len, out_p, evicted,
+                               fine ? pf : p, ctx->ws, env);
+    else
+        e = launch_decode_step(q, k_new, v_new, dtype, n_heads, G, pos, budget, w, cap, K_c, V_c, idx, cum, len, out_p, evicted,
+                               env);
     if (e != hipSuccess) return hip_fail(ctx, e, "decode_step: launch");
     return UNCOMP_OK;
 }

@@ -27,6 +27,7 @@ struct uncomp_ctx {
     int num_cu;
     char* ws;            // device workspace
     size_t ws_bytes;
+    uint32_t* counters;  // behind the workspace: zero between calls (kSplitHeads of them)
     char err[256];
     uncomp::Profiler prof;
     bool force_alu = false;
@@ -212,15 +213,24 @@ struct DecodePlan {
     size_t bytes;
 };
 DecodePlan plan_decode(int n_heads, int G, int cap, int wave_rows = 0);       // wave_rows 0: 128 or 256
-// The one-kernel step (decode_head_kernel) for at least kHeadStepHeads heads whose tables fit kDecodeHeadLdsMax bytes of
-// LDS: two workgroups of the four-wave variants per CU.  The eight-wave ones use 160 and 211 registers, so that one fits
+// The one-kernel step (decode_head_kernel) for at least kHeadStepHeads heads, or rows of at most kHeadStepRows, whose tables
+// fit kDecodeHeadLdsMax bytes of LDS: two workgroups of the four-wave variants per CU.  The eight-wave ones use 160 and 211 registers, so that one fits
 // a CU whatever its LDS; they keep the same bound, and what a larger one would give is not measured.
-constexpr int kHeadStepHeads = 256;
+constexpr int kHeadStepHeads = 160, kHeadStepRows = 384;
 constexpr size_t kDecodeHeadLdsMax = 80 * 1024 - 1024;
 size_t decode_head_lds_bytes(int n_heads, int G, int cap);
 hipError_t launch_decode_head(const void* q, const void* k_new, const void* v_new, int n_heads, int G, const int32_t* pos,
                               const int32_t* budget, int w, int cap, void* Kc, void* Vc, int32_t* idx, float* cum,
                               int32_t* len, float* out, int32_t* evicted, const Env& env);
+// The step of few heads whose rows are spread over workgroups of kSplitThreads threads, merged by the last of them
+// (decode_split_kernel; G <= 8, at most kSplitHeads heads of together kSplitRows rows, kSplitParts workgroups a head).
+// counters: kSplitHeads zeros, left zero.
+constexpr int kSplitThreads = 512, kSplitHeads = 256, kSplitParts = 1024, kSplitRows = 160 * 1024;
+DecodePlan plan_decode_split(int n_heads, int G, int cap);
+hipError_t launch_decode_split(const void* q, const void* k_new, const void* v_new, int n_heads, int G, const int32_t* pos,
+                               const int32_t* budget, int w, int cap, void* Kc, void* Vc, int32_t* idx, float* cum,
+                               int32_t* len, float* out, int32_t* evicted, const DecodePlan& p, char* ws, uint32_t* counters,
+                               const Env& env);
 hipError_t launch_decode_wave(const void* q, const void* k_new, const void* v_new, int n_heads, int G,
                               const int32_t* pos, const int32_t* budget, int w, int cap, void* Kc, void* Vc,
                               int32_t* idx, float* cum, int32_t* len, float* out, int32_t* evicted,

@@ -381,7 +381,7 @@ __global__ __launch_bounds__(256) void decode_attend_wave_kernel(
     // ---- pass 1: logits of the wave's rows; lane holds query head c16, rows 16t + 4j + v ----
     // Short waves (kAll) have all their keys and values in flight at once: with few waves on the chip their time is
     // that of the round trips to memory (8 heads of 2048 rows: 8.4 us, two tiles ahead 9.6).
-    constexpr bool kAll = WR == 64 && GT <= 8;
+    constexpr bool kAll = WR == 64 && GT == 4;
     constexpr int kSlots = kAll ? kTiles : 2;
     f32x4_t s[kTiles];
     uint4 kt[kSlots][4], vt[kSlots][4];
@@ -980,6 +980,319 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_head_kernel(
                 victim_slot, (int)(uint32_t)best, posh, new_cum_s);
 }
 
+// Floats that another workgroup of the same launch writes or reads.  The accesses carry the agent scope (sc1): they go past
+// the caches that workgroups on different XCDs do not share, so that no fence has to write back or invalidate a whole L2 (a
+// fence of that scope per workgroup: 92 us for 8 heads of 8000 rows).  A store is where others can read it once the wave has
+// waited for it.
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+constexpr int kAgentScope = 16;                                     // the sc1 bit of a buffer access
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t shared_floats(float* p, int n) {
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, n * (int)sizeof(float), 0x00027000);
+}
+__device__ __forceinline__ void put4(__amdgpu_buffer_rsrc_t b, int i, float4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)}, b,
+                                           i * (int)sizeof(float), 0, kAgentScope);
+}
+__device__ __forceinline__ float4 get4(__amdgpu_buffer_rsrc_t b, int i) {
+    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(b, i * (int)sizeof(float), 0, kAgentScope);
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+}
+
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void put2(__amdgpu_buffer_rsrc_t b, int i, float2 v) {
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{__float_as_uint(v.x), __float_as_uint(v.y)}, b, i * (int)sizeof(float), 0, kAgentScope);
+}
+__device__ __forceinline__ float2 get2(__amdgpu_buffer_rsrc_t b, int i) {
+    const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(b, i * (int)sizeof(float), 0, kAgentScope);
+    return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+}
+
+// One launch for few heads whose rows are spread over several workgroups: eight waves of WR rows each, every load of a wave
+// requested before the first is needed.  A workgroup leaves its probabilities, its output and their maximum and sum in the
+// workspace and counts itself; the last one of a head merges them and makes the step's update (what decode_update_kernel does
+// in a launch of its own).  Nothing waits for another workgroup.  All workgroups of a head count, also those without rows:
+// the last one changes the length that they all read.  The counters are zero before and after every call.
+template <int GT, int WR>
+__global__ __launch_bounds__(kSplitThreads) void decode_split_kernel(
+    const bf16_bits* __restrict__ q, const bf16_bits* __restrict__ k_new, const bf16_bits* __restrict__ v_new, int G,
+    const int32_t* __restrict__ pos, const int32_t* __restrict__ budget, int w, int cap, bf16_bits* Kc, bf16_bits* Vc,
+    int32_t* idx, float* cum, int32_t* len, float* __restrict__ out, int32_t* __restrict__ evicted, int s_rows, float* ws_p,
+    float* ws_ml, float* ws_acc, uint32_t* counters) {
+    constexpr int NT = kSplitThreads, NW = NT / 64, kTiles = WR / 16, kRows = NW * WR;
+    __shared__ __align__(16) float prob[kRows * GT];
+    __shared__ __align__(16) float accs[NW * GT * kD];
+    __shared__ float wave_m[NW][GT], wave_l[NW][GT];
+    __shared__ __align__(16) float wave_f[NW * GT];                 // exp2(m_wave - m)
+    __shared__ unsigned long long wave_best[NW];
+    __shared__ int victim_slot, is_last;
+    __shared__ float new_cum_s;
+    const int part = blockIdx.x, np_max = gridDim.x, h = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c16 = lane & 15, j = lane >> 4;
+    int n = len[h];
+    n = n < 0 ? 0 : (n > cap ? cap : n);
+    const int n1 = n + 1, row0 = part * kRows, wave0 = row0 + wave * WR;
+    bf16_bits* Kh = Kc + (int64_t)h * cap * kD;
+    bf16_bits* Vh = Vc + (int64_t)h * cap * kD;
+    int32_t* idxh = idx + (int64_t)h * cap;
+    float* cumh = cum + (int64_t)h * cap;
+    const bf16_bits* kn = k_new + (int64_t)h * kD;
+    const bf16_bits* vn = v_new + (int64_t)h * kD;
+    const auto ph = shared_floats(ws_p + (int64_t)h * s_rows * GT, s_rows * GT);
+    const auto mlh = shared_floats(ws_ml + (int64_t)h * np_max * GT * 2, np_max * GT * 2);
+    const auto acch = shared_floats(ws_acc + (int64_t)h * np_max * GT * kD, np_max * GT * kD);
+    if (row0 < n1) {
+        uint4 kt[kTiles][4], vt[kTiles][4];
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) {                          // rows past the end re-read the new token
+            const int r = wave0 + 16 * t + c16;
+            const bf16_bits* src = (r < n ? Kh + (int64_t)r * kD : kn) + 8 * j;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) kt[t][ks] = *reinterpret_cast<const uint4*>(src + 32 * ks);
+        }
+        bf16x8_t qb[4];                                              // column c16 = query head, zero beyond G
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            uint4 v = make_uint4(0u, 0u, 0u, 0u);
+            if (c16 < G) v = *reinterpret_cast<const uint4*>(q + ((int64_t)h * G + c16) * kD + 32 * ks + 8 * j);
+            qb[ks] = __builtin_bit_cast(bf16x8_t, v);
+        }
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int r = wave0 + 16 * t + 4 * u + j;
+                const bf16_bits* src = (r < n ? Vh + (int64_t)r * kD : vn) + 8 * c16;
+                vt[t][u] = *reinterpret_cast<const uint4*>(src);
+            }
+        __builtin_amdgcn_sched_barrier(0);                           // everything is on its way
+        const float qs = 0.08838834764831845f * 1.4426950408889634f; // 1/sqrt(128) * log2(e)
+        f32x4_t s[kTiles];
+        float mx = -3.402823466e38f, sum = 0.f;                      // finite: logits of -inf weigh nothing
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) {
+            f32x4_t c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kt[t][ks]), qb[ks], c, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                s[t][v] = wave0 + 16 * t + 4 * j + v < n1 ? c[v] * qs : -INFINITY;
+                mx = fmaxf(mx, s[t][v]);
+            }
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        float* pl = prob + wave * WR * GT;
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float e = exp2f(s[t][v] - mx);
+                sum += e;
+                if (c16 < GT) pl[(16 * t + 4 * j + v) * GT + c16] = e;
+            }
+        sum += __shfl_xor(sum, 16, 64);
+        sum += __shfl_xor(sum, 32, 64);
+        if (j == 0 && c16 < GT) {
+            wave_m[wave][c16] = mx;
+            wave_l[wave][c16] = sum;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");       // the wave's own probabilities
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        float acc[GT][8];
+#pragma unroll
+        for (int g = 0; g < GT; ++g)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float vf[8];
+                const uint32_t wds[4] = {vt[t][u].x, vt[t][u].y, vt[t][u].z, vt[t][u].w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    vf[2 * i] = __uint_as_float(wds[i] << 16);
+                    vf[2 * i + 1] = __uint_as_float(wds[i] & 0xffff0000u);
+                }
+                const float* prow = pl + (16 * t + 4 * u + j) * GT;
+#pragma unroll
+                for (int g4 = 0; g4 < GT; g4 += 4) {
+                    const float4 pr = *reinterpret_cast<const float4*>(prow + g4);
+                    const float prs[4] = {pr.x, pr.y, pr.z, pr.w};
+#pragma unroll
+                    for (int gg = 0; gg < 4; ++gg)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) acc[g4 + gg][e] = fmaf(prs[gg], vf[e], acc[g4 + gg][e]);
+                }
+            }
+        // lane row j receives query head g4 + {0,2,1,3}[j]
+        const int gsel = ((j & 1) << 1) | (j >> 1);
+#pragma unroll
+        for (int g4 = 0; g4 < GT; g4 += 4) {
+            float tot[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                tot[e] = reduce4_over_rows(acc[g4][e], acc[g4 + 1][e], acc[g4 + 2][e], acc[g4 + 3][e]);
+            float* dst = accs + (wave * GT + g4 + gsel) * kD + 8 * c16;
+            reinterpret_cast<float4*>(dst)[0] = make_float4(tot[0], tot[1], tot[2], tot[3]);
+            reinterpret_cast<float4*>(dst)[1] = make_float4(tot[4], tot[5], tot[6], tot[7]);
+        }
+        __syncthreads();
+        if (tid < NW * GT) {
+            const int g = tid % GT;
+            float m = wave_m[0][g];
+#pragma unroll
+            for (int x = 1; x < NW; ++x) m = fmaxf(m, wave_m[x][g]);
+            wave_f[tid] = exp2f(wave_m[tid / GT][g] - m);
+            if (tid < GT) {
+                float l = 0.f;
+#pragma unroll
+                for (int x = 0; x < NW; ++x) l += wave_l[x][g] * exp2f(wave_m[x][g] - m);
+                put2(mlh, (part * GT + g) * 2, make_float2(m, l));
+            }
+        }
+        __syncthreads();
+        if (2 * tid < GT * kD) {
+            const int o = 2 * tid;
+            float2 v = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int x = 0; x < NW; ++x) {
+                const float2 a = *reinterpret_cast<const float2*>(accs + x * GT * kD + o);
+                const float f = wave_f[x * GT + (o >> 7)];
+                v.x = fmaf(a.x, f, v.x);
+                v.y = fmaf(a.y, f, v.y);
+            }
+            put2(acch, part * GT * kD + o, v);
+        }
+        const int n_f4 = min(kRows, n1 - row0) * (GT / 4);           // n1 <= s_rows
+        for (int i = tid; i < n_f4; i += NT) {
+            float4 v = *reinterpret_cast<const float4*>(prob + 4 * i);
+            const float4 f = *reinterpret_cast<const float4*>(wave_f + i / (WR * GT / 4) * GT + 4 * (i % (GT / 4)));
+            v.x *= f.x;
+            v.y *= f.y;
+            v.z *= f.z;
+            v.w *= f.w;
+            put4(ph, row0 * GT + 4 * i, v);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // what this wave put has arrived
+    __syncthreads();
+    if (tid == 0) {
+        const uint32_t before = __hip_atomic_fetch_add(&counters[h], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        is_last = before == (uint32_t)(np_max - 1);
+        if (is_last) __hip_atomic_store(&counters[h], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        victim_slot = -1;
+    }
+    __syncthreads();
+    if (!is_last) return;
+
+    const int posh = pos[h], np = (n1 + kRows - 1) / kRows;
+    int b = budget[h];
+    b = b < w ? w : b;
+    b = b > cap ? cap : b;
+    const bool over = n1 > b;
+    constexpr int U = GT == 4 ? 8 : 4;
+    float4 pr[U][GT / 4];
+    float c_in[U];
+    int id_in[U];
+    auto load_rows = [&](int r0) {                                   // clamped; skipped where no thread has a row
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u > 0 && r0 - tid + u * NT > n) continue;
+            const int r = min(r0 + u * NT, n), rc = min(r, cap - 1);
+#pragma unroll
+            for (int g4 = 0; g4 < GT / 4; ++g4) pr[u][g4] = get4(ph, r * GT + 4 * g4);
+            c_in[u] = cumh[rc];
+            id_in[u] = idxh[rc];
+        }
+    };
+    load_rows(tid);
+    float* coef = accs;                                              // [np][GT]: exp2(m_part - m) / sum
+    for (int g = wave; g < GT; g += NW) {                            // a lane per part, once more for every 64 parts
+        auto ml = [&](int x) { return get2(mlh, (x * GT + g) * 2); };
+        const float2 first = lane < np ? ml(lane) : make_float2(-3.402823466e38f, 0.f);
+        float m = first.x;
+        for (int x = lane + 64; x < np; x += 64) m = fmaxf(m, ml(x).x);
+        m = wave_max(m);
+        float l = first.y * exp2f(first.x - m);
+        for (int x = lane + 64; x < np; x += 64) {
+            const float2 v = ml(x);
+            l += v.y * exp2f(v.x - m);
+        }
+        const float inv = g < G ? 1.0f / wave_sum(l) : 0.f;
+        if (lane < np) coef[lane * GT + g] = exp2f(first.x - m) * inv;
+        for (int x = lane + 64; x < np; x += 64) coef[x * GT + g] = exp2f(ml(x).x - m) * inv;
+    }
+    __syncthreads();
+    static_assert(GT * kD <= 2 * NT, "two outputs a thread");
+    if (2 * tid < G * kD) {
+        const int o = 2 * tid;
+        float v0 = 0.f, v1 = 0.f;
+        for (int x0 = 0; x0 < np; x0 += 8) {
+            float2 a[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a[e] = get2(acch, min(x0 + e, np - 1) * GT * kD + o);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (x0 + e < np) {
+                    const float f = coef[(x0 + e) * GT + (o >> 7)];
+                    v0 = fmaf(a[e].x, f, v0);
+                    v1 = fmaf(a[e].y, f, v1);
+                }
+            }
+        }
+        out[(int64_t)h * G * kD + o] = v0;
+        out[(int64_t)h * G * kD + o + 1] = v1;
+    }
+    unsigned long long best = ~0ull;
+    int best_r = -1;
+    for (int r0 = tid; r0 < n1; r0 += U * NT) {
+        if (r0 != tid) load_rows(r0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + u * NT;
+            if (r < n1) {
+                const float* cf = coef + (r / kRows) * GT;
+                float inc = 0.f;                                     // sum over the query heads of p_gr
+#pragma unroll
+                for (int g4 = 0; g4 < GT / 4; ++g4) {
+                    const float4 cc = *reinterpret_cast<const float4*>(cf + 4 * g4);
+                    inc += pr[u][g4].x * cc.x;
+                    inc += pr[u][g4].y * cc.y;
+                    inc += pr[u][g4].z * cc.z;
+                    inc += pr[u][g4].w * cc.w;
+                }
+                if (r < n) {
+                    const float c = c_in[u] + inc;
+                    cumh[r] = c;
+                    if (id_in[u] <= posh - w) {
+                        const unsigned long long key = ((unsigned long long)ascending_key(c) << 32) | (uint32_t)id_in[u];
+                        if (key < best) {
+                            best = key;
+                            best_r = r;
+                        }
+                    }
+                } else {
+                    new_cum_s = inc;
+                }
+            }
+        }
+    }
+    const unsigned long long mine = best;
+    best = wave_min_u64(best);
+    if (lane == 0) wave_best[wave] = best;
+    __syncthreads();
+    best = wave_best[0];
+#pragma unroll
+    for (int x = 1; x < NW; ++x) best = wave_best[x] < best ? wave_best[x] : best;
+    if (over && best_r >= 0 && mine == best) victim_slot = best_r;
+    __syncthreads();
+    place_token(kn, vn, Kh, Vh, idxh, cumh, len + h, evicted != nullptr ? evicted + h : nullptr, tid, n, cap, over,
+                victim_slot, (int)(uint32_t)best, posh, new_cum_s);
+}
+
 DecodePlan plan_decode(int n_heads, int G, int cap, int wave_rows) {
     DecodePlan p;
     p.GT = G <= 4 ? 4 : (G <= 8 ? 8 : 16);
@@ -1061,7 +1374,6 @@ hipError_t launch_decode_wave(const void* q, const void* k_new, const void* v_ne
     }
     if (p.wave_rows == 64) {
         if (p.GT == 4) UNCOMP_WAVE_CASE(4, 64);
-        if (p.GT == 8) UNCOMP_WAVE_CASE(8, 64);
         UNCOMP_WAVE_CASE(16, 64);
     }
     if (p.GT == 4) UNCOMP_WAVE_CASE(4, 128);
@@ -1103,6 +1415,38 @@ hipError_t launch_decode_head(const void* q, const void* k_new, const void* v_ne
                                            static_cast<const bf16_bits*>(v_new), G, pos, budget, w, cap,
                                            static_cast<bf16_bits*>(Kc), static_cast<bf16_bits*>(Vc), idx, cum, len, out,
                                            evicted, (cap + 16) / 16 * 16);
+    env.end();
+    return hipGetLastError();
+}
+
+// 16 rows a wave while that keeps to sixteen parts and half the chip, so that a CU has few rows to fetch; 32 beyond, so that
+// there are few parts to merge (us): 8 heads of 1000 rows 9.8 / 11.0, of 2000 rows 11.5 / 11.8, of 3238 rows 14.1 / 13.3; 64
+// heads of 500 rows 10.6 / 11.2, of 700 rows 12.4 / 12.2.  64 rows are slower up to 90 thousand rows in all (8 heads of 3238
+// rows 15.2) and within 5 % of 32 rows above.
+DecodePlan plan_decode_split(int n_heads, int G, int cap) {
+    const int wave_rows = cap <= 2048 && (int64_t)n_heads * cap <= 32768 ? 16 : 32;
+    DecodePlan p = plan_decode(n_heads, G, cap, kSplitThreads / 64 * wave_rows);
+    p.s_rows = (cap + 16) / 16 * 16;                                 // rows that are there: the others are not written
+    p.wave_rows = wave_rows;
+    p.ml_off = align_up(p.p_off + (size_t)n_heads * p.s_rows * p.GT * sizeof(float), 256);
+    p.acc_off = align_up(p.ml_off + (size_t)n_heads * p.np_max * p.GT * 2 * sizeof(float), 256);
+    p.bytes = align_up(p.acc_off + (size_t)n_heads * p.np_max * p.GT * kD * sizeof(float), 256);
+    return p;
+}
+
+hipError_t launch_decode_split(const void* q, const void* k_new, const void* v_new, int n_heads, int G, const int32_t* pos,
+                               const int32_t* budget, int w, int cap, void* Kc, void* Vc, int32_t* idx, float* cum,
+                               int32_t* len, float* out, int32_t* evicted, const DecodePlan& p, char* ws, uint32_t* counters,
+                               const Env& env) {
+    if (n_heads > kSplitHeads || p.GT > 8 || p.np_max > kSplitParts) return hipErrorInvalidValue;   // the interface checks before
+    auto kern = p.GT == 4 ? (p.wave_rows == 16 ? decode_split_kernel<4, 16> : decode_split_kernel<4, 32>)
+                          : (p.wave_rows == 16 ? decode_split_kernel<8, 16> : decode_split_kernel<8, 32>);
+    env.begin("decode_split");
+    kern<<<dim3((unsigned)p.np_max, (unsigned)n_heads), dim3(kSplitThreads), 0, env.s>>>(
+        static_cast<const bf16_bits*>(q), static_cast<const bf16_bits*>(k_new), static_cast<const bf16_bits*>(v_new), G, pos,
+        budget, w, cap, static_cast<bf16_bits*>(Kc), static_cast<bf16_bits*>(Vc), idx, cum, len, out, evicted, p.s_rows,
+        reinterpret_cast<float*>(ws + p.p_off), reinterpret_cast<float*>(ws + p.ml_off), reinterpret_cast<float*>(ws + p.acc_off),
+        counters);
     env.end();
     return hipGetLastError();
 }

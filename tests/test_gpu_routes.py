@@ -336,6 +336,44 @@ def test_decode_two_kernels(n_heads, G, cap, rows):
         c.close()
 
 
+# The step of few heads whose rows are spread over workgroups that the last one merges: 16- and 32-row waves, caches just above
+# those that one workgroup takes, the rows where the wave length changes, many parts, the most rows; lengths around the parts,
+# heads that grow into a new part, several steps (the counters are left as they were found).
+@pytest.mark.parametrize("n_heads,G,cap", [(1, 4, 385), (12, 8, 400), (159, 3, 386), (16, 4, 2048), (12, 4, 2049), (17, 8, 2048),
+                                           (8, 4, 3238), (9, 7, 5000), (1, 1, 163840), (2, 8, 81920)])
+def test_decode_spread_heads(n_heads, G, cap):
+    from paper_2410_03090_amd import binding
+    from tests.test_gpu_decode import D, State, _check_step
+    w, g = 8, torch.Generator(device=DEV).manual_seed(cap + G)
+    rand = lambda *sh: torch.randn(*sh, generator=g, device=DEV).to(torch.bfloat16)  # noqa: E731
+    edges = [cap, 0, 1, 126, 127, 128, 129, 254, 255, 256, 257, 383, cap // 2, cap - 1, cap - 2]
+    ln = torch.tensor([min(cap, edges[h % len(edges)]) for h in range(n_heads)], dtype=torch.int32, device=DEV)
+    budget = torch.where(torch.arange(n_heads, device=DEV) % 3 == 1, ln + 5, ln).to(torch.int32)
+    idx = torch.argsort(torch.rand(n_heads, cap + 60, generator=g, device=DEV), dim=1)[:, :cap].to(torch.int32).contiguous()
+    cum = torch.rand(n_heads, cap, generator=g, device=DEV) * 2
+    st = State(rand(n_heads, cap, D), rand(n_heads, cap, D), idx, cum, ln)
+    for h in range(n_heads):                                        # rows that were never written hold anything
+        st.Kc[h, int(ln[h]):] = float("nan")
+        st.Vc[h, int(ln[h]):] = float("nan")
+    pick = torch.tensor(sorted(set(range(min(n_heads, 15))) | {n_heads - 1}), device=DEV)
+    sample = lambda: State(*(t[pick] for t in (st.Kc, st.Vc, st.idx, st.cum, st.ln))).host()  # noqa: E731
+    c = binding.Context(0, binding.Context.decode_workspace_bytes(n_heads, G, cap))
+    try:
+        for t in range(3):
+            q, kn, vn = 2 * rand(n_heads, G, D), rand(n_heads, D), rand(n_heads, D)
+            pos = torch.full((n_heads,), cap + 100 + t, dtype=torch.int32, device=DEV)
+            before, ln0 = sample(), st.ln.clone()
+            out, ev = c.decode_step(q, kn, vn, pos, budget, w, st.Kc, st.Vc, st.idx, st.cum, st.ln)
+            torch.cuda.synchronize()
+            host = [x[pick].cpu() for x in (out, ev, q, kn, vn, pos, budget)]
+            assert torch.isfinite(out).all()
+            assert _check_step(before, sample(), host[0].numpy(), host[1].numpy(), *host[2:5], host[5].numpy(), host[6].numpy(), w,
+                               cap) <= 1
+            assert torch.equal(st.ln, torch.where(ev == -1, ln0 + 1, ln0))
+    finally:
+        c.close()
+
+
 # The longest cache that 16 query heads may have: the update kernel's three tables fill 64 KiB but for 64 bytes.
 def test_decode_longest_cache():
     from paper_2410_03090_amd import binding
