@@ -6,6 +6,8 @@
 #include <hip/hip_bf16.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace uncomp {
 
 typedef uint16_t bf16_bits;   // storage of one bf16 element
@@ -71,6 +73,26 @@ __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
+}
+
+// fp64 products with a value of another lane of the row of 16: acc +- rows[lane row's lane U] * m.  The DPP operand must not have been written by the two vector
+// instructions before (the compiler does not look into the statement): dpp_ready() stands between.
+template <int U>
+__device__ __forceinline__ void fmac_bc(double& acc, double rows, double m) {
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(rows), "v"(m), "n"(U));
+}
+template <int U>
+__device__ __forceinline__ void fnmac_bc(double& acc, double rows, double m) {
+    asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(rows), "v"(m), "n"(U));
+}
+__device__ __forceinline__ void dpp_ready(double& a, double& b) { asm volatile("s_nop 1" : "+v"(a), "+v"(b)); }
+
+template <int U, int END = 16, typename F>
+__device__ __forceinline__ void each16(F&& f) {
+    if constexpr (U < END) {
+        f(std::integral_constant<int, U>{});
+        each16<U + 1, END>(f);
+    }
 }
 
 }  // namespace uncomp

@@ -509,13 +509,6 @@ __global__ __launch_bounds__(256) void sub_zgram_finish_kernel(const float* __re
     if (q == 0) gram[e] = (float)(((a + quarter[0][i]) + quarter[1][i]) + quarter[2][i]);
 }
 
-// value of x in lane `src` (a compile-time constant after unrolling) as a wave-uniform double
-__device__ __forceinline__ double lane_value(double x, int src) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(x), src);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(x), src);
-    return __hiloint2double(hi, lo);
-}
-
 // 1 / sqrt(x) of a positive fp64 number: the hardware's estimate (2^-24) and one third-order step (the library function
 // spends more on denormals and infinities, which a pivot above the tolerance of a finite Gram is not).
 __device__ __forceinline__ double inv_sqrt(double x) {
@@ -524,158 +517,136 @@ __device__ __forceinline__ double inv_sqrt(double x) {
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-// One workgroup: Cholesky G = L L^T in LDS (fp64), then Rinv = L^-T as fp32 so that Q = W Rinv has
-// orthonormal columns.  A pivot below 1e-12 of the largest diagonal entry retires its column (its
-// row and column of Rinv are zero).  Bound by the chain of the 128 pivots.  By 16-wide block columns, three barriers each:
-//   factor   lanes 0-15 of three waves hold the 16 rows of the diagonal block (values of other rows by v_readlane) and
-//            factor it, each for itself; their other lanes carry the rows below it and the rows of a 16 x 16 identity
-//            through the same instructions, which leaves them as the panel of L and as the inverse of the diagonal
-//            block.  The other five waves meanwhile update what the previous panel left to be updated;
-//   update   the next block column, one 16 x 16 tile per wave (v_mfma_f64_16x16x4_f64).
-// Then X = L^-1 block row by block row as products of tiles.  X[k][c], k > c, lives at G[c][k] in the unused upper triangle.
-// With the diagonal block on one wave, the panel a substitution with a thread per row and four waves: 55 us; now 47.
+// One workgroup: Cholesky G = L L^T (fp64), then Rinv = L^-T as fp32 so that Q = W Rinv has orthonormal columns.  A pivot below
+// 1e-12 of the largest diagonal entry retires its column (its row and column of Rinv are zero).
+// The elimination runs on G with an identity below it, [G; I] L^-T = [L; L^-T], by columns of 16: whatever the step, 128 rows are
+// in play, the rows of G that are left and the rows of I that are no longer zero, so that the inverse costs no phase of its own.
+// Row slot r of block column K is the tile (r, K) of G for r >= K and that of I for r < K (tile (K, K) of I is the identity until
+// its own step).  Two barriers a step:
+//   factor   two waves, a lane per row: 16 pivots in registers.  Every row of 16 lanes also holds the diagonal block, a row a
+//            lane, and reads its columns through the DPP broadcast.  The other six waves, which keep the tiles of the columns to
+//            come in registers, apply the previous panel to those beyond the next column (v_mfma_f64_16x16x4_f64);
+//   update   the next column's tiles get the new panel and go to LDS for the next step.
+// Bound by the chain of the 128 pivots: 47 us before (the panel's rows and the diagonal block in one lane's registers, values of
+// other rows by v_readlane, three barriers a step, then the inverse by block rows).
 constexpr int kCholThreads = 512;
 __global__ __launch_bounds__(kCholThreads) void sub_chol_kernel(const double* __restrict__ gsum, float* __restrict__ Rinv) {
-    extern __shared__ __align__(16) double G[];                // [128][129]
-    __shared__ double dinv[kP];
-    __shared__ double maxdiag;
-    constexpr int LD = kP + 1, B = 16, NB = kP / B, NT = kCholThreads, NW = NT / 64, kFactorWaves = 3;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    {
-        const double2* g2 = reinterpret_cast<const double2*>(gsum);
-        constexpr int kLoads = kP * kP / 2 / NT;
-        double2 v[kLoads];
+    constexpr int B = 16, NB = kP / B, LD = B + 1, kRowWaves = kP / 64, kTileWaves = kCholThreads / 64 - kRowWaves;
+    constexpr int kTiles = ((NB - 1) * NB + kTileWaves - 1) / kTileWaves;   // columns 1 .. 7, eight slots each
+    __shared__ double raw[kP][LD], pan[2][kP][LD];                   // the column about to be factored; the factored ones
+    __shared__ double maxdiag[kRowWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, kk = lane >> 4, w = wv - kRowWaves;
+    f64x4_t acc[kTiles];
+    if (w >= 0) {
 #pragma unroll
-        for (int u = 0; u < kLoads; ++u) v[u] = g2[tid + NT * u];
+        for (int s = 0; s < kTiles; ++s) {
+            const int t = w + kTileWaves * s, K = t / NB + 1, r = t % NB;
+            acc[s] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+            if (K < NB && r >= K) {
 #pragma unroll
-        for (int u = 0; u < kLoads; ++u) {
-            const int e = tid + NT * u, row = e >> 6, col = 2 * (e & 63);
-            G[row * LD + col] = v[u].x;
-            G[row * LD + col + 1] = v[u].y;
+                for (int v = 0; v < 4; ++v) acc[s][v] = gsum[(B * r + 4 * v + kk) * kP + B * K + c];
+            }
         }
-    }
-    __syncthreads();
-    if (wv == 0) {
-        double m = fmax(G[lane * LD + lane], G[(lane + 64) * LD + lane + 64]);
+    } else {
+        const double2* g2 = reinterpret_cast<const double2*>(gsum + tid * kP);
+        double2 v[B / 2];
+#pragma unroll
+        for (int k = 0; k < B / 2; ++k) v[k] = g2[k];
+        double m = gsum[tid * (kP + 1)];
+#pragma unroll
+        for (int k = 0; k < B / 2; ++k) {
+            raw[tid][2 * k] = v[k].x;
+            raw[tid][2 * k + 1] = v[k].y;
+        }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
-        if (lane == 0) maxdiag = m;
+        if (lane == 0) maxdiag[wv] = m;
     }
     __syncthreads();
-    const double tol = maxdiag * 1e-12;
-    // Tile (I, K) -= L[I][p] L[K][p]^T on the fp64 matrix cores.  Operand lane (c, kk) holds row c of its factor at column
-    // 4 s + kk of the panel; result register v is row 4 v + kk, column c.  Diagonal tiles are computed whole: what lands
-    // above the diagonal is not read by the factorisation.
-    auto update_tile = [&](int p, int I, int K) {
-        const int j0 = B * p, r0 = B * I, c0 = B * K;
-        const int c = lane & 15, kk = lane >> 4;
-        f64x4_t acc;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] = G[(r0 + 4 * v + kk) * LD + c0 + c];
+    const double tol = fmax(maxdiag[0], maxdiag[1]) * 1e-12;
+    // tile (r, K) of a column beyond p minus panel rows r times panel rows K, transposed
+    auto apply = [&](f64x4_t& x, int p, int r, int K) {
+        double av[4], bv[4];
 #pragma unroll
         for (int sx = 0; sx < 4; ++sx) {
-            const double av = -G[(r0 + c) * LD + j0 + 4 * sx + kk];
-            const double bv = G[(c0 + c) * LD + j0 + 4 * sx + kk];
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+            av[sx] = -pan[p & 1][B * r + c][4 * sx + kk];
+            bv[sx] = pan[p & 1][B * K + c][4 * sx + kk];
         }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) G[(r0 + 4 * v + kk) * LD + c0 + c] = acc[v];
+        for (int sx = 0; sx < 4; ++sx) x = __builtin_amdgcn_mfma_f64_16x16x4f64(av[sx], bv[sx], x, 0, 0, 0);
     };
     for (int p = 0; p < NB; ++p) {
-        const int j0 = B * p;
-        if (p > 0 && p + wv < NB) update_tile(p - 1, p + wv, p);
-        __syncthreads();
-        // ext: -1 a row of the diagonal block, 0..15 a row of the identity, from 16 on the rows below
-        const int i = lane & (B - 1);
-        const int ext = lane < B ? -1 : (64 - B) * wv + lane - B;
-        const int row = ext < 0 ? j0 + i : j0 + ext;                 // of G; the identity rows (j0 .. j0 + 15) are not read from it
-        const bool factoring = wv < kFactorWaves && (64 - B) * wv < kP - j0;
-        const bool live_row = row < kP;
-        double a[B];
-        if (factoring) {
+        if (w < 0) {
+            const int row = tid, slot = row >> 4;
+            double d[B], a[B];                                       // row c of the diagonal block, this lane's row
 #pragma unroll
             for (int k = 0; k < B; ++k) {
-                const double g = G[(live_row ? row : j0) * LD + j0 + k];
-                a[k] = ext >= 0 && ext < B ? (k == ext ? 1.0 : 0.0) : g;
+                d[k] = raw[B * p + c][k];
+                a[k] = raw[row][k];
+            }
+#pragma unroll
+            for (int k = 0; k < B; ++k) a[k] = slot == p ? (k == c ? 1.0 : 0.0) : a[k];
+            // pivot j: row j of the diagonal block is in lane j of every row of lanes
+            auto rows_from = [&](auto J, auto K0, auto K1, double dj) {      // columns K0 .. K1 - 1 minus their multiple of column J
+                each16<K0.value, K1.value>([&](auto k) {
+                    if constexpr (k.value > J.value + 1) fnmac_bc<k.value>(d[k.value], dj, dj);
+                    if constexpr (k.value > J.value) fnmac_bc<k.value>(a[k.value], dj, a[J.value]);
+                });
+            };
+            double piv = 0.0;
+            dpp_ready(d[0], piv);
+            fmac_bc<0>(piv, d[0], 1.0);
+            double di = piv > tol ? inv_sqrt(piv) : 0.0;
+            each16<0>([&](auto J) {
+                constexpr int j = J.value;
+                double dj = d[j] * di;
+                a[j] *= di;
+                piv = 0.0;
+                dpp_ready(dj, piv);
+                using I = std::integral_constant<int, j>;
+                // the next pivot's chain, the other columns in its waits
+                if constexpr (j + 1 < B) {
+                    fnmac_bc<j + 1>(d[j + 1], dj, dj);
+                    rows_from(I{}, std::integral_constant<int, j + 1>{}, std::integral_constant<int, (j + 3 < B ? j + 3 : B)>{}, dj);
+                    dpp_ready(d[j + 1], piv);
+                    fmac_bc<j + 1>(piv, d[j + 1], 1.0);
+                    rows_from(I{}, std::integral_constant<int, (j + 3 < B ? j + 3 : B)>{}, std::integral_constant<int, (j + 5 < B ? j + 5 : B)>{}, dj);
+                    const double y = __builtin_amdgcn_rsq(piv);
+                    rows_from(I{}, std::integral_constant<int, (j + 5 < B ? j + 5 : B)>{}, std::integral_constant<int, (j + 8 < B ? j + 8 : B)>{}, dj);
+                    const double e = fma(-piv * y, y, 1.0);
+                    rows_from(I{}, std::integral_constant<int, (j + 8 < B ? j + 8 : B)>{}, std::integral_constant<int, (j + 11 < B ? j + 11 : B)>{}, dj);
+                    di = piv > tol ? fma(y * e, fma(e, 0.375, 0.5), y) : 0.0;
+                    rows_from(I{}, std::integral_constant<int, (j + 11 < B ? j + 11 : B)>{}, std::integral_constant<int, B>{}, dj);
+                }
+            });
+#pragma unroll
+            for (int k = 0; k < B; ++k) pan[p & 1][row][k] = a[k];
+            float4* out = reinterpret_cast<float4*>(Rinv + row * kP + B * p);
+#pragma unroll
+            for (int k = 0; k < B; k += 4)
+                out[k / 4] = slot <= p ? make_float4((float)a[k], (float)a[k + 1], (float)a[k + 2], (float)a[k + 3])
+                                       : make_float4(0.f, 0.f, 0.f, 0.f);
+        } else if (p > 0) {
+#pragma unroll
+            for (int s = 0; s < kTiles; ++s) {
+                const int t = w + kTileWaves * s, K = t / NB + 1, r = t % NB;
+                if (K < NB && K > p && (r >= K || r < p)) apply(acc[s], p - 1, r, K);
             }
         }
-        __syncthreads();                                             // every wave has its copy of the diagonal block
-        if (factoring) {
+        __syncthreads();
+        if (w >= 0 && p + 1 < NB) {
 #pragma unroll
-            for (int j = 0; j < B; ++j) {
-                const double piv = lane_value(a[j], j);
-                const double di = piv > tol ? inv_sqrt(piv) : 0.0;
-                a[j] = lane == j ? piv * di : a[j] * di;             // diagonal rows above j: values nobody reads
+            for (int s = 0; s < kTiles; ++s) {
+                const int t = w + kTileWaves * s, K = t / NB + 1, r = t % NB;
+                if (K == p + 1) {
+                    apply(acc[s], p, r, K);
 #pragma unroll
-                for (int k = j + 1; k < B; ++k) a[k] = fma(-a[j], lane_value(a[j], k), a[k]);   // L[k][j] is in lane k
-                if (wv == 0 && lane == 0) dinv[j0 + j] = di;
-            }
-            if (ext < 0) {
-                if (wv == 0) {
-#pragma unroll
-                    for (int k = 0; k < B; ++k)
-                        if (k <= i) G[row * LD + j0 + k] = a[k];
+                    for (int v = 0; v < 4; ++v) raw[B * r + 4 * v + kk][c] = acc[s][v];
                 }
-            } else if (ext < B) {                                    // row c of L_pp^-T: X[j0 + k][j0 + c] for k > c
-#pragma unroll
-                for (int k = 0; k < B; ++k)
-                    if (k > ext) G[row * LD + j0 + k] = a[k];
-            } else if (live_row) {
-#pragma unroll
-                for (int k = 0; k < B; ++k) G[row * LD + j0 + k] = a[k];
-            }
-        } else if (p > 0 && wv >= kFactorWaves) {
-            // the columns behind the next one, which the previous panel has not reached yet: tile t of the triangle
-            const int m = NB - 1 - p, n_tiles = m * (m + 1) / 2;
-            for (int t = wv - kFactorWaves; t < n_tiles; t += NW - kFactorWaves) {
-                int ti = 0, rem = t;
-                while (rem > ti) {
-                    rem -= ti + 1;
-                    ++ti;
-                }
-                update_tile(p - 1, p + 1 + ti, p + 1 + rem);
             }
         }
         __syncthreads();
-    }
-    // X = L^-1.  X[k][c] (k > c) is kept at G[c][k]; X[c][c] = dinv[c].  The diagonal tiles T_I = L_II^-1 are there.
-    // Then block row I by tiles on the fp64 matrix cores:
-    //   S(I, C) = -sum_{K=C}^{I-1} L(I, K) X(K, C)   (X(K, C) sits transposed in the upper triangle, so both operands
-    //                                                 are read along rows of G; X(C, C) = T_C is lower triangular)
-    //   X(I, C) = T_I S(I, C)                         (register v of the result S is row 4 v + kk: exactly the lane's
-    //                                                 operand of contraction step v, so S never leaves the registers)
-    for (int I = 1; I < NB; ++I) {
-        const int i0 = B * I;
-        const int c = lane & 15, kk = lane >> 4;
-        for (int C = wv; C < I; C += NW) {                           // a wave per column tile
-            f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
-            for (int K = C; K < I; ++K) {
-#pragma unroll
-                for (int sx = 0; sx < 4; ++sx) {
-                    const int k = 4 * sx + kk;                       // row of X / column of L inside tile K
-                    const double av = -G[(i0 + c) * LD + B * K + k];
-                    double bv = G[(B * C + c) * LD + B * K + k];
-                    if (K == C) bv = k > c ? bv : (k == c ? dinv[B * C + c] : 0.0);
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
-                }
-            }
-            f64x4_t xt = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int sx = 0; sx < 4; ++sx) {
-                const int k = 4 * sx + kk;                           // T_I[c][k], kept at G[i0 + k][i0 + c] for k < c
-                const double tv = k < c ? G[(i0 + k) * LD + i0 + c] : (k == c ? dinv[i0 + c] : 0.0);
-                xt = __builtin_amdgcn_mfma_f64_16x16x4f64(tv, acc[sx], xt, 0, 0, 0);
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) G[(B * C + c) * LD + i0 + 4 * v + kk] = xt[v];
-        }
-        __syncthreads();
-    }
-    // Rinv = (L^-1)^T: Rinv[c][i] = X[i][c], zero for i < c.  Written once, in rows, after the loop: a store to
-    // global memory inside it would be waited for at every workgroup barrier.
-    for (int e = tid; e < kP * kP; e += NT) {
-        const int c = e >> 7, i = e & (kP - 1);
-        Rinv[e] = i > c ? (float)G[c * LD + i] : (i == c ? (float)dinv[c] : 0.f);
     }
 }
 
@@ -761,7 +732,6 @@ static hipError_t run_matrix_entropy(const T* X, int n_mat, int N, int D, int64_
     double* gsum = gpart + (size_t)(p.gram_slices > p.zgram_slices ? p.gram_slices : p.zgram_slices) * kP * kP;
     double* spart = reinterpret_cast<double*>(ws + p.spart_off);
     float* Rinv = reinterpret_cast<float*>(ws + p.rinv_off);
-    const size_t chol_lds = (size_t)kP * (kP + 1) * sizeof(double);
     const unsigned dp_blocks = (unsigned)(((int64_t)D * kP + 255) / 256);
     // bf16 inputs with 16-byte aligned rows take the MFMA products, everything else the fp32 ALUs
     // (rows at most 2^22 elements apart: those kernels address 256 rows with 32-bit byte offsets)
@@ -780,7 +750,7 @@ static hipError_t run_matrix_entropy(const T* X, int n_mat, int N, int D, int64_
     auto orth = [&]() {
         sub_gram64_kernel<0><<<dim3((unsigned)p.gram_slices), dim3(256), 0, s>>>(W, 0, kP, D, p.gram_rows, gpart, nullptr, nullptr, nullptr);
         sub_gram64_sum_kernel<<<dim3(kP * kP / 256), dim3(256), 0, s>>>(gpart, p.gram_slices, gsum);
-        sub_chol_kernel<<<dim3(1), dim3(kCholThreads), chol_lds, s>>>(gsum, Rinv);
+        sub_chol_kernel<<<dim3(1), dim3(kCholThreads), 0, s>>>(gsum, Rinv);
         apply_rinv();
     };
     float* Zpart = reinterpret_cast<float*>(ws + p.zpart_off);
@@ -881,9 +851,7 @@ hipError_t init_subspace_mfma_kernels();
 hipError_t init_subspace_kernels() {
     hipError_t e = init_subspace_mfma_kernels();
     if (e != hipSuccess) return e;
-    e = allow_dynamic_lds(reinterpret_cast<const void*>(sub_q_kernel), kQLdsBytes);
-    if (e != hipSuccess) return e;
-    return allow_dynamic_lds(reinterpret_cast<const void*>(sub_chol_kernel), (size_t)kP * (kP + 1) * sizeof(double));
+    return allow_dynamic_lds(reinterpret_cast<const void*>(sub_q_kernel), kQLdsBytes);
 }
 
 }  // namespace uncomp

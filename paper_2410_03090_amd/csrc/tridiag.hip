@@ -39,8 +39,6 @@
 #include "common.h"
 #include "device_utils.h"
 
-#include <type_traits>
-
 namespace uncomp {
 
 namespace {
@@ -107,26 +105,6 @@ __device__ __forceinline__ double block_sum(double v, double* red, int tid) {
 #pragma unroll
     for (int x = 1; x < kTriWaves; ++x) t += red[x];
     return t;
-}
-
-// acc +- rows[lane row's lane U] * m.  The DPP operand must not have been written by the two vector
-// instructions before (the compiler does not look into the statement): dpp_ready() stands between.
-template <int U>
-__device__ __forceinline__ void fmac_bc(double& acc, double rows, double m) {
-    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(rows), "v"(m), "n"(U));
-}
-template <int U>
-__device__ __forceinline__ void fnmac_bc(double& acc, double rows, double m) {
-    asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(rows), "v"(m), "n"(U));
-}
-__device__ __forceinline__ void dpp_ready(double& a, double& b) { asm volatile("s_nop 1" : "+v"(a), "+v"(b)); }
-
-template <int U, int END = 16, typename F>
-__device__ __forceinline__ void each16(F&& f) {
-    if constexpr (U < END) {
-        f(std::integral_constant<int, U>{});
-        each16<U + 1, END>(f);
-    }
 }
 
 // Number of eigenvalues of the tridiagonal matrix below x: sign changes along
