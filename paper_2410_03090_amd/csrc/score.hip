@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256) void score_vote_wave_kernel(
     constexpr int kRowBytes = row_bytes(DD), kPieces = DD / 8, kKs = DD / 32;
     constexpr int kRowThreads = 256 / (16 * NRB);                         // threads per row that fold its partial statistics
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ float2 folded[kRowThreads > 1 ? 16 * NRB : 1];
+    __shared__ float2 folded[2][kRowThreads > 1 ? 16 * NRB : 1];
     unsigned char* qs = smem;                                             // [16*NRB][kRowBytes]
     float* nls = reinterpret_cast<float*>(smem + 16 * NRB * kRowBytes);   // [16*NRB] minus lse (base 2)
     const int rg = blockIdx.x % n_rg, bc = blockIdx.x / n_rg;
@@ -283,28 +283,48 @@ __global__ __launch_bounds__(256) void score_vote_wave_kernel(
     if (stats == nullptr) {
         for (int r = tid; r < 16 * NRB; r += 256) nls[r] = r < R ? -lse[row0 + r] : 0.f;
     } else {
-        // few partials: every workgroup folds them for itself, which saves the launch of the merge kernel
-        constexpr int kLoads = 8;
+        // Few partials: every workgroup folds them for itself, which saves the launch of the merge kernel.  Every fourth
+        // partial in a chain of its own, the chains in order, as that kernel does it.
+        constexpr int kChains = 4 / kRowThreads;
         const int r = tid % (16 * NRB), q = tid / (16 * NRB);
-        float sum = 0.f, mx = -INFINITY;
+        float sum[kChains], mx[kChains];
+#pragma unroll
+        for (int x = 0; x < kChains; ++x) {
+            mx[x] = -INFINITY;
+            sum[x] = 0.f;
+        }
         if (r < R) {
             const float2* st = stats + ((int64_t)bh * n_parts * n_rg + rg) * R + r;
             const int64_t stride = (int64_t)R * n_rg;
-            for (int c = q; c < n_parts; c += kLoads * kRowThreads) {
-                float2 v[kLoads];
+            for (int c = 0; c < n_parts; c += 16) {
+                float2 v[4][kChains];
 #pragma unroll
-                for (int u = 0; u < kLoads; ++u) v[u] = st[min(c + u * kRowThreads, n_parts - 1) * stride];
+                for (int u = 0; u < 4; ++u)
 #pragma unroll
-                for (int u = 0; u < kLoads; ++u)
-                    if (c + u * kRowThreads < n_parts) lse_fold(mx, sum, v[u]);
+                    for (int x = 0; x < kChains; ++x) v[u][x] = st[min(c + 4 * u + q + kRowThreads * x, n_parts - 1) * stride];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int x = 0; x < kChains; ++x)
+                        if (c + 4 * u + q + kRowThreads * x < n_parts) lse_fold(mx[x], sum[x], v[u][x]);
             }
         }
-        if constexpr (kRowThreads > 1) {
-            if (q == 1) folded[r] = make_float2(mx, sum);
+        if constexpr (kRowThreads > 1) {                     // chains 1 and 3 come from the row's other thread
+            if (q == 1) {
+                folded[0][r] = make_float2(mx[0], sum[0]);
+                folded[1][r] = make_float2(mx[1], sum[1]);
+            }
             __syncthreads();
-            if (q == 0) lse_fold(mx, sum, folded[r]);
+            if (q == 0) {
+                lse_fold(mx[0], sum[0], folded[0][r]);
+                lse_fold(mx[0], sum[0], make_float2(mx[1], sum[1]));
+                lse_fold(mx[0], sum[0], folded[1][r]);
+            }
+        } else {
+#pragma unroll
+            for (int x = 1; x < kChains; ++x) lse_fold(mx[0], sum[0], make_float2(mx[x], sum[x]));
         }
-        if (q == 0) nls[r] = r < R ? -(mx + log2f(sum)) : 0.f;
+        if (q == 0) nls[r] = r < R ? -(mx[0] + log2f(sum[0])) : 0.f;
     }
     __syncthreads();
 
