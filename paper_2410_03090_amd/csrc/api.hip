@@ -30,6 +30,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 constexpr size_t kDefaultWorkspace = 64ull << 20;
 constexpr size_t kBudgetScratch = 4096 * sizeof(double);
+constexpr size_t kCounterBytes = kSplitHeads * sizeof(uint32_t);
 
 }  // namespace
 
@@ -55,13 +56,8 @@ uncomp_status uncomp_create(uncomp_ctx** ctx_out, int device, size_t workspace_b
     if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
     if (e == hipSuccess) {
         ctx->num_cu = prop.multiProcessorCount;
-        const size_t counter_bytes = kSplitHeads * sizeof(uint32_t);
-        e = hipMalloc(reinterpret_cast<void**>(&ctx->ws), ctx->ws_bytes + counter_bytes);
-        if (e == hipSuccess) {
-            ctx->counters = reinterpret_cast<uint32_t*>(ctx->ws + ctx->ws_bytes);
-            e = hipMemset(ctx->counters, 0, counter_bytes);
-            if (e == hipSuccess) e = hipDeviceSynchronize();     // the first call may come on any stream
-        }
+        e = hipMalloc(reinterpret_cast<void**>(&ctx->ws), ctx->ws_bytes + kCounterBytes);
+        if (e == hipSuccess) ctx->counters = reinterpret_cast<uint32_t*>(ctx->ws + ctx->ws_bytes);
     }
     // kernels with more than 64 KiB of dynamic LDS get their limit raised here, not in the hot calls
     if (e == hipSuccess) e = init_gram_kernels();
@@ -71,6 +67,9 @@ uncomp_status uncomp_create(uncomp_ctx** ctx_out, int device, size_t workspace_b
     if (e == hipSuccess) e = init_decode_kernels();
     if (e == hipSuccess) e = init_subspace_kernels();
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking);
+    // zero before the first call, which may come on any stream; cleared on a stream that waits for no other work
+    if (e == hipSuccess) e = hipMemsetAsync(ctx->counters, 0, kCounterBytes, ctx->side);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->side);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming);
     (void)hipSetDevice(prev);
