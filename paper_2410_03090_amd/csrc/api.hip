@@ -257,7 +257,7 @@ uncomp_status uncomp_assign_budgets(uncomp_ctx* ctx, const float* entropy, int n
     // in overlap mode the entropies are being produced on the side stream: follow them there
     hipStream_t bs = (ctx->overlap && ctx->side_pending) ? ctx->side : static_cast<hipStream_t>(stream);
     hipError_t e = launch_budgets(entropy, n_layer, n_batch, H, M, n_max, step, N, w, eps, delta_n, flags,
-                                  head_budget, head_group, layer_group, layer_tokens, ctx->ws,
+                                  head_budget, head_group, layer_group, layer_tokens,
                                   Env{bs, &ctx->prof, ctx->force_alu});
     if (e != hipSuccess) return hip_fail(ctx, e, "assign_budgets: launch");
     return UNCOMP_OK;

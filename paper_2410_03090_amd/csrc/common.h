@@ -116,7 +116,7 @@ hipError_t launch_tridiag_entropy(int n_mat, int N, int k_trunc, unsigned flags,
 hipError_t launch_budgets(const float* entropy, int L, int B, int H, int M, int n_max, int step,
                           int N, int w, float eps, int delta_n, unsigned flags,
                           int32_t* head_budget, int32_t* head_group, int32_t* layer_group,
-                          int32_t* layer_tokens, char* ws, const Env& env);
+                          int32_t* layer_tokens, const Env& env);
 // lse_nat: optional DEVICE [B*H*G*w] natural-log normalisers of the window rows; when given the
 // softmax-statistics pass is skipped.
 hipError_t launch_window_score(const void* Q, const void* K, uncomp_dtype dt, int B, int H, int G,

@@ -465,3 +465,15 @@ def test_score_normalisers_folded(ctx, H, G, N, w):
     K, V, Q = synth.gen_all(cfg, seed0=N + G)
     ref = O.window_score(to_f64(Q[0]), to_f64(K[0]), G=G, pool=7)
     np.testing.assert_allclose(ctx.window_score(Q[0].to(DEV), K[0].to(DEV), G=G, pool=7).cpu().numpy(), ref, rtol=2e-5)
+
+
+# Layer stages of more layers than a wave and than a workgroup takes at once, of more heads than a wave, against the oracle.
+@pytest.mark.parametrize("L,B,H", [(1, 1, 8), (63, 1, 8), (65, 3, 8), (130, 2, 40), (1500, 1, 4), (4096, 1, 2)])
+def test_budgets_many_layers(ctx, L, B, H):
+    g = torch.Generator().manual_seed(L)
+    ent = (3 + torch.rand(L, B, H, generator=g) + torch.cumsum(torch.randn(L, 1, 1, generator=g) * 0.02, 0)).float()
+    for flags in (0, 4):
+        got = ctx.assign_budgets(ent.to(DEV), H // 2 if H < 8 else 4, 640, 74, 100000, 32, 0.05, 64, flags=flags)
+        ref = O.assign_budgets(ent.numpy(), H // 2 if H < 8 else 4, 640, 74, 100000, 32, 0.05, 64, flags=flags)
+        for x, y in zip(got, ref):
+            assert np.array_equal(x.cpu().numpy(), y)
