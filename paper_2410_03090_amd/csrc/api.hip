@@ -107,7 +107,14 @@ size_t uncomp_workspace_bytes(int n_mat, int N, int D, int B, int H, int G, int 
     (void)D;
     // three regions that may be live at once in overlap mode: budgets | entropy | score
     size_t need = kBudgetScratch;
-    if (n_mat > 0 && N > 0) need += plan_entropy(n_mat, N).bytes;
+    if (n_mat > 0 && N > 0) {
+        size_t partials = plan_entropy(n_mat, N).bytes;
+        for (bool f32 : {false, true}) {
+            const size_t bytes = plan_entropy_chunks(n_mat, N, f32, 0).bytes;
+            partials = bytes > partials ? bytes : partials;
+        }
+        need += partials;
+    }
     if (B > 0 && H > 0 && G > 0 && N > 0 && w > 0 && w < N) need += plan_score(B, H, G, N, w).bytes;
     return need;
 }
@@ -207,16 +214,18 @@ uncomp_status uncomp_head_entropy(uncomp_ctx* ctx, const void* X, uncomp_dtype d
     if (ldx < D || (ldx & 7) || (mat_stride & 7) || mat_stride < 0 || !aligned16(X))
         return fail(ctx, UNCOMP_ERR_INVALID_ARG, "head_entropy: strides must be multiples of 8 elements, ldx >= D, X 16-byte aligned");
     if ((int64_t)n_mat * 64 > 0x7fffffffLL) return fail(ctx, UNCOMP_ERR_UNSUPPORTED, "head_entropy: too many matrices");
-    EntropyPlan p = plan_entropy(n_mat, N);
-    if (kBudgetScratch + p.bytes > ctx->ws_bytes)
+    const EntropyPlan least = plan_entropy(n_mat, N);
+    if (kBudgetScratch + least.bytes > ctx->ws_bytes)
         return fail(ctx, UNCOMP_ERR_WORKSPACE, "head_entropy: needs %zu workspace bytes, context has %zu",
-                    kBudgetScratch + p.bytes, ctx->ws_bytes);
+                    kBudgetScratch + least.bytes, ctx->ws_bytes);
+    const EntropyPlan p = plan_entropy_chunks(n_mat, N, dtype == UNCOMP_F32, ctx->ws_bytes - kBudgetScratch);
     ctx->key_range.ptr = nullptr;
     // an eigen stage of an earlier call may still be reading the Gram partials on the side stream
     uncomp_status js = uncomp_join(ctx, stream);
     if (js != UNCOMP_OK) return js;
     char* ws = ctx->ws + kBudgetScratch;
     ctx->score_ws_off = kBudgetScratch + p.bytes;
+    ctx->score_ws_least = kBudgetScratch + least.bytes;
     Env env{static_cast<hipStream_t>(stream), &ctx->prof, ctx->force_alu};
     hipError_t e = launch_gram(X, dtype, n_mat, N, mat_stride, ldx, p, ws, env, D);
     if (e != hipSuccess) return hip_fail(ctx, e, "head_entropy: gram launch");
@@ -282,10 +291,18 @@ uncomp_status uncomp_window_score(uncomp_ctx* ctx, const void* Qwin, const void*
     if ((int64_t)B * H * ((N + 255) / 256) > 0x7fffffffLL) return fail(ctx, UNCOMP_ERR_UNSUPPORTED, "window_score: problem too large");
     ScorePlan p = plan_score(B, H, G, N, w);
     // keep clear of the entropy region while side-stream work may still read it
-    const size_t off = ctx->side_pending ? ctx->score_ws_off : kBudgetScratch;
+    size_t off = ctx->side_pending ? ctx->score_ws_least : kBudgetScratch;
     if (off + p.bytes > ctx->ws_bytes)
         return fail(ctx, UNCOMP_ERR_WORKSPACE, "window_score: needs %zu workspace bytes, context has %zu",
                     off + p.bytes, ctx->ws_bytes);
+    if (ctx->side_pending) {
+        off = ctx->score_ws_off;
+        if (off + p.bytes > ctx->ws_bytes) {     // room for the fewest partials only: one after the other
+            uncomp_status js = uncomp_join(ctx, stream);
+            if (js != UNCOMP_OK) return js;
+            off = kBudgetScratch;
+        }
+    }
     ctx->key_range.ptr = nullptr;
     hipError_t e = launch_window_score(Qwin, K, dtype, B, H, G, N, w, pool, k_strides, p, ctx->ws + off, score_out,
                                        Env{static_cast<hipStream_t>(stream), &ctx->prof, ctx->force_alu}, lse_opt, D);

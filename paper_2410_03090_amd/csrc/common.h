@@ -38,6 +38,7 @@ struct uncomp_ctx {
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     size_t score_ws_off = 0;         // where the scoring workspace starts (after the entropy region)
+    size_t score_ws_least = 0;       // where it would start with the fewest Gram partials: what a context must have room for
     // Key ranges left in the workspace by the last uncomp_window_score, for the selection that follows it.
     // Cleared by every call that may overwrite that part of the workspace; the selection kernel checks the
     // range against every score anyway, so a range that does not belong to the scores costs time, not results.
@@ -63,7 +64,8 @@ struct EntropyPlan {
     size_t sum_off;      // float [n_mat][n_chunks][D]
     size_t bytes;
 };
-EntropyPlan plan_entropy(int n_mat, int N, size_t max_bytes = 0);
+EntropyPlan plan_entropy(int n_mat, int N, size_t max_bytes = 0);            // the least that a context must have room for
+EntropyPlan plan_entropy_chunks(int n_mat, int N, bool f32, size_t max_bytes);    // as many chunks as pay (max_bytes 0: no limit)
 
 struct ScorePlan {
     int R;               // query rows per KV head = G*w

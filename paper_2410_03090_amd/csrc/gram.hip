@@ -109,16 +109,8 @@ __global__ __launch_bounds__(512, 1) void gram_mfma_kernel(const bf16_bits* __re
                       sum_part + ((int64_t)m_idx * n_chunks + c) * kD);
 }
 
-EntropyPlan plan_entropy(int n_mat, int N, size_t max_bytes) {
+static EntropyPlan entropy_plan(int n_mat, int N, int nc, size_t max_bytes) {
     EntropyPlan p;
-    // Two workgroups per CU, one after the other (152 KB of LDS let one in), keep the chip even; fewer, longer
-    // chunks mean fewer 64 KiB partials to write and to add up again (128K workload: 8 chunks per matrix
-    // 1.54 ms, 2 chunks 1.46 ms), and chunks stay above 4096 tokens.  A byte limit (max_bytes > 0) lowers the chunk
-    // count until the partials fit; p.bytes still exceeds it if even one chunk per matrix does not.
-    int max_chunks = N / 4096 > 0 ? N / 4096 : 1;
-    int want = (512 + n_mat - 1) / (n_mat > 0 ? n_mat : 1);
-    int nc = want < 1 ? 1 : want;
-    if (nc > max_chunks) nc = max_chunks;
     for (;;) {
         int chunk = (N + nc - 1) / nc;
         chunk = (chunk + kGramTile - 1) / kGramTile * kGramTile;
@@ -133,6 +125,46 @@ EntropyPlan plan_entropy(int n_mat, int N, size_t max_bytes) {
         nc = n > 1 ? n - 1 : 1;
     }
     return p;
+}
+
+// Two workgroups per CU, chunks above 4096 tokens.  A byte limit (max_bytes > 0) lowers the chunk count until the partials
+// fit; p.bytes still exceeds it if even one chunk per matrix does not.
+static int least_chunks(int n_mat, int N) {
+    const int max_chunks = N / 4096 > 0 ? N / 4096 : 1, want = (512 + n_mat - 1) / (n_mat > 0 ? n_mat : 1);
+    return want > max_chunks ? max_chunks : want < 1 ? 1 : want;
+}
+EntropyPlan plan_entropy(int n_mat, int N, size_t max_bytes) { return entropy_plan(n_mat, N, least_chunks(n_mat, N), max_bytes); }
+
+// Chunks per matrix by a model of the launch (us): a CU takes one workgroup at a time (152 KB of LDS); a round of them takes
+// 5.6 ns a token and workgroup, or what their keys take at 5.9 TB/s, and 6 to start and to fold the waves; every chunk costs
+// the eigen stage 1.2.  Head entropies in us, chunks in brackets: 256 matrices of 8192 tokens 250 (2) and 237 (1), of 131072
+// tokens 1567 (2) and 1543 (1); 128 of 16384 252 (4) and 234 (2); 300 of 8192 361 (1) and 352 (2); 8 of 4096 152 (1) and 146 (4).
+// fp32 matrices go through the fp64 matrix cores, 27 ns a token: few of them take more chunks, 8 matrices of 1024 tokens
+// 156 (1) and 142 (4), 8 of 4096 242 (1) and 163 (8), 64 of 1024 179 (1) and 164 (4).
+EntropyPlan plan_entropy_chunks(int n_mat, int N, bool f32, size_t max_bytes) {
+    constexpr int kCus = 256;
+    int best = 1;
+    if (f32) {
+        best = least_chunks(n_mat, N);
+        const int few = min(min(kCus / n_mat, N / 256), 8);
+        if (few > best) best = few;
+    } else {
+        double best_cost = 0.0;
+        for (int nc = 1; nc <= 64 && (nc == 1 || nc <= N / 512); ++nc) {
+            const int chunk = ((N + nc - 1) / nc + kGramTile - 1) / kGramTile * kGramTile, n = (N + chunk - 1) / chunk;
+            const int64_t wgs = (int64_t)n_mat * n, rest = wgs % kCus;
+            auto round = [&](int64_t active) {
+                const double own = 0.0056 * chunk, keys = (double)active * chunk * 256.0 / 5.9e6;
+                return (own > keys ? own : keys) + 6.0;
+            };
+            const double cost = (double)(wgs / kCus) * round(kCus) + (rest > 0 ? round(rest) : 0.0) + 1.2 * n * ((n_mat + 511) / 512);
+            if (best_cost == 0.0 || cost < best_cost) {
+                best_cost = cost;
+                best = nc;
+            }
+        }
+    }
+    return entropy_plan(n_mat, N, best, max_bytes);
 }
 
 hipError_t launch_gram(const void* X, uncomp_dtype dt, int n_mat, int N, int64_t mat_stride,

@@ -278,16 +278,19 @@ __global__ __launch_bounds__(kTriThreads, 2) void tridiag_entropy_kernel(
             for (int u = 0; u < 16; ++u) a[j][s][u] = 0.0;
     for (int ch = 0; ch < n_chunks; ++ch) {
         const float* g = Gm + (int64_t)ch * (kD * kD) + 16 * q * kD + lane;
+        float t[2][2][16];                                       // a chunk's loads are all in flight
 #pragma unroll
         for (int j = JS0; j < 2; ++j)
 #pragma unroll
-            for (int s = JS0; s < 2; ++s) {                      // 16 independent loads in flight
-                float t[16];
+            for (int s = JS0; s < 2; ++s)
 #pragma unroll
-                for (int u = 0; u < 16; ++u) t[u] = g[(64 * (j - JS0) + u) * kD + 64 * (s - JS0)];
+                for (int u = 0; u < 16; ++u) t[j][s][u] = g[(64 * (j - JS0) + u) * kD + 64 * (s - JS0)];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) a[j][s][u] += (double)t[u];
-            }
+        for (int j = JS0; j < 2; ++j)
+#pragma unroll
+            for (int s = JS0; s < 2; ++s)
+#pragma unroll
+                for (int u = 0; u < 16; ++u) a[j][s][u] += (double)t[j][s][u];
     }
     {
         const double inv_tr = 1.0 / trace;

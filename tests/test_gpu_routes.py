@@ -467,6 +467,34 @@ def test_score_normalisers_folded(ctx, H, G, N, w):
     np.testing.assert_allclose(ctx.window_score(Q[0].to(DEV), K[0].to(DEV), G=G, pool=7).cpu().numpy(), ref, rtol=2e-5)
 
 
+# Chunks of the Gram sums: a context with room for the fewest partials only runs and agrees with a larger one to rounding
+# (fp32 partial sums in another split: 1e-6), also with the eigen stage beside the scoring kernels.
+@pytest.mark.parametrize("dtype,n_mat,N", [("f32", 8, 1024), ("f32", 3, 5000), ("bf16", 8, 4100), ("bf16", 24, 9000)])
+def test_entropy_chunks_and_small_workspace(ctx, dtype, n_mat, N):
+    from paper_2410_03090_amd import binding
+    cfg = synth.tiny_config(dtype=dtype, B=1, H=n_mat, G=2, N=N, w=32, rank_lo=2, rank_hi=48)
+    K, V, Q = synth.gen_all(cfg, seed0=N)
+    Kd, Qd = K[0].to(DEV), Q[0].to(DEV)
+    Href, _ = O.head_entropy(to_f64(K[0, 0]), k_trunc=32)
+    least = max(N // 4096, 1)
+    chunk = (-(-N // least) + 127) // 128 * 128
+    n = -(-N // chunk)
+    bytes_least = 32768 + n_mat * n * 128 * 128 * 4 + (n_mat * n * 128 * 4 + 255) // 256 * 256
+    score = binding.Context.workspace_bytes(0, N, 128, 1, n_mat, 2, 32) - 32768
+    want = ctx.window_score(Qd, Kd, 2, 7)
+    for size, overlap in ((bytes_least, False), (bytes_least + score, True), (binding.Context.workspace_bytes(n_mat, N, 128, 1, n_mat, 2, 32), True)):
+        c = binding.Context(0, size)
+        c.set_overlap(overlap)
+        H = c.head_entropy(Kd.view(n_mat, N, 128), k_trunc=32)
+        got = c.window_score(Qd, Kd, 2, 7) if overlap else want
+        c.join()
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(H.cpu().numpy(), Href, rtol=1e-5)
+        assert torch.equal(got, want)
+        c.close()
+    np.testing.assert_allclose(ctx.head_entropy(Kd.view(n_mat, N, 128), k_trunc=32).cpu().numpy(), Href, rtol=1e-5)
+
+
 # Layer stages of more layers than a wave and than a workgroup takes at once, of more heads than a wave, against the oracle.
 @pytest.mark.parametrize("L,B,H", [(1, 1, 8), (63, 1, 8), (65, 3, 8), (130, 2, 40), (1500, 1, 4), (4096, 1, 2)])
 def test_budgets_many_layers(ctx, L, B, H):
