@@ -159,9 +159,11 @@ uncomp_status uncomp_head_entropy(uncomp_ctx* ctx, const void* X, uncomp_dtype d
 /*
  * Truncated matrix entropy of wide token matrices (same definition as uncomp_head_entropy, for
  * D = 256 ... 16384 in multiples of 128: e.g. the hidden states H_m of Sec. 3.3.2, whose erank
- * the paper's layer analysis plots).  The D x D covariance is never formed: the k_trunc <= 128
+ * the paper's layer analysis plots).  The k_trunc <= 128
  * largest eigenvalues are taken as the Ritz values of a 128-dimensional subspace after n_iter
- * rounds of block power iteration (each round reads X twice).  Their error falls like
+ * rounds of block power iteration.  A round reads X twice, or, for bf16 matrices where that takes
+ * less time in all and the workspace has room, the covariance, formed once and kept to 17 bits an
+ * entry.  The error of the Ritz values falls like
  * (sigma_129 / sigma_k)^(2 n_iter): a few rounds when the spectrum drops before the 129th
  * eigenvalue, many when it is flat there.  For bf16 inputs the rounds multiply by factors rounded
  * to bf16 (the iterated block keeps 17 bits only in the last round and in the final projection):
@@ -170,7 +172,9 @@ uncomp_status uncomp_head_entropy(uncomp_ctx* ctx, const void* X, uncomp_dtype d
  * entropy_out [n_mat]; eig_out, if not NULL, receives
  * the 128 Ritz values of each matrix as shares of the full trace, descending ([n_mat][128]).
  * X as in uncomp_head_entropy (ldx >= D, strides multiples of 8 elements, 16-byte aligned).
- * Matrices are processed one after the other.  Workspace: uncomp_matrix_workspace_bytes(N, D).
+ * Matrices are processed one after the other.  Workspace: uncomp_matrix_workspace_bytes(N, D),
+ * which includes the covariance where 8 rounds over it are the faster ones (less without it is
+ * enough for the call).
  */
 size_t uncomp_matrix_workspace_bytes(int N, int D);
 uncomp_status uncomp_matrix_entropy(uncomp_ctx* ctx, const void* X, uncomp_dtype dtype,

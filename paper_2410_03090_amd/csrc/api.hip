@@ -390,9 +390,14 @@ HiddenPlan plan_hidden(int B, int H, int G, int N, int w) {
 }
 }  // namespace
 
+// rounds that the workspace for a wide matrix is meant for: with so many it holds the covariance where that is the faster way
+// (the call itself decides by its own rounds and by what the context has)
+constexpr int kUsualRounds = 8;
+
 size_t uncomp_matrix_workspace_bytes(int N, int D) {
     if (N <= 0 || D <= 0 || D % kD != 0) return 0;
-    return kBudgetScratch + plan_matrix(N, D).bytes;
+    const MatrixPlan p = plan_matrix(N, D);
+    return kBudgetScratch + (D >= 2 * kD && cov_pays(p, N, D, kUsualRounds) ? p.cov_total : p.bytes);
 }
 
 uncomp_status uncomp_matrix_entropy(uncomp_ctx* ctx, const void* X, uncomp_dtype dtype, int n_mat, int N, int D,
@@ -418,7 +423,7 @@ uncomp_status uncomp_matrix_entropy(uncomp_ctx* ctx, const void* X, uncomp_dtype
     uncomp_status js = uncomp_join(ctx, stream);
     if (js != UNCOMP_OK) return js;
     hipError_t e = launch_matrix_entropy(X, dtype, n_mat, N, D, mat_stride, ldx, k_trunc, flags, n_iter, p,
-                                         ctx->ws + kBudgetScratch, entropy_out, eig_out,
+                                         ctx->ws + kBudgetScratch, ctx->ws_bytes - kBudgetScratch, entropy_out, eig_out,
                                          Env{static_cast<hipStream_t>(stream), &ctx->prof, ctx->force_alu});
     if (e != hipSuccess) return hip_fail(ctx, e, "matrix_entropy: launch");
     return UNCOMP_OK;

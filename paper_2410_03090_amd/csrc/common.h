@@ -178,6 +178,15 @@ hipError_t launch_prepare_finish(int L, int H, int M, const double* erank_sum, c
                                  const Env& env);
 hipError_t launch_labels_to_budget(const int32_t* labels, int L, int B, int H, int n_max, int step, int N, int w,
                                    int32_t* head_budget, const Env& env);
+// Covariance of a wide bf16 matrix as two bf16 matrices, high parts and what they leave ([2D][D]); see covariance.hip.
+struct CovPlan {
+    int n_tiles, n_chunks, chunk;    // 256 x 256 tiles of the lower triangle, token chunks
+    size_t part_bytes, cov_bytes;
+    double cost_us;                  // estimate
+};
+CovPlan plan_cov(int N, int D);
+hipError_t launch_cov(const uint16_t* X, int64_t ldx, int N, int D, const double* s, const CovPlan& p, float* part, uint16_t* Cs,
+                      hipStream_t st);
 // Workspace of the wide-matrix entropy (one matrix at a time).
 struct MatrixPlan {
     int stat_chunks, stat_chunk;     // token chunks of the column statistics
@@ -190,18 +199,25 @@ struct MatrixPlan {
     EntropyPlan ep;                  // the 128-wide entropy path on the projected tokens
     size_t ep_off, statpart_off, s_off, trace_off, zsum_off, q_off, w_off, wpart_off, z_off, gpart_off, spart_off, rinv_off;
     size_t bytes;
+    // rounds over the covariance instead of the tokens: C and its partials behind the rest
+    CovPlan cov;
+    int c_splits;                    // split of the sum over d in C Q
+    size_t cov_off, cov_part_off, cov_total;     // cov_total: workspace of this route
 };
 MatrixPlan plan_matrix(int N, int D);
+bool cov_pays(const MatrixPlan& p, int N, int D, int n_iter);
 hipError_t launch_xtz_mfma(const uint16_t* X, int64_t ldx, int N, int D, const uint16_t* Zt, int t_chunk, int n_tchunks,
                            float* Wpart, hipStream_t s);
 hipError_t launch_xq_mfma(const uint16_t* X, int64_t ldx, int N, int D, const uint16_t* Qt_hi, const uint16_t* Qt_lo,
                           int n_split, float* Zpart, float* Z, hipStream_t s, bool precise, bool want_zt, uint16_t* Zt,
                           const double* zshare, int n_share, double* zsum, bool* zsum_written);
+hipError_t launch_cq_mfma(const uint16_t* Cs, int D, const uint16_t* Qt_hi, const uint16_t* Qt_lo, int n_split, float* Wpart,
+                          bool precise, hipStream_t s, int* n_parts);
 hipError_t launch_gram_f32_mfma(const float* X, int n_mat, int N, int64_t mat_stride, int64_t ldx, int n_chunks, int chunk,
                                 float* gram_part, float* sum_part, hipStream_t s);
 hipError_t launch_matrix_entropy(const void* X, uncomp_dtype dt, int n_mat, int N, int D, int64_t mat_stride,
                                  int64_t ldx, int k_trunc, unsigned flags, int n_iter, const MatrixPlan& p, char* ws,
-                                 float* entropy_out, float* eig_out, const Env& env);
+                                 size_t ws_bytes, float* entropy_out, float* eig_out, const Env& env);
 // Workspace of the two-kernel step of bf16 caches.
 struct DecodePlan {
     int GT;              // query heads per KV head rounded up to 4, 8 or 16

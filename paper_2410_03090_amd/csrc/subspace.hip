@@ -1,17 +1,18 @@
 // Truncated matrix entropy of wide token matrices (Sec. 3.1 Eq. 1, Lemma 2; Sec. 3.2 Eq. 5-6 for
-// D = 256 ... 8192, e.g. the hidden states H_m of Sec. 3.3.2) without ever forming the D x D
-// covariance: only its k largest eigenvalues enter Eq. 5, and those are the Ritz values of a
+// D = 256 ... 8192, e.g. the hidden states H_m of Sec. 3.3.2) without the eigenvalues of the whole
+// D x D covariance: only the k largest enter Eq. 5, and those are the Ritz values of a
 // 128-dimensional subspace that block power iteration drives onto the dominant eigenvectors.
 //
-//   x_bar = mean token, C = sum_t (x_t - x_bar)(x_t - x_bar)^T            (never stored)
+//   x_bar = mean token, C = sum_t (x_t - x_bar)(x_t - x_bar)^T
 //   Q_0   = fixed pseudo-random D x 128 block
 //   repeat:  Z = X Q  (N x 128),  W = C Q = X^T Z - s (s^T Q)/N  (D x 128),  Q = orth(W)
 //   end:     Z = X Q;  the centred covariance of the N projected tokens z_t is Q^T C Q, whose
 //            eigenvalues (the ordinary 128-wide entropy path) are the Ritz values; Eq. 5 without
 //            renormalisation divides them by trace(C), which one pass over X provides.
 //
-// Every iteration reads X twice (HBM-bound: 2 N D e bytes) and costs 4 N D 128 flops; forming C
-// would cost 2 N D^2.  orth() is a Cholesky QR with the 128 x 128 Gram of W accumulated in fp64;
+// An iteration over the tokens reads X twice (HBM-bound: 2 N D e bytes) and costs 4 N D 128 flops.
+// Forming C (covariance.hip, bf16 matrices) costs N D^2 once, on the matrix cores, after which an
+// iteration reads 4 D^2 bytes: cov_pays() tells which is less time.  orth() is a Cholesky QR with the 128 x 128 Gram of W accumulated in fp64;
 // a pivot that vanishes (rank below 128) retires its column.  Convergence of the k-th value goes
 // with (lambda_129 / lambda_k)^(2 iterations): fast when the spectrum falls off before the 129th
 // eigenvalue, as it does for the matrices the method looks at (that fall-off is the paper's point).
@@ -711,12 +712,29 @@ MatrixPlan plan_matrix(int N, int D) {
     p.zpart_off = take(zs > 1 ? (size_t)zs * N * kP * sizeof(float) : 0);
     p.zsplit_off = take((((size_t)N + 127) / 128 * 128) * kP * sizeof(bf16_bits));      // Z^T rounded to bf16
     p.bytes = off;
+    p.cov = plan_cov(N, D);
+    p.c_splits = 256 * 256 / (2 * D);                    // one workgroup per CU, at least 128 features each
+    if (p.c_splits > D / 128) p.c_splits = D / 128;
+    if (p.c_splits < 1) p.c_splits = 1;
+    p.cov_off = take(p.cov.cov_bytes);
+    const size_t c_part = (size_t)p.c_splits * 2 * D * kP * sizeof(float);      // partials of C Q, over those of C
+    p.cov_part_off = take(p.cov.part_bytes > c_part ? p.cov.part_bytes : c_part);
+    p.cov_total = off;
     return p;
+}
+
+// Whether C pays.  A round over the tokens reads X twice and writes Z in between, a round over C reads C once.  Their difference
+// (us): measured 14 at 2048 tokens of 256 features, 15 at 4096 of 1024, 26 at 8192 of 4096, 130 at 32768 of 4096, 435 at 131072 of
+// 4096; C itself 20, 29, 188, 564 and 2018.  Eight rounds at 8192 x 4096 are the line: 1170 us in all over X, 1148 over C;
+// 131072 x 4096: 5049 and 3589, 131072 x 1024: 2682 and 1103; at 65536 x 8192 X is the better one (5442 and 6514).
+bool cov_pays(const MatrixPlan& p, int N, int D, int n_iter) {
+    const double gain = 12.0 + N * (3e-4 + 8e-7 * D) - 1e-6 * D * D;
+    return p.cov.cost_us < 0.95 * n_iter * gain;
 }
 
 template <typename T>
 static hipError_t run_matrix_entropy(const T* X, int n_mat, int N, int D, int64_t mat_stride, int64_t ldx,
-                                     int k_trunc, unsigned flags, int n_iter, const MatrixPlan& p, char* ws,
+                                     int k_trunc, unsigned flags, int n_iter, const MatrixPlan& p, char* ws, size_t ws_bytes,
                                      float* entropy_out, float* eig_out, const Env& env) {
     hipStream_t s = env.s;
     const bool center = (flags & UNCOMP_CENTER) != 0;
@@ -739,6 +757,9 @@ static hipError_t run_matrix_entropy(const T* X, int n_mat, int N, int D, int64_
     if constexpr (sizeof(T) == 2)
         mfma = !env.force_alu && (ldx % 8) == 0 && (mat_stride % 8) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0 &&
                ldx <= ((int64_t)1 << 22);
+    const bool use_cov = mfma && p.cov_total <= ws_bytes && cov_pays(p, N, D, n_iter);
+    bf16_bits* Cs = reinterpret_cast<bf16_bits*>(ws + p.cov_off);
+    float* cov_part = reinterpret_cast<float*>(ws + p.cov_part_off);
     bf16_bits* Qt_hi = reinterpret_cast<bf16_bits*>(ws + p.qt_off);
     bf16_bits* Qt_lo = Qt_hi + (size_t)kP * D;
     auto apply_rinv = [&]() {
@@ -786,19 +807,33 @@ static hipError_t run_matrix_entropy(const T* X, int n_mat, int N, int D, int64_
                                                                                           trace + 2);
         sub_trace_kernel<<<dim3(1), dim3(64), 0, s>>>(trace + 2, (D + 255) / 256, trace);
         env.end();
+        if constexpr (sizeof(T) == 2) {
+            if (use_cov) {
+                env.begin("matrix_covariance");
+                hipError_t e = launch_cov(Xm, ldx, N, D, center ? sv : nullptr, p.cov, cov_part, Cs, s);
+                if (e != hipSuccess) return e;
+                env.end();
+            }
+        }
         env.begin("matrix_subspace");
         sub_start_kernel<<<dim3(dp_blocks), dim3(256), 0, s>>>(W, D, Rinv);
         apply_rinv();
         for (int it = 0; it < n_iter; ++it) {
             const bool precise = it >= first_precise;
-            project(Xm, precise, true);
-            if (center && !zsum_ready) {
-                sub_zsum_kernel<<<dim3(1), dim3(1024), 0, s>>>(zsum + kP, D / kQRows, zsum);
-            }
             int w_parts = p.w_chunks;
             bool done = false;
+            if (use_cov) {
+                hipError_t e = launch_cq_mfma(Cs, D, Qt_hi, Qt_lo, p.c_splits, cov_part, precise, s, &w_parts);
+                if (e != hipSuccess) return e;
+                done = true;
+            } else {
+                project(Xm, precise, true);
+                if (center && !zsum_ready) {
+                    sub_zsum_kernel<<<dim3(1), dim3(1024), 0, s>>>(zsum + kP, D / kQRows, zsum);
+                }
+            }
             if constexpr (sizeof(T) == 2) {
-                if (mfma) {
+                if (mfma && !done) {
                     hipError_t e = launch_xtz_mfma(Xm, ldx, N, D, Zt, p.t_chunk, p.t_chunks, Wpart, s);
                     if (e != hipSuccess) return e;
                     w_parts = p.t_chunks;
@@ -808,8 +843,8 @@ static hipError_t run_matrix_entropy(const T* X, int n_mat, int N, int D, int64_
             if (!done)
                 sub_gemm_kernel<T, true><<<dim3((unsigned)((D + 63) / 64), (unsigned)p.w_chunks), dim3(256), 0, s>>>(
                     Xm, ldx, Z, D, N, p.w_chunk, Wpart);
-            sub_reduce_kernel<<<dim3(dp_blocks), dim3(256), 0, s>>>(Wpart, w_parts, D, center ? sv : nullptr, zsum,
-                                                                    1.0 / (double)N, W);
+            sub_reduce_kernel<<<dim3(dp_blocks), dim3(256), 0, s>>>(use_cov ? cov_part : Wpart, w_parts, D,
+                                                                    center && !use_cov ? sv : nullptr, zsum, 1.0 / (double)N, W);
             orth();
             if (it == n_iter - 1) {          // once more: the last Q is orthonormal to fp32 rounding
                 hipError_t e = hipMemcpyAsync(W, Q, (size_t)D * kP * sizeof(float), hipMemcpyDeviceToDevice, s);
@@ -838,11 +873,11 @@ static hipError_t run_matrix_entropy(const T* X, int n_mat, int N, int D, int64_
 
 hipError_t launch_matrix_entropy(const void* X, uncomp_dtype dt, int n_mat, int N, int D, int64_t mat_stride,
                                  int64_t ldx, int k_trunc, unsigned flags, int n_iter, const MatrixPlan& p, char* ws,
-                                 float* entropy_out, float* eig_out, const Env& env) {
+                                 size_t ws_bytes, float* entropy_out, float* eig_out, const Env& env) {
     if (dt == UNCOMP_BF16)
         return run_matrix_entropy(static_cast<const bf16_bits*>(X), n_mat, N, D, mat_stride, ldx, k_trunc, flags, n_iter,
-                                  p, ws, entropy_out, eig_out, env);
-    return run_matrix_entropy(static_cast<const float*>(X), n_mat, N, D, mat_stride, ldx, k_trunc, flags, n_iter, p, ws,
+                                  p, ws, ws_bytes, entropy_out, eig_out, env);
+    return run_matrix_entropy(static_cast<const float*>(X), n_mat, N, D, mat_stride, ldx, k_trunc, flags, n_iter, p, ws, ws_bytes,
                               entropy_out, eig_out, env);
 }
 

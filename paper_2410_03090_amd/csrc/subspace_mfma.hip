@@ -439,6 +439,20 @@ hipError_t launch_xq_mfma(const bf16_bits* X, int64_t ldx, int N, int D, const b
     return hipGetLastError();
 }
 
+// Wpart[part][D][128], *n_parts of them, whose sum is C Q: the rows of Cs [2D][D] are the high parts of C, then the low parts.
+hipError_t launch_cq_mfma(const bf16_bits* Cs, int D, const bf16_bits* Qt_hi, const bf16_bits* Qt_lo, int n_split, float* Wpart,
+                          bool precise, hipStream_t s, int* n_parts) {
+    const int k_chunk = ((D + n_split - 1) / n_split + kQStep - 1) / kQStep * kQStep;
+    const int splits = (D + k_chunk - 1) / k_chunk;
+    const dim3 grid((unsigned)(2 * D / 256), (unsigned)splits);
+    if (precise)
+        sub_xq_mfma_kernel<true, false><<<grid, dim3(256), xq_lds_bytes<true>(), s>>>(Cs, D, Qt_hi, Qt_lo, 2 * D, D, k_chunk, Wpart, nullptr, 0);
+    else
+        sub_xq_mfma_kernel<false, false><<<grid, dim3(256), xq_lds_bytes<false>(), s>>>(Cs, D, Qt_hi, Qt_lo, 2 * D, D, k_chunk, Wpart, nullptr, 0);
+    *n_parts = 2 * splits;
+    return hipGetLastError();
+}
+
 // Wpart[tc][D][128] = partial X^T bf16(Z) over token chunks (t_chunk a multiple of 128); Zt: Z^T rounded to bf16,
 // [128][n_pad] with n_pad = N rounded up to 128.
 hipError_t launch_xtz_mfma(const bf16_bits* X, int64_t ldx, int N, int D, const bf16_bits* Zt, int t_chunk, int n_tchunks,

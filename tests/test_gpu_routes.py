@@ -505,3 +505,34 @@ def test_budgets_many_layers(ctx, L, B, H):
         ref = O.assign_budgets(ent.numpy(), H // 2 if H < 8 else 4, 640, 74, 100000, 32, 0.05, 64, flags=flags)
         for x, y in zip(got, ref):
             assert np.array_equal(x.cpu().numpy(), y)
+
+
+# Wide bf16 matrices whose rounds run over the covariance (a tile of 256 features a workgroup, 32 tokens a step): token counts
+# below a step, with 1 and 31 tokens behind whole steps, several chunks; half and one and a half tiles of features; rows further
+# apart than their length; two matrices; with and without the mean.  A context without room for the covariance goes over the tokens.
+@pytest.mark.parametrize("N,D,pad", [(20, 256, 0), (33, 384, 8), (700, 640, 0), (2079, 256, 24), (5001, 896, 0), (20000, 512, 8)])
+def test_matrix_rounds_over_the_covariance(N, D, pad):
+    from paper_2410_03090_amd import binding
+    g = torch.Generator().manual_seed(N)
+    r = 40
+    X = torch.randn(2, N, r, generator=g) @ (torch.randn(r, D, generator=g) * torch.linspace(1.0, 0.05, r)[:, None]) / r
+    X = X + 0.01 * torch.randn(2, N, D, generator=g) + 0.2 * torch.randn(D, generator=g)
+    X = torch.cat([X, torch.full((2, N, pad), 3.0)], dim=2).to(torch.bfloat16)
+    Xd = X.to(DEV)[:, :, :D]
+    full = binding.Context.matrix_workspace_bytes(N, D)
+    room, tight = binding.Context(0, full), binding.Context(0, full - 4 * D * D)
+    try:
+        for flags in (O.DEFAULT_FLAGS, O.DEFAULT_FLAGS & ~O.FLAG_CENTER):
+            Href, eref = O.head_entropy(to_f64(X[:, :, :D]), k_trunc=32, flags=flags)
+            for c, over in ((room, True), (tight, False)):
+                c.profile(True)
+                H, eig = c.matrix_entropy(Xd, k_trunc=32, n_iter=12, flags=flags, want_eig=True)
+                torch.cuda.synchronize()
+                assert ("matrix_covariance" in [name for name, _ in c.profile_read()]) == over
+                c.profile(False)
+                # the final values come from the tokens on either way: the tolerances of the other tests of this call
+                np.testing.assert_allclose(H.cpu().numpy(), Href, rtol=1e-4)
+                np.testing.assert_allclose(eig.cpu().numpy()[:, :32], eref[:, :32], rtol=0, atol=2e-5)
+    finally:
+        room.close()
+        tight.close()
