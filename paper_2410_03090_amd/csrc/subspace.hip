@@ -213,24 +213,26 @@ __global__ __launch_bounds__(256) void sub_gemm_kernel(const T* __restrict__ A, 
     }
 }
 
-// Q = W Rinv for 32 rows of W per workgroup (fp32 ALUs, a thread owns 2 rows x 8 columns), together with what the next
-// round needs of Q besides: its transposed bf16 halves Qt_hi / Qt_lo
+// Q = W Rinv for 32 rows of W per workgroup (fp32 matrix instructions), together with what the next round needs of Q besides:
+// its transposed bf16 halves Qt_hi / Qt_lo
 // [128][D] (the operand that the MFMA version of Z = X Q streams; skipped when Qt_hi is null) and, when centring
 // (s not null), this row block's share of s^T Q in fp64: zpart[block][128].  D is a multiple of 128.
-// Bound by latency: Rinv goes to LDS whole, all of it in flight at once (11 us at D = 4096; 14 with sixteen rows
-// at a time).
+// Bound by latency: Rinv goes to LDS whole, all of it in flight at once.  Rinv is upper triangular: a wave takes columns 16 w and
+// on and the mirrored ones of the other end, and of the sum only the terms that are not zero.  6.6 us at D = 4096 (12.5 with the
+// products on the fp32 ALUs, three LDS reads to sixteen of them; 14 with Rinv in pieces of sixteen rows).
 constexpr int kQRows = 32;
-constexpr size_t kQLdsBytes = (size_t)(kP * kP + kQRows * (kP + 4)) * sizeof(float);
+constexpr int kRsLd = kP + 16;           // floats per row of Rinv in LDS: the four rows of an operand start 16 banks apart
+constexpr size_t kQLdsBytes = (size_t)(kP * kRsLd + kQRows * (kP + 4)) * sizeof(float);
 __global__ __launch_bounds__(256) void sub_q_kernel(const float* __restrict__ W, const float* __restrict__ Rinv, int D,
                                                     const double* __restrict__ s, float* __restrict__ Q,
                                                     uint16_t* __restrict__ Qt_hi, uint16_t* __restrict__ Qt_lo,
                                                     double* __restrict__ zpart) {
     extern __shared__ __align__(16) float qlds[];
-    float(*Rs)[kP] = reinterpret_cast<float(*)[kP]>(qlds);
-    float(*Ws)[kP + 4] = reinterpret_cast<float(*)[kP + 4]>(qlds + kP * kP);
+    float(*Rs)[kRsLd] = reinterpret_cast<float(*)[kRsLd]>(qlds);
+    float(*Ws)[kP + 4] = reinterpret_cast<float(*)[kP + 4]>(qlds + kP * kRsLd);
     float(*Qs)[kP + 1] = reinterpret_cast<float(*)[kP + 1]>(qlds);   // over Rs, once that has been read
     const int d0 = blockIdx.x * kQRows;
-    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, c = lane & 15, kk = lane >> 4;
     {
         float4 wr[4], rr[16];
 #pragma unroll
@@ -240,35 +242,37 @@ __global__ __launch_bounds__(256) void sub_q_kernel(const float* __restrict__ W,
 #pragma unroll
         for (int e = 0; e < 4; ++e) *reinterpret_cast<float4*>(&Ws[(tid + 256 * e) >> 5][4 * (tid & 31)]) = wr[e];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) *reinterpret_cast<float4*>(qlds + 4 * (tid + 256 * e)) = rr[e];
+        for (int e = 0; e < 16; ++e) *reinterpret_cast<float4*>(&Rs[(tid + 256 * e) >> 5][4 * (tid & 31)]) = rr[e];
     }
     __syncthreads();
-    float acc[2][8];
+    const int J[2] = {7 - wv, wv};                                   // blocks of sixteen columns, the longer sum first
+    f32x4_t acc[2][2];                                               // [column block][row block]
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int b = 0; b < 2; ++b) acc[b][0] = acc[b][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = 0.f;
-#pragma unroll 8
-    for (int k = 0; k < kP; ++k) {
-        const float a0 = Ws[2 * ty][k], a1 = Ws[2 * ty + 1][k];
-        const float4 b0 = *reinterpret_cast<const float4*>(&Rs[k][8 * tx]);
-        const float4 b1 = *reinterpret_cast<const float4*>(&Rs[k][8 * tx + 4]);
-        const float bv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+    for (int b = 0; b < 2; ++b) {
+        const int n_k = 16 * (J[b] + 1);
+        for (int k0 = 0; k0 < n_k; k0 += 16) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            acc[0][j] = fmaf(a0, bv[j], acc[0][j]);
-            acc[1][j] = fmaf(a1, bv[j], acc[1][j]);
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + 4 * u + kk;
+                const float r = Rs[k][16 * J[b] + c];
+                acc[b][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(Ws[c][k], r, acc[b][0], 0, 0, 0);
+                acc[b][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(Ws[16 + c][k], r, acc[b][1], 0, 0, 0);
+            }
         }
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        float* o = Q + (int64_t)(d0 + 2 * ty + i) * kP + 8 * tx;
-        *reinterpret_cast<float4*>(o) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
-        *reinterpret_cast<float4*>(o + 4) = make_float4(acc[i][4], acc[i][5], acc[i][6], acc[i][7]);
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) Qs[2 * ty + i][8 * tx + j] = acc[i][j];
-    }
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = 16 * i + 4 * kk + v, col = 16 * J[b] + c;
+                Q[(int64_t)(d0 + r) * kP + col] = acc[b][i][v];
+                Qs[r][col] = acc[b][i][v];
+            }
     __syncthreads();
     if (Qt_hi != nullptr) {
         // thread = (column, half of the 32 rows): 16 consecutive d of one column = 32 bytes per bf16 half
@@ -449,17 +453,19 @@ hipError_t launch_gram_f32_mfma(const float* X, int n_mat, int N, int64_t mat_st
     return hipGetLastError();
 }
 
-// gsum = sum of the slices (fixed order); four loads in flight per thread.
+// gsum = sum of the slices (fixed order); sixteen loads in flight per thread (64 slices: 4.6 us; 7.2 with four).
 __global__ __launch_bounds__(256) void sub_gram64_sum_kernel(const double* __restrict__ gpart, int n_slices,
                                                              double* __restrict__ gsum) {
     const int e = blockIdx.x * 256 + threadIdx.x;
     const double* g = gpart + e;
     double a = 0.0;
     int sl = 0;
-    for (; sl + 3 < n_slices; sl += 4) {
-        const double v0 = g[(int64_t)sl * kP * kP], v1 = g[(int64_t)(sl + 1) * kP * kP];
-        const double v2 = g[(int64_t)(sl + 2) * kP * kP], v3 = g[(int64_t)(sl + 3) * kP * kP];
-        a = (((a + v0) + v1) + v2) + v3;
+    for (; sl + 15 < n_slices; sl += 16) {
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = g[(int64_t)(sl + u) * kP * kP];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) a += v[u];
     }
     for (; sl < n_slices; ++sl) a += g[(int64_t)sl * kP * kP];
     gsum[e] = a;
@@ -665,7 +671,7 @@ MatrixPlan plan_matrix(int N, int D) {
     if (kc < 1) kc = 1;
     p.w_chunk = ((N + kc - 1) / kc + 15) / 16 * 16;
     p.w_chunks = (N + p.w_chunk - 1) / p.w_chunk;
-    // Gram of W: 64-row slices (one staged tile per workgroup: 14 + 7 us against 20 + 5 with 128 rows at D = 4096); Gram of the projected tokens: one workgroup per CU at most, whole 64-row tiles each
+    // Gram of W: 64-row slices (one staged tile per workgroup); Gram of the projected tokens: one workgroup per CU at most, whole 64-row tiles each
     p.gram_rows = kGramRows;
     p.gram_slices = (D + p.gram_rows - 1) / p.gram_rows;
     p.zgram_rows = ((N + 255) / 256 + kGramRows - 1) / kGramRows * kGramRows;
@@ -769,7 +775,11 @@ static hipError_t run_matrix_entropy(const T* X, int n_mat, int N, int D, int64_
     // Q = orth(W): Cholesky QR with the Gram in fp64; the last kernel also leaves the bf16 halves of Q^T and the
     // shares of s^T Q for the round that follows
     auto orth = [&]() {
-        sub_gram64_kernel<0><<<dim3((unsigned)p.gram_slices), dim3(256), 0, s>>>(W, 0, kP, D, p.gram_rows, gpart, nullptr, nullptr, nullptr);
+        // a slice's tiles over as many workgroups as leave the launch under two per CU: D = 4096, 64 slices, 15 us with all
+        // of a slice's tiles in one workgroup, 7.0 with a third; the sums are the same
+        auto gram = p.gram_slices * 9 <= 512 ? sub_gram64_kernel<0, 1> : (p.gram_slices * 3 <= 512 ? sub_gram64_kernel<0, 3> : sub_gram64_kernel<0>);
+        const unsigned split = p.gram_slices * 9 <= 512 ? 9u : (p.gram_slices * 3 <= 512 ? 3u : 1u);
+        gram<<<dim3((unsigned)p.gram_slices, 1, split), dim3(256), 0, s>>>(W, 0, kP, D, p.gram_rows, gpart, nullptr, nullptr, nullptr);
         sub_gram64_sum_kernel<<<dim3(kP * kP / 256), dim3(256), 0, s>>>(gpart, p.gram_slices, gsum);
         sub_chol_kernel<<<dim3(1), dim3(kCholThreads), 0, s>>>(gsum, Rinv);
         apply_rinv();
