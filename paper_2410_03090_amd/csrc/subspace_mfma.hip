@@ -45,7 +45,9 @@ constexpr size_t xq_lds_bytes() {
 // ZT: the result goes out as what the X^T Z kernel streams, Z^T rounded to bf16 (Zt [128][n_pad] with zeros for
 // the tokens from N to n_pad), instead of as fp32 rows: the rounds of the iteration need nothing else of Z,
 // which saves writing it as fp32 and reading it back to round it.
-template <bool LO, bool ZT>
+// RB: 16-row blocks per wave.  Where the sum over d is split, launches are short and two blocks (128 rows per workgroup, two
+// workgroups per CU) are better: eight rounds at 512 x 4096 855 -> 793 us, at 8192 x 4096 1054 -> 1033, at 4000 x 8192 1254 -> 1166.
+template <bool LO, bool ZT, int RB = 4>
 __global__ __launch_bounds__(256) void sub_xq_mfma_kernel(const bf16_bits* __restrict__ X, int64_t ldx,
                                                           const bf16_bits* __restrict__ Qt_hi,
                                                           const bf16_bits* __restrict__ Qt_lo, int N, int D,
@@ -55,28 +57,29 @@ __global__ __launch_bounds__(256) void sub_xq_mfma_kernel(const bf16_bits* __res
     constexpr int kHalf = kP * kQtRow, kBuf = (LO ? 2 : 1) * kHalf;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int n = lane & 15, kq = lane >> 4;
-    const int row0 = blockIdx.x * 256 + wv * 64;
+    static_assert(RB == 4 || !ZT, "the transposed write-out packs 64 rows per wave");
+    const int row0 = blockIdx.x * (64 * RB) + wv * (16 * RB);
     const int kc = blockIdx.y;
     const int k_begin = kc * k_chunk, k_end = min(D, k_begin + k_chunk);
     const int n_steps = (k_end - k_begin) / kQStep;
-    f32x4_t acc[4][8];
+    f32x4_t acc[RB][8];
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int cb = 0; cb < 8; ++cb) acc[rb][cb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     // staging: 128 columns x 8 pieces of 8 d per half: four 16-byte loads per thread and half
     const int s_col0 = tid >> 3, s_piece = tid & 7;                    // columns s_col0 + 32 i
     uint4 sh0, sh1, sh2, sh3, sl0, sl1, sl2, sl3;                    // (named: an array here ends up in scratch)
-    uint4 a[2][2][4];                                                // X rows: [set][32-d half of the step][row block]
+    uint4 a[2][2][RB];                                               // X rows: [set][32-d half of the step][row block]
     // rows past the end re-read the last row (clamped, never predicated); their results are not stored
     // addresses = a base that is uniform over the workgroup + a 32-bit byte offset per lane (the launcher
     // checks that 256 rows of X and all of Q^T span less than 4 GiB)
-    const char* xwg = reinterpret_cast<const char*>(X + (int64_t)blockIdx.x * 256 * ldx + k_begin);
-    uint32_t xoff[4];
+    const char* xwg = reinterpret_cast<const char*>(X + (int64_t)blockIdx.x * (64 * RB) * ldx + k_begin);
+    uint32_t xoff[RB];
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
-        xoff[rb] = (uint32_t)(min(row0 + 16 * rb + n, N - 1) - blockIdx.x * 256) * (uint32_t)(ldx * 2) + 16u * kq;
+    for (int rb = 0; rb < RB; ++rb)
+        xoff[rb] = (uint32_t)(min(row0 + 16 * rb + n, N - 1) - blockIdx.x * (64 * RB)) * (uint32_t)(ldx * 2) + 16u * kq;
     const char* qwg = reinterpret_cast<const char*>(Qt_hi + k_begin);
     const int64_t lo_bytes = reinterpret_cast<const char*>(Qt_lo) - reinterpret_cast<const char*>(Qt_hi);
     const uint32_t qoff = ((uint32_t)s_col0 * (uint32_t)D + 8u * s_piece) * 2u;
@@ -118,7 +121,7 @@ __global__ __launch_bounds__(256) void sub_xq_mfma_kernel(const bf16_bits* __res
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int rb = 0; rb < 4; ++rb) a[S][h][rb] = *reinterpret_cast<const uint4*>(xs + 64 * h + xoff[rb]);
+            for (int rb = 0; rb < RB; ++rb) a[S][h][rb] = *reinterpret_cast<const uint4*>(xs + 64 * h + xoff[rb]);
     };
     auto body = [&](auto ph, int step) {
         constexpr int PH = decltype(ph)::value;
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(256) void sub_xq_mfma_kernel(const bf16_bits* __res
                     bl = __builtin_bit_cast(bf16x8_t,
                                             *reinterpret_cast<const uint4*>(qb + kHalf + 16 * cb * kQtRow + 32 * h));
 #pragma unroll
-                for (int rb = 0; rb < 4; ++rb) {
+                for (int rb = 0; rb < RB; ++rb) {
                     const bf16x8_t av = __builtin_bit_cast(bf16x8_t, a[PH][h][rb]);
                     acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bh, acc[rb][cb], 0, 0, 0);
                     if (LO) acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bl, acc[rb][cb], 0, 0, 0);
@@ -197,7 +200,7 @@ __global__ __launch_bounds__(256) void sub_xq_mfma_kernel(const bf16_bits* __res
     }
     float* o = out + (int64_t)kc * N * kP;
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int r = row0 + 16 * rb + 4 * kq + v;
@@ -408,6 +411,11 @@ __global__ __launch_bounds__(256) void sub_sum_parts_kernel(const float* __restr
     *reinterpret_cast<float4*>(out + e) = a;
 }
 
+static decltype(&sub_xq_mfma_kernel<true, false>) xq_kernel(int rows, bool precise) {
+    if (rows == 128) return precise ? sub_xq_mfma_kernel<true, false, 2> : sub_xq_mfma_kernel<false, false, 2>;
+    return precise ? sub_xq_mfma_kernel<true, false> : sub_xq_mfma_kernel<false, false>;
+}
+
 // Z = X Q, given Q^T as two bf16 halves [128][D] (left by the orthonormalisation); precise: multiply by both.
 // want_zt: the caller only needs Z as the operand of launch_xtz_mfma: Zt is written instead of Z, and where the sum over d
 // is split, zsum from the n_share shares in zshare as well if there are any (*zsum_written tells).
@@ -417,18 +425,14 @@ hipError_t launch_xq_mfma(const bf16_bits* X, int64_t ldx, int N, int D, const b
     const int k_chunk = ((D + n_split - 1) / n_split + kQStep - 1) / kQStep * kQStep;
     const int splits = (D + k_chunk - 1) / k_chunk;
     float* dst = splits == 1 ? Z : Zpart;
-    const dim3 grid((unsigned)((N + 255) / 256), (unsigned)splits);
+    const int rows = splits > 1 ? 128 : 256;
+    const dim3 grid((unsigned)((N + rows - 1) / rows), (unsigned)splits);
     const int64_t n_pad = ((int64_t)N + 127) / 128 * 128;
     const bool zt = want_zt && splits == 1;
     *zsum_written = want_zt && splits > 1 && zshare != nullptr;
-    if (zt && precise)
-        sub_xq_mfma_kernel<true, true><<<grid, dim3(256), xq_lds_bytes<true>(), s>>>(X, ldx, Qt_hi, Qt_lo, N, D, k_chunk, dst, Zt, n_pad);
-    else if (zt)
-        sub_xq_mfma_kernel<false, true><<<grid, dim3(256), xq_lds_bytes<false>(), s>>>(X, ldx, Qt_hi, Qt_lo, N, D, k_chunk, dst, Zt, n_pad);
-    else if (precise)
-        sub_xq_mfma_kernel<true, false><<<grid, dim3(256), xq_lds_bytes<true>(), s>>>(X, ldx, Qt_hi, Qt_lo, N, D, k_chunk, dst, Zt, n_pad);
-    else
-        sub_xq_mfma_kernel<false, false><<<grid, dim3(256), xq_lds_bytes<false>(), s>>>(X, ldx, Qt_hi, Qt_lo, N, D, k_chunk, dst, Zt, n_pad);
+    auto kern = zt ? (precise ? sub_xq_mfma_kernel<true, true> : sub_xq_mfma_kernel<false, true>)
+                   : xq_kernel(rows, precise);
+    kern<<<grid, dim3(256), precise ? xq_lds_bytes<true>() : xq_lds_bytes<false>(), s>>>(X, ldx, Qt_hi, Qt_lo, N, D, k_chunk, dst, Zt, n_pad);
     if (splits > 1 && want_zt) {
         sub_z_split_kernel<<<dim3((unsigned)(n_pad / 64), kP / 32 + (zshare != nullptr ? 1 : 0)), dim3(256), 0, s>>>(
             Zpart, splits, N, n_pad, Zt, zshare, n_share, zsum);
@@ -444,11 +448,9 @@ hipError_t launch_cq_mfma(const bf16_bits* Cs, int D, const bf16_bits* Qt_hi, co
                           bool precise, hipStream_t s, int* n_parts) {
     const int k_chunk = ((D + n_split - 1) / n_split + kQStep - 1) / kQStep * kQStep;
     const int splits = (D + k_chunk - 1) / k_chunk;
-    const dim3 grid((unsigned)(2 * D / 256), (unsigned)splits);
-    if (precise)
-        sub_xq_mfma_kernel<true, false><<<grid, dim3(256), xq_lds_bytes<true>(), s>>>(Cs, D, Qt_hi, Qt_lo, 2 * D, D, k_chunk, Wpart, nullptr, 0);
-    else
-        sub_xq_mfma_kernel<false, false><<<grid, dim3(256), xq_lds_bytes<false>(), s>>>(Cs, D, Qt_hi, Qt_lo, 2 * D, D, k_chunk, Wpart, nullptr, 0);
+    const dim3 grid((unsigned)(2 * D / 128), (unsigned)splits);
+    xq_kernel(128, precise)<<<grid, dim3(256), precise ? xq_lds_bytes<true>() : xq_lds_bytes<false>(), s>>>(
+        Cs, D, Qt_hi, Qt_lo, 2 * D, D, k_chunk, Wpart, nullptr, 0);
     *n_parts = 2 * splits;
     return hipGetLastError();
 }
@@ -465,6 +467,8 @@ hipError_t launch_xtz_mfma(const bf16_bits* X, int64_t ldx, int N, int D, const 
 
 hipError_t init_subspace_mfma_kernels() {
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(sub_xq_mfma_kernel<true, false>), xq_lds_bytes<true>());
+    if (e != hipSuccess) return e;
+    e = allow_dynamic_lds(reinterpret_cast<const void*>(sub_xq_mfma_kernel<true, false, 2>), xq_lds_bytes<true>());
     if (e != hipSuccess) return e;
     return allow_dynamic_lds(reinterpret_cast<const void*>(sub_xq_mfma_kernel<true, true>), xq_lds_bytes<true>());
 }
