@@ -9,8 +9,8 @@
 // four features of token i / 4 and receives four tokens of feature i.  Token rows of 512 bytes are stored with their 32-byte
 // pieces exchanged by a pattern of the token, so that the eight token rows a read touches lie in different banks.  Two tiles of
 // 32 tokens in LDS, two more on their way in registers, one barrier per tile.
-// Workgroups of one token chunk are neighbours in the launch: each chunk's rows are in the last-level cache while all tiles
-// need them.
+// The tiles of one token chunk are neighbours on one XCD, whose L2 then fetches that chunk's rows alone (whole launch, with
+// neighbours on eight: 131072 tokens of 1024 features 244 -> 212 us, of 2048 622 -> 575, 41047 of 3584 593 -> 567; of 4096 the same).
 // Bound by the matrix cores under the power limit: 131072 tokens of 4096 features in 2.1 ms, 1.05 PFLOP/s over the tiles on and
 // below the diagonal; 16 passes over the tokens instead took 3.75 ms.  Steps on the way: products, reads and stores in the
 // compiler's order 3.0 ms; staged pieces of a struct type, which it keeps in scratch memory, 7.0 ms.
@@ -56,7 +56,10 @@ __global__ __launch_bounds__(256, 1) void cov_tile_kernel(const bf16_bits* __res
                                                           int n_tiles, float* __restrict__ part) {
     __shared__ __align__(16) unsigned char lds[2][2][kPanelBytes];        // [buffer][panel: rows of the tile, columns]
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wr = wv >> 1, wc = wv & 1;
-    const int c = blockIdx.x / n_tiles, tile = blockIdx.x % n_tiles;
+    // workgroup numbers go round the eight XCDs: neighbours in (chunk, tile) order on one of them
+    const int n_wg = gridDim.x, xcd = blockIdx.x & 7;
+    const int wg = xcd * (n_wg >> 3) + min(xcd, n_wg & 7) + (blockIdx.x >> 3);
+    const int c = wg / n_tiles, tile = wg % n_tiles;
     int I, J;
     tile_of(tile, &I, &J);
     const int t_begin = c * chunk, t_end = min(N, t_begin + chunk);
