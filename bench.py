@@ -315,8 +315,9 @@ def gram_resident_leg(cfg, ctx, Kf):
 
 def matrix_leg(cfg, ctx, args):
     """Not part of `value`: truncated entropy of one [N, 4096] hidden-state matrix (low rank plus noise, as the
-    keys) by uncomp_matrix_entropy, 8 rounds of two tall-skinny products each (matrix cores for bf16).
-    HBM-bound in principle: reports the time and the rate at which the matrix is streamed."""
+    keys) by uncomp_matrix_entropy, 8 rounds, either of two tall-skinny products over the matrix each or of one over its
+    covariance, formed first (matrix cores for bf16).  Reports the time, the rate at which the matrix is streamed (statistics,
+    rounds or covariance, projection) and the flops of the products over it (of the covariance: both triangles)."""
     import math
 
     import torch
@@ -336,11 +337,13 @@ def matrix_leg(cfg, ctx, args):
     for name, m in ctx.profile_read():
         per[name] = per.get(name, 0.0) + m
     ctx.profile(False)
-    flops = (2 * n_iter + 1) * 2.0 * N * D * 128
+    over_cov = "matrix_covariance" in per
+    flops = 2.0 * N * D * (D + 128) if over_cov else (2 * n_iter + 1) * 2.0 * N * D * 128
+    reads = 3 if over_cov else 2 * n_iter + 2
     e = 2 if cfg.dtype == "bf16" else 4
     return {"tokens": N, "width": D, "rounds": n_iter, "entropy": round(float(H[0]), 5), "ms": round(dt * 1e3, 2),
-            "TFLOPs": round(flops / dt / 1e12, 1), "x_read_GBps": round((2 * n_iter + 2) * N * D * e / dt / 1e9, 1),
-            "hbm_frac": round((2 * n_iter + 2) * N * D * e / dt / 1e9 / HBM_PEAK_GBS, 4),
+            "TFLOPs": round(flops / dt / 1e12, 1), "x_read_GBps": round(reads * N * D * e / dt / 1e9, 1),
+            "hbm_frac": round(reads * N * D * e / dt / 1e9 / HBM_PEAK_GBS, 4),
             "stages_ms": {k: round(v, 3) for k, v in per.items()}}
 
 
