@@ -347,17 +347,16 @@ uncomp_status uncomp_select_gather(uncomp_ctx* ctx, const float* score, const in
                         ctx->key_range.groups == B * H && ctx->key_range.P == N - w;
     // A layer's worth of heads with long rows (the call as a layer-by-layer prefill makes it) would leave most of
     // the chip idle with one workgroup per head: split every row over many workgroups.  Their scratch takes the
-    // front of the workspace, which is free on this stream after the join; key ranges that it would cover are found again.
+    // front of the workspace, which is free on this stream after the join; the key ranges there are not needed.
     const SelectWidePlan sw = plan_select_wide(B * H, N, w);
-    const bool wide = !ctx->force_alu && B * H <= kWideSelectRows && N - w >= kWideSelectScores && sw.fits &&
+    const bool wide = !ctx->force_alu && B * H <= kWideSelectRows && N - w >= kWideSelectScores &&
                       kBudgetScratch + sw.bytes <= ctx->ws_bytes;
-    const bool covered = wide && reinterpret_cast<const char*>(ctx->key_range.ptr) < ctx->ws + kBudgetScratch + sw.bytes;
-    const uint32_t* range = ranged && !covered ? ctx->key_range.ptr : nullptr;
-    if (covered) ctx->key_range.ptr = nullptr;
+    if (wide) ctx->key_range.ptr = nullptr;
     hipError_t e = launch_select_gather(score, budget, all_kv ? K : nullptr, V, dtype, B, H, N, w,
                                         all_kv ? kv_strides : zero_strides, cap, K_out, V_out, idx_out, len_out,
                                         Env{static_cast<hipStream_t>(stream), &ctx->prof, ctx->force_alu},
-                                        range, range != nullptr ? ctx->key_range.n_tiles : 0, D, wide ? &sw : nullptr,
+                                        ranged && !wide ? ctx->key_range.ptr : nullptr,
+                                        ranged && !wide ? ctx->key_range.n_tiles : 0, D, wide ? &sw : nullptr,
                                         ctx->ws + kBudgetScratch);
     if (e != hipSuccess) return hip_fail(ctx, e, "select_gather: launch");
     return UNCOMP_OK;
@@ -369,8 +368,7 @@ struct HiddenPlan {
     LastTokenPlan lt;            // the bf16 path's regions start where the general path's scoring region does
     SelectWidePlan sw;           // in the scoring region, which has been read by then
     bool wide_select;            // few rows, long ones: the selection is split over many workgroups
-    int n_range;                 // pairs of the scores' ranges per row, from the kernel that writes them; 0: none
-    size_t score_off, sum_off, range_off, bytes;
+    size_t score_off, sum_off, bytes;
 };
 HiddenPlan plan_hidden(int B, int H, int G, int N, int w) {
     HiddenPlan p;
@@ -379,13 +377,9 @@ HiddenPlan plan_hidden(int B, int H, int G, int N, int w) {
     const size_t scoring = p.sp.bytes > p.lt.bytes ? p.sp.bytes : p.lt.bytes;
     p.score_off = align_up(kBudgetScratch + scoring, 256);
     p.sum_off = align_up(p.score_off + (size_t)B * H * (N - 1) * sizeof(float), 256);
-    p.range_off = align_up(p.sum_off + (size_t)B * (N - w) * sizeof(float), 256);
     p.sw = plan_select_wide(B, N, w);
-    p.wide_select = B <= kWideSelectRows && N - w >= kWideSelectScores && p.sw.fits && p.sw.bytes <= scoring;
-    constexpr int kMaxRange = 3072;          // pairs a row: 24 KB, prompts of up to 786432 tokens
-    const int n_range = (N - w + kLastTokenTile - 1) / kLastTokenTile;
-    p.n_range = p.wide_select && n_range <= kMaxRange ? n_range : 0;
-    p.bytes = p.range_off + align_up((size_t)B * p.n_range * 2 * sizeof(uint32_t), 256);
+    p.wide_select = B <= kWideSelectRows && N - w >= kWideSelectScores && p.sw.bytes <= scoring;
+    p.bytes = align_up(p.sum_off + (size_t)B * (N - w) * sizeof(float), 256);
     return p;
 }
 }  // namespace
@@ -473,11 +467,9 @@ uncomp_status uncomp_hidden_evict(uncomp_ctx* ctx, const void* q_last, const voi
     float* score = reinterpret_cast<float*>(ctx->ws + p.score_off);
     float* sum = score_out != nullptr ? score_out : reinterpret_cast<float*>(ctx->ws + p.sum_off);
     hipError_t e;
-    uint32_t* range = nullptr;
     if (dtype == UNCOMP_BF16 && !ctx->force_alu && G <= 16) {
         // bf16: one streamed MFMA pass over the keys and a merge
-        if (p.n_range > 0) range = reinterpret_cast<uint32_t*>(ctx->ws + p.range_off);
-        e = launch_last_token_score(q_last, K, B, H, G, N, k_strides, N - w, p.lt, ctx->ws + kBudgetScratch, sum, range, env);
+        e = launch_last_token_score(q_last, K, B, H, G, N, k_strides, N - w, p.lt, ctx->ws + kBudgetScratch, sum, env);
     } else {
         // the last token's attention = window score with a one-token window and no pooling
         e = launch_window_score(q_last, K, dtype, B, H, G, N, 1, 1, k_strides, p.sp, ctx->ws + kBudgetScratch, score,
@@ -486,8 +478,7 @@ uncomp_status uncomp_hidden_evict(uncomp_ctx* ctx, const void* q_last, const voi
     }
     if (e == hipSuccess) {
         if (p.wide_select)
-            e = launch_select_rows_wide(sum, n_keep, 0, B, N, w, cap, p.sw, ctx->ws + kBudgetScratch, range, p.n_range, idx_out,
-                                        len_out, env);
+            e = launch_select_rows_wide(sum, n_keep, 0, B, N, w, cap, p.sw, ctx->ws + kBudgetScratch, idx_out, len_out, env);
         else
             e = launch_select_rows(sum, n_keep, 0, B, N, w, cap, idx_out, len_out, env);
     }

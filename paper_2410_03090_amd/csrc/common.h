@@ -139,21 +139,19 @@ hipError_t launch_select_gather(const float* score, const int32_t* budget, const
                                 int32_t* idx_out, int32_t* len_out, const Env& env,
                                 const uint32_t* tile_range = nullptr, int n_range_tiles = 0, int D = kD,
                                 const struct SelectWidePlan* wide = nullptr, char* wide_ws = nullptr);
-// The same selection for a few long rows, each split over n_wg workgroups (select_wide.hip); ws: p.bytes.  range: n_range
-// pairs (smallest, largest key) per row that together cover its scores, or nullptr.
+// The same selection for a few long rows, each split over n_wg workgroups (select_wide.hip); ws: p.bytes.
 struct SelectWidePlan {
-    int n_wg, chunk;     // workgroups per row, positions each of them takes
-    int list_cap;        // keys of the threshold's bin that a chunk lists
-    bool fits;           // false: too long a row for one thread per chunk
-    size_t bytes;        // scratch; about 3 bytes per score
+    int n_wg;            // workgroups (chunks of 2048 positions) per row
+    size_t bytes;        // scratch: 24 KB a row and 8 bytes a chunk
 };
-// Few rows (at most kWideSelectRows), long ones (at least kWideSelectScores scores): worth splitting.  One workgroup a row
-// against many, with the gather: 8 rows of 8192 scores 17.1 / 18.1 us, of 24576 22.8 / 19.6; 32 rows 19.9 / 21.6 and 25.7 / 25.7.
+// Few rows (at most kWideSelectRows), long ones (at least kWideSelectScores scores): worth splitting.  One workgroup a row, with
+// the ranges that the scoring call left, against many, with the gather (us): 8 rows of 16384 scores 23.0 / 25.1, of 24576 26.4 /
+// 25.2, of 28001 42.4 / 24.6; 32 rows of 16384 25.3 / 29.5, of 24576 with a quarter kept 58 / 66, of 28001 44.1 / 31.8.
 constexpr int kWideSelectRows = 32, kWideSelectScores = 24576;
 SelectWidePlan plan_select_wide(int n_groups, int N, int w);
 hipError_t launch_select_rows_wide(const float* score, const int32_t* budget, int budget_stride, int n_groups, int N,
-                                   int w, int cap, const SelectWidePlan& p, char* ws, const uint32_t* range, int n_range,
-                                   int32_t* idx_out, int32_t* len_out, const Env& env);
+                                   int w, int cap, const SelectWidePlan& p, char* ws, int32_t* idx_out, int32_t* len_out,
+                                   const Env& env);
 hipError_t launch_select_rows(const float* score, const int32_t* budget, int budget_stride, int n_groups,
                               int N, int w, int cap, int32_t* idx_out, int32_t* len_out, const Env& env);
 hipError_t launch_gather_rows(const void* src, const int32_t* idx, const int32_t* len, int n_groups, int cap,
@@ -166,8 +164,7 @@ struct LastTokenPlan {
 };
 LastTokenPlan plan_last_token(int B, int H, int G, int N);
 hipError_t launch_last_token_score(const void* q, const void* K, int B, int H, int G, int N, const int64_t ks[3],
-                                   int P_out, const LastTokenPlan& p, char* ws, float* out, uint32_t* range, const Env& env);
-constexpr int kLastTokenTile = 256;      // positions per pair of its range (smallest, largest key of out; not written if nullptr)
+                                   int P_out, const LastTokenPlan& p, char* ws, float* out, const Env& env);
 hipError_t launch_head_sum(const float* score, int B, int H, int P_in, int P_out, float* out, const Env& env);
 hipError_t launch_prepare_reset(int L, int H, int M, double* erank_sum, int32_t* votes, int32_t* count,
                                 const Env& env);

@@ -138,10 +138,10 @@ __global__ __launch_bounds__(256) void lasttoken_merge_kernel(const float* __res
                                                               const float2* __restrict__ ws_ml,
                                                               const float2* __restrict__ head, int H, int G, int np,
                                                               int wave_rows, int s_rows, int P_out,
-                                                              float* __restrict__ out, uint32_t* __restrict__ range) {
-    __shared__ uint32_t wave_range[4][2];
+                                                              float* __restrict__ out) {
     const int b = blockIdx.y;
-    const int pos = blockIdx.x * kLastTokenTile + threadIdx.x, jpos = min(pos, P_out - 1);
+    const int jpos = blockIdx.x * 256 + threadIdx.x;
+    if (jpos >= P_out) return;
     const int part = jpos / wave_rows;
     float acc = 0.f;
     for (int h = 0; h < H; ++h) {
@@ -155,28 +155,7 @@ __global__ __launch_bounds__(256) void lasttoken_merge_kernel(const float* __res
             if (g < G) a += pr[g] * (exp2f(ml[g].x - hd[g].x) * hd[g].y);
         acc += a;
     }
-    if (pos < P_out) out[(int64_t)b * P_out + pos] = acc;
-    if (range == nullptr) return;
-    uint32_t lo = order_key(acc), hi = lo;                        // positions past the end repeat the last one
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        lo = min(lo, (uint32_t)__shfl_xor(lo, o, 64));
-        hi = max(hi, (uint32_t)__shfl_xor(hi, o, 64));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        wave_range[threadIdx.x >> 6][0] = lo;
-        wave_range[threadIdx.x >> 6][1] = hi;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < 4; ++i) {
-            lo = min(lo, wave_range[i][0]);
-            hi = max(hi, wave_range[i][1]);
-        }
-        uint32_t* r = range + ((int64_t)b * gridDim.x + blockIdx.x) * 2;
-        r[0] = lo;
-        r[1] = hi;
-    }
+    out[(int64_t)b * P_out + jpos] = acc;
 }
 
 LastTokenPlan plan_last_token(int B, int H, int G, int N) {
@@ -200,7 +179,7 @@ LastTokenPlan plan_last_token(int B, int H, int G, int N) {
 template <int GT, int WR>
 static hipError_t last_token_score_t(const bf16_bits* q, const bf16_bits* K, int B, int H, int G, int N,
                                      const int64_t ks[3], int P_out, const LastTokenPlan& p, char* ws, float* out,
-                                     uint32_t* range, const Env& env) {
+                                     const Env& env) {
     float* ws_p = reinterpret_cast<float*>(ws + p.p_off);
     float2* ws_ml = reinterpret_cast<float2*>(ws + p.ml_off);
     float2* head = reinterpret_cast<float2*>(ws + p.head_off);
@@ -212,18 +191,18 @@ static hipError_t last_token_score_t(const bf16_bits* q, const bf16_bits* K, int
     env.end();
     env.begin("lasttoken_merge");
     lasttoken_head_kernel<<<dim3((unsigned)((BH * G + 3) / 4)), dim3(256), 0, env.s>>>(ws_ml, BH, G, GT, p.np, head);
-    lasttoken_merge_kernel<GT><<<dim3((unsigned)((P_out + kLastTokenTile - 1) / kLastTokenTile), (unsigned)B), dim3(kLastTokenTile), 0, env.s>>>(
-        ws_p, ws_ml, head, H, G, p.np, WR, p.s_rows, P_out, out, range);
+    lasttoken_merge_kernel<GT><<<dim3((unsigned)((P_out + 255) / 256), (unsigned)B), dim3(256), 0, env.s>>>(
+        ws_p, ws_ml, head, H, G, p.np, WR, p.s_rows, P_out, out);
     env.end();
     return hipGetLastError();
 }
 
 // score[b][j], j < P_out, of the last position's queries q [B][H*G][128] over the N keys of each head (bf16).
 hipError_t launch_last_token_score(const void* q, const void* K, int B, int H, int G, int N, const int64_t ks[3],
-                                   int P_out, const LastTokenPlan& p, char* ws, float* out, uint32_t* range, const Env& env) {
+                                   int P_out, const LastTokenPlan& p, char* ws, float* out, const Env& env) {
     const bf16_bits* qq = static_cast<const bf16_bits*>(q);
     const bf16_bits* kk = static_cast<const bf16_bits*>(K);
-#define UNCOMP_LT_CASE(GT, WR) return last_token_score_t<GT, WR>(qq, kk, B, H, G, N, ks, P_out, p, ws, out, range, env)
+#define UNCOMP_LT_CASE(GT, WR) return last_token_score_t<GT, WR>(qq, kk, B, H, G, N, ks, P_out, p, ws, out, env)
     if (p.wave_rows == 256) {
         if (p.GT == 4) UNCOMP_LT_CASE(4, 256);
         UNCOMP_LT_CASE(8, 256);

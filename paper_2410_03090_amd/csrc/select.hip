@@ -470,7 +470,7 @@ hipError_t launch_select_gather(const float* score, const int32_t* budget, const
     hipError_t e;
     if (wide != nullptr) {
         // a layer's few heads with long rows: many workgroups per row (same indices as select_kernel)
-        e = launch_select_rows_wide(score, budget, 1, BH, N, w, cap, *wide, wide_ws, tile_range, n_range_tiles, idx_out, len_out, env);
+        e = launch_select_rows_wide(score, budget, 1, BH, N, w, cap, *wide, wide_ws, idx_out, len_out, env);
     } else {
         env.begin("select");
         select_kernel<<<dim3(BH), dim3(kSelThreads), kSelDynLds, s>>>(score, budget, 1, N, w, cap, tile_range, n_range_tiles,

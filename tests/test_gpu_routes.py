@@ -438,6 +438,36 @@ def test_select_rows_over_workgroups(ctx, rows, P, w):
             assert np.array_equal(idx[0, r, : len(ref)].cpu().numpy(), ref), (kind, r)
 
 
+# Rows whose scores crowd (all equal, a few values, all but an outlier within an octave, most of them zero) take about what
+# spread ones take: at most twice, two fifths more were measured.
+@pytest.mark.parametrize("rows,P", [(8, 24576), (8, 40009), (1, 131072), (2, 1_000_003)])
+def test_select_time_of_crowded_rows(ctx, rows, P):
+    w, k = 32, P // 2
+    g = torch.Generator(device=DEV).manual_seed(P)
+    u = torch.rand(1, rows, P, generator=g, device=DEV)
+    outlier = 1.0 + 0.9 * u
+    outlier[:, :, 5] = 0.0
+    kinds = dict(spread=torch.exp(6.0 * u - 3.0), equal=torch.full_like(u, 0.25), outlier=outlier, narrow=outlier ** 0.03,
+                 few=torch.floor(300.0 * u) / 7.0, zeros=torch.where(u < 0.9, 0.0, u))
+    budget = torch.full((1, rows), k, dtype=torch.int32, device=DEV)
+    out = (None, None, torch.empty(1, rows, k, dtype=torch.int32, device=DEV), torch.empty(1, rows, dtype=torch.int32, device=DEV))
+    took = {}
+    for kind, score in kinds.items():
+        best = float("inf")
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(20):
+                ctx.select_gather(score, budget, None, None, w, k, N=P + w, out=out)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 20)
+        took[kind] = best
+        ref = O.select_indices(score[0, 0].cpu().numpy().astype(np.float64), k, P + w, w)
+        assert np.array_equal(out[2][0, 0].cpu().numpy(), ref), kind
+    assert max(took.values()) <= 2.0 * took["spread"], took
+
+
 def test_select_over_workgroups_stale_range_and_small_workspace(ctx):
     from paper_2410_03090_amd import binding
     cfg = synth.tiny_config(dtype="bf16", B=1, H=2, G=2, N=40009, w=32, rank_lo=2, rank_hi=24)
