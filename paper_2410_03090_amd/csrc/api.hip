@@ -628,15 +628,20 @@ uncomp_status uncomp_decode_step(uncomp_ctx* ctx, const void* q, const void* k_n
     // (head / spread / two kernels): 8 heads of 300 rows 8.1 / 9.0 / 11.9, of 500 rows 10.4 / 9.1 / 12.6, of 3238 rows
     // 34.8 / 13.3 / 15.7; 32 heads of 5000 rows - / 24.0 / 30.6, of 8000 rows - / 37.6 / 36.6; 128 heads of 1000 rows
     // 20.8 / 17.7 / 21.5, of 1400 rows 25.6 / 27.1 / 26.1; 200 heads of 2000 rows 38.1 / 46.8 / 48.8.
+    // Four parts of 256 rows of more than 128 heads are more workgroups than run at a time (two a CU) and a second round for
+    // little: up to where the two kernels' own rounds end they are the faster ones (spread / two kernels): 136 heads of 767 rows
+    // 15.9 / 19.0, of 768 21.8 / 18.3, of 928 21.4 / 18.9, of 960 21.2 / 21.4, of 1100 18.5 / 22.1; eight query heads 17.5 / 22.8,
+    // 24.1 / 22.3, 24.2 / 23.9, 23.9 / 25.8, 20.8 / 28.2 (of 896 rows 24.2 / 23.8, 152 heads 24.8 / 26.5).
     const bool head_step = wave_path && G <= 8 && (n_heads >= kHeadStepHeads || cap <= kHeadStepRows) &&
                            decode_head_lds_bytes(n_heads, G, cap) <= kDecodeHeadLdsMax;
     const int64_t rows = (int64_t)n_heads * cap;
     const DecodePlan ps = plan_decode_split(n_heads, G, cap);
-    const bool split = wave_path && !head_step && G <= 8 && n_heads <= kSplitHeads && rows <= kSplitRows &&
+    const bool second_round = (int64_t)n_heads * ps.np_max > 512 && cap < (G <= 4 ? 960 : 896);
+    const bool split = wave_path && !head_step && G <= 8 && n_heads <= kSplitHeads && rows <= kSplitRows && !second_round &&
                        ps.np_max <= kSplitParts && ps.bytes <= ctx->ws_bytes;
     // two kernels: 64-row waves where the workspace holds their partials (a context sized for the 128-row ones keeps those)
     const DecodePlan pf = plan_decode(n_heads, G, cap, 64);
-    const bool fine = (G <= 4 || G > 8) && fine_decode_waves(n_heads, G, cap) && pf.bytes <= ctx->ws_bytes &&
+    const bool fine = fine_decode_waves(n_heads, G, cap) && pf.bytes <= ctx->ws_bytes &&
                       decode_update_lds_bytes(pf) <= kLdsDefaultLimit;
     hipError_t e;
     if (head_step)

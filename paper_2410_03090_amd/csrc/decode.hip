@@ -383,7 +383,7 @@ __global__ __launch_bounds__(256) void decode_attend_wave_kernel(
     // ---- pass 1: logits of the wave's rows; lane holds query head c16, rows 16t + 4j + v ----
     // Short waves (kAll) have all their keys and values in flight at once: with few waves on the chip their time is
     // that of the round trips to memory (8 heads of 2048 rows: 8.4 us, two tiles ahead 9.6).
-    constexpr bool kAll = WR == 64 && GT == 4;
+    constexpr bool kAll = WR == 64 && GT <= 8;
     constexpr int kSlots = kAll ? kTiles : 2;
     f32x4_t s[kTiles];
     uint4 kt[kSlots][4], vt[kSlots][4];
@@ -1376,6 +1376,7 @@ hipError_t launch_decode_wave(const void* q, const void* k_new, const void* v_ne
     }
     if (p.wave_rows == 64) {
         if (p.GT == 4) UNCOMP_WAVE_CASE(4, 64);
+        if (p.GT == 8) UNCOMP_WAVE_CASE(8, 64);
         UNCOMP_WAVE_CASE(16, 64);
     }
     if (p.GT == 4) UNCOMP_WAVE_CASE(4, 128);

@@ -374,6 +374,43 @@ def test_decode_spread_heads(n_heads, G, cap):
         c.close()
 
 
+def _decode_names(c):
+    """Kernels of the last decode step of a context that profiles, in order (the read clears them)."""
+    return [name for name, _ in c.profile_read()]
+
+
+HEAD, SPREAD, TWO = ["decode_head"], ["decode_split"], ["decode_attend_wave", "decode_update"]
+
+
+# Which form a call takes, on both sides of every line: 160 heads, 384 rows, 163840 rows in all, what fits in LDS, more than 128
+# heads of four parts, eight query heads.
+@pytest.mark.parametrize("n_heads,G,cap,form", [
+    (1, 4, 384, HEAD), (1, 4, 385, SPREAD), (159, 4, 385, SPREAD), (160, 4, 385, HEAD), (159, 8, 384, HEAD), (40, 4, 4096, SPREAD),
+    (40, 4, 4097, TWO), (128, 4, 800, SPREAD), (129, 4, 767, SPREAD), (129, 4, 768, TWO), (159, 1, 959, TWO), (159, 1, 960, SPREAD),
+    (150, 8, 895, TWO), (150, 8, 896, SPREAD), (170, 4, 4100, TWO), (1, 9, 64, TWO), (300, 16, 64, TWO)])
+def test_decode_forms(n_heads, G, cap, form):
+    from paper_2410_03090_amd import binding
+    from tests.test_gpu_decode import D, State, _check_step
+    g = torch.Generator(device=DEV).manual_seed(cap)
+    rand = lambda *sh: torch.randn(*sh, generator=g, device=DEV).to(torch.bfloat16)  # noqa: E731
+    full = lambda v: torch.full((n_heads,), v, dtype=torch.int32, device=DEV)  # noqa: E731
+    idx = torch.arange(cap, dtype=torch.int32, device=DEV).repeat(n_heads, 1)
+    st = State(rand(n_heads, cap, D), rand(n_heads, cap, D), idx, torch.rand(n_heads, cap, generator=g, device=DEV), full(cap))
+    q, kn, vn, pos = rand(n_heads, G, D), rand(n_heads, D), rand(n_heads, D), cap + 40
+    c = binding.Context(0, binding.Context.decode_workspace_bytes(n_heads, G, cap))
+    try:
+        one = lambda: State(*(t[-1:] for t in (st.Kc, st.Vc, st.idx, st.cum, st.ln))).host()  # noqa: E731
+        before = one()
+        c.profile(True)
+        out, ev = c.decode_step(q, kn, vn, full(pos), full(cap), 8, st.Kc, st.Vc, st.idx, st.cum, st.ln)
+        torch.cuda.synchronize()
+        assert _decode_names(c) == form
+        host = [t[-1:].cpu() for t in (out, ev, q, kn, vn)]
+        assert _check_step(before, one(), host[0].numpy(), host[1].numpy(), *host[2:], np.array([pos]), np.array([cap]), 8, cap) <= 1
+    finally:
+        c.close()
+
+
 # The longest cache that 16 query heads may have: the update kernel's three tables fill 64 KiB but for 64 bytes.
 def test_decode_longest_cache():
     from paper_2410_03090_amd import binding
