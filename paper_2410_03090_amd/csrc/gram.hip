@@ -137,20 +137,22 @@ EntropyPlan plan_entropy(int n_mat, int N, size_t max_bytes) { return entropy_pl
 
 // Chunks per matrix by a model of the launch (us): a CU takes one workgroup at a time (152 KB of LDS); a round of them takes
 // 5.6 ns a token and workgroup, or what their keys take at 5.9 TB/s, and 6 to start and to fold the waves; every chunk costs
-// the eigen stage 1.2.  Head entropies in us, chunks in brackets: 256 matrices of 8192 tokens 250 (2) and 237 (1), of 131072
-// tokens 1567 (2) and 1543 (1); 128 of 16384 252 (4) and 234 (2); 300 of 8192 361 (1) and 352 (2); 8 of 4096 152 (1) and 146 (4).
+// the eigen stage 1.2.  Never fewer than least_chunks(): a wave's sums are fp32, across chunks they are fp64, so longer chunks
+// lose digits (131072 tokens in one chunk instead of two: twice the error of the covariance), although they are faster.
+// Head entropies in us, chunks in brackets: 300 matrices of 8192 tokens 361 (1) and 352 (2); 8 of 4096 152 (1) and 146 (4);
+// 256 of 8192 250 (2) and 237 (1), of 131072 tokens 1567 (2) and 1543 (1).
 // fp32 matrices go through the fp64 matrix cores, 27 ns a token: few of them take more chunks, 8 matrices of 1024 tokens
 // 156 (1) and 142 (4), 8 of 4096 242 (1) and 163 (8), 64 of 1024 179 (1) and 164 (4).
 EntropyPlan plan_entropy_chunks(int n_mat, int N, bool f32, size_t max_bytes) {
     constexpr int kCus = 256;
-    int best = 1;
+    const int least = least_chunks(n_mat, N);
+    int best = least;
     if (f32) {
-        best = least_chunks(n_mat, N);
         const int few = min(min(kCus / n_mat, N / 256), 8);
         if (few > best) best = few;
     } else {
         double best_cost = 0.0;
-        for (int nc = 1; nc <= 64 && (nc == 1 || nc <= N / 512); ++nc) {
+        for (int nc = least; nc <= max(least, min(64, N / 512)); ++nc) {
             const int chunk = ((N + nc - 1) / nc + kGramTile - 1) / kGramTile * kGramTile, n = (N + chunk - 1) / chunk;
             const int64_t wgs = (int64_t)n_mat * n, rest = wgs % kCus;
             auto round = [&](int64_t active) {

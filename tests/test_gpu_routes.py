@@ -562,6 +562,21 @@ def test_entropy_chunks_and_small_workspace(ctx, dtype, n_mat, N):
     np.testing.assert_allclose(ctx.head_entropy(Kd.view(n_mat, N, 128), k_trunc=32).cpu().numpy(), Href, rtol=1e-5)
 
 
+# Sums longer than 4096 tokens meet in fp64: tokens 2^11 times larger in the first half of the prompt leave the second half, whose
+# products are 2^-32 of the first half's fp32 sums and would vanish there, its own eigenvalue (2^-22 of the trace).  Small whole
+# numbers times powers of two: both halves' sums are exact.  1 %: the last bracket of an eigenvalue is 2.9e-10 wide.
+@pytest.mark.parametrize("n_mat,N", [(256, 8192), (128, 16384), (300, 8192)])
+def test_entropy_halves_of_a_prompt(ctx, n_mat, N):
+    v = torch.ones(2, 128)
+    v[0, 64:] = -1.0
+    X = torch.cat([2048.0 * v[:1].expand(N // 2, 128), v[1:].expand(N // 2, 128)]).to(torch.bfloat16).to(DEV)
+    H, eig = ctx.head_entropy(X.expand(n_mat, N, 128), k_trunc=32, flags=0, want_eig=True)
+    share = 2.0 ** -22 / (1.0 + 2.0 ** -22)
+    want = -share * np.log(share) - (1.0 - share) * np.log1p(-share)
+    np.testing.assert_allclose(eig.cpu().numpy()[:, 1], share, rtol=1e-2)
+    np.testing.assert_allclose(H.cpu().numpy(), want, rtol=1e-2)
+
+
 # Layer stages of more layers than a wave and than a workgroup takes at once, of more heads than a wave, against the oracle.
 @pytest.mark.parametrize("L,B,H", [(1, 1, 8), (63, 1, 8), (65, 3, 8), (130, 2, 40), (1500, 1, 4), (4096, 1, 2)])
 def test_budgets_many_layers(ctx, L, B, H):
