@@ -214,18 +214,16 @@ __global__ __launch_bounds__(256, 2) void score_stats_wave_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int R_head = R * n_rg, row0 = R * rg;        // rows of the KV head, first row of this group
     const bf16_bits* Qh = Q + ((int64_t)bh * R_head + row0) * DD;
-    auto stage = [&] {
-        for (int idx = tid; idx < 16 * NRB * kPieces; idx += 256) {
-            const int row = idx / kPieces, piece = idx % kPieces;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (row < R) v = *reinterpret_cast<const uint4*>(Qh + (int64_t)row * DD + piece * 8);
-            *reinterpret_cast<uint4*>(qs + row * kRowBytes + piece * 16) = v;
-        }
-        __syncthreads();
-    };
+    for (int idx = tid; idx < 16 * NRB * kPieces; idx += 256) {
+        const int row = idx / kPieces, piece = idx % kPieces;
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (row < R) v = *reinterpret_cast<const uint4*>(Qh + (int64_t)row * DD + piece * 8);
+        *reinterpret_cast<uint4*>(qs + row * kRowBytes + piece * 16) = v;
+    }
+    __syncthreads();
     float2* part = reinterpret_cast<float2*>(smem + 16 * NRB * kRowBytes);   // [4][16*NRB]
     float2* mine = fold ? part + wv * (16 * NRB) : stats + ((int64_t)bh * (n_chunks * 4) + c * 4 + wv) * R_head + row0;
-    score_stats_wave_body<NRB, DD>(stage, qs, K + b * ks_b + h * ks_h, ks_t, c * chunk, min(N, (c + 1) * chunk), N - w, w, R, wv, lane, mine);
+    score_stats_wave_body<NRB, DD>(qs, K + b * ks_b + h * ks_h, ks_t, c * chunk, min(N, (c + 1) * chunk), N - w, w, R, wv, lane, mine);
     if (fold) {
         __syncthreads();
         if (tid < R) {
@@ -271,7 +269,11 @@ __global__ __launch_bounds__(256) void score_vote_wave_kernel(
             for (int ks = 0; ks < kKs; ++ks) dst[st][ks] = *reinterpret_cast<const uint4*>(src + 32 * ks);
         }
     };
-    load_tile(ka, wv);                                   // on its way while queries and normalisers are fetched
+    // The first tile on its way while queries and normalisers are fetched, up to 128 query rows: 16 heads of 8192 tokens 36.2 us
+    // and 38.5, 8 of 16384 36.7 and 38.3; with 256 rows, 1 head of 2100 tokens, 61.9 and 61.3.  (In the statistics it costs 1 to
+    // 2 us everywhere.)
+    constexpr bool kAhead = NRB <= 8;
+    if constexpr (kAhead) load_tile(ka, wv);
     const int64_t row0 = (int64_t)bh * G * w + R * rg;
     const bf16_bits* Qh = Q + row0 * DD;
     for (int idx = tid; idx < 16 * NRB * kPieces; idx += 256) {
@@ -395,6 +397,7 @@ __global__ __launch_bounds__(256) void score_vote_wave_kernel(
             }
         }
     };
+    if constexpr (!kAhead) load_tile(ka, wv);
     for (int tile = wv; tile < n_tiles; tile += 8) {
         process(ka, kb, tile);
         if (tile + 4 < n_tiles) process(kb, ka, tile + 4);
@@ -667,9 +670,11 @@ static int wave_chunk(int64_t heads, int N, int n_parts) {
     }
     return best * kRound;
 }
-// Partial statistics per query row that the vote workgroups fold for themselves, at most, for each thread that a row gets:
-// two round trips to memory of eight loads, where the merge kernel is a launch of 5 us.  More go through that kernel.
-constexpr int kFoldPartsPerThread = 32;
+// Partial statistics per query row that the vote workgroups fold for themselves, at most; more go through the merge kernel, a
+// launch of 5 us.  Up to 128 query rows two threads share a row: four trips to memory of eight loads each for 64 partials, 4 us.
+// Beyond, a row has one thread: two trips of eight for 16; with 32 (1 head of 16384 tokens, 256 rows) the fold takes 3.8 us
+// longer than reading a normaliser, no less than the launch: 55.1 us in all, 54.6 with the merge kernel; 64-wide 47.3 and 46.8.
+constexpr int kFoldParts = 64, kFoldPartsWide = 16;
 
 template <typename T>
 static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, int w, int pool,
@@ -736,7 +741,7 @@ static hipError_t run_score(const T* Q, const T* K, int B, int H, int G, int N, 
         env.end();
         n_parts = nca;
     }
-    const bool vote_folds = mfma && own_stats && n_parts <= kFoldPartsPerThread * (R_group <= 128 ? 2 : 1);
+    const bool vote_folds = mfma && own_stats && n_parts <= (R_group <= 128 ? kFoldParts : kFoldPartsWide);
     if (own_stats && !vote_folds) {
         env.begin("score_lse");
         score_lse_kernel<<<dim3((rows + 63) / 64), dim3(256), 0, s>>>(stats, rows, p.R, n_parts, lse);

@@ -15,12 +15,11 @@ constexpr float kLog2e = 1.4426950408889634f;
 // has no normaliser.
 constexpr float kNoLogit = -3.402823466e38f;
 
-// qs: the head's query rows in LDS (rows of row_bytes(DD)), put there by stage_queries(), which the whole workgroup calls
-// once the first key tile is on its way and which ends with a barrier.  The wave (wv = 0..3 of the four that share a
+// qs: the head's query rows staged in LDS (rows of row_bytes(DD)).  The wave (wv = 0..3 of the four that share a
 // chunk) streams key tiles wv, wv + 4, ... of tokens [t_begin, t_end) and writes its partial (reference,
-// sum) of every query row to stats_rows[row] (global memory or LDS).  No other workgroup barrier inside.
-template <int NRB, int DD, typename Stage>      // 16-row blocks held, features per head (128 or 64)
-__device__ __forceinline__ void score_stats_wave_body(Stage&& stage_queries, const unsigned char* qs, const bf16_bits* __restrict__ Kh,
+// sum) of every query row to stats_rows[row] (global memory or LDS).  No workgroup barrier inside.
+template <int NRB, int DD>      // 16-row blocks held, features per head (128 or 64)
+__device__ __forceinline__ void score_stats_wave_body(const unsigned char* qs, const bf16_bits* __restrict__ Kh,
                                                       int64_t ks_t, int t_begin, int t_end, int P, int w, int R,
                                                       int wv, int lane, float2* __restrict__ stats_rows) {
     constexpr int kKs = DD / 32, kRowBytes = row_bytes(DD);
@@ -133,9 +132,8 @@ __device__ __forceinline__ void score_stats_wave_body(Stage&& stage_queries, con
             }
         }
     };
-    if (t_end > t_begin) load_tile(ka, wv);
-    stage_queries();
     if (n_tiles > 0) {
+        load_tile(ka, wv);
         for (int tile = wv; tile < n_tiles; tile += 8) {
             process(ka, kb, tile);
             if (tile + 4 < n_tiles) process(kb, ka, tile + 4);

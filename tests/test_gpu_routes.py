@@ -562,6 +562,22 @@ def test_entropy_chunks_and_small_workspace(ctx, dtype, n_mat, N):
     np.testing.assert_allclose(ctx.head_entropy(Kd.view(n_mat, N, 128), k_trunc=32).cpu().numpy(), Href, rtol=1e-5)
 
 
+# Who folds the normalisers: the vote workgroups up to 64 partials a row, up to 16 where a row has one thread (more than 128 query
+# rows), the merge kernel beyond.
+@pytest.mark.parametrize("G,N,merged", [(4, 16384, False), (8, 8192, False), (8, 10240, True), (8, 16384, True)])
+def test_score_who_folds(ctx, G, N, merged):
+    cfg = synth.tiny_config(dtype="bf16", B=1, H=1, G=G, N=N, w=32, rank_lo=2, rank_hi=24)
+    K, V, Q = synth.gen_all(cfg, seed0=N)
+    ctx.profile(True)
+    try:
+        got = ctx.window_score(Q[0].to(DEV), K[0].to(DEV), G=G, pool=7)
+        torch.cuda.synchronize()
+        assert ("score_lse" in [name for name, _ in ctx.profile_read()]) == merged
+    finally:
+        ctx.profile(False)
+    np.testing.assert_allclose(got.cpu().numpy(), O.window_score(to_f64(Q[0]), to_f64(K[0]), G=G, pool=7), rtol=2e-5)
+
+
 # Sums longer than 4096 tokens meet in fp64: tokens 2^11 times larger in the first half of the prompt leave the second half, whose
 # products are 2^-32 of the first half's fp32 sums and would vanish there, its own eigenvalue (2^-22 of the trace).  Small whole
 # numbers times powers of two: both halves' sums are exact.  1 %: the last bracket of an eigenvalue is 2.9e-10 wide.
