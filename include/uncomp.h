@@ -173,8 +173,9 @@ uncomp_status uncomp_head_entropy(uncomp_ctx* ctx, const void* X, uncomp_dtype d
  * the 128 Ritz values of each matrix as shares of the full trace, descending ([n_mat][128]).
  * X as in uncomp_head_entropy (ldx >= D, strides multiples of 8 elements, 16-byte aligned).
  * Matrices are processed one after the other.  Workspace: uncomp_matrix_workspace_bytes(N, D),
- * which includes the covariance where 8 rounds over it are the faster ones (less without it is
- * enough for the call).
+ * which has room for the covariance where 8 rounds over it are the faster ones.  fp32 matrices
+ * do not take that way, and bf16 ones go over X with less: the message of UNCOMP_ERR_WORKSPACE
+ * names the least that a call needs (131072 x 4096: 175 MiB of 545).
  */
 size_t uncomp_matrix_workspace_bytes(int N, int D);
 uncomp_status uncomp_matrix_entropy(uncomp_ctx* ctx, const void* X, uncomp_dtype dtype,
@@ -308,9 +309,12 @@ uncomp_status uncomp_decode_init(uncomp_ctx* ctx, const float* score, const int3
  * old enough to leave appends while n < cap, else drops the token and reports -2.
  * Requires 1 <= w <= cap, 1 <= G <= 16, D == 128, 16-byte aligned q / k_new / v_new / K_c /
  * V_c; the others need their type's alignment only.  bf16 caches need
- * uncomp_decode_workspace_bytes(n_heads, G, cap) of workspace: the step runs as one kernel for
- * 256 heads and more with G <= 8 and up to some 2 000 (G > 4) or 4 000 rows, and as two that leave
- * partial results there otherwise.  They are limited to caches whose per-head merge tables fit
+ * uncomp_decode_workspace_bytes(n_heads, G, cap) of workspace.  With G <= 8 the step runs as one
+ * kernel for 160 heads and more, or for up to 384 rows (a workgroup per head, up to some 2 000 rows
+ * at G > 4 and 4 000 otherwise), and for fewer heads of together up to 163 840 rows (several
+ * workgroups per head, which leave partial results in the workspace and the last of which merges
+ * them; except 129 to 159 heads of 768 to some 900 rows); as two kernels that leave partial
+ * results there otherwise.  All are limited to caches whose per-head merge tables fit
  * 64 KiB of LDS (cap up to about 43 000 rows at G > 8, 87 000 at G > 4, 174 000 at G <= 4, the
  * latter two doubled when the launch uses 256-row parts; beyond it UNCOMP_ERR_UNSUPPORTED,
  * before anything is launched); fp32 caches need no workspace but are limited to

@@ -292,19 +292,21 @@ def test_decode_without_output_buffers(ctx):
         assert np.array_equal(raw_bits(a) if isinstance(a, torch.Tensor) else a, raw_bits(b) if isinstance(b, torch.Tensor) else b)
 
 
-def test_decode_steps_replayed_from_a_hip_graph(ctx):
+@pytest.mark.parametrize("n_heads,cap,form", [(12, 300, ["decode_head"]), (12, 600, ["decode_split"]),
+                                              (132, 800, ["decode_attend_wave", "decode_update"])])
+def test_decode_steps_replayed_from_a_hip_graph(ctx, n_heads, cap, form):
     """Four decode steps captured in a HIP graph (the calls only enqueue kernels: no allocation, no
     memset, no synchronisation) give, on every replay, exactly the state and outputs of the eager calls.
     Replays alternate with eager work and synchronisations."""
-    dtype, G, cap, w, n_heads, T = torch.bfloat16, 4, 300, 8, 12, 4
-    lens = [300, 299, 150, 0, 300, 257, 256, 255, 40, 300, 7, 128]
+    dtype, G, w, T = torch.bfloat16, 4, 8, 4
+    lens = [(cap, cap - 1, cap // 2, 0, cap, 257, 256, 255, 40, cap, 7, 128)[h % 12] for h in range(n_heads)]
     g = torch.Generator().manual_seed(5)
     q = (torch.randn(T, n_heads, G, D, generator=g) * 2).to(dtype).to(DEV)
     kn = torch.randn(T, n_heads, D, generator=g).to(dtype).to(DEV)
     vn = torch.randn(T, n_heads, D, generator=g).to(dtype).to(DEV)
-    pos = [torch.full((n_heads,), 600 + t, dtype=torch.int32, device=DEV) for t in range(T)]
+    pos = [torch.full((n_heads,), 2 * cap + t, dtype=torch.int32, device=DEV) for t in range(T)]
     bud = torch.randint(w, cap + 20, (n_heads,), generator=g, dtype=torch.int32).to(DEV)
-    start = _random_state(n_heads, cap, lens, [600] * n_heads, dtype, seed=8, w=w)
+    start = _random_state(n_heads, cap, lens, [2 * cap] * n_heads, dtype, seed=8, w=w)
     init = [t.clone() for t in (start.Kc, start.Vc, start.idx, start.cum, start.ln)]
     outs = [torch.empty(n_heads, G, D, device=DEV) for _ in range(T)]
     evs = [torch.empty(n_heads, dtype=torch.int32, device=DEV) for _ in range(T)]
@@ -318,8 +320,12 @@ def test_decode_steps_replayed_from_a_hip_graph(ctx):
             ctx.decode_step(q[t], kn[t], vn[t], pos[t], bud, w, start.Kc, start.Vc, start.idx, start.cum, start.ln,
                             out=outs[t], evicted=evs[t])
 
+    ctx.profile(True)
     run_steps()                                                   # eager reference (also warms everything up)
     torch.cuda.synchronize()
+    names = [name for name, _ in ctx.profile_read()]
+    ctx.profile(False)
+    assert names == T * form
     want = [t.clone() for t in (start.Kc, start.Vc, start.idx, start.cum, start.ln)] + [o.clone() for o in outs] + \
            [e.clone() for e in evs]
     reset()

@@ -171,6 +171,14 @@ def test_entropy_fp32_tile_split(ctx, n_mat, N):
     np.testing.assert_allclose(eig.cpu().numpy(), eref, rtol=0, atol=2e-5)
 
 
+def _decode_names(c):
+    """Kernels of the last decode step of a context that profiles, in order (the read clears them)."""
+    return [name for name, _ in c.profile_read()]
+
+
+HEAD, SPREAD, TWO = ["decode_head"], ["decode_split"], ["decode_attend_wave", "decode_update"]
+
+
 # The decode step of many heads in one kernel: eight, four and two waves per head, lengths around the 16-row tiles and the
 # waves' turns, evictions, growth and full caches, and a key far down the cache whose logit is 34 above all others (the
 # waves' reference has to follow it).  Tolerances of the step as everywhere (_check_step).
@@ -204,12 +212,15 @@ def test_decode_many_heads(ctx, n_heads, G, cap, w):
     assert swaps <= 2                               # near ties at fp32 resolution, each checked to be one
 
 
-# Logits at the end of the range and beyond it: the one-kernel step of many heads gives what the two kernels of few heads
-# give for the same heads, and what the oracle gives where that is finite.
-def test_decode_many_heads_extreme_logits(ctx):
+# Logits at the end of the range and beyond it: the one-kernel step of many heads gives what the step of fewer heads gives for
+# the same heads (one kernel too for short caches; spread over workgroups; two kernels), and what the oracle gives where that is
+# finite.  The infinity and the NaN lie in the first part of a head's rows and in a later one.
+@pytest.mark.parametrize("cap,few,form,at", [(60, 8, HEAD, 37), (400, 8, SPREAD, 37), (400, 8, SPREAD, 301), (800, 136, TWO, 37),
+                                             (800, 136, TWO, 700)])
+def test_decode_many_heads_extreme_logits(ctx, cap, few, form, at):
     from tests.test_gpu_decode import D, State, _check_step, _random_state
-    n_heads, G, cap, w = 256, 4, 60, 4
-    lens, pos0 = [cap - 1 - h % 7 for h in range(n_heads)], [200] * n_heads
+    n_heads, G, w = 256, 4, 4
+    lens, pos0 = [cap - 1 - h % 7 for h in range(n_heads)], [cap + 140] * n_heads
     st = _random_state(n_heads, cap, lens, pos0, torch.bfloat16, seed=3, w=w)
     g = torch.Generator().manual_seed(4)
     q = torch.rand(n_heads, G, D, generator=g) + 0.5
@@ -218,40 +229,48 @@ def test_decode_many_heads_extreme_logits(ctx):
     row = torch.arange(1, cap + 1).view(1, cap, 1)
     q[0::4], kn[0::4] = 1e16 * q[0::4], -4e16                       # logits of -1e33 and less, one or more per cent apart
     st.Kc[0::4] = (-1e16 * (1 + 0.02 * row)).to(torch.bfloat16).expand(n_heads // 4, cap, D).to(DEV)
-    st.Kc[1::4, 37, 5] = float("inf")
+    st.Kc[1::4, at, 5] = float("inf")
     st.Kc[2::4, ::3, 9] = float("-inf")
-    st.Kc[3::4, 11, 0] = float("nan")
+    st.Kc[3::4, at - 26, 0] = float("nan")
     q, kn = q.to(torch.bfloat16), kn.to(torch.bfloat16)
     pos, budget = torch.tensor(pos0, dtype=torch.int32), torch.full((n_heads,), cap, dtype=torch.int32)
     before = st.host()
-    few = State(*(t[:8].clone() for t in (st.Kc, st.Vc, st.idx, st.cum, st.ln)))
+    part = State(*(t[:few].clone() for t in (st.Kc, st.Vc, st.idx, st.cum, st.ln)))
     args = [t.to(DEV) for t in (q, kn, vn, pos, budget)]
-    out, ev = ctx.decode_step(*args, w, st.Kc, st.Vc, st.idx, st.cum, st.ln)
-    out8, ev8 = ctx.decode_step(*(t[:8].contiguous() for t in args), w, few.Kc, few.Vc, few.idx, few.cum, few.ln)
-    torch.cuda.synchronize()
-    # both kernels sum in fp32 over the same rows, in another order: the tolerances of _check_step
-    np.testing.assert_allclose(out[:8].cpu().numpy(), out8.cpu().numpy(), rtol=0, atol=1e-4)
-    np.testing.assert_allclose(st.cum[:8].cpu().numpy(), few.cum.cpu().numpy(), rtol=2e-5, atol=2e-6)
-    assert torch.equal(ev[:8], ev8) and torch.equal(st.ln[:8], few.ln)
+    ctx.profile(True)
+    try:
+        out, ev = ctx.decode_step(*args, w, st.Kc, st.Vc, st.idx, st.cum, st.ln)
+        out8, ev8 = ctx.decode_step(*(t[:few].contiguous() for t in args), w, part.Kc, part.Vc, part.idx, part.cum, part.ln)
+        torch.cuda.synchronize()
+        assert _decode_names(ctx) == HEAD + form
+    finally:
+        ctx.profile(False)
+    # both sum in fp32 over the same rows, in another order: the tolerances of _check_step
+    np.testing.assert_allclose(out[:few].cpu().numpy(), out8.cpu().numpy(), rtol=0, atol=1e-4)
+    np.testing.assert_allclose(st.cum[:few].cpu().numpy(), part.cum.cpu().numpy(), rtol=2e-5, atol=2e-6)
+    finite = [h for h in range(n_heads) if h % 4 in (0, 2)]
+    seen = [h for h in finite if h < few]
+    assert torch.equal(ev[seen], ev8[seen]) and torch.equal(st.ln[:few], part.ln)
     for h in range(n_heads):
         assert bool(torch.isfinite(out[h]).all()) == (h % 4 in (0, 2)), kinds[h % 4]
         assert bool(torch.isnan(out[h]).all()) == (h % 4 in (1, 3)), kinds[h % 4]
-    finite = [h for h in range(n_heads) if h % 4 in (0, 2)]
     assert _check_step(before, st.host(), out.cpu().numpy(), ev.cpu().numpy(), q, kn, vn, pos.numpy(), budget.numpy(), w, cap,
-                       heads=finite) == 0
+                       heads=finite[:64]) == 0
 
 
 # The attention output needs a float's alignment and no more, on each route of the step.
-@pytest.mark.parametrize("n_heads,G", [(3, 4), (3, 16), (256, 8)])
-def test_decode_output_at_any_float(ctx, n_heads, G):
+@pytest.mark.parametrize("n_heads,G,cap,form", [(3, 4, 150, HEAD), (3, 16, 150, TWO), (256, 8, 150, HEAD), (3, 4, 400, SPREAD),
+                                                (3, 8, 400, SPREAD), (130, 4, 800, TWO), (130, 8, 800, TWO)])
+def test_decode_output_at_any_float(ctx, n_heads, G, cap, form):
     from tests.test_gpu_decode import D, State, _random_state
-    cap, w = 150, 4
-    st = _random_state(n_heads, cap, [cap - h % 50 for h in range(n_heads)], [300] * n_heads, torch.bfloat16, seed=G, w=w)
+    w = 4
+    st = _random_state(n_heads, cap, [cap - h % 50 for h in range(n_heads)], [cap + 150] * n_heads, torch.bfloat16, seed=G, w=w)
     g = torch.Generator().manual_seed(G)
     q = torch.randn(n_heads, G, D, generator=g).to(torch.bfloat16).to(DEV)
     kn, vn = (torch.randn(n_heads, D, generator=g).to(torch.bfloat16).to(DEV) for _ in range(2))
-    pos, budget = (torch.full((n_heads,), v, dtype=torch.int32, device=DEV) for v in (300, cap))
+    pos, budget = (torch.full((n_heads,), v, dtype=torch.int32, device=DEV) for v in (cap + 150, cap))
     outs = []
+    ctx.profile(True)
     for off in range(4):
         s = State(*(t.clone() for t in (st.Kc, st.Vc, st.idx, st.cum, st.ln)))
         buf = torch.full((n_heads * G * D + 8,), 7.0, device=DEV)
@@ -260,6 +279,9 @@ def test_decode_output_at_any_float(ctx, n_heads, G):
         torch.cuda.synchronize()
         assert bool((buf[:off] == 7.0).all()) and bool((buf[off + n_heads * G * D:] == 7.0).all())
         outs.append(out.clone())
+    names = _decode_names(ctx)
+    ctx.profile(False)
+    assert names == 4 * form
     assert all(torch.equal(outs[0], o) for o in outs[1:])
 
 
@@ -271,9 +293,11 @@ def _decode_bytes(n_heads, G, cap, wave_rows):
     return sum((n_heads * r * 4 + 255) // 256 * 256 for r in regions)
 
 
-# Few heads: 64-row waves, and the 128-row ones of a workspace that only holds their partials.
-@pytest.mark.parametrize("n_heads,G,cap", [(1, 4, 64), (3, 8, 64), (5, 16, 130), (8, 4, 1290)])
-def test_decode_few_heads_both_plans(ctx, n_heads, G, cap):
+# Few heads: 64-row waves, and the 128-row ones of a workspace that only holds their partials; calls that take another form are
+# the same in either.
+@pytest.mark.parametrize("n_heads,G,cap,form", [(1, 4, 64, HEAD), (3, 8, 64, HEAD), (5, 16, 130, TWO), (8, 4, 1290, SPREAD),
+                                                (136, 4, 800, TWO), (130, 8, 769, TWO), (84, 4, 2000, TWO)])
+def test_decode_few_heads_both_plans(ctx, n_heads, G, cap, form):
     from paper_2410_03090_amd import binding
     from tests.test_gpu_decode import D, _check_step, _random_state
     fine, coarse = _decode_bytes(n_heads, G, cap, 64), _decode_bytes(n_heads, G, cap, 128)
@@ -281,18 +305,22 @@ def test_decode_few_heads_both_plans(ctx, n_heads, G, cap):
     small = binding.Context(0, coarse)              # too small for 64-row waves
     try:
         for c in (ctx, small):
-            lens = [min(cap, cap - 3 * h) for h in range(n_heads)]
+            lens = [cap - 3 * (h % 40) if h < 40 else cap - h for h in range(n_heads)]
             pos0 = [cap + 50 + h for h in range(n_heads)]
             st = _random_state(n_heads, cap, lens, pos0, torch.bfloat16, seed=cap, w=4)
-            budget = torch.tensor([cap - h for h in range(n_heads)], dtype=torch.int32)
+            budget = torch.tensor([cap - h % 50 for h in range(n_heads)], dtype=torch.int32)
             g = torch.Generator().manual_seed(G)
             q = torch.randn(n_heads, G, D, generator=g).to(torch.bfloat16)
             kn, vn = (torch.randn(n_heads, D, generator=g).to(torch.bfloat16) for _ in range(2))
             pos = torch.tensor(pos0, dtype=torch.int32)
             before = st.host()
+            c.profile(True)
             out, ev = c.decode_step(q.to(DEV), kn.to(DEV), vn.to(DEV), pos.to(DEV), budget.to(DEV), 4, st.Kc, st.Vc, st.idx,
                                     st.cum, st.ln)
             torch.cuda.synchronize()
+            names = _decode_names(c)
+            c.profile(False)
+            assert names == form
             assert _check_step(before, st.host(), out.cpu().numpy(), ev.cpu().numpy(), q, kn, vn, pos.numpy(),
                                budget.numpy(), 4, cap) == 0
     finally:
@@ -300,11 +328,14 @@ def test_decode_few_heads_both_plans(ctx, n_heads, G, cap):
 
 
 # The two-kernel step in every form: waves of 64, 128 and 256 rows, the update kernel of few (early and not), some and many
-# heads, lengths around the waves' parts, evictions and growth.  Sampled heads against the oracle.
-@pytest.mark.parametrize("n_heads,G,cap,rows", [
-    (255, 4, 2300, 256), (255, 8, 2300, 256), (512, 8, 2050, 256), (1280, 8, 2050, 256), (300, 4, 4100, 256),
-    (512, 4, 5100, 256), (1290, 3, 5100, 256), (8, 8, 3100, 64), (9, 8, 700, 64), (2, 16, 3100, 64), (600, 16, 70, 64), (255, 7, 900, 128), (1300, 16, 200, 128)])
-def test_decode_two_kernels(n_heads, G, cap, rows):
+# heads, lengths around the waves' parts, evictions and growth.  Sampled heads against the oracle.  (Sizes of other forms, for
+# which the workspace is asked all the same, stand beside them.)
+@pytest.mark.parametrize("n_heads,G,cap,rows,form", [
+    (255, 4, 2300, 256, HEAD), (255, 8, 2300, 256, TWO), (512, 8, 2050, 256, TWO), (1280, 8, 2050, 256, TWO), (300, 4, 4100, 256, TWO),
+    (512, 4, 5100, 256, TWO), (1290, 3, 5100, 256, TWO), (8, 8, 3100, 64, SPREAD), (9, 8, 700, 64, SPREAD), (2, 16, 3100, 64, TWO),
+    (600, 16, 70, 64, TWO), (255, 7, 900, 128, HEAD), (1300, 16, 200, 128, TWO), (84, 4, 2000, 64, TWO), (100, 4, 2000, 128, TWO),
+    (100, 8, 2000, 128, TWO), (150, 8, 1200, 128, TWO), (145, 7, 800, 64, TWO)])
+def test_decode_two_kernels(n_heads, G, cap, rows, form):
     from paper_2410_03090_amd import binding
     from tests.test_gpu_decode import D, State, _check_step
     need = binding.Context.decode_workspace_bytes(n_heads, G, cap)
@@ -324,9 +355,11 @@ def test_decode_two_kernels(n_heads, G, cap, rows):
     c = binding.Context(0, need)
     try:
         before, ln0 = sample(), ln.clone()
+        c.profile(True)
         out, ev = c.decode_step(q, kn, vn, pos, budget, w, st.Kc, st.Vc, st.idx, st.cum, st.ln)
         torch.cuda.synchronize()
         after = sample()
+        assert _decode_names(c) == form
         assert torch.isfinite(out).all() and torch.isfinite(st.cum).all()
         host = [t[pick].cpu() for t in (out, ev, q, kn, vn, pos, budget)]
         assert _check_step(before, after, host[0].numpy(), host[1].numpy(), *host[2:5], host[5].numpy(), host[6].numpy(), w,
@@ -358,6 +391,7 @@ def test_decode_spread_heads(n_heads, G, cap):
     pick = torch.tensor(sorted(set(range(min(n_heads, 15))) | {n_heads - 1}), device=DEV)
     sample = lambda: State(*(t[pick] for t in (st.Kc, st.Vc, st.idx, st.cum, st.ln))).host()  # noqa: E731
     c = binding.Context(0, binding.Context.decode_workspace_bytes(n_heads, G, cap))
+    c.profile(True)
     try:
         for t in range(3):
             q, kn, vn = 2 * rand(n_heads, G, D), rand(n_heads, D), rand(n_heads, D)
@@ -365,6 +399,7 @@ def test_decode_spread_heads(n_heads, G, cap):
             before, ln0 = sample(), st.ln.clone()
             out, ev = c.decode_step(q, kn, vn, pos, budget, w, st.Kc, st.Vc, st.idx, st.cum, st.ln)
             torch.cuda.synchronize()
+            assert _decode_names(c) == SPREAD
             host = [x[pick].cpu() for x in (out, ev, q, kn, vn, pos, budget)]
             assert torch.isfinite(out).all()
             assert _check_step(before, sample(), host[0].numpy(), host[1].numpy(), *host[2:5], host[5].numpy(), host[6].numpy(), w,
@@ -372,14 +407,6 @@ def test_decode_spread_heads(n_heads, G, cap):
             assert torch.equal(st.ln, torch.where(ev == -1, ln0 + 1, ln0))
     finally:
         c.close()
-
-
-def _decode_names(c):
-    """Kernels of the last decode step of a context that profiles, in order (the read clears them)."""
-    return [name for name, _ in c.profile_read()]
-
-
-HEAD, SPREAD, TWO = ["decode_head"], ["decode_split"], ["decode_attend_wave", "decode_update"]
 
 
 # Which form a call takes, on both sides of every line: 160 heads, 384 rows, 163840 rows in all, what fits in LDS, more than 128
@@ -448,9 +475,8 @@ def test_matrix_entropy_ranks_and_splits(ctx, N, D, r):
         np.testing.assert_allclose(eig.cpu().numpy()[:, :32], eref[:, :32], rtol=0, atol=2e-5)
 
 
-# Rows split over workgroups: chunk counts that are odd, that need longer chunks, rows that are no multiple of 4, 2048 or the
-# chunk; budgets from none to all; scores with one outlier (nearly all in one bin: lists overflow), with a few hundred ties at
-# the threshold, and scores that no longer fit the range that the scoring call left.  Indices are exact.
+# Rows split over workgroups: one chunk and many, odd counts, rows that are no multiple of 4 or of a chunk's 2048; budgets from
+# none to all; scores with one outlier, with a few hundred ties at the threshold, all equal.  Indices are exact.
 @pytest.mark.parametrize("rows,P,w", [(1, 24576, 4), (3, 32769, 8), (2, 67591, 32), (1, 131064, 8), (32, 33333, 1), (1, 1_000_003, 64)])
 def test_select_rows_over_workgroups(ctx, rows, P, w):
     rng = np.random.default_rng(P)
@@ -515,7 +541,7 @@ def test_select_over_workgroups_stale_range_and_small_workspace(ctx):
         score = ctx.window_score(Q[0].to(DEV), K[0].to(DEV), G=2, pool=7)
         if change is not None:
             change(score)
-        for c in (ctx, ctx, small):                                 # twice: the range is still there, or found again
+        for c in (ctx, ctx, small):                                 # twice: the first call takes the range's place
             _, _, idx, ln = c.select_gather(score, budget, None, None, 32, 1777, N=40009)
             sc = score.cpu().numpy().astype(np.float64)
             for h in range(2):
