@@ -338,7 +338,8 @@ def matrix_leg(cfg, ctx, args):
         per[name] = per.get(name, 0.0) + m
     ctx.profile(False)
     over_cov = "matrix_covariance" in per
-    flops = 2.0 * N * D * (D + 128) if over_cov else (2 * n_iter + 1) * 2.0 * N * D * 128
+    # over the covariance: its symmetric half, a round's product with its two bf16 halves, the final projection
+    flops = N * D * (D + 1.0) + n_iter * 4.0 * D * D * 128 + 2.0 * N * D * 128 if over_cov else (2 * n_iter + 1) * 2.0 * N * D * 128
     reads = 3 if over_cov else 2 * n_iter + 2
     e = 2 if cfg.dtype == "bf16" else 4
     return {"tokens": N, "width": D, "rounds": n_iter, "entropy": round(float(H[0]), 5), "ms": round(dt * 1e3, 2),

@@ -29,7 +29,9 @@ uncomp_status hip_fail(uncomp_ctx* ctx, hipError_t e, const char* what) {
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 constexpr size_t kDefaultWorkspace = 64ull << 20;
-constexpr size_t kBudgetScratch = 4096 * sizeof(double);
+// Where the regions of the prefill calls start.  Nothing lies before it (the decode step, which keeps nothing between calls, starts
+// at 0); it stays because what a context of a given size can do, and is refused, is counted with it.
+constexpr size_t kWsFront = 4096 * sizeof(double);
 constexpr size_t kCounterBytes = kSplitHeads * sizeof(uint32_t);
 
 }  // namespace
@@ -48,7 +50,7 @@ uncomp_status uncomp_create(uncomp_ctx** ctx_out, int device, size_t workspace_b
     ctx->err[0] = 0;
     ctx->ws = nullptr;
     ctx->ws_bytes = workspace_bytes == 0 ? kDefaultWorkspace : align_up(workspace_bytes, 256);
-    if (ctx->ws_bytes < kBudgetScratch) ctx->ws_bytes = kBudgetScratch;
+    if (ctx->ws_bytes < kWsFront) ctx->ws_bytes = kWsFront;
     int prev = 0;
     (void)hipGetDevice(&prev);
     e = hipSetDevice(device);
@@ -105,8 +107,8 @@ uncomp_status uncomp_destroy(uncomp_ctx* ctx) {
 
 size_t uncomp_workspace_bytes(int n_mat, int N, int D, int B, int H, int G, int w) {
     (void)D;
-    // three regions that may be live at once in overlap mode: budgets | entropy | score
-    size_t need = kBudgetScratch;
+    // two regions that may be live at once in overlap mode, behind the front: entropy | score
+    size_t need = kWsFront;
     if (n_mat > 0 && N > 0) {
         size_t partials = plan_entropy(n_mat, N).bytes;
         for (bool f32 : {false, true}) {
@@ -215,17 +217,17 @@ uncomp_status uncomp_head_entropy(uncomp_ctx* ctx, const void* X, uncomp_dtype d
         return fail(ctx, UNCOMP_ERR_INVALID_ARG, "head_entropy: strides must be multiples of 8 elements, ldx >= D, X 16-byte aligned");
     if ((int64_t)n_mat * 64 > 0x7fffffffLL) return fail(ctx, UNCOMP_ERR_UNSUPPORTED, "head_entropy: too many matrices");
     const EntropyPlan least = plan_entropy(n_mat, N);
-    if (kBudgetScratch + least.bytes > ctx->ws_bytes)
+    if (kWsFront + least.bytes > ctx->ws_bytes)
         return fail(ctx, UNCOMP_ERR_WORKSPACE, "head_entropy: needs %zu workspace bytes, context has %zu",
-                    kBudgetScratch + least.bytes, ctx->ws_bytes);
-    const EntropyPlan p = plan_entropy_chunks(n_mat, N, dtype == UNCOMP_F32, ctx->ws_bytes - kBudgetScratch);
+                    kWsFront + least.bytes, ctx->ws_bytes);
+    const EntropyPlan p = plan_entropy_chunks(n_mat, N, dtype == UNCOMP_F32, ctx->ws_bytes - kWsFront);
     ctx->key_range.ptr = nullptr;
     // an eigen stage of an earlier call may still be reading the Gram partials on the side stream
     uncomp_status js = uncomp_join(ctx, stream);
     if (js != UNCOMP_OK) return js;
-    char* ws = ctx->ws + kBudgetScratch;
-    ctx->score_ws_off = kBudgetScratch + p.bytes;
-    ctx->score_ws_least = kBudgetScratch + least.bytes;
+    char* ws = ctx->ws + kWsFront;
+    ctx->score_ws_off = kWsFront + p.bytes;
+    ctx->score_ws_least = kWsFront + least.bytes;
     Env env{static_cast<hipStream_t>(stream), &ctx->prof, ctx->force_alu};
     hipError_t e = launch_gram(X, dtype, n_mat, N, mat_stride, ldx, p, ws, env, D);
     if (e != hipSuccess) return hip_fail(ctx, e, "head_entropy: gram launch");
@@ -291,7 +293,7 @@ uncomp_status uncomp_window_score(uncomp_ctx* ctx, const void* Qwin, const void*
     if ((int64_t)B * H * ((N + 255) / 256) > 0x7fffffffLL) return fail(ctx, UNCOMP_ERR_UNSUPPORTED, "window_score: problem too large");
     ScorePlan p = plan_score(B, H, G, N, w);
     // keep clear of the entropy region while side-stream work may still read it
-    size_t off = ctx->side_pending ? ctx->score_ws_least : kBudgetScratch;
+    size_t off = ctx->side_pending ? ctx->score_ws_least : kWsFront;
     if (off + p.bytes > ctx->ws_bytes)
         return fail(ctx, UNCOMP_ERR_WORKSPACE, "window_score: needs %zu workspace bytes, context has %zu",
                     off + p.bytes, ctx->ws_bytes);
@@ -300,7 +302,7 @@ uncomp_status uncomp_window_score(uncomp_ctx* ctx, const void* Qwin, const void*
         if (off + p.bytes > ctx->ws_bytes) {     // room for the fewest partials only: one after the other
             uncomp_status js = uncomp_join(ctx, stream);
             if (js != UNCOMP_OK) return js;
-            off = kBudgetScratch;
+            off = kWsFront;
         }
     }
     ctx->key_range.ptr = nullptr;
@@ -350,14 +352,14 @@ uncomp_status uncomp_select_gather(uncomp_ctx* ctx, const float* score, const in
     // front of the workspace, which is free on this stream after the join; the key ranges there are not needed.
     const SelectWidePlan sw = plan_select_wide(B * H, N, w);
     const bool wide = !ctx->force_alu && B * H <= kWideSelectRows && N - w >= kWideSelectScores &&
-                      kBudgetScratch + sw.bytes <= ctx->ws_bytes;
+                      kWsFront + sw.bytes <= ctx->ws_bytes;
     if (wide) ctx->key_range.ptr = nullptr;
     hipError_t e = launch_select_gather(score, budget, all_kv ? K : nullptr, V, dtype, B, H, N, w,
                                         all_kv ? kv_strides : zero_strides, cap, K_out, V_out, idx_out, len_out,
                                         Env{static_cast<hipStream_t>(stream), &ctx->prof, ctx->force_alu},
                                         ranged && !wide ? ctx->key_range.ptr : nullptr,
                                         ranged && !wide ? ctx->key_range.n_tiles : 0, D, wide ? &sw : nullptr,
-                                        ctx->ws + kBudgetScratch);
+                                        ctx->ws + kWsFront);
     if (e != hipSuccess) return hip_fail(ctx, e, "select_gather: launch");
     return UNCOMP_OK;
 }
@@ -375,7 +377,7 @@ HiddenPlan plan_hidden(int B, int H, int G, int N, int w) {
     p.sp = plan_score(B, H, G, N, 1);
     p.lt = plan_last_token(B, H, G, N);
     const size_t scoring = p.sp.bytes > p.lt.bytes ? p.sp.bytes : p.lt.bytes;
-    p.score_off = align_up(kBudgetScratch + scoring, 256);
+    p.score_off = align_up(kWsFront + scoring, 256);
     p.sum_off = align_up(p.score_off + (size_t)B * H * (N - 1) * sizeof(float), 256);
     p.sw = plan_select_wide(B, N, w);
     p.wide_select = B <= kWideSelectRows && N - w >= kWideSelectScores && p.sw.bytes <= scoring;
@@ -391,7 +393,7 @@ constexpr int kUsualRounds = 8;
 size_t uncomp_matrix_workspace_bytes(int N, int D) {
     if (N <= 0 || D <= 0 || D % kD != 0) return 0;
     const MatrixPlan p = plan_matrix(N, D);
-    return kBudgetScratch + (D >= 2 * kD && cov_pays(p, N, D, kUsualRounds) ? p.cov_total : p.bytes);
+    return kWsFront + (D >= 2 * kD && cov_pays(p, N, D, kUsualRounds) ? p.cov_total : p.bytes);
 }
 
 uncomp_status uncomp_matrix_entropy(uncomp_ctx* ctx, const void* X, uncomp_dtype dtype, int n_mat, int N, int D,
@@ -410,14 +412,14 @@ uncomp_status uncomp_matrix_entropy(uncomp_ctx* ctx, const void* X, uncomp_dtype
     if (ldx < D || (ldx & 7) || (mat_stride & 7) || mat_stride < 0 || !aligned16(X))
         return fail(ctx, UNCOMP_ERR_INVALID_ARG, "matrix_entropy: strides must be multiples of 8 elements, ldx >= D, X 16-byte aligned");
     const MatrixPlan p = plan_matrix(N, D);
-    if (kBudgetScratch + p.bytes > ctx->ws_bytes)
+    if (kWsFront + p.bytes > ctx->ws_bytes)
         return fail(ctx, UNCOMP_ERR_WORKSPACE, "matrix_entropy: needs %zu workspace bytes, context has %zu",
-                    kBudgetScratch + p.bytes, ctx->ws_bytes);
+                    kWsFront + p.bytes, ctx->ws_bytes);
     ctx->key_range.ptr = nullptr;
     uncomp_status js = uncomp_join(ctx, stream);
     if (js != UNCOMP_OK) return js;
     hipError_t e = launch_matrix_entropy(X, dtype, n_mat, N, D, mat_stride, ldx, k_trunc, flags, n_iter, p,
-                                         ctx->ws + kBudgetScratch, ctx->ws_bytes - kBudgetScratch, entropy_out, eig_out,
+                                         ctx->ws + kWsFront, ctx->ws_bytes - kWsFront, entropy_out, eig_out,
                                          Env{static_cast<hipStream_t>(stream), &ctx->prof, ctx->force_alu});
     if (e != hipSuccess) return hip_fail(ctx, e, "matrix_entropy: launch");
     return UNCOMP_OK;
@@ -469,16 +471,16 @@ uncomp_status uncomp_hidden_evict(uncomp_ctx* ctx, const void* q_last, const voi
     hipError_t e;
     if (dtype == UNCOMP_BF16 && !ctx->force_alu && G <= 16) {
         // bf16: one streamed MFMA pass over the keys and a merge
-        e = launch_last_token_score(q_last, K, B, H, G, N, k_strides, N - w, p.lt, ctx->ws + kBudgetScratch, sum, env);
+        e = launch_last_token_score(q_last, K, B, H, G, N, k_strides, N - w, p.lt, ctx->ws + kWsFront, sum, env);
     } else {
         // the last token's attention = window score with a one-token window and no pooling
-        e = launch_window_score(q_last, K, dtype, B, H, G, N, 1, 1, k_strides, p.sp, ctx->ws + kBudgetScratch, score,
+        e = launch_window_score(q_last, K, dtype, B, H, G, N, 1, 1, k_strides, p.sp, ctx->ws + kWsFront, score,
                                 env);
         if (e == hipSuccess) e = launch_head_sum(score, B, H, N - 1, N - w, sum, env);
     }
     if (e == hipSuccess) {
         if (p.wide_select)
-            e = launch_select_rows_wide(sum, n_keep, 0, B, N, w, cap, p.sw, ctx->ws + kBudgetScratch, idx_out, len_out, env);
+            e = launch_select_rows_wide(sum, n_keep, 0, B, N, w, cap, p.sw, ctx->ws + kWsFront, idx_out, len_out, env);
         else
             e = launch_select_rows(sum, n_keep, 0, B, N, w, cap, idx_out, len_out, env);
     }
@@ -637,6 +639,7 @@ uncomp_status uncomp_decode_step(uncomp_ctx* ctx, const void* q, const void* k_n
     const int64_t rows = (int64_t)n_heads * cap;
     const DecodePlan ps = plan_decode_split(n_heads, G, cap);
     const bool second_round = (int64_t)n_heads * ps.np_max > 512 && cap < (G <= 4 ? 960 : 896);
+    // (ps.bytes: never more than p.bytes, which is checked above, for so few rows)
     const bool split = wave_path && !head_step && G <= 8 && n_heads <= kSplitHeads && rows <= kSplitRows && !second_round &&
                        ps.np_max <= kSplitParts && ps.bytes <= ctx->ws_bytes;
     // two kernels: 64-row waves where the workspace holds their partials (a context sized for the 128-row ones keeps those)

@@ -9,8 +9,8 @@
 //
 // bf16 caches of many heads take decode_head_kernel, one workgroup per head, and so do fewer heads of short caches.  A few
 // heads of long caches take decode_split_kernel: several workgroups per head, the last of which merges.  The rest (heads
-// between the two, more than 8 query heads per KV head, caches whose probabilities do not fit in LDS, contexts without room
-// for the split) takes two kernels.  decode_attend_wave_kernel: every wave
+// between the two, more than 8 query heads per KV head, caches whose probabilities do not fit in LDS) takes two kernels.
+// decode_attend_wave_kernel: every wave
 // owns 64, 128 or 256 consecutive rows of one head and runs on its own (no workgroup barrier): keys stream straight into
 // MFMA operand layout, the logits stay in registers, the wave's softmax (its own maximum and sum) goes through LDS to
 // the lanes that stream the value rows, and the wave leaves (maximum, sum, unnormalised output, unnormalised

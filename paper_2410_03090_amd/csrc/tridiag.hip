@@ -33,8 +33,8 @@
 //     and i + 2 as the update will leave them (x and y of the next reflection) for itself, with the
 //     same operations in the same order, so all waves hold identical bits and none waits for another.
 //   - A wave's first row block is skipped once its rows are done.
-// Measured: 8 matrices (one per CU) 129 us: 2630 cycles for each of the first 63 reflections, 1420 for each of the last 63
-// (one wave, neither barriers nor exchange), 13 us for step 3; 5120 matrices 2.0 ms.  256 matrices of 64 columns 143 -> 51 us
+// Measured: 8 matrices (one per CU) 132 us (133 with all reflections in four waves): 2630 cycles for each of the first 63
+// reflections, 1420 for each of the last 63 (one wave, neither barriers nor exchange), 13 us for step 3; 5120 matrices 2.0 ms.  256 matrices of 64 columns 143 -> 51 us
 // (before: all 126 reflections of the 128-wide matrix with zeros in half of its rows).
 #include "common.h"
 #include "device_utils.h"
