@@ -351,8 +351,7 @@ uncomp_status uncomp_select_gather(uncomp_ctx* ctx, const float* score, const in
     // the chip idle with one workgroup per head: split every row over many workgroups.  Their scratch takes the
     // front of the workspace, which is free on this stream after the join; the key ranges there are not needed.
     const SelectWidePlan sw = plan_select_wide(B * H, N, w);
-    const bool wide = !ctx->force_alu && B * H <= kWideSelectRows && N - w >= kWideSelectScores &&
-                      kWsFront + sw.bytes <= ctx->ws_bytes;
+    const bool wide = !ctx->force_alu && wide_select_pays(B * H, N - w) && kWsFront + sw.bytes <= ctx->ws_bytes;
     if (wide) ctx->key_range.ptr = nullptr;
     hipError_t e = launch_select_gather(score, budget, all_kv ? K : nullptr, V, dtype, B, H, N, w,
                                         all_kv ? kv_strides : zero_strides, cap, K_out, V_out, idx_out, len_out,
@@ -380,7 +379,7 @@ HiddenPlan plan_hidden(int B, int H, int G, int N, int w) {
     p.score_off = align_up(kWsFront + scoring, 256);
     p.sum_off = align_up(p.score_off + (size_t)B * H * (N - 1) * sizeof(float), 256);
     p.sw = plan_select_wide(B, N, w);
-    p.wide_select = B <= kWideSelectRows && N - w >= kWideSelectScores && p.sw.bytes <= scoring;
+    p.wide_select = wide_select_pays(B, N - w) && p.sw.bytes <= scoring;
     p.bytes = align_up(p.sum_off + (size_t)B * (N - w) * sizeof(float), 256);
     return p;
 }

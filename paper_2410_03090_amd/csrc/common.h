@@ -144,10 +144,12 @@ struct SelectWidePlan {
     int n_wg;            // workgroups (chunks of 2048 positions) per row
     size_t bytes;        // scratch: 24 KB a row and 8 bytes a chunk
 };
-// Few rows (at most kWideSelectRows), long ones (at least kWideSelectScores scores): worth splitting.  One workgroup a row, with
-// the ranges that the scoring call left, against many, with the gather (us): 8 rows of 16384 scores 23.0 / 25.1, of 24576 26.4 /
-// 25.2, of 28001 42.4 / 24.6; 32 rows of 16384 25.3 / 29.5, of 24576 with a quarter kept 58 / 66, of 28001 44.1 / 31.8.
-constexpr int kWideSelectRows = 32, kWideSelectScores = 24576;
+// Few long rows are worth splitting: up to sixteen of at least 24576 scores, up to kWideSelectRows of at least 32768.  One
+// workgroup a row, with the ranges that the scoring call left, against many, with the gather (us): 8 rows of 16384 scores 23.0 /
+// 25.1, of 24576 26.4 / 25.2, of 28001 42.4 / 24.6; 32 rows of 16384 25.3 / 29.5, of 24576 58 / 66 with a quarter kept, of 32768
+// 82.5 / 83.8, of 40009 122 / 98.  (Equal scores are one workgroup's best case: 8 rows of 24576 13 / 24.)
+constexpr int kWideSelectRows = 32;
+inline bool wide_select_pays(int rows, int scores) { return rows <= kWideSelectRows && scores >= (rows <= 16 ? 24576 : 32768); }
 SelectWidePlan plan_select_wide(int n_groups, int N, int w);
 hipError_t launch_select_rows_wide(const float* score, const int32_t* budget, int budget_stride, int n_groups, int N,
                                    int w, int cap, const SelectWidePlan& p, char* ws, int32_t* idx_out, int32_t* len_out,

@@ -477,7 +477,7 @@ def test_matrix_entropy_ranks_and_splits(ctx, N, D, r):
 
 # Rows split over workgroups: one chunk and many, odd counts, rows that are no multiple of 4 or of a chunk's 2048; budgets from
 # none to all; scores with one outlier, with a few hundred ties at the threshold, all equal.  Indices are exact.
-@pytest.mark.parametrize("rows,P,w", [(1, 24576, 4), (3, 32769, 8), (2, 67591, 32), (1, 131064, 8), (32, 33333, 1), (1, 1_000_003, 64)])
+@pytest.mark.parametrize("rows,P,w", [(1, 24576, 4), (16, 24577, 3), (17, 32767, 8), (3, 32769, 8), (2, 67591, 32), (1, 131064, 8), (32, 33333, 1), (1, 1_000_003, 64)])
 def test_select_rows_over_workgroups(ctx, rows, P, w):
     rng = np.random.default_rng(P)
     N = P + w
