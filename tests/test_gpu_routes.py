@@ -502,7 +502,7 @@ def test_select_rows_over_workgroups(ctx, rows, P, w):
 
 
 # Rows whose scores crowd (all equal, a few values, all but an outlier within an octave, most of them zero) take about what
-# spread ones take: at most twice, two fifths more were measured.
+# spread ones take: at most twice, half as much again was measured (a million equal scores).
 @pytest.mark.parametrize("rows,P", [(8, 24576), (8, 40009), (1, 131072), (2, 1_000_003)])
 def test_select_time_of_crowded_rows(ctx, rows, P):
     w, k = 32, P // 2
